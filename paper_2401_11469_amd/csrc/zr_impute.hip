@@ -91,22 +91,61 @@ __global__ __launch_bounds__(256) void average_cols_kernel(
     }
 }
 
-// axis 0, AVERAGE: thread <-> one column; kept rows summed in ascending order.
+// axis 0, AVERAGE: one workgroup per 32 columns; its 32 half-wavefronts take the kept rows h,
+// h + 32, ... and their sums are added in that order: a fixed order, so the result is
+// deterministic.  Bound by latency at a weight shard's sizes: with one thread walking all kept
+// rows of its column every load waited for the list entry in front of it (299 us for 768 kept of
+// 1024 rows, 1024 bf16 columns); here a half asks for eight rows at a time while the next eight
+// list entries are on their way (9 us).
+constexpr int AVG_PARTS = 32, AVG_COLS = 32;
+
 template <typename T>
-__global__ __launch_bounds__(256) void average_rows_kernel(
+__global__ __launch_bounds__(AVG_PARTS * AVG_COLS) void average_rows_kernel(
     T* __restrict__ out, int64_t ld, int rows, int cols,
     const int32_t* __restrict__ keep, int n_keep)
 {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= cols) return;
+    __shared__ float part[AVG_PARTS][AVG_COLS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = threadIdx.x % AVG_COLS, h = threadIdx.x / AVG_COLS;
+    const int c = min((int)blockIdx.x * AVG_COLS + col, cols - 1);       // lanes past the edge repeat the last column
+    const bool mine = (int)blockIdx.x * AVG_COLS + col < cols;
+    constexpr int U = 8;
+    int next[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) next[u] = keep[min(h + u * AVG_PARTS, n_keep - 1)];
     float acc = 0.f;
-    for (int q = 0; q < n_keep; ++q)
-        acc += Elem<T>::load(out + (size_t)clamp_idx(keep[q], rows) * (size_t)ld + c);
-    const float mean = acc / (float)n_keep;
-    for (int q = 0; q <= n_keep; ++q) {
-        const int lo = q == 0 ? 0 : clamp_idx(keep[q - 1], rows) + 1;
-        const int hi = q == n_keep ? rows : clamp_idx(keep[q], rows);
-        for (int p = lo; p < hi; ++p) Elem<T>::store(out + (size_t)p * (size_t)ld + c, mean);
+    for (int q0 = h; q0 < n_keep; q0 += U * AVG_PARTS) {
+        float v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = Elem<T>::load(out + (size_t)clamp_idx(next[u], rows) * (size_t)ld + c);
+#pragma unroll
+        for (int u = 0; u < U; ++u) next[u] = keep[min(q0 + (U + u) * AVG_PARTS, n_keep - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) acc += q0 + u * AVG_PARTS < n_keep ? v[u] : 0.f;
+    }
+    part[h][col] = acc;
+    __syncthreads();
+    float sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < AVG_PARTS; ++w) sum += part[w][col];
+    const float mean = sum / (float)n_keep;
+    // gap q lies before kept row keep[q]; gap n_keep lies after the last one.  A wavefront looks
+    // 64 gaps up at once and then walks the ones that hold a row, its halves on alternate rows.
+    for (int q0 = wave * 64; q0 <= n_keep; q0 += AVG_PARTS * AVG_COLS) {
+        const int q = q0 + lane;
+        int lo = 0, hi = 0;
+        if (q <= n_keep) {
+            lo = q == 0 ? 0 : clamp_idx(keep[q - 1], rows) + 1;
+            hi = q == n_keep ? rows : clamp_idx(keep[q], rows);
+        }
+        unsigned long long todo = __ballot(hi > lo);
+        while (todo) {
+            const int src = __ffsll((long long)todo) - 1;
+            todo &= todo - 1;
+            const int p1 = __builtin_amdgcn_readlane(hi, src);
+            for (int p = __builtin_amdgcn_readlane(lo, src) + (lane >> 5); p < p1; p += 2)
+                if (mine) Elem<T>::store(out + (size_t)p * (size_t)ld + c, mean);
+        }
     }
 }
 
@@ -182,7 +221,8 @@ int impute_typed(T* out, int64_t ld, int rows, int cols, int axis, const int32_t
             hipLaunchKernelGGL(average_cols_kernel<T>, dim3(rows), dim3(256), 0, stream,
                                out, ld, rows, cols, keep, n_keep);
         else
-            hipLaunchKernelGGL(average_rows_kernel<T>, dim3((cols + 255) / 256), dim3(256), 0, stream,
+            hipLaunchKernelGGL(average_rows_kernel<T>, dim3((cols + AVG_COLS - 1) / AVG_COLS), dim3(AVG_PARTS * AVG_COLS), 0,
+                               stream,
                                out, ld, rows, cols, keep, n_keep);
     } else {
         const bool same = policy == ZR_IMPUTE_SAME;
