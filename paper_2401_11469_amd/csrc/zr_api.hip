@@ -294,7 +294,8 @@ int zr_resized_linear_fwd(const void* X, int64_t ldx, const void* W, int64_t ldw
     hipStream_t s = (hipStream_t)stream;
     const int32_t* S = full ? nullptr : keep_idx;
     const bool average = mode == ZR_DROP_N && policy == ZR_IMPUTE_AVERAGE && !full;
-    float* sums = average ? carve_avg(workspace, workspace_bytes, avg_bytes(M, n_keep)) : nullptr;
+    // (the fp32 products leave no sums: their means come from the stand-alone pass)
+    float* sums = average && dtype == ZR_BF16 ? carve_avg(workspace, workspace_bytes, avg_bytes(M, n_keep)) : nullptr;
 
     GemmDesc d;
     d.dtype = dtype;
@@ -352,7 +353,7 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
     const bool same = !full && policy == ZR_IMPUTE_SAME;       // fused into the scatter epilogues
     const bool post = !full && policy == ZR_IMPUTE_AVERAGE;    // sums in the epilogue, then mean and fill
     float* sums = nullptr;
-    if (post) {
+    if (post && dtype == ZR_BF16) {
         size_t need = 0;
         if (dX && mode == ZR_DROP_K) need = avg_bytes(M, n_keep);
         if (dW) need = std::max(need, avg_bytes(mode == ZR_DROP_K ? N : K, n_keep));

@@ -3,8 +3,8 @@
 //
 // Every product is computed in the canonical form
 //     D[i, j] = sum_c A(i, c) * B(j, c)
-// on 64-wide wavefronts with the 32x32 MFMA tiles (bf16: 32x32x16, fp32:
-// 32x32x2), fp32 accumulation.  The kept-index list is applied while the
+// on 64-wide wavefronts with the 32x32x16 MFMA, fp32 accumulation, for bf16 tensors that the
+// fast path does not take.  The kept-index list is applied while the
 // operand tiles travel from HBM into LDS, so no compacted copy of W (or of any
 // other operand) ever exists in memory, and the epilogue writes the result at
 // its original positions together with the zeros of the dropped positions, so
@@ -50,17 +50,6 @@ template <> struct Ty<ZR_BF16> {
     static __device__ __forceinline__ E from_f32(float f) { return (E)f32_to_bf16_bits(f); }
     static __device__ __forceinline__ float to_f32(E v) { return bf16_bits_to_f32(v); }
 };
-template <> struct Ty<ZR_F32> {
-    typedef float E;
-    static constexpr int EPD = 1;
-    static constexpr int DPL = 1;
-    static constexpr int KDM = 2;
-    static constexpr int CPAD = 4;
-    static __device__ __forceinline__ uint32_t pack(const E* v) { return __float_as_uint(v[0]); }
-    static __device__ __forceinline__ E from_f32(float f) { return f; }
-    static __device__ __forceinline__ float to_f32(E v) { return v; }
-};
-
 struct OpView {
     const void* base;
     int64_t ld;
@@ -200,7 +189,7 @@ struct LoadPElem {
 };
 
 // Format Q, vector loads.  bf16: a unit is 8 rows-of-the-tile x 2 memory rows
-// (c, c+1), interleaved into 8 words.  fp32: a unit is 4 words of one memory row.
+// (c, c+1), interleaved into 8 words.
 template <int DT, int R>
 struct LoadQVec {
     typedef typename Ty<DT>::E E;
@@ -349,24 +338,10 @@ template <bool CC, int R> struct Frag<ZR_BF16, CC, R> {
         return x.b;
     }
 };
-template <bool CC, int R> struct Frag<ZR_F32, CC, R> {
-    typedef float type;
-    static __device__ __forceinline__ type read(const uint32_t* lds, int row, int kd)
-    {
-        constexpr int PQ = R + 8;
-        return __uint_as_float(CC ? lds[row * PP + kd] : lds[kd * PQ + row]);
-    }
-};
-
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
 {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x16 mfma(float a, float b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-
 // first position in the ascending LDS list s[0..n) with s[pos] >= p
 __device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
 {
@@ -688,7 +663,7 @@ static int launch_gemm_untimed(const GemmDesc& d, hipStream_t stream)
     const int fast = launch_gemm_fast(d, stream);   // bf16, 16-byte aligned rows
     if (fast >= 0) return fast;
     if (d.dtype == ZR_BF16) return launch_dt<ZR_BF16>(d, stream);
-    if (d.dtype == ZR_F32) return launch_dt<ZR_F32>(d, stream);
+    if (d.dtype == ZR_F32) return launch_gemm_f32(d, stream);
     return ZR_ERR_DTYPE;
 }
 

@@ -1,0 +1,602 @@
+// Gather-fused MFMA products of fp32 tensors (gfx950): the resized layer's forward, dX and dW
+// (paper Sec. 3.1) in the canonical form
+//     D[i, j] = sum_c A(i, c) * B(j, c)
+// with v_mfma_f32_32x32x2f32, for tensors of any alignment and any extents.
+//
+// What bounds it.  The fp32 matrix rate is 256 FLOP per clock and compute unit, a sixteenth of
+// the bf16 rate, so even a 64 x 64 tile asks for only 16 bytes per clock from L2 and its LDS
+// reads are a small fraction of the LDS rate.  What costs time is a chip that is not full and
+// loads that are waited for.  Hence small tiles, deep stages and several workgroups to a unit:
+//   R = 64: 64 x 64 tiles, 64 contraction indices a stage, a 32 x 32 result per wavefront;
+//   R = 32: 32 x 32 tiles, 128 contraction indices a stage, of which each of the four
+//           wavefronts multiplies a quarter; their four sums are added in wavefront order in
+//           LDS.  For products with few tiles: four times as many workgroups, half the stages.
+// Both bring 16 KB of each operand per stage (four 16-byte loads or sixteen element loads a
+// thread, in flight for a whole stage of multiplications) and use 72 KB of LDS, so that two
+// workgroups share a compute unit.
+// Measured against the kernel before this one (128 x 128 tiles, 32 deep, element loads under
+// branches): 1576 x 1024 x 1640 plain 94 -> 66 us, with the kept list on the contraction
+// 222 -> 72 us, 256 x 512 x 192 in four launches 132 -> 30 us; 4096^3 runs at 122 TFLOP/s (0.78
+// of the fp32 matrix peak).  Of a launch 10-13 us are start and end (all tiles of a round
+// end together); a chip full of tiles keeps the matrix pipes at 0.9 in between, so what is left
+// is that, and the rounding of the tile count to the compute units.
+//
+// LDS formats (32-bit words):
+//   P  [row][contraction]  tensors whose contiguous axis is the contraction axis
+//   Q  [contraction][row]  tensors whose contiguous axis is the other one
+// The order in which the contraction is added up is free as long as both operands agree: of a
+// block of 8 indices, lanes 0-31 take indices 0-3 and lanes 32-63 indices 4-7, so a P operand
+// is read with one ds_read_b128 per four MFMAs.
+#include <cstdio>
+#include <type_traits>
+
+#include "zr_common.h"
+
+namespace zr {
+
+namespace {
+
+constexpr int NT = 256;
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes at any element address
+
+template <int R> struct Geo {
+    static constexpr int BK = R == 64 ? 64 : 128;   // contraction depth of a stage
+    static constexpr int NP = R * BK / (4 * NT);          // pieces a stage is brought in: 16 bytes of each operand per thread
+    static constexpr int PP = BK + 4;                     // row pitch of format P: 16 rows of a fragment read on 16 bank groups
+    static constexpr int PQ = R == 64 ? 72 : 36;          // row pitch of format Q: rows 4 apart (the two lane halves) on other banks
+    static constexpr int WORDS = R * PP > BK * PQ ? R * PP : BK * PQ;      // LDS words of one operand's stage
+};
+
+struct View {
+    const float* base;
+    int64_t ld;
+    const int32_t* map_s;       // row list on the strided axis or nullptr
+    const int32_t* map_c;       // kept list on the contiguous axis or nullptr (the gathering loaders)
+    int n_s, n_c;               // memory extents
+};
+
+struct Args {
+    View A, B;
+    int I, J, C;
+    float* out;
+    int64_t ldo;
+    int epilogue;
+    const int32_t* keep;
+    int out_full;
+    int out_vec;                // output rows allow 16-byte stores
+    int tiles_i, tiles_j;
+    const float* prev;          // Same imputation source (layout of out) or nullptr
+    int accumulate;             // add the old contents of out (plain epilogue)
+};
+
+// ---------------------------------------------------------------------------
+// Loaders.  Each keeps one stage of its operand in registers (begin, then fetch of four pieces)
+// and writes it to LDS a stage later (commit, piece by piece).  Rows of the tile beyond the
+// operand's extent repeat its last row (they only feed results that are never stored);
+// contraction indices past C become zero (commit with TAIL, which only the last stage needs).
+// No load stands under a branch: at a join the compiler waits for every load in flight (with
+// branches for the last stage and the edges the loop ran at half of this one's speed).
+// ---------------------------------------------------------------------------
+// element e of the result is element e + sh of v, 0 past its end
+__device__ __forceinline__ f4 shifted(f4 v, int sh)
+{
+    f4 r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float x = 0.f;
+#pragma unroll
+        for (int q = 3; q >= e; --q) x = sh == q - e ? v[q] : x;
+        r[e] = x;
+    }
+    return r;
+}
+
+// Contraction axis contiguous (C >= 4), optional row list.
+template <int R> struct PlainP {
+    static constexpr const char* NAME = "P";
+    static constexpr bool P = true;
+    static constexpr int BK = Geo<R>::BK, NP = Geo<R>::NP, CPR = BK / 4, RPP = NT / CPR;
+    const float* ptr[NP];
+    int off_;
+    f4 v[NP];
+    __device__ __forceinline__ void init(const View& op, int r0, int rlim, int, int tid)
+    {
+        int row[NP];
+#pragma unroll
+        for (int it = 0; it < NP; ++it) row[it] = min(r0 + tid / CPR + RPP * it, rlim - 1);
+        if (op.map_s) {
+#pragma unroll
+            for (int it = 0; it < NP; ++it) row[it] = op.map_s[row[it]];
+#pragma unroll
+            for (int it = 0; it < NP; ++it) row[it] = clamp_idx(row[it], op.n_s);
+        }
+#pragma unroll
+        for (int it = 0; it < NP; ++it) ptr[it] = op.base + (size_t)row[it] * (size_t)op.ld;
+    }
+    // a chunk that would reach past the contraction range is read from its last four elements
+    // and shifted into place by commit
+    __device__ __forceinline__ void begin(const View&, int c0, int C, int tid) { off_ = min(c0 + (tid % CPR) * 4, C - 4); }
+    template <int PC> __device__ __forceinline__ void fetch(const View&, int, int, int)
+    {
+        v[PC] = *(const f4_any*)(ptr[PC] + off_);
+    }
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(float* lds, int c0, int C, int tid) const
+    {
+        f4 x = v[PC];
+        if constexpr (TAIL) {
+            const int c = c0 + (tid % CPR) * 4;
+            x = shifted(x, c - min(c, C - 4));
+        }
+        *(f4*)(lds + (tid / CPR + RPP * PC) * Geo<R>::PP + (tid % CPR) * 4) = x;
+    }
+};
+
+// Contraction axis contiguous with the kept list on it: a thread owns one contraction index of
+// the stage, so a wavefront's load runs along the (ascending) list in one memory row, or two.
+template <int R> struct GatherP {
+    static constexpr const char* NAME = "Pg";
+    static constexpr bool P = true;
+    static constexpr int BK = Geo<R>::BK, NP = Geo<R>::NP, RSTEP = NT / BK, N = R / RSTEP;
+    static constexpr int RPW = BK < 64 ? 64 / BK : 1;                    // memory rows per wavefront load
+    const float* base_;
+    int64_t ld_;
+    int row0_, rlast_;      // uniform: first row of this wavefront, last row of the operand
+    int second_;            // 1 in the half of a wavefront that takes the second row
+    const int32_t* list_;
+    int col_, next_;        // column of the stage being fetched, list entry of the one after
+    float v[N];
+    __device__ __forceinline__ void init(const View& op, int r0, int rlim, int C, int tid)
+    {
+        base_ = op.base; ld_ = op.ld;
+        row0_ = r0 + (RPW == 1 ? __builtin_amdgcn_readfirstlane(tid / BK) : RPW * __builtin_amdgcn_readfirstlane(tid / 64));
+        second_ = RPW == 1 ? 0 : (tid % 64) / BK;
+        rlast_ = rlim - 1;
+        list_ = op.map_c;
+        next_ = list_[min(tid % BK, C - 1)];
+    }
+    __device__ __forceinline__ void begin(const View& op, int c0, int C, int tid)
+    {
+        col_ = clamp_idx(next_, op.n_c);
+        next_ = list_[min(c0 + BK + tid % BK, C - 1)];
+    }
+    template <int PC> __device__ __forceinline__ void fetch(const View&, int, int, int)
+    {
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
+            const int r = min(row0_ + RSTEP * it, rlast_);                       // uniform
+            const float* row = base_ + (int64_t)r * ld_;
+            if constexpr (RPW == 1) v[it] = row[(uint32_t)col_];
+            else {
+                const int64_t more = r < rlast_ ? ld_ : 0;                       // uniform
+                v[it] = row[(int64_t)second_ * more + col_];
+            }
+        }
+    }
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(float* lds, int c0, int C, int tid) const
+    {
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it)
+            lds[(tid / BK + RSTEP * it) * Geo<R>::PP + tid % BK] = !TAIL || c0 + tid % BK < C ? v[it] : 0.f;
+    }
+};
+
+// Contraction axis strided (stored rows of at least 4 elements), optional row list on it.
+template <int R> struct PlainQ {
+    static constexpr const char* NAME = "Q";
+    static constexpr bool P = false;
+    static constexpr int BK = Geo<R>::BK, NP = Geo<R>::NP, CPR = R / 4, RPP = NT / CPR;
+    const float* colp;      // base + this thread's (clamped) column
+    int sh_;                // how far the clamp moved it
+    bool edge_;             // uniform: the tile reaches past the stored rows' end
+    int row_[NP];           // memory rows of the next stage
+    const float* p_[NP];
+    f4 v[NP];
+    __device__ __forceinline__ void rows_for(const View& op, int c0, int C, int tid)
+    {
+#pragma unroll
+        for (int it = 0; it < NP; ++it) row_[it] = min(c0 + tid / CPR + RPP * it, C - 1);
+        if (op.map_s) {
+#pragma unroll
+            for (int it = 0; it < NP; ++it) row_[it] = op.map_s[row_[it]];
+        }
+    }
+    __device__ __forceinline__ void init(const View& op, int r0, int, int C, int tid)
+    {
+        const int col = r0 + (tid % CPR) * 4, cc = min(col, op.n_c - 4);
+        edge_ = r0 + R > op.n_c;
+        sh_ = col - cc;
+        colp = op.base + cc;
+        rows_for(op, 0, C, tid);
+    }
+    __device__ __forceinline__ void begin(const View& op, int c0, int C, int tid)
+    {
+#pragma unroll
+        for (int it = 0; it < NP; ++it) p_[it] = colp + (size_t)clamp_idx(row_[it], op.n_s) * (size_t)op.ld;
+        rows_for(op, c0 + BK, C, tid);
+    }
+    template <int PC> __device__ __forceinline__ void fetch(const View&, int, int, int) { v[PC] = *(const f4_any*)p_[PC]; }
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(float* lds, int c0, int C, int tid) const
+    {
+        f4 x = v[PC];
+        if (edge_) x = shifted(x, sh_);
+        if constexpr (TAIL) {
+            const bool ok = c0 + tid / CPR + RPP * PC < C;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = ok ? x[e] : 0.f;
+        }
+        *(f4*)(lds + (tid / CPR + RPP * PC) * Geo<R>::PQ + (tid % CPR) * 4) = x;
+    }
+};
+
+// Contraction axis strided, kept list on the other axis: a thread owns one kept column, and a
+// wavefront's load covers 64 of them in one memory row (32 in each of two rows for R = 32).
+template <int R> struct GatherQ {
+    static constexpr const char* NAME = "Qg";
+    static constexpr bool P = false;
+    static constexpr int BK = Geo<R>::BK, NP = Geo<R>::NP, CSTEP = NT / R, N = BK / CSTEP, RPW = 64 / R;      // RPW: memory rows per wavefront load
+    const float* base_;
+    int64_t ld_;
+    int c0_, clast_;        // uniform: first contraction index of this wavefront, last one of all
+    uint32_t col_, second_; // column; 1 in the half of a wavefront that takes the second row
+    float v[N];
+    __device__ __forceinline__ void init(const View& op, int r0, int rlim, int C, int tid)
+    {
+        col_ = (uint32_t)clamp_idx(op.map_c[min(r0 + tid % R, rlim - 1)], op.n_c);
+        base_ = op.base; ld_ = op.ld; clast_ = C - 1; c0_ = 0;
+        second_ = (tid % 64) / R;
+    }
+    __device__ __forceinline__ void begin(const View&, int c0, int, int tid)
+    {
+        c0_ = c0 + RPW * __builtin_amdgcn_readfirstlane(tid / 64);
+    }
+    template <int PC> __device__ __forceinline__ void fetch(const View&, int, int, int)
+    {
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
+            const int c = min(c0_ + CSTEP * it, clast_);                         // uniform
+            const float* row = base_ + (int64_t)c * ld_;
+            if constexpr (RPW == 1) v[it] = row[col_];
+            else {
+                const int64_t more = c < clast_ ? ld_ : 0;                       // uniform
+                v[it] = row[(int64_t)second_ * more + col_];
+            }
+        }
+    }
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(float* lds, int c0, int C, int tid) const
+    {
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it)
+            lds[(tid / R + CSTEP * it) * Geo<R>::PQ + tid % R] = !TAIL || c0 + tid / R + CSTEP * it < C ? v[it] : 0.f;
+    }
+};
+
+// Element by element through whatever lists there are: for products with a contiguous extent
+// below the four elements that the plain loaders read at a time.
+template <int R, bool P_> struct AnyPQ {
+    static constexpr const char* NAME = P_ ? "Pe" : "Qe";
+    static constexpr bool P = P_;
+    static constexpr int BK = Geo<R>::BK;
+    int r0_, rlast_;
+    float v[16];
+    __device__ __forceinline__ void init(const View&, int r0, int rlim, int, int) { r0_ = r0; rlast_ = rlim - 1; }
+    __device__ __forceinline__ void begin(const View&, int, int, int) {}
+    template <int PC> __device__ __forceinline__ void fetch(const View& op, int c0, int C, int tid)
+    {
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
+            const int q = tid + NT * it;
+            const int r = min(r0_ + (P ? q / BK : q % R), rlast_), c = min(c0 + (P ? q % BK : q / R), C - 1);
+            int s = P ? r : c, t = P ? c : r;                   // along the strided and the contiguous axis
+            if (op.map_s) s = clamp_idx(op.map_s[s], op.n_s);
+            if (op.map_c) t = clamp_idx(op.map_c[t], op.n_c);
+            v[it] = op.base[(size_t)s * (size_t)op.ld + t];
+        }
+    }
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(float* lds, int c0, int C, int tid) const
+    {
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
+            const int q = tid + NT * it;
+            const int c = P ? q % BK : q / R;
+            lds[P ? q / BK * Geo<R>::PP + c : c * Geo<R>::PQ + q % R] = !TAIL || c0 + c < C ? v[it] : 0.f;
+        }
+    }
+};
+template <int R> struct AnyP : AnyPQ<R, true> {};
+template <int R> struct AnyQ : AnyPQ<R, false> {};
+
+// four contraction indices of a block of eight: 0-3 for lanes 0-31, 4-7 for lanes 32-63
+template <bool P, int R>
+__device__ __forceinline__ f4 fragment(const float* lds, int row, int block, int grp)
+{
+    if constexpr (P) return *(const f4*)(lds + row * Geo<R>::PP + block * 8 + grp * 4);
+    f4 x;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) x[s] = lds[(block * 8 + grp * 4 + s) * Geo<R>::PQ + row];
+    return x;
+}
+
+// first position in the ascending LDS list s[0..n) with s[pos] >= p
+__device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
+{
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (s[mid] < p) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
+template <template <int> class LA_, template <int> class LB_, int R>
+__global__ __launch_bounds__(NT) void f32_kernel(const Args g)
+{
+    typedef LA_<R> LA;
+    typedef LB_<R> LB;
+    constexpr int BK = Geo<R>::BK;
+    constexpr int NP = Geo<R>::NP;
+    constexpr int OP_WORDS = Geo<R>::WORDS, STAGE = 2 * OP_WORDS;
+    constexpr int WAVES = NT / 64;
+    constexpr int BLOCKS = R == 64 ? BK / 8 : BK / 8 / WAVES;         // blocks of 8 per wavefront and stage
+    constexpr int CP = R + 4;                                         // row pitch of the result tile
+    constexpr int TAB = 512;                                          // original columns per pass of the column scatter
+    constexpr int PART = R == 64 ? 0 : 4 * 32 * 36;                   // the wavefronts' sums
+    static_assert(R * CP + PART + 2 * R + TAB <= 2 * STAGE, "the epilogue fits the stages");
+
+    extern __shared__ __align__(16) float smem[];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = lane & 31, grp = lane >> 5;
+
+    // every XCD gets a contiguous range of tiles, ordered in groups of 4 tile rows
+    const int lin = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (lin >= g.tiles_i * g.tiles_j) return;
+    const int grp_sz = 4 * g.tiles_j;
+    const int first_i = lin / grp_sz * 4, within = lin % grp_sz;
+    const int rows_in = min(4, g.tiles_i - first_i);
+    const int i0 = (first_i + within % rows_in) * R, j0 = within / rows_in * R;
+
+    const int wr0 = R == 64 ? (wave >> 1) * 32 : 0, wc0 = R == 64 ? (wave & 1) * 32 : 0;
+    const int blk0 = R == 64 ? 0 : wave * BLOCKS;
+
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+
+    // While stage k is multiplied, stage k + 1 (requested during stage k - 1) goes from registers
+    // to the other LDS buffer and stage k + 2 is requested, a piece at a time between the blocks
+    // of MFMAs.  (Written at the end of the stage instead, after its MFMAs, a lone workgroup on a
+    // compute unit took 1.5 us per stage of R = 64 where the MFMAs take 0.85; now 1.1.)
+    LA la;
+    LB lb;
+    const int KT = (g.C + BK - 1) / BK;
+    la.init(g.A, i0, g.I, g.C, tid);
+    lb.init(g.B, j0, g.J, g.C, tid);
+    auto begin = [&](int kt) { la.begin(g.A, kt * BK, g.C, tid); lb.begin(g.B, kt * BK, g.C, tid); };
+    auto fetch = [&](int kt, auto piece) {
+        la.template fetch<decltype(piece)::value>(g.A, kt * BK, g.C, tid);
+        lb.template fetch<decltype(piece)::value>(g.B, kt * BK, g.C, tid);
+    };
+    auto commit = [&](float* stage, int kt, auto piece, auto tail) {
+        la.template commit<decltype(piece)::value, decltype(tail)::value>(stage, kt * BK, g.C, tid);
+        lb.template commit<decltype(piece)::value, decltype(tail)::value>(stage + OP_WORDS, kt * BK, g.C, tid);
+    };
+    auto all = [](auto f) {
+        f(std::integral_constant<int, 0>());
+        if constexpr (NP > 1) f(std::integral_constant<int, 1>());
+        if constexpr (NP > 2) { f(std::integral_constant<int, 2>()); f(std::integral_constant<int, 3>()); }
+    };
+    begin(0);
+    all([&](auto p) { fetch(0, p); });
+    begin(1);                            // (past the end of a short contraction: valid addresses, zeros)
+    all([&](auto p) { commit(smem, 0, p, std::true_type()); fetch(1, p); });
+    __syncthreads();
+
+    // fetches: there is a stage k + 2; else stage k + 1, if there is one, is the last
+    auto step = [&](int kt, auto commits, auto fetches) {
+        const float* as = smem + (kt & 1) * STAGE;
+        const float* bs = as + OP_WORDS;
+        float* nx = smem + ((kt + 1) & 1) * STAGE;
+        if constexpr (decltype(fetches)::value) begin(kt + 2);
+        f4 a = fragment<LA::P, R>(as, wr0 + l32, blk0, grp), b = fragment<LB::P, R>(bs, wc0 + l32, blk0, grp);
+        all([&](auto piece) {
+            constexpr int PC = decltype(piece)::value;
+            if constexpr (decltype(commits)::value)
+                commit(nx, kt + 1, piece, std::integral_constant<bool, !decltype(fetches)::value>());
+            if constexpr (decltype(fetches)::value) fetch(kt + 2, piece);
+#pragma unroll
+            for (int k = PC * BLOCKS / NP; k < (PC + 1) * BLOCKS / NP; ++k) {
+                f4 an = a, bn = b;
+                if (k + 1 < BLOCKS) {
+                    an = fragment<LA::P, R>(as, wr0 + l32, blk0 + k + 1, grp);
+                    bn = fragment<LB::P, R>(bs, wc0 + l32, blk0 + k + 1, grp);
+                }
+                __builtin_amdgcn_sched_barrier(0);       // the next block's reads stay above this block's MFMAs
+#pragma unroll
+                for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                a = an;
+                b = bn;
+            }
+        });
+        __syncthreads();
+    };
+    int kt = 0;
+    for (; kt + 2 < KT; ++kt) step(kt, std::true_type(), std::true_type());
+    if (kt + 1 < KT) step(kt++, std::true_type(), std::false_type());
+    step(kt, std::false_type(), std::false_type());
+
+    // ---- result tile in LDS ---------------------------------------------------
+    float* Cs = smem;
+    if constexpr (R == 64) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) Cs[(wr0 + (r >> 2) * 8 + grp * 4 + (r & 3)) * CP + wc0 + l32] = acc[r];
+    } else {
+        float* part = smem + R * CP;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[(wave * 32 + (r >> 2) * 8 + grp * 4 + (r & 3)) * 36 + l32] = acc[r];
+        __syncthreads();
+        const int row = tid >> 3, col = (tid & 7) * 4;
+        f4 sum = *(const f4*)(part + row * 36 + col);
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) {
+            const f4 x = *(const f4*)(part + (w * 32 + row) * 36 + col);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += x[e];
+        }
+        *(f4*)(Cs + row * CP + col) = sum;
+    }
+    int* sidx = (int*)(smem + R * CP + PART);
+    const int rows_valid = min(R, g.I - i0), cols_valid = min(R, g.J - j0);
+    const bool scatter_c = g.epilogue == EPI_COL_SCATTER, scatter_r = g.epilogue == EPI_ROW_SCATTER;
+    if (scatter_c && tid < cols_valid) sidx[tid] = clamp_idx(g.keep[j0 + tid], g.out_full);
+    if (scatter_r && tid < rows_valid) sidx[tid] = clamp_idx(g.keep[i0 + tid], g.out_full);
+    __syncthreads();
+
+    if (scatter_c) {
+        // The tile owns the original columns from its first kept column (0 for the first tile) up to
+        // the next tile's first kept column (the full width for the last tile).  A table says which
+        // result column, if any, belongs to each; then whole rows of owned columns leave, kept and
+        // imputed ones together, 256 contiguous bytes per wavefront.
+        int* tab = sidx + 2 * R;
+        const int start = j0 == 0 ? 0 : sidx[0];
+        const int end = j0 + R >= g.J ? g.out_full : clamp_idx(g.keep[j0 + R], g.out_full);
+        for (int base = start; base < end; base += TAB) {
+            const int width = min(TAB, end - base);
+            for (int q = tid; q < width; q += NT) tab[q] = -1;
+            __syncthreads();
+            if (tid < cols_valid) {
+                const int p = sidx[tid] - base;
+                if (p >= 0 && p < width) tab[p] = tid;
+            }
+            __syncthreads();
+            for (int q = lane; q < width; q += 64) {
+                const int jj = tab[q];
+                float* o = g.out + (size_t)i0 * (size_t)g.ldo + base + q;
+                const float* pv = g.prev ? g.prev + (size_t)i0 * (size_t)g.ldo + base + q : nullptr;
+                constexpr int UB = R / WAVES / 2;
+                for (int r0 = wave; r0 < rows_valid; r0 += WAVES * UB) {
+                    float x[UB];
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) {
+                        const int row = min(r0 + WAVES * u, rows_valid - 1);
+                        x[u] = jj >= 0 ? Cs[row * CP + jj] : 0.f;
+                        if (jj < 0 && pv) x[u] = pv[(size_t)row * (size_t)g.ldo];
+                    }
+#pragma unroll
+                    for (int u = 0; u < UB; ++u)
+                        if (r0 + WAVES * u < rows_valid) o[(size_t)(r0 + WAVES * u) * (size_t)g.ldo] = x[u];
+                }
+            }
+            __syncthreads();
+        }
+        return;
+    }
+
+    constexpr int CPR = R / 4;
+#pragma unroll
+    for (int it = 0; it < R * CPR / NT; ++it) {
+        const int q = tid + NT * it;
+        const int row = q / CPR, j = (q % CPR) * 4;
+        if (row >= rows_valid || j >= cols_valid) continue;
+        float* o = g.out + (size_t)(scatter_r ? sidx[row] : i0 + row) * (size_t)g.ldo + j0 + j;
+        f4 x = *(const f4*)(Cs + row * CP + j);
+        if (j + 4 <= cols_valid && g.out_vec) {
+            if (g.accumulate) x += *(const f4*)o;
+            *(f4*)o = x;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j + e < cols_valid) o[e] = g.accumulate ? o[e] + x[e] : x[e];
+        }
+    }
+    if (scatter_r) {
+        // the dropped rows this tile owns (same ownership rule as above): every lane looks one row
+        // up, the wavefront then writes the dropped ones together
+        const int start = i0 == 0 ? 0 : sidx[0];
+        const int end = i0 + R >= g.I ? g.out_full : clamp_idx(g.keep[i0 + R], g.out_full);
+        for (int base = start + wave * 64; base < end; base += NT) {
+            const int mine = base + lane;
+            bool dropped = false;
+            if (mine < end) {
+                const int ii = lower_bound_lds(sidx, rows_valid, mine);
+                dropped = !(ii < rows_valid && sidx[ii] == mine);
+            }
+            unsigned long long todo = __ballot(dropped);
+            while (todo) {
+                const int p = base + (__ffsll((long long)todo) - 1);
+                todo &= todo - 1;
+                if (lane < cols_valid) {
+                    const size_t off = (size_t)p * (size_t)g.ldo + j0 + lane;
+                    g.out[off] = g.prev ? g.prev[off] : 0.f;
+                }
+            }
+        }
+    }
+}
+
+template <template <int> class LA, template <int> class LB, int R>
+int launch_inst(const Args& a, hipStream_t stream)
+{
+    constexpr int smem = 2 * 2 * Geo<R>::WORDS * 4;
+    auto fn = f32_kernel<LA, LB, R>;
+    static AttrFlags attr_set;      // per instantiation and device
+    if (!ensure_max_dynamic_lds((const void*)fn, smem, &attr_set)) return ZR_ERR_HIP;
+    if (debug_names_wanted())
+        snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "f32_kernel<%s, %s, %d>", LA<R>::NAME, LB<R>::NAME, R);
+    Args k = a;
+    k.tiles_i = (a.I + R - 1) / R;
+    k.tiles_j = (a.J + R - 1) / R;
+    const int64_t tiles = (int64_t)k.tiles_i * k.tiles_j;
+    if (tiles > 0x7ffffff0) return ZR_ERR_LIMIT;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(NT), smem, stream, k);
+    return hip_status(hipGetLastError());
+}
+
+template <template <int> class LA, template <int> class LB>
+int launch_shape(const Args& a, hipStream_t stream)
+{
+    // 64 x 64 tiles once there is one for most compute units (contraction 1024: 128 tiles 22.0 us
+    // against 15.2 on 32 x 32, 192 tiles 22.7 against 21.8, 256 tiles 23.3 against 27.8, 512 tiles
+    // 41.1 against 52.1)
+    const int64_t t64 = (int64_t)((a.I + 63) / 64) * ((a.J + 63) / 64);
+    return t64 < 192 ? launch_inst<LA, LB, 32>(a, stream) : launch_inst<LA, LB, 64>(a, stream);
+}
+
+}  // namespace
+
+int launch_gemm_f32(const GemmDesc& d, hipStream_t stream)
+{
+    if (d.I < 1 || d.J < 1 || d.C < 1) return ZR_ERR_SHAPE;
+    Args a;
+    a.A = View{(const float*)d.A.base, d.A.ld, d.A.map_strided, d.A.map_contig, d.A.n_strided, d.A.n_contig};
+    a.B = View{(const float*)d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
+    a.I = d.I; a.J = d.J; a.C = d.C;
+    a.out = (float*)d.out; a.ldo = d.ldo; a.epilogue = d.epilogue; a.keep = d.keep_idx; a.out_full = d.out_full;
+    a.out_vec = (uintptr_t)d.out % 16 == 0 && d.ldo % 4 == 0;
+    a.tiles_i = a.tiles_j = 0;
+    a.prev = (const float*)d.prev; a.accumulate = d.accumulate ? 1 : 0;
+    const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
+    auto too_short = [&](const Operand& o) { return !o.map_contig && (o.c_contig ? d.C : o.n_contig) < 4; };
+    if (too_short(d.A) || too_short(d.B)) {
+        if (d.A.c_contig) return d.B.c_contig ? launch_inst<AnyP, AnyP, 32>(a, stream) : launch_inst<AnyP, AnyQ, 32>(a, stream);
+        return d.B.c_contig ? ZR_ERR_MODE : launch_inst<AnyQ, AnyQ, 32>(a, stream);
+    }
+    if (d.A.c_contig && !d.B.c_contig) {            // forward, weight stored [K x N]
+        if (ag) return bg ? ZR_ERR_MODE : launch_shape<GatherP, PlainQ>(a, stream);
+        return bg ? launch_shape<PlainP, GatherQ>(a, stream) : launch_shape<PlainP, PlainQ>(a, stream);
+    }
+    if (d.A.c_contig && d.B.c_contig) {
+        if (ag) return bg ? launch_shape<GatherP, GatherP>(a, stream) : launch_shape<GatherP, PlainP>(a, stream);
+        return bg ? launch_shape<PlainP, GatherP>(a, stream) : launch_shape<PlainP, PlainP>(a, stream);
+    }
+    if (!d.A.c_contig && !d.B.c_contig) {           // dW
+        if (ag) return bg ? ZR_ERR_MODE : launch_shape<GatherQ, PlainQ>(a, stream);
+        return bg ? launch_shape<PlainQ, GatherQ>(a, stream) : launch_shape<PlainQ, PlainQ>(a, stream);
+    }
+    return ZR_ERR_MODE;
+}
+
+}  // namespace zr
