@@ -109,7 +109,7 @@ int gemm_with_average(GemmDesc& d, float* sums, void* out, int64_t ld, int rows,
                       const int32_t* keep_idx, int n_keep, int dtype, hipStream_t s)
 {
     int st;
-    if (sums) {
+    if (sums && gemm_fast_eligible(d)) {
         const int len = axis == 1 ? rows : cols;
         const int slots = (n_keep + 127) / 128;
         st = launch_zero_f32(sums, (size_t)slots * (size_t)len, s);
@@ -294,7 +294,7 @@ int zr_resized_linear_fwd(const void* X, int64_t ldx, const void* W, int64_t ldw
     hipStream_t s = (hipStream_t)stream;
     const int32_t* S = full ? nullptr : keep_idx;
     const bool average = mode == ZR_DROP_N && policy == ZR_IMPUTE_AVERAGE && !full;
-    // (the fp32 products leave no sums: their means come from the stand-alone pass)
+    // (fp32 products leave no sums: their means come from the stand-alone pass)
     float* sums = average && dtype == ZR_BF16 ? carve_avg(workspace, workspace_bytes, avg_bytes(M, n_keep)) : nullptr;
 
     GemmDesc d;

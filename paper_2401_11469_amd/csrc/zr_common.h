@@ -103,7 +103,8 @@ struct AttrFlags {
 bool ensure_max_dynamic_lds(const void* fn, int bytes, void* flags16);
 int launch_gemm(const GemmDesc& d, hipStream_t stream);
 int launch_gemm_fast(const GemmDesc& d, hipStream_t stream);   // -1: not eligible
-int launch_gemm_f32(const GemmDesc& d, hipStream_t stream);    // avg_partial is not supported
+bool gemm_fast_eligible(const GemmDesc& d);                    // (only these products leave the sums of Average imputation)
+int launch_gemm_f32(const GemmDesc& d, hipStream_t stream);
 int launch_select(const float* scores, int n, int batch, int n_keep,
                   int32_t* keep_idx, int32_t* drop_idx, int64_t ld_idx, hipStream_t stream);
 // one long vector on many workgroups, with caller scratch of select_wide_workspace_bytes()

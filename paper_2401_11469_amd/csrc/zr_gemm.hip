@@ -1,30 +1,31 @@
-// Gather-fused MFMA GEMM for the resized shard products (paper Sec. 3.1:
-// forward, grad_output and grad_weight of the pruned layer), gfx950 only.
-//
-// Every product is computed in the canonical form
+// Gather-fused MFMA products of bf16 tensors of any alignment and any extents (gfx950): the
+// resized layer's forward, dX and dW (paper Sec. 3.1) in the canonical form
 //     D[i, j] = sum_c A(i, c) * B(j, c)
-// on 64-wide wavefronts with the 32x32x16 MFMA, fp32 accumulation, for bf16 tensors that the
-// fast path does not take.  The kept-index list is applied while the
-// operand tiles travel from HBM into LDS, so no compacted copy of W (or of any
-// other operand) ever exists in memory, and the epilogue writes the result at
-// its original positions together with the zeros of the dropped positions, so
-// the output has its normal shape after one pass (the paper's "recover +
-// impute" fused into the product).
+// on 64-wide wavefronts with the 16 x 16 x 32 MFMA and fp32 accumulation, for what the kernels
+// with 16-byte aligned rows do not take.  The kept-index list is applied while the operand tiles
+// travel into LDS, and the epilogue writes the result at its original positions together with the
+// imputed values, so no compacted copy of an operand exists and one pass gives the normal shape.
 //
-// LDS tile formats (32-bit words; a bf16 word holds two consecutive
-// contraction indices c, c+1 of one row):
-//   P  [row][word]  for tensors whose contiguous axis is the contraction axis
-//   Q  [word][row]  for tensors whose contiguous axis is the other axis; the
-//      two bf16 halves of a word come from two consecutive memory rows, which
-//      is what turns the "transposed" operand into MFMA's per-lane k-vectors
-//      without any LDS transpose.
-// Loader kinds per operand:
-//   VEC   16-byte global loads (optionally through a row list: gathers whole
-//         rows, e.g. W[S,:])
-//   ELEM  element loads through an index list on the contiguous axis (e.g.
-//         X[:,S], W[:,S]) - two bf16 loads are packed into one LDS word - and
-//         the fallback for unaligned tensors.
+// What bounds it.  Not the matrix cores: loads of 2-byte granularity that are waited for, and a
+// chip that is not full.  So
+//   * no load stands under a branch (at a join the compiler waits for every load in flight): rows
+//     and columns are clamped, a chunk at the end of a row is read from the row's last elements and
+//     shifted into place, contraction indices past the end become zeros on the way into LDS;
+//   * a stage is 16 KB of each operand, requested two stages ahead;
+//   * plain operands come in 16-byte loads at 2-byte alignment; kept columns come as the dword that
+//     starts at the element (loads of 16 bits run at a quarter of the rate), two to an LDS word;
+//   * tiles of 128 x 128, 64 x 64 or 32 x 32 by how many of them there are; the 32 x 32 tiles split
+//     each stage's contraction over the four wavefronts.
+// Measured against the kernel before this one (128 x 128 tiles, element loads under branches; three
+// quarters of an axis kept): 985 x 1001 x 771 forward 151 -> 18 us, both backward products 253 -> 38;
+// 4095 x 2001 x 1999 forward 544 -> 120 us (205 TFLOP/s), backward 1570 -> 229; accumulating
+// 8192 x 4096 x 229 from misaligned rows 201 -> 70 us.
+//
+// LDS formats (bf16):
+//   P  [row][contraction]  tensors whose contiguous axis is the contraction axis: ds_read_b128
+//   Q  [contraction][row]  tensors whose contiguous axis is the other one: transposing reads
 #include <cstdio>
+#include <type_traits>
 
 #include "zr_common.h"
 
@@ -32,316 +33,305 @@ namespace zr {
 
 namespace {
 
-constexpr int NT = 256;          // threads per workgroup: 4 wavefronts as 2 x 2
-constexpr int BKD = 32;          // contraction depth of one LDS tile, in 32-bit words
-constexpr int PP = BKD + 4;      // row pitch of format P (words): keeps 16-byte alignment
+constexpr int NT = 256;          // threads per workgroup
+constexpr int NP = 4;            // pieces a stage is brought in: 16 bytes of each operand per thread
 
+typedef uint16_t E;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short v4i16 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(2)));      // 16 bytes at any element
+typedef uint32_t u1_any __attribute__((aligned(2)));                          // 4 bytes at any element
 
-template <int DT> struct Ty;
-template <> struct Ty<ZR_BF16> {
-    typedef uint16_t E;
-    static constexpr int EPD = 2;       // elements per 32-bit word
-    static constexpr int DPL = 4;       // words per lane per MFMA
-    static constexpr int KDM = 8;       // words of contraction per MFMA (16 elements)
-    static constexpr int CPAD = 8;      // C tile pitch padding (elements)
-    static __device__ __forceinline__ uint32_t pack(const E* v) { return (uint32_t)v[0] | ((uint32_t)v[1] << 16); }
-    static __device__ __forceinline__ E from_f32(float f) { return (E)f32_to_bf16_bits(f); }
-    static __device__ __forceinline__ float to_f32(E v) { return bf16_bits_to_f32(v); }
+// R x R tiles, BK contraction indices a stage (16 KB of each operand)
+template <int R> struct Geo {
+    static constexpr int BK = 8192 / R;
+    static constexpr int PP = BK / 2 + 4;                 // words per row of format P: 16 rows of a fragment on 16 bank groups
+    static constexpr int PQ = R / 2;                      // words per contraction index of format Q (swizzled)
+    static constexpr int WORDS = R * PP;                  // LDS words of one operand's stage (the larger format)
+    static_assert(WORDS >= BK * PQ, "format P is the larger one");
+    // Format Q keeps 16-byte chunk `ch` of contraction index c at chunk ch ^ swz(c).  The transposing
+    // reads of 32 lanes take 32 bytes from each of the contraction indices 8 g .. 8 g + 3 and
+    // 8 g + 8 .. 8 g + 11: the swizzle gives these eight pieces eight different groups of 8 banks.
+    static __device__ __forceinline__ constexpr int swz(int c)
+    {
+        return R == 128 ? 2 * ((c & 3) | ((c >> 1) & 4)) : R == 64 ? 2 * (((c >> 1) & 1) | ((c >> 2) & 2)) : 2 * ((c >> 3) & 1);
+    }
 };
-struct OpView {
-    const void* base;
+
+struct View {
+    const E* base;
     int64_t ld;
-    const int32_t* map_s;   // list on the strided axis or nullptr
-    const int32_t* map_c;   // list on the contiguous axis or nullptr
-    int n_s, n_c;           // memory extents (for clamping list entries)
+    const int32_t* map_s;       // row list on the strided axis or nullptr
+    const int32_t* map_c;       // kept list on the contiguous axis or nullptr (the gathering loaders)
+    int n_s, n_c;               // memory extents
 };
 
-struct KArgs {
-    OpView A, B;
+struct Args {
+    View A, B;
     int I, J, C;
-    void* out;
+    E* out;
     int64_t ldo;
     int epilogue;
     const int32_t* keep;
     int out_full;
-    int out_vec;            // output rows allow 16-byte stores
-    int tiles_j;
-    const void* prev;       // Same imputation source (layout of out) or nullptr
-    int accumulate;         // add the old contents of out (plain epilogue)
-    float* avg_partial;     // Average imputation: per-tile sums of the stored results, or nullptr
-    int avg_len;            // entries per slot of avg_partial
+    int tiles_i, tiles_j;
+    const E* prev;              // Same imputation source (layout of out) or nullptr
+    int accumulate;             // add the old contents of out (plain epilogue)
 };
 
-// ---------------------------------------------------------------------------
-// Operand loaders.  R = rows of the tile along the operand's non-contraction
-// index (BM for A, BN for B).  Each loader keeps one tile in registers
-// (fetch) and later writes it to LDS (commit), so the global loads of tile
-// k+1 overlap the MFMAs of tile k.
-// ---------------------------------------------------------------------------
-
-// Format P, vector loads: 8 chunks of 4 words per row.
-template <int DT, int R>
-struct LoadPVec {
-    typedef typename Ty<DT>::E E;
-    static constexpr int EPD = Ty<DT>::EPD;
-    static constexpr int N = R / 32;            // chunks per thread
-    static constexpr int LDS_WORDS = R * PP;
-    const E* rowptr[N];
-    uint4 v[N];
-
-    __device__ __forceinline__ void init(const OpView& op, int r0, int rlim, int tid)
-    {
-#pragma unroll
-        for (int it = 0; it < N; ++it) {
-            const int row = (tid + NT * it) >> 3;
-            const int i = r0 + row;
-            if (i < rlim) {
-                const int srow = op.map_s ? clamp_idx(op.map_s[i], op.n_s) : i;
-                rowptr[it] = (const E*)op.base + (size_t)srow * (size_t)op.ld;
-            } else {
-                rowptr[it] = nullptr;
-            }
-        }
-    }
-    __device__ __forceinline__ void fetch(const OpView&, int c0, int C, int tid)
-    {
-#pragma unroll
-        for (int it = 0; it < N; ++it) {
-            const int ch = (tid + NT * it) & 7;
-            const int c = c0 + ch * 4 * EPD;
-            uint4 val = make_uint4(0, 0, 0, 0);
-            if (rowptr[it] != nullptr && c < C) {
-                if (c + 4 * EPD <= C) {
-                    val = *(const uint4*)(rowptr[it] + c);
-                } else {
-                    uint32_t w[4];
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        E e[2] = {E(0), E(0)};
-#pragma unroll
-                        for (int q = 0; q < EPD; ++q) {
-                            const int cc = c + d * EPD + q;
-                            if (cc < C) e[q] = rowptr[it][cc];
-                        }
-                        w[d] = Ty<DT>::pack(e);
-                    }
-                    val = make_uint4(w[0], w[1], w[2], w[3]);
-                }
-            }
-            v[it] = val;
-        }
-    }
-    __device__ __forceinline__ void commit(uint32_t* lds, int tid) const
-    {
-#pragma unroll
-        for (int it = 0; it < N; ++it) {
-            const int q = tid + NT * it;
-            *(uint4*)(lds + (q >> 3) * PP + (q & 7) * 4) = v[it];
-        }
-    }
-};
-
-// Format P, element loads through optional lists on both axes.
-template <int DT, int R>
-struct LoadPElem {
-    typedef typename Ty<DT>::E E;
-    static constexpr int EPD = Ty<DT>::EPD;
-    static constexpr int N = R / 8;             // words per thread
-    static constexpr int LDS_WORDS = R * PP;
-    int r0_, rlim_;
-    uint32_t v[N];
-
-    __device__ __forceinline__ void init(const OpView&, int r0, int rlim, int) { r0_ = r0; rlim_ = rlim; }
-    __device__ __forceinline__ void fetch(const OpView& op, int c0, int C, int tid)
-    {
-        const int kd = tid & 31;
-        int col[2];
-        bool ok[2];
-#pragma unroll
-        for (int q = 0; q < EPD; ++q) {
-            const int c = c0 + kd * EPD + q;
-            ok[q] = c < C;
-            col[q] = 0;
-            if (ok[q]) col[q] = op.map_c ? clamp_idx(op.map_c[c], op.n_c) : c;
-        }
-#pragma unroll
-        for (int it = 0; it < N; ++it) {
-            const int i = r0_ + (tid >> 5) + 8 * it;
-            E e[2] = {E(0), E(0)};
-            if (i < rlim_) {
-                const int srow = op.map_s ? clamp_idx(op.map_s[i], op.n_s) : i;
-                const E* p = (const E*)op.base + (size_t)srow * (size_t)op.ld;
-#pragma unroll
-                for (int q = 0; q < EPD; ++q)
-                    if (ok[q]) e[q] = p[col[q]];
-            }
-            v[it] = Ty<DT>::pack(e);
-        }
-    }
-    __device__ __forceinline__ void commit(uint32_t* lds, int tid) const
-    {
-#pragma unroll
-        for (int it = 0; it < N; ++it)
-            lds[((tid >> 5) + 8 * it) * PP + (tid & 31)] = v[it];
-    }
-};
-
-// Format Q, vector loads.  bf16: a unit is 8 rows-of-the-tile x 2 memory rows
-// (c, c+1), interleaved into 8 words.
-template <int DT, int R>
-struct LoadQVec {
-    typedef typename Ty<DT>::E E;
-    static constexpr int EPD = Ty<DT>::EPD;
-    static constexpr int PQ = R + 8;
-    static constexpr int LDS_WORDS = BKD * PQ;
-    static constexpr int JCH = (DT == ZR_BF16) ? 8 : 4;        // tile rows per unit
-    static constexpr int UPR = R / JCH;                         // units per word-row
-    static constexpr int N = BKD * UPR / NT;                    // units per thread
-    int r0_, rlim_;
-    uint4 lo[N];
-    uint4 hi[(DT == ZR_BF16) ? N : 1];
-
-    __device__ __forceinline__ void init(const OpView&, int r0, int rlim, int) { r0_ = r0; rlim_ = rlim; }
-
-    __device__ __forceinline__ uint4 load_row(const OpView& op, int c, int C, int j) const
-    {
-        uint4 val = make_uint4(0, 0, 0, 0);
-        if (c < C && j < rlim_) {
-            const int srow = op.map_s ? clamp_idx(op.map_s[c], op.n_s) : c;
-            const E* p = (const E*)op.base + (size_t)srow * (size_t)op.ld + j;
-            if (j + JCH <= rlim_) {
-                val = *(const uint4*)p;
-            } else {
-                E e[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) e[q] = (q < JCH && j + q < rlim_) ? p[q] : E(0);
-                if constexpr (DT == ZR_BF16)
-                    val = make_uint4(Ty<DT>::pack(e), Ty<DT>::pack(e + 2), Ty<DT>::pack(e + 4), Ty<DT>::pack(e + 6));
-                else
-                    val = make_uint4(Ty<DT>::pack(e), Ty<DT>::pack(e + 1), Ty<DT>::pack(e + 2), Ty<DT>::pack(e + 3));
-            }
-        }
-        return val;
-    }
-    __device__ __forceinline__ void fetch(const OpView& op, int c0, int C, int tid)
-    {
-#pragma unroll
-        for (int it = 0; it < N; ++it) {
-            const int q = tid + NT * it;
-            const int kd = q / UPR;
-            const int j = r0_ + (q % UPR) * JCH;
-            if constexpr (DT == ZR_BF16) {
-                lo[it] = load_row(op, c0 + 2 * kd, C, j);
-                hi[it] = load_row(op, c0 + 2 * kd + 1, C, j);
-            } else {
-                lo[it] = load_row(op, c0 + kd, C, j);
-            }
-        }
-    }
-    __device__ __forceinline__ void commit(uint32_t* lds, int tid) const
-    {
-#pragma unroll
-        for (int it = 0; it < N; ++it) {
-            const int q = tid + NT * it;
-            uint32_t* dst = lds + (q / UPR) * PQ + (q % UPR) * JCH;
-            if constexpr (DT == ZR_BF16) {
-                const uint32_t a[4] = {lo[it].x, lo[it].y, lo[it].z, lo[it].w};
-                const uint32_t b[4] = {hi[it].x, hi[it].y, hi[it].z, hi[it].w};
-                uint32_t w[8];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    w[2 * t] = (a[t] & 0xffffu) | (b[t] << 16);
-                    w[2 * t + 1] = (a[t] >> 16) | (b[t] & 0xffff0000u);
-                }
-                *(uint4*)dst = make_uint4(w[0], w[1], w[2], w[3]);
-                *(uint4*)(dst + 4) = make_uint4(w[4], w[5], w[6], w[7]);
-            } else {
-                *(uint4*)dst = lo[it];
-            }
-        }
-    }
-};
-
-// Format Q, element loads: thread <-> one tile row j (its memory column is
-// looked up once per tile), looping over the words of the contraction tile.
-template <int DT, int R>
-struct LoadQElem {
-    typedef typename Ty<DT>::E E;
-    static constexpr int EPD = Ty<DT>::EPD;
-    static constexpr int PQ = R + 8;
-    static constexpr int LDS_WORDS = BKD * PQ;
-    static constexpr int N = R / 8;             // words per thread
-    static constexpr int KSTEP = NT / R > 0 ? NT / R : 1;
-    static_assert(R <= NT, "tile rows beyond the thread count are not laid out");
-    int col_;
-    bool okj_;
-    uint32_t v[N];
-
-    __device__ __forceinline__ void init(const OpView& op, int r0, int rlim, int tid)
-    {
-        const int j = r0 + (tid % R);
-        okj_ = j < rlim;
-        col_ = 0;
-        if (okj_) col_ = op.map_c ? clamp_idx(op.map_c[j], op.n_c) : j;
-    }
-    __device__ __forceinline__ void fetch(const OpView& op, int c0, int C, int tid)
-    {
-#pragma unroll
-        for (int it = 0; it < N; ++it) {
-            const int kd = tid / R + KSTEP * it;
-            E e[2] = {E(0), E(0)};
-#pragma unroll
-            for (int q = 0; q < EPD; ++q) {
-                const int c = c0 + kd * EPD + q;
-                if (okj_ && c < C) {
-                    const int srow = op.map_s ? clamp_idx(op.map_s[c], op.n_s) : c;
-                    e[q] = ((const E*)op.base)[(size_t)srow * (size_t)op.ld + col_];
-                }
-            }
-            v[it] = Ty<DT>::pack(e);
-        }
-    }
-    __device__ __forceinline__ void commit(uint32_t* lds, int tid) const
-    {
-#pragma unroll
-        for (int it = 0; it < N; ++it)
-            lds[(tid / R + KSTEP * it) * PQ + (tid % R)] = v[it];
-    }
-};
-
-template <int DT, bool CC, bool VEC, int R> struct PickLoader;
-template <int DT, int R> struct PickLoader<DT, true, true, R> { typedef LoadPVec<DT, R> type; };
-template <int DT, int R> struct PickLoader<DT, true, false, R> { typedef LoadPElem<DT, R> type; };
-template <int DT, int R> struct PickLoader<DT, false, true, R> { typedef LoadQVec<DT, R> type; };
-template <int DT, int R> struct PickLoader<DT, false, false, R> { typedef LoadQElem<DT, R> type; };
-
-// ---------------------------------------------------------------------------
-// MFMA fragment reads
-// ---------------------------------------------------------------------------
-template <int DT, bool CC, int R> struct Frag;
-
-template <bool CC, int R> struct Frag<ZR_BF16, CC, R> {
-    typedef bf16x8 type;
-    // row: tile row of this lane; kd: first word of this lane's 4-word k-vector
-    static __device__ __forceinline__ type read(const uint32_t* lds, int row, int kd)
-    {
-        union { uint4 u; bf16x8 b; } x;
-        if (CC) {
-            x.u = *(const uint4*)(lds + row * PP + kd);
-        } else {
-            constexpr int PQ = R + 8;
-            x.u = make_uint4(lds[kd * PQ + row], lds[(kd + 1) * PQ + row],
-                             lds[(kd + 2) * PQ + row], lds[(kd + 3) * PQ + row]);
-        }
-        return x.b;
-    }
-};
-__device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c)
+// element e of the result is element e + sh of v, 0 past its end (sh >= 0)
+__device__ __forceinline__ u4 shifted(u4 v, int sh)
 {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    const uint64_t lo = (uint64_t)v.x | ((uint64_t)v.y << 32), hi = (uint64_t)v.z | ((uint64_t)v.w << 32);
+    const int s = 16 * (sh & 3);
+    const uint64_t a = s ? (lo >> s) | (hi << (64 - s)) : lo, b = hi >> s;
+    const uint64_t l = sh >= 8 ? 0 : sh >= 4 ? b : a, h = sh >= 4 ? 0 : b;
+    u4 r;
+    r.x = (uint32_t)l; r.y = (uint32_t)(l >> 32); r.z = (uint32_t)h; r.w = (uint32_t)(h >> 32);
+    return r;
 }
+
+// ---------------------------------------------------------------------------
+// Loaders.  Both LDS formats are lines (P: tile rows, Q: contraction indices) of elements that are
+// neighbours in memory.  A loader keeps one stage of its operand in registers (begin, then fetch of
+// four pieces) and writes it to LDS a stage later (commit, piece by piece).  Tile rows beyond the
+// operand's extent repeat its last row (they only feed results that are never stored);
+// contraction indices past C become zero (commit with TAIL, which only the last stage needs).
+// ---------------------------------------------------------------------------
+template <int R, bool P> struct Lines {
+    static constexpr int BK = Geo<R>::BK;
+    static constexpr int COUNT = P ? R : BK;              // lines of a stage
+    static constexpr int LEN = P ? BK : R;                // elements of a line
+    // LDS word of 16-byte chunk ch of a line
+    static __device__ __forceinline__ int chunk_at(int line, int ch)
+    {
+        return P ? line * Geo<R>::PP + ch * 4 : line * Geo<R>::PQ + (ch ^ Geo<R>::swz(line)) * 4;
+    }
+};
+
+// No list on the contiguous axis, which has at least 8 elements; optional row list.
+template <int R, bool P_> struct Plain {
+    static constexpr bool P = P_;
+    typedef Lines<R, P> L;
+    static constexpr int CPL = L::LEN / 8, LPP = NT / CPL;       // chunks per line, lines per piece
+    static_assert(L::COUNT == NP * LPP, "four pieces");
+    const E* ptr[NP];       // P: the lines; Q: the lines of the stage being fetched, at this thread's column
+    const E* colp;
+    int row_[NP];           // Q: memory rows of the next stage
+    int off_;               // P: element offset of the stage being fetched
+    int sh_;                // Q: how far the clamp moved the column
+    bool edge_;             // Q, uniform: the tile reaches past the stored rows' end
+    u4 v[NP];
+
+    __device__ __forceinline__ void rows_for(const View& op, int c0, int C, int tid)
+    {
+#pragma unroll
+        for (int it = 0; it < NP; ++it) row_[it] = min(c0 + tid / CPL + LPP * it, C - 1);
+        if (op.map_s) {
+#pragma unroll
+            for (int it = 0; it < NP; ++it) row_[it] = op.map_s[row_[it]];
+        }
+    }
+    __device__ __forceinline__ void init(const View& op, int r0, int rlim, int C, int tid)
+    {
+        if constexpr (P) {
+            int row[NP];
+#pragma unroll
+            for (int it = 0; it < NP; ++it) row[it] = min(r0 + tid / CPL + LPP * it, rlim - 1);
+            if (op.map_s) {
+#pragma unroll
+                for (int it = 0; it < NP; ++it) row[it] = op.map_s[row[it]];
+#pragma unroll
+                for (int it = 0; it < NP; ++it) row[it] = clamp_idx(row[it], op.n_s);
+            }
+#pragma unroll
+            for (int it = 0; it < NP; ++it) ptr[it] = op.base + (size_t)row[it] * (size_t)op.ld;
+        } else {
+            const int col = r0 + (tid % CPL) * 8, cc = min(col, op.n_c - 8);
+            edge_ = r0 + R > op.n_c;
+            sh_ = col - cc;
+            colp = op.base + cc;
+            rows_for(op, 0, C, tid);
+        }
+    }
+    __device__ __forceinline__ void begin(const View& op, int c0, int C, int tid)
+    {
+        if constexpr (P) {
+            // a chunk that would reach past the contraction range is read from its last eight
+            // elements and shifted into place by commit
+            off_ = min(c0 + (tid % CPL) * 8, C - 8);
+        } else {
+#pragma unroll
+            for (int it = 0; it < NP; ++it) ptr[it] = colp + (size_t)clamp_idx(row_[it], op.n_s) * (size_t)op.ld;
+            rows_for(op, c0 + L::BK, C, tid);
+        }
+    }
+    template <int PC> __device__ __forceinline__ void fetch(const View&, int, int, int)
+    {
+        v[PC] = *(const u4_any*)(P ? ptr[PC] + off_ : ptr[PC]);
+    }
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(uint32_t* lds, int c0, int C, int tid) const
+    {
+        const int line = tid / CPL + LPP * PC;
+        u4 x = v[PC];
+        if constexpr (P) {
+            if constexpr (TAIL) {
+                const int c = c0 + (tid % CPL) * 8;
+                x = shifted(x, c - min(c, C - 8));
+            }
+        } else {
+            if (edge_) x = shifted(x, sh_);
+            if constexpr (TAIL) {
+                const bool ok = c0 + line < C;
+                x.x = ok ? x.x : 0u; x.y = ok ? x.y : 0u; x.z = ok ? x.z : 0u; x.w = ok ? x.w : 0u;
+            }
+        }
+        *(u4*)(lds + L::chunk_at(line, tid % CPL)) = x;
+    }
+};
+
+// Kept list on the contiguous axis (of at least 2 elements): a thread owns two neighbours of the
+// list, one LDS word, in every line it visits, so a wavefront's load runs along the (ascending)
+// list in one memory row, or a few.
+template <int R, bool P_> struct Gather {
+    static constexpr bool P = P_;
+    typedef Lines<R, P> L;
+    static constexpr int WPL = L::LEN / 2;                       // words per line
+    static constexpr int LPI = NT / WPL;                         // lines per step of the workgroup
+    static constexpr int N = L::COUNT / LPI;                     // words per thread
+    static_assert(N == 4 * NP, "four words a piece");
+    const E* base_;
+    int64_t ld_;
+    int line0_, llast_;     // first line of this thread in memory, last line there is
+    const int32_t* list_;
+    uint32_t a_, b_;        // columns of the stage being fetched
+    int na_, nb_;           // list entries of the one after (P)
+    uint32_t sel_, nsel_;   // byte selectors of the stage being written and of the one being fetched
+    uint32_t lo[N], hi[N];
+
+    // the dword that starts at the element; at the row's last element the one before it
+    __device__ __forceinline__ void columns(int a, int b, int n_c, bool oka, bool okb)
+    {
+        a = clamp_idx(a, n_c);
+        b = clamp_idx(b, n_c);
+        a_ = (uint32_t)min(a, n_c - 2);
+        b_ = (uint32_t)min(b, n_c - 2);
+        // v_perm byte selectors: 0-3 pick from lo, 4-7 from hi, 0x0c gives 0
+        const uint32_t s0 = oka ? ((uint32_t)a == a_ ? 0x0100u : 0x0302u) : 0x0c0cu;
+        const uint32_t s1 = okb ? ((uint32_t)b == b_ ? 0x0504u : 0x0706u) : 0x0c0cu;
+        nsel_ = s0 | (s1 << 16);
+    }
+    __device__ __forceinline__ void entries(int c0, int C, int tid)
+    {
+        na_ = list_[min(c0 + 2 * (tid % WPL), C - 1)];
+        nb_ = list_[min(c0 + 2 * (tid % WPL) + 1, C - 1)];
+    }
+    __device__ __forceinline__ void init(const View& op, int r0, int rlim, int C, int tid)
+    {
+        base_ = op.base; ld_ = op.ld; list_ = op.map_c;
+        nsel_ = 0;
+        if constexpr (P) {
+            line0_ = r0 + tid / WPL;
+            llast_ = rlim - 1;
+            entries(0, C, tid);
+        } else {
+            llast_ = C - 1;
+            const int j = r0 + 2 * (tid % WPL);
+            columns(list_[min(j, rlim - 1)], list_[min(j + 1, rlim - 1)], op.n_c, true, true);
+        }
+    }
+    __device__ __forceinline__ void begin(const View& op, int c0, int C, int tid)
+    {
+        sel_ = nsel_;
+        if constexpr (P) {
+            const int c = c0 + 2 * (tid % WPL);
+            columns(na_, nb_, op.n_c, c < C, c + 1 < C);
+            entries(c0 + L::BK, C, tid);
+        } else {
+            line0_ = c0 + tid / WPL;
+        }
+    }
+    template <int PC> __device__ __forceinline__ void fetch(const View&, int, int, int)
+    {
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
+            int line = min(line0_ + LPI * it, llast_);
+            // (the same for a wavefront whose 64 threads share a line: scalar address arithmetic)
+            if constexpr (WPL >= 64) line = __builtin_amdgcn_readfirstlane(line);
+            const E* row = base_ + (int64_t)line * ld_;
+            lo[it] = *(const u1_any*)(row + a_);
+            hi[it] = *(const u1_any*)(row + b_);
+        }
+    }
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(uint32_t* lds, int c0, int C, int tid) const
+    {
+        const int w = tid % WPL;
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
+            const int line = tid / WPL + LPI * it;
+            uint32_t x = __builtin_amdgcn_perm(hi[it], lo[it], sel_);
+            if constexpr (!P && TAIL) x = c0 + line < C ? x : 0u;
+            lds[L::chunk_at(line, w / 4) + w % 4] = x;
+        }
+    }
+};
+
+// Element by element through whatever lists there are: for products with a contiguous extent
+// below what the loaders above read at a time.
+template <int R, bool P_> struct Any {
+    static constexpr bool P = P_;
+    typedef Lines<R, P> L;
+    static constexpr int WPL = L::LEN / 2, LPI = NT / WPL, N = L::COUNT / LPI;
+    int r0_, rlast_;
+    uint32_t w_[N];
+    __device__ __forceinline__ void init(const View&, int r0, int rlim, int, int) { r0_ = r0; rlast_ = rlim - 1; }
+    __device__ __forceinline__ void begin(const View&, int, int, int) {}
+    __device__ __forceinline__ uint32_t element(const View& op, int c0, int C, int line, int e) const
+    {
+        const int r = min(r0_ + (P ? line : e), rlast_), c = c0 + (P ? e : line), cc = min(c, C - 1);
+        int s = P ? r : cc, t = P ? cc : r;                     // along the strided and the contiguous axis
+        if (op.map_s) s = clamp_idx(op.map_s[s], op.n_s);
+        if (op.map_c) t = clamp_idx(op.map_c[t], op.n_c);
+        const uint32_t x = op.base[(size_t)s * (size_t)op.ld + t];
+        return c < C ? x : 0u;
+    }
+    template <int PC> __device__ __forceinline__ void fetch(const View& op, int c0, int C, int tid)
+    {
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
+            const int line = tid / WPL + LPI * it, e = 2 * (tid % WPL);
+            w_[it] = element(op, c0, C, line, e) | (element(op, c0, C, line, e + 1) << 16);
+        }
+    }
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(uint32_t* lds, int, int, int tid) const
+    {
+        const int w = tid % WPL;
+#pragma unroll
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) lds[L::chunk_at(tid / WPL + LPI * it, w / 4) + w % 4] = w_[it];
+    }
+};
+
+// Operand of a 16 x 16 x 32 MFMA: tile rows r0 .. r0 + 15 (lane & 15), eight contraction indices
+// from 8 (lane >> 4) of the 32 that start at k0.
+template <int R, bool P>
+__device__ __forceinline__ bf16x8 fragment(const uint32_t* lds, int r0, int k0, int lane)
+{
+    union { u4 u; v4i16 h[2]; bf16x8 b; } x;
+    if constexpr (P) {
+        x.u = *(const u4*)(lds + (r0 + (lane & 15)) * Geo<R>::PP + k0 / 2 + 4 * (lane >> 4));
+    } else {
+        // a 16-lane group reads 4 contraction indices x 16 rows; its lane n gets row n's four
+        typedef __attribute__((address_space(3))) v4i16* lp;
+        const int t16 = lane & 15, c = k0 + 8 * (lane >> 4) + (t16 >> 2), col = r0 + 4 * (t16 & 3);
+        const uint32_t* p = lds + c * Geo<R>::PQ + (((col >> 3) ^ Geo<R>::swz(c)) << 2) + ((col & 7) >> 1);
+        x.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)p);
+        x.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 4 * Geo<R>::PQ));       // (the same swizzle)
+    }
+    return x.b;
+}
+
 // first position in the ascending LDS list s[0..n) with s[pos] >= p
 __device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
 {
@@ -353,219 +343,235 @@ __device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
     return lo;
 }
 
-template <int BM, int BN, int DT>
-constexpr int smem_bytes()
-{
-    // operand stages: the larger of the two formats for each operand, two stages
-    constexpr int a_words = BM * PP > BKD * (BM + 8) ? BM * PP : BKD * (BM + 8);
-    constexpr int b_words = BN * PP > BKD * (BN + 8) ? BN * PP : BKD * (BN + 8);
-    constexpr int stage_bytes = 2 * (a_words + b_words) * 4;
-    // epilogue: C tile in the output type plus the index tile
-    constexpr int esz = DT == ZR_BF16 ? 2 : 4;
-    constexpr int c_bytes = BM * (BN + Ty<DT>::CPAD) * esz + (BM > BN ? BM : BN) * 4;
-    return stage_bytes > c_bytes ? stage_bytes : c_bytes;
-}
+__device__ __forceinline__ uint32_t two(float a, float b) { return f32_to_bf16_bits(a) | (f32_to_bf16_bits(b) << 16); }
 
-// ---------------------------------------------------------------------------
-// The kernel
-// ---------------------------------------------------------------------------
-template <int DT, bool ACC, bool AVEC, bool BCC, bool BVEC, int BM, int BN>
-__global__ __launch_bounds__(NT) void gemm_kernel(const KArgs g)
+template <template <int, bool> class LA_, bool AP, template <int, bool> class LB_, bool BP, int R>
+__global__ __launch_bounds__(NT, 2) void gemm_kernel(const Args g)
 {
-    typedef typename Ty<DT>::E E;
-    constexpr int DPL = Ty<DT>::DPL;
-    constexpr int KDM = Ty<DT>::KDM;
-    constexpr int EPD = Ty<DT>::EPD;
-    constexpr int TM = BM / 64, TN = BN / 64;          // 32x32 tiles per wavefront
-    constexpr int A_WORDS = BM * PP > BKD * (BM + 8) ? BM * PP : BKD * (BM + 8);
-    constexpr int B_WORDS = BN * PP > BKD * (BN + 8) ? BN * PP : BKD * (BN + 8);
-    constexpr int CP = BN + Ty<DT>::CPAD;
-    typedef typename PickLoader<DT, ACC, AVEC, BM>::type LA;
-    typedef typename PickLoader<DT, BCC, BVEC, BN>::type LB;
+    typedef LA_<R, AP> LA;
+    typedef LB_<R, BP> LB;
+    constexpr int BK = Geo<R>::BK;
+    constexpr int OP_WORDS = Geo<R>::WORDS, STAGE = 2 * OP_WORDS;
+    constexpr int WAVES = NT / 64;
+    constexpr bool SPLIT = R == 32;                                   // the wavefronts share the contraction, not the tile
+    constexpr int T = SPLIT ? 2 : R / 32;                             // 16 x 16 results per wavefront and direction
+    constexpr int STEPS = (SPLIT ? BK / WAVES : BK) / 32;             // 32-deep steps per wavefront and stage
+    constexpr int CP = R + 4;                                         // row pitch of the result tile (floats)
+    constexpr int TAB = 512;                                          // original columns per pass of the column scatter
+    constexpr int PART = SPLIT ? WAVES * 32 * 36 : 0;                 // the wavefronts' sums
+    static_assert(R * CP + PART + 2 * R + TAB <= 2 * STAGE, "the epilogue fits the stages");
 
     extern __shared__ __align__(16) uint32_t smem[];
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int l32 = lane & 31;
-    const int grp = lane >> 5;
-    const int wr0 = (wave >> 1) * (BM / 2);
-    const int wc0 = (wave & 1) * (BN / 2);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-    const int ti = blockIdx.x / g.tiles_j;
-    const int tj = blockIdx.x % g.tiles_j;
-    const int i0 = ti * BM, j0 = tj * BN;
+    // every XCD gets a contiguous range of tiles, ordered in groups of 4 tile rows
+    const int lin = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
+    if (lin >= g.tiles_i * g.tiles_j) return;
+    const int grp_sz = 4 * g.tiles_j;
+    const int first_i = lin / grp_sz * 4, within = lin % grp_sz;
+    const int rows_in = min(4, g.tiles_i - first_i);
+    const int i0 = (first_i + within % rows_in) * R, j0 = within / rows_in * R;
 
-    constexpr int STAGE_WORDS = A_WORDS + B_WORDS;   // stage s: A tile, then B tile
+    const int wr0 = SPLIT ? 0 : (wave >> 1) * (R / 2), wc0 = SPLIT ? 0 : (wave & 1) * (R / 2);
+    const int k0 = SPLIT ? wave * (BK / WAVES) : 0;
 
-    f32x16 acc[TM][TN];
+    f32x4 acc[T][T];
 #pragma unroll
-    for (int a = 0; a < TM; ++a)
+    for (int a = 0; a < T; ++a)
 #pragma unroll
-        for (int b = 0; b < TN; ++b)
+        for (int b = 0; b < T; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] = 0.f;
-    if (g.accumulate) {
-        // the accumulators start from the old contents of the output (one rounding
-        // at the end); done here, where no other registers are live yet
-        const int rows_in_tile = min(BM, g.I - i0), cols_in_tile = min(BN, g.J - j0);
-        const E* old = (const E*)g.out;
-#pragma unroll
-        for (int a = 0; a < TM; ++a)
-#pragma unroll
-            for (int b = 0; b < TN; ++b)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    // coordinates clamped into the tile instead of a guard: the loads need no
-                    // branches and go out together; accumulators outside the tile are never stored
-                    const int row = min(wr0 + a * 32 + (r >> 2) * 8 + grp * 4 + (r & 3), rows_in_tile - 1);
-                    const int col = min(wc0 + b * 32 + l32, cols_in_tile - 1);
-                    acc[a][b][r] = Ty<DT>::to_f32(old[(size_t)(i0 + row) * (size_t)g.ldo + j0 + col]);
-                }
-    }
+            for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.f;
 
+    // While stage k is multiplied, stage k + 1 (requested during stage k - 1) goes from registers
+    // to the other LDS buffer and stage k + 2 is requested, a piece at a time between the MFMAs.
     LA la;
     LB lb;
-    la.init(g.A, i0, g.I, tid);
-    lb.init(g.B, j0, g.J, tid);
-
-    const int KT = (g.C + BKD * EPD - 1) / (BKD * EPD);
-    la.fetch(g.A, 0, g.C, tid);
-    lb.fetch(g.B, 0, g.C, tid);
-    la.commit(smem, tid);
-    lb.commit(smem + A_WORDS, tid);
+    const int KT = (g.C + BK - 1) / BK;
+    la.init(g.A, i0, g.I, g.C, tid);
+    lb.init(g.B, j0, g.J, g.C, tid);
+    auto begin = [&](int kt) { la.begin(g.A, kt * BK, g.C, tid); lb.begin(g.B, kt * BK, g.C, tid); };
+    auto fetch = [&](int kt, auto piece) {
+        la.template fetch<decltype(piece)::value>(g.A, kt * BK, g.C, tid);
+        lb.template fetch<decltype(piece)::value>(g.B, kt * BK, g.C, tid);
+    };
+    auto commit = [&](uint32_t* stage, int kt, auto piece, auto tail) {
+        la.template commit<decltype(piece)::value, decltype(tail)::value>(stage, kt * BK, g.C, tid);
+        lb.template commit<decltype(piece)::value, decltype(tail)::value>(stage + OP_WORDS, kt * BK, g.C, tid);
+    };
+    auto all = [](auto f) {
+        f(std::integral_constant<int, 0>());
+        f(std::integral_constant<int, 1>());
+        f(std::integral_constant<int, 2>());
+        f(std::integral_constant<int, 3>());
+    };
+    begin(0);
+    all([&](auto p) { fetch(0, p); });
+    begin(1);                            // (past the end of a short contraction: valid addresses, zeros)
+    all([&](auto p) { commit(smem, 0, p, std::true_type()); fetch(1, p); });
     __syncthreads();
 
-    for (int kt = 0; kt < KT; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < KT;
-        if (more) {
-            la.fetch(g.A, (kt + 1) * BKD * EPD, g.C, tid);
-            lb.fetch(g.B, (kt + 1) * BKD * EPD, g.C, tid);
-        }
-        const uint32_t* as = smem + cur * STAGE_WORDS;
-        const uint32_t* bs = as + A_WORDS;
+    // fetches: there is a stage k + 2; else stage k + 1, if there is one, is the last
+    auto step = [&](int kt, auto commits, auto fetches) {
+        const uint32_t* as = smem + (kt & 1) * STAGE;
+        const uint32_t* bs = as + OP_WORDS;
+        uint32_t* nx = smem + ((kt + 1) & 1) * STAGE;
+        if constexpr (decltype(commits)::value) begin(kt + 2);
+        all([&](auto piece) {
+            constexpr int PC = decltype(piece)::value;
+            if constexpr (decltype(commits)::value)
+                commit(nx, kt + 1, piece, std::integral_constant<bool, !decltype(fetches)::value>());
+            if constexpr (decltype(fetches)::value) fetch(kt + 2, piece);
 #pragma unroll
-        for (int step = 0; step < BKD / KDM; ++step) {
-            const int kd = step * KDM + grp * DPL;
-            typename Frag<DT, ACC, BM>::type af[TM];
-            typename Frag<DT, BCC, BN>::type bf[TN];
+            for (int k = PC * STEPS / NP; k < (PC + 1) * STEPS / NP; ++k) {
+                bf16x8 af[T], bf[T];
 #pragma unroll
-            for (int a = 0; a < TM; ++a) af[a] = Frag<DT, ACC, BM>::read(as, wr0 + a * 32 + l32, kd);
+                for (int a = 0; a < T; ++a) af[a] = fragment<R, AP>(as, wr0 + 16 * a, k0 + 32 * k, lane);
 #pragma unroll
-            for (int b = 0; b < TN; ++b) bf[b] = Frag<DT, BCC, BN>::read(bs, wc0 + b * 32 + l32, kd);
+                for (int b = 0; b < T; ++b) bf[b] = fragment<R, BP>(bs, wc0 + 16 * b, k0 + 32 * k, lane);
 #pragma unroll
-            for (int a = 0; a < TM; ++a)
+                for (int a = 0; a < T; ++a)
 #pragma unroll
-                for (int b = 0; b < TN; ++b) acc[a][b] = mfma(af[a], bf[b], acc[a][b]);
-        }
-        if (more) {
-            la.commit(smem + (cur ^ 1) * STAGE_WORDS, tid);
-            lb.commit(smem + (cur ^ 1) * STAGE_WORDS + A_WORDS, tid);
-        }
+                    for (int b = 0; b < T; ++b)
+                        acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
+            }
+        });
         __syncthreads();
+    };
+    int kt = 0;
+    for (; kt + 2 < KT; ++kt) step(kt, std::true_type(), std::true_type());
+    if (kt + 1 < KT) step(kt++, std::true_type(), std::false_type());
+    step(kt, std::false_type(), std::false_type());
+
+    // ---- result tile in LDS, in fp32 --------------------------------------------
+    float* Cs = (float*)smem;
+    float* dst = SPLIT ? Cs + R * CP + wave * 32 * 36 : Cs;
+    constexpr int DP = SPLIT ? 36 : CP;
+#pragma unroll
+    for (int a = 0; a < T; ++a)
+#pragma unroll
+        for (int b = 0; b < T; ++b)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                dst[(wr0 + 16 * a + 4 * (lane >> 4) + r) * DP + wc0 + 16 * b + (lane & 15)] = acc[a][b][r];
+    if constexpr (SPLIT) {
+        // the wavefronts' sums, in wavefront order
+        __syncthreads();
+        const int row = tid >> 3, col = (tid & 7) * 4;
+        const float* part = Cs + R * CP + row * 36 + col;
+        f32x4 sum = *(const f32x4*)part;
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) {
+            const f32x4 x = *(const f32x4*)(part + w * 32 * 36);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[e] += x[e];
+        }
+        *(f32x4*)(Cs + row * CP + col) = sum;
     }
+    int* sidx = (int*)(smem + R * CP + PART);
+    const int rows_valid = min(R, g.I - i0), cols_valid = min(R, g.J - j0);
+    const bool scatter_c = g.epilogue == EPI_COL_SCATTER, scatter_r = g.epilogue == EPI_ROW_SCATTER;
+    if (scatter_c && tid < cols_valid) sidx[tid] = clamp_idx(g.keep[j0 + tid], g.out_full);
+    if (scatter_r && tid < rows_valid) sidx[tid] = clamp_idx(g.keep[i0 + tid], g.out_full);
+    __syncthreads();
 
-    // ---- epilogue: accumulators -> C tile in LDS (output type) ---------------
-    E* Cs = (E*)smem;
-    int* sidx = (int*)(Cs + BM * CP);
-    const int rows_valid = min(BM, g.I - i0);
-    const int cols_valid = min(BN, g.J - j0);
-    E* out = (E*)g.out;
-    const E* prev = (const E*)g.prev;
-#pragma unroll
-    for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = wr0 + a * 32 + (r >> 2) * 8 + grp * 4 + (r & 3);
-                Cs[row * CP + wc0 + b * 32 + l32] = Ty<DT>::from_f32(acc[a][b][r]);
-            }
-    constexpr int VEC = 16 / (int)sizeof(E);
-
-    if (g.epilogue == EPI_COL_SCATTER) {
-        // this tile owns the original columns from its first kept column (0 for
-        // the first tile) up to the next tile's first kept column (the full
-        // width for the last tile); kept ones receive results, the rest +0
-        for (int q = tid; q < cols_valid; q += NT) sidx[q] = clamp_idx(g.keep[j0 + q], g.out_full);
-        __syncthreads();
-        if (g.avg_partial) {
-            // sum of this tile's stored (rounded) results per output row, in column order
-            float* dst = g.avg_partial + (size_t)tj * (size_t)g.avg_len + i0;
-            for (int row = tid; row < rows_valid; row += NT) {
-                float sum = 0.f;
-                for (int c = 0; c < cols_valid; ++c) sum += Ty<DT>::to_f32(Cs[row * CP + c]);
-                dst[row] = sum;
-            }
-        }
+    if (scatter_c) {
+        // The tile owns the original columns from its first kept column (0 for the first tile) up to
+        // the next tile's first kept column (the full width for the last tile).  A table says which
+        // result column, if any, belongs to each; then whole rows of owned columns leave, kept and
+        // imputed ones together, two columns to a thread and 256 contiguous bytes to a wavefront.
+        int* tab = sidx + 2 * R;
         const int start = j0 == 0 ? 0 : sidx[0];
-        const int end = j0 + BN >= g.J ? g.out_full : clamp_idx(g.keep[j0 + BN], g.out_full);
-        for (int chunk = start; chunk < end; chunk += NT) {
-            const int p = chunk + tid;
-            if (p < end) {
-                const int jj = lower_bound_lds(sidx, cols_valid, p);
-                const bool hit = jj < cols_valid && sidx[jj] == p;
-                E* o = out + (size_t)i0 * (size_t)g.ldo + p;
-                if (hit || !prev) {
-                    for (int row = 0; row < rows_valid; ++row)
-                        o[(size_t)row * (size_t)g.ldo] = hit ? Cs[row * CP + jj] : E(0);
-                } else {
-                    // Same: a position is read and written by this thread only (also when the
-                    // previous tensor is the output itself), so loads go out in batches
-                    const E* pv = prev + (size_t)i0 * (size_t)g.ldo + p;
-                    constexpr int RB = 16;
-                    for (int row = 0; row < rows_valid; row += RB) {
-                        E old[RB];
+        const int end = j0 + R >= g.J ? g.out_full : clamp_idx(g.keep[j0 + R], g.out_full);
+        for (int base = start; base < end; base += TAB) {
+            const int width = min(TAB, end - base);
+            for (int q = tid; q < TAB; q += NT) tab[q] = -1;
+            __syncthreads();
+            if (tid < cols_valid) {
+                const int p = sidx[tid] - base;
+                if (p >= 0 && p < width) tab[p] = tid;
+            }
+            __syncthreads();
+            for (int q = 2 * lane; q < width; q += 128) {
+                const int ja = tab[q], jb = tab[q + 1];
+                const bool pair = q + 1 < width;
+                E* o = g.out + (size_t)i0 * (size_t)g.ldo + base + q;
+                const E* pv = g.prev ? g.prev + (size_t)i0 * (size_t)g.ldo + base + q : nullptr;
+                constexpr int UB = 8;
+                for (int r0 = wave; r0 < rows_valid; r0 += WAVES * UB) {
+                    uint32_t x[UB];
 #pragma unroll
-                        for (int u = 0; u < RB; ++u)
-                            old[u] = row + u < rows_valid ? pv[(size_t)(row + u) * (size_t)g.ldo] : E(0);
+                    for (int u = 0; u < UB; ++u) x[u] = 0u;
+                    if (pv && (ja < 0 || jb < 0)) {
+                        // (a position is read and written by this thread only, also where the
+                        // previous tensor is the output itself)
+                        if (pair) {
 #pragma unroll
-                        for (int u = 0; u < RB; ++u) {
-                            if (row + u >= rows_valid) break;
-                            o[(size_t)(row + u) * (size_t)g.ldo] = old[u];
+                            for (int u = 0; u < UB; ++u)
+                                x[u] = *(const u1_any*)(pv + (size_t)min(r0 + WAVES * u, rows_valid - 1) * (size_t)g.ldo);
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < UB; ++u)
+                                x[u] = pv[(size_t)min(r0 + WAVES * u, rows_valid - 1) * (size_t)g.ldo];
                         }
+                    }
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) {
+                        const int row = min(r0 + WAVES * u, rows_valid - 1);
+                        if (ja >= 0) x[u] = (x[u] & 0xffff0000u) | f32_to_bf16_bits(Cs[row * CP + ja]);
+                        if (jb >= 0) x[u] = (x[u] & 0xffffu) | (f32_to_bf16_bits(Cs[row * CP + jb]) << 16);
+                    }
+#pragma unroll
+                    for (int u = 0; u < UB; ++u) {
+                        if (r0 + WAVES * u >= rows_valid) break;
+                        E* p = o + (size_t)(r0 + WAVES * u) * (size_t)g.ldo;
+                        if (pair) *(u1_any*)p = x[u];
+                        else *p = (E)x[u];
                     }
                 }
             }
+            __syncthreads();
         }
         return;
     }
 
-    const bool scatter_rows = g.epilogue == EPI_ROW_SCATTER;
-    if (scatter_rows) {
-        for (int q = tid; q < rows_valid; q += NT) sidx[q] = clamp_idx(g.keep[i0 + q], g.out_full);
-    }
-    __syncthreads();
-    if (scatter_rows && g.avg_partial) {
-        // sum of this tile's stored (rounded) results per output column, in row order
-        float* dst = g.avg_partial + (size_t)ti * (size_t)g.avg_len + j0;
-        for (int col = tid; col < cols_valid; col += NT) {
-            float sum = 0.f;
-            for (int r = 0; r < rows_valid; ++r) sum += Ty<DT>::to_f32(Cs[r * CP + col]);
-            dst[col] = sum;
-        }
-    }
-    constexpr int CPR = BN / VEC;               // 16-byte chunks per tile row
-    for (int q = tid; q < BM * CPR; q += NT) {
-        const int row = q / CPR;
-        const int j = (q % CPR) * VEC;
+    constexpr int CPR = R / 8;
+#pragma unroll
+    for (int it = 0; it < (R * CPR + NT - 1) / NT; ++it) {
+        const int q = tid + NT * it;
+        const int row = q / CPR, j = (q % CPR) * 8;
         if (row >= rows_valid || j >= cols_valid) continue;
-        const int orow = scatter_rows ? sidx[row] : i0 + row;
-        E* o = out + (size_t)orow * (size_t)g.ldo + j0 + j;
-        const E* c = Cs + row * CP + j;
-        if (g.out_vec && j + VEC <= cols_valid) {
-            *(uint4*)o = *(const uint4*)c;
+        E* o = g.out + (size_t)(scatter_r ? sidx[row] : i0 + row) * (size_t)g.ldo + j0 + j;
+        f32x4 x0 = *(const f32x4*)(Cs + row * CP + j), x1 = *(const f32x4*)(Cs + row * CP + j + 4);
+        if (j + 8 <= cols_valid) {
+            if (g.accumulate) {
+                const u4 old = *(const u4_any*)o;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    x0[2 * e] += __uint_as_float(old[e] << 16);
+                    x0[2 * e + 1] += __uint_as_float(old[e] & 0xffff0000u);
+                    x1[2 * e] += __uint_as_float(old[e + 2] << 16);
+                    x1[2 * e + 1] += __uint_as_float(old[e + 2] & 0xffff0000u);
+                }
+            }
+            u4 w;
+            w.x = two(x0[0], x0[1]); w.y = two(x0[2], x0[3]); w.z = two(x1[0], x1[1]); w.w = two(x1[2], x1[3]);
+            *(u4_any*)o = w;
         } else {
-            for (int t = 0; t < VEC && j + t < cols_valid; ++t) o[t] = c[t];
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (j + e < cols_valid) {
+                    const float x = e < 4 ? x0[e & 3] : x1[e & 3];
+                    o[e] = (E)f32_to_bf16_bits(g.accumulate ? bf16_bits_to_f32(o[e]) + x : x);
+                }
         }
     }
-    if (scatter_rows) {
-        // zero the dropped rows this tile owns (same ownership rule as above)
+    if (scatter_r) {
+        // the dropped rows this tile owns (same ownership rule as above): every lane looks one row
+        // up, the wavefront then writes the dropped ones together
         const int start = i0 == 0 ? 0 : sidx[0];
-        const int end = i0 + BM >= g.I ? g.out_full : clamp_idx(g.keep[i0 + BM], g.out_full);
-        // every lane looks one row up, the wavefront then writes the dropped ones together
+        const int end = i0 + R >= g.I ? g.out_full : clamp_idx(g.keep[i0 + R], g.out_full);
         for (int base = start + wave * 64; base < end; base += NT) {
             const int mine = base + lane;
             bool dropped = false;
@@ -577,9 +583,10 @@ __global__ __launch_bounds__(NT) void gemm_kernel(const KArgs g)
             while (todo) {
                 const int p = base + (__ffsll((long long)todo) - 1);
                 todo &= todo - 1;
-                E* o = out + (size_t)p * (size_t)g.ldo + j0;
-                const E* pv = prev ? prev + (size_t)p * (size_t)g.ldo + j0 : nullptr;
-                for (int j = lane; j < cols_valid; j += 64) o[j] = pv ? pv[j] : E(0);
+                for (int j = lane; j < cols_valid; j += 64) {
+                    const size_t off = (size_t)p * (size_t)g.ldo + j0 + j;
+                    g.out[off] = g.prev ? g.prev[off] : E(0);
+                }
             }
         }
     }
@@ -588,56 +595,65 @@ __global__ __launch_bounds__(NT) void gemm_kernel(const KArgs g)
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-template <int DT, bool ACC, bool AVEC, bool BCC, bool BVEC, int BM, int BN>
-int launch_inst(const KArgs& k, hipStream_t stream)
+template <template <int, bool> class LA, bool AP, template <int, bool> class LB, bool BP, int R>
+int launch_inst(const Args& a, const char* name, hipStream_t stream)
 {
-    constexpr int smem = smem_bytes<BM, BN, DT>();
-    auto fn = gemm_kernel<DT, ACC, AVEC, BCC, BVEC, BM, BN>;
+    constexpr int smem = 2 * 2 * Geo<R>::WORDS * 4;
+    auto fn = gemm_kernel<LA, AP, LB, BP, R>;
     static AttrFlags attr_set;      // per instantiation and device
     if (!ensure_max_dynamic_lds((const void*)fn, smem, &attr_set)) return ZR_ERR_HIP;
     if (debug_names_wanted())
-        snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "gemm_kernel<%d, %s, %s, %s, %s, %d, %d>", DT,
-                 ACC ? "true" : "false", AVEC ? "true" : "false", BCC ? "true" : "false", BVEC ? "true" : "false", BM, BN);
-    KArgs kk = k;
-    kk.tiles_j = (k.J + BN - 1) / BN;
-    const int64_t tiles = (int64_t)((k.I + BM - 1) / BM) * kk.tiles_j;
-    if (tiles > 0x7fffffff) return ZR_ERR_LIMIT;
-    hipLaunchKernelGGL(fn, dim3((unsigned)tiles), dim3(NT), smem, stream, kk);
+        snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "gemm_kernel<%s, %d>", name, R);
+    Args k = a;
+    k.tiles_i = (a.I + R - 1) / R;
+    k.tiles_j = (a.J + R - 1) / R;
+    const int64_t tiles = (int64_t)k.tiles_i * k.tiles_j;
+    if (tiles > 0x7ffffff0) return ZR_ERR_LIMIT;
+    hipLaunchKernelGGL(fn, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(NT), smem, stream, k);
     return hip_status(hipGetLastError());
 }
 
-template <int DT, bool ACC, bool BCC>
-int launch_fmt(const KArgs& k, bool avec, bool bvec, hipStream_t stream)
+template <template <int, bool> class LA, bool AP, template <int, bool> class LB, bool BP>
+int launch_shape(const Args& a, const char* name, hipStream_t stream)
 {
-    constexpr int BM = 128, BN = 128;
-    if (avec && bvec) return launch_inst<DT, ACC, true, BCC, true, BM, BN>(k, stream);
-    if (avec) return launch_inst<DT, ACC, true, BCC, false, BM, BN>(k, stream);
-    if (bvec) return launch_inst<DT, ACC, false, BCC, true, BM, BN>(k, stream);
-    return launch_inst<DT, ACC, false, BCC, false, BM, BN>(k, stream);
+    const int64_t t64 = (int64_t)((a.I + 63) / 64) * ((a.J + 63) / 64), t128 = (int64_t)((a.I + 127) / 128) * ((a.J + 127) / 128);
+    // 128 x 128 tiles once there is one for every compute unit (M x K x N = 4001 x 752 x 1003: 256 tiles
+    // 28.8 us against 39.0 on 64 x 64; 4001 x 1001 x 752: 192 tiles 49.2 against 40.5); 32 x 32 tiles
+    // below 96 of 64 x 64 (dW 376 x 471 over 985 tokens: 48 tiles, 8 us against 15; 985 x 501 x 353:
+    // 96 tiles, 14.1 against 13.6)
+    if (t128 >= 256) return launch_inst<LA, AP, LB, BP, 128>(a, name, stream);
+    return t64 < 96 ? launch_inst<LA, AP, LB, BP, 32>(a, name, stream) : launch_inst<LA, AP, LB, BP, 64>(a, name, stream);
 }
 
-template <int DT>
-int launch_dt(const GemmDesc& d, hipStream_t stream)
+int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
 {
-    constexpr int esz = DT == ZR_BF16 ? 2 : 4;
-    constexpr int VEC = 16 / esz;
-    auto vec_ok = [&](const Operand& o) {
-        return o.map_contig == nullptr && ((uintptr_t)o.base % 16 == 0) && (o.ld % VEC == 0);
-    };
-    KArgs k;
-    k.A = OpView{d.A.base, d.A.ld, d.A.map_strided, d.A.map_contig, d.A.n_strided, d.A.n_contig};
-    k.B = OpView{d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
-    k.I = d.I; k.J = d.J; k.C = d.C;
-    k.out = d.out; k.ldo = d.ldo; k.epilogue = d.epilogue; k.keep = d.keep_idx; k.out_full = d.out_full;
-    k.out_vec = ((uintptr_t)d.out % 16 == 0) && (d.ldo % VEC == 0);
-    k.tiles_j = 0;
-    k.prev = d.prev; k.accumulate = d.accumulate ? 1 : 0;
-    k.avg_partial = d.epilogue == EPI_PLAIN ? nullptr : d.avg_partial; k.avg_len = d.avg_len;
-    const bool av = vec_ok(d.A), bv = vec_ok(d.B);
-    if (d.A.c_contig && !d.B.c_contig) return launch_fmt<DT, true, false>(k, av, bv, stream);
-    if (d.A.c_contig && d.B.c_contig) return launch_fmt<DT, true, true>(k, av, bv, stream);
-    if (!d.A.c_contig && !d.B.c_contig) return launch_fmt<DT, false, false>(k, av, bv, stream);
-    return ZR_ERR_MODE;
+    if (d.I < 1 || d.J < 1 || d.C < 1) return ZR_ERR_SHAPE;
+    Args a;
+    a.A = View{(const E*)d.A.base, d.A.ld, d.A.map_strided, d.A.map_contig, d.A.n_strided, d.A.n_contig};
+    a.B = View{(const E*)d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
+    a.I = d.I; a.J = d.J; a.C = d.C;
+    a.out = (E*)d.out; a.ldo = d.ldo; a.epilogue = d.epilogue; a.keep = d.keep_idx; a.out_full = d.out_full;
+    a.tiles_i = a.tiles_j = 0;
+    a.prev = (const E*)d.prev; a.accumulate = d.accumulate ? 1 : 0;
+    const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
+    auto too_short = [&](const Operand& o) { return o.map_contig ? o.n_contig < 2 : (o.c_contig ? d.C : o.n_contig) < 8; };
+    const bool ap = d.A.c_contig, bp = d.B.c_contig;
+    if (!ap && bp) return ZR_ERR_MODE;
+    if (too_short(d.A) || too_short(d.B)) {
+        if (ap) return bp ? launch_inst<Any, true, Any, true, 32>(a, "Pe, Pe", stream) : launch_inst<Any, true, Any, false, 32>(a, "Pe, Qe", stream);
+        return launch_inst<Any, false, Any, false, 32>(a, "Qe, Qe", stream);
+    }
+    if (ap && !bp) {            // forward, weight stored [K x N]; dX, weight stored [N x K]
+        if (ag) return bg ? ZR_ERR_MODE : launch_shape<Gather, true, Plain, false>(a, "Pg, Q", stream);
+        return bg ? launch_shape<Plain, true, Gather, false>(a, "P, Qg", stream) : launch_shape<Plain, true, Plain, false>(a, "P, Q", stream);
+    }
+    if (ap && bp) {
+        if (ag) return bg ? launch_shape<Gather, true, Gather, true>(a, "Pg, Pg", stream) : ZR_ERR_MODE;
+        return bg ? launch_shape<Plain, true, Gather, true>(a, "P, Pg", stream) : launch_shape<Plain, true, Plain, true>(a, "P, P", stream);
+    }
+    // dW
+    if (ag) return bg ? ZR_ERR_MODE : launch_shape<Gather, false, Plain, false>(a, "Qg, Q", stream);
+    return bg ? launch_shape<Plain, false, Gather, false>(a, "Q, Qg", stream) : launch_shape<Plain, false, Plain, false>(a, "Q, Q", stream);
 }
 
 }  // namespace
@@ -662,7 +678,7 @@ static int launch_gemm_untimed(const GemmDesc& d, hipStream_t stream)
 {
     const int fast = launch_gemm_fast(d, stream);   // bf16, 16-byte aligned rows
     if (fast >= 0) return fast;
-    if (d.dtype == ZR_BF16) return launch_dt<ZR_BF16>(d, stream);
+    if (d.dtype == ZR_BF16) return launch_gemm_any(d, stream);
     if (d.dtype == ZR_F32) return launch_gemm_f32(d, stream);
     return ZR_ERR_DTYPE;
 }

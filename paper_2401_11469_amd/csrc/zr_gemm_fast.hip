@@ -1858,13 +1858,12 @@ int launch_shape(const FArgs& a, hipStream_t stream)
 
 }  // namespace
 
-// Returns -1 when the problem is not eligible for this path (the caller then
-// uses the general kernel), else a zr_status.
-int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
+// Whether this path takes the product (else the kernel for any alignment does).
+bool gemm_fast_eligible(const GemmDesc& d)
 {
-    if (d.dtype != ZR_BF16) return -1;
+    if (d.dtype != ZR_BF16) return false;
     auto aligned = [](const void* p, int64_t ld) { return ((uintptr_t)p % 16 == 0) && (ld % 8 == 0); };
-    if (!aligned(d.A.base, d.A.ld) || !aligned(d.B.base, d.B.ld) || !aligned(d.out, d.ldo)) return -1;
+    if (!aligned(d.A.base, d.A.ld) || !aligned(d.B.base, d.B.ld) || !aligned(d.out, d.ldo)) return false;
     // every memory row that is walked in 16-byte chunks must be a multiple of 8 long
     auto chunked_ok = [](const Operand& o) {
         if (o.map_contig) {
@@ -1873,12 +1872,23 @@ int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
         }
         return o.n_contig % 8 == 0;
     };
-    if (!chunked_ok(d.A) || !chunked_ok(d.B)) return -1;
-    if (d.epilogue != EPI_COL_SCATTER && d.J % 8 != 0) return -1;
-    if (d.I < 1 || d.J < 1 || d.C < 1) return -1;
-    if (d.prev && (uintptr_t)d.prev % 16 != 0) return -1;
-    if (d.accumulate && d.epilogue != EPI_PLAIN) return -1;
+    if (!chunked_ok(d.A) || !chunked_ok(d.B)) return false;
+    if (d.epilogue != EPI_COL_SCATTER && d.J % 8 != 0) return false;
+    if (d.I < 1 || d.J < 1 || d.C < 1) return false;
+    if (d.prev && (uintptr_t)d.prev % 16 != 0) return false;
+    if (d.accumulate && d.epilogue != EPI_PLAIN) return false;
+    // which pairs of operands there are loaders for
+    const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
+    if (d.A.c_contig && !d.B.c_contig) return !(ag && bg);
+    if (d.A.c_contig && d.B.c_contig) return bg || !ag;
+    if (!d.A.c_contig && !d.B.c_contig) return !d.A.map_strided && !d.B.map_strided && !(ag && bg);
+    return false;
+}
 
+// Returns -1 when the problem is not eligible, else a zr_status.
+int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
+{
+    if (!gemm_fast_eligible(d)) return -1;
     FArgs a;
     a.A = FOp{(const E*)d.A.base, d.A.ld, d.A.map_strided, d.A.map_contig, d.A.n_strided, d.A.n_contig};
     a.B = FOp{(const E*)d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
