@@ -78,6 +78,8 @@ struct GemmDesc {
     // axis.  The buffer holds ceil(extent / 128) slots and must be zero beforehand.
     float* avg_partial = nullptr;
     int avg_len = 0;
+    // set to false by launch_gemm where the product's kernel does not write those sums
+    mutable bool sums_left = true;
     // Scratch for a split contraction (16-byte aligned; products with too few tiles to fill the
     // chip cut the contraction into slices and add them up in a second launch); nullptr: never split.
     void* split_scratch = nullptr;
@@ -103,7 +105,6 @@ struct AttrFlags {
 bool ensure_max_dynamic_lds(const void* fn, int bytes, void* flags16);
 int launch_gemm(const GemmDesc& d, hipStream_t stream);
 int launch_gemm_fast(const GemmDesc& d, hipStream_t stream);   // -1: not eligible
-bool gemm_fast_eligible(const GemmDesc& d);                    // (only these products leave the sums of Average imputation)
 int launch_gemm_f32(const GemmDesc& d, hipStream_t stream);
 int launch_select(const float* scores, int n, int batch, int n_keep,
                   int32_t* keep_idx, int32_t* drop_idx, int64_t ld_idx, hipStream_t stream);

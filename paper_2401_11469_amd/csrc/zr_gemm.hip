@@ -678,6 +678,7 @@ static int launch_gemm_untimed(const GemmDesc& d, hipStream_t stream)
 {
     const int fast = launch_gemm_fast(d, stream);   // bf16, 16-byte aligned rows
     if (fast >= 0) return fast;
+    d.sums_left = false;
     if (d.dtype == ZR_BF16) return launch_gemm_any(d, stream);
     if (d.dtype == ZR_F32) return launch_gemm_f32(d, stream);
     return ZR_ERR_DTYPE;

@@ -1859,7 +1859,7 @@ int launch_shape(const FArgs& a, hipStream_t stream)
 }  // namespace
 
 // Whether this path takes the product (else the kernel for any alignment does).
-bool gemm_fast_eligible(const GemmDesc& d)
+static bool eligible(const GemmDesc& d)
 {
     if (d.dtype != ZR_BF16) return false;
     auto aligned = [](const void* p, int64_t ld) { return ((uintptr_t)p % 16 == 0) && (ld % 8 == 0); };
@@ -1888,7 +1888,7 @@ bool gemm_fast_eligible(const GemmDesc& d)
 // Returns -1 when the problem is not eligible, else a zr_status.
 int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
 {
-    if (!gemm_fast_eligible(d)) return -1;
+    if (!eligible(d)) return -1;
     FArgs a;
     a.A = FOp{(const E*)d.A.base, d.A.ld, d.A.map_strided, d.A.map_contig, d.A.n_strided, d.A.n_contig};
     a.B = FOp{(const E*)d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
