@@ -124,13 +124,13 @@ struct FArgs {
     float* avg_partial;     // Average imputation: per-tile sums of the stored results, or nullptr
     int avg_len;            // entries per slot of avg_partial
     int avg_slot_base;      // slot of this launch's first tile along the summed axis
-    // Split contraction (products with too few tiles to fill the chip): phase 1 = every workgroup
-    // multiplies one slice of the contraction of one tile and stores its fp32 accumulators to
-    // `partial`; phase 2 = one workgroup per tile adds the slices in slice order and runs the
-    // epilogue.  split <= 1: the ordinary single launch.
+    // Split contraction (products with too few tiles to fill the chip): every workgroup multiplies
+    // one slice of the contraction of one tile and stores its fp32 accumulators to `partial`; a
+    // second kernel adds the slices in slice order and runs the epilogue.  split <= 1: one launch.
     float* partial;
     size_t partial_bytes;       // host side only: room at `partial`
-    int split, phase, kt_per;   // kt_per: 64-deep contraction tiles per slice
+    const GemmDesc* desc;       // host side only: where to say that no sums were left
+    int split, kt_per;          // kt_per: 64-deep contraction tiles per slice
     // sub-rectangle of D this launch covers, in elements (multiples of 256 except at
     // the far edges of D) and its tile grid
     int i_base, j_base, i_end, j_end;
@@ -1125,9 +1125,21 @@ __device__ __forceinline__ void pipeline_step(
     }
 }
 
-// PHASE: 0 = the whole product in one launch; 1 / 2 = the two launches of a split contraction
-// (instantiated for the 128 x 128 direct-to-LDS tiles only: separate kernels, so that the
-// ordinary one keeps its register allocation).
+// Tile t of a launch: groups of 4 tile rows, column by column within a group.
+__device__ __forceinline__ void tile_at(const FArgs& g, int t, int& ti, int& tj)
+{
+    constexpr int GI = 4;
+    const int grp_sz = GI * g.tiles_j;
+    const int gidx = t / grp_sz, first_i = gidx * GI;
+    const int rows_in = min(GI, g.tiles_i - first_i);
+    const int within = t - gidx * grp_sz;
+    ti = first_i + within % rows_in;
+    tj = within / rows_in;
+}
+
+// PHASE: 0 = the whole product; 1 = the first launch of a split contraction (instantiated for the
+// 128 x 128 direct-to-LDS tiles only: a separate kernel, so that the ordinary one keeps its
+// register allocation).
 template <template <int, int> class LA_, template <int, int> class LB_, int BM, int BN, int WM, int WN, int PHASE = 0>
 __global__ __launch_bounds__(64 * WM * WN) void fast_kernel(const FArgs g)
 {
@@ -1184,14 +1196,8 @@ __global__ __launch_bounds__(64 * WM * WN) void fast_kernel(const FArgs g)
     const int z = PHASE == 1 ? lin / total : 0;
     const int t = PHASE == 1 ? lin - z * total : lin;
     if (lin >= total * (PHASE == 1 ? g.split : 1)) return;
-    constexpr int GI = 4;
-    const int grp_sz = GI * g.tiles_j;
-    const int gidx = t / grp_sz;
-    const int first_i = gidx * GI;
-    const int rows_in = min(GI, g.tiles_i - first_i);
-    const int within = t - gidx * grp_sz;
-    const int ti = first_i + within % rows_in;
-    const int tj = within / rows_in;
+    int ti, tj;
+    tile_at(g, t, ti, tj);
     const int i0 = g.i_base + ti * BM, j0 = g.j_base + tj * BN;
 
     if (LA::NEEDS_IDX) {
@@ -1247,68 +1253,13 @@ __global__ __launch_bounds__(64 * WM * WN) void fast_kernel(const FArgs g)
     const int KT_all = (g.C + BK - 1) / BK;
     const int kt0 = PHASE == 1 ? z * g.kt_per : 0;
     const int kt1 = PHASE == 1 ? min(kt0 + g.kt_per, KT_all) : KT_all;
-    // accumulator sub-tiles (a, b) of this wavefront that hold anything of the output: the
-    // slices of a split contraction are only exchanged for those
-    auto sub_valid = [&](int a, int b) {
-        return wr0 + a * MT < min(BM, g.I - i0) && wc0 + b * MT < min(BN, g.J - j0);
-    };
     float4* part = nullptr;
     if constexpr (M16 && PHASE != 0)
         part = (float4*)g.partial + ((size_t)z * (size_t)total + (size_t)t) * (size_t)(TM * TN * NT) + tid;
 
     LA la;
     LB lb;
-    if constexpr (PHASE == 2) {
-        // the slices in slice order (a fixed order: results are repeatable bit by bit)
-        if constexpr (M16) {
-            const size_t zstride = (size_t)total * (size_t)(TM * TN * NT);
-            const bool whole_tile = g.I - i0 >= BM && g.J - j0 >= BN;       // uniform over the workgroup
-            if (TM * TN <= 16 && whole_tile) {
-                // a whole tile: two slices of ALL sub-tiles are requested before any is added (one
-                // memory latency per pair of slices; 19 -> 11-16 us per launch on the workload's
-                // shapes).  Same order of additions as below.
-                for (int z0 = 0; z0 < g.split; z0 += 2) {
-                    float4 v[2][TM][TN];
-#pragma unroll
-                    for (int zz = 0; zz < 2; ++zz)
-#pragma unroll
-                        for (int a = 0; a < TM; ++a)
-#pragma unroll
-                            for (int b = 0; b < TN; ++b)
-                                v[zz][a][b] = part[(size_t)min(z0 + zz, g.split - 1) * zstride + (a * TN + b) * NT];
-#pragma unroll
-                    for (int zz = 0; zz < 2; ++zz) {
-                        if (z0 + zz >= g.split) break;
-#pragma unroll
-                        for (int a = 0; a < TM; ++a)
-#pragma unroll
-                            for (int b = 0; b < TN; ++b) {
-                                acc[a][b][0] += v[zz][a][b].x; acc[a][b][1] += v[zz][a][b].y;
-                                acc[a][b][2] += v[zz][a][b].z; acc[a][b][3] += v[zz][a][b].w;
-                            }
-                    }
-                }
-            } else
-            // a tile at the edge (a panel of a few columns, say): all slices of a sub-tile are requested
-            // together (one memory latency per sub-tile that holds output, not one per slice) and added
-            // in slice order; split <= 8.  (The scheme above measured slower here: 9 -> 12-13 us.)
-#pragma unroll
-            for (int a = 0; a < TM; ++a)
-#pragma unroll
-                for (int b = 0; b < TN; ++b)
-                    if (sub_valid(a, b)) {
-                        float4 v[8];
-#pragma unroll
-                        for (int zz = 0; zz < 8; ++zz)
-                            v[zz] = part[(size_t)min(zz, g.split - 1) * zstride + (a * TN + b) * NT];
-#pragma unroll
-                        for (int zz = 0; zz < 8; ++zz)
-                            if (zz < g.split) {
-                                acc[a][b][0] += v[zz].x; acc[a][b][1] += v[zz].y; acc[a][b][2] += v[zz].z; acc[a][b][3] += v[zz].w;
-                            }
-                    }
-        }
-    } else if constexpr (RING) {
+    if constexpr (RING) {
         if constexpr (LA::MAPPED || LB::MAPPED) {
             // the row list of the contraction axis, clamped, for the loads of every stage
             const FOp& lop = LA::MAPPED ? g.A : g.B;
@@ -1354,13 +1305,14 @@ __global__ __launch_bounds__(64 * WM * WN) void fast_kernel(const FArgs g)
     }
 
     if constexpr (PHASE == 1) {
-        // this slice's accumulators, as they are; phase 2 adds the slices and stores the output
+        // this slice's accumulators, as they are, where they hold anything of the output;
+        // split_reduce_kernel adds the slices and stores the output
         if constexpr (M16) {
 #pragma unroll
             for (int a = 0; a < TM; ++a)
 #pragma unroll
                 for (int b = 0; b < TN; ++b)
-                    if (sub_valid(a, b))
+                    if (wr0 + a * MT < min(BM, g.I - i0) && wc0 + b * MT < min(BN, g.J - j0))
                         part[(a * TN + b) * NT] = make_float4(acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]);
         }
         return;
@@ -1618,6 +1570,160 @@ __global__ __launch_bounds__(64 * WM * WN) void fast_kernel(const FArgs g)
     }
 }
 
+// Second launch of a split contraction on 128 x 128 tiles (four wavefronts as 2 x 2): adds the
+// slices of a tile in slice order (a fixed order: results are repeatable bit by bit) and runs the
+// epilogue.  It is a copy in all but name (the slices come from the last-level cache), so what
+// counts is how many loads are in flight: four workgroups to a tile, each with one 16-row
+// sub-tile row of both wavefront rows, all sub-tiles of up to four slices requested together.
+// (One workgroup to a tile, as before: 48 tiles in 8 slices 14.8-17 us, now 8.5; 8 tiles 14 -> 7.5.)
+__global__ __launch_bounds__(256) void split_reduce_kernel(const FArgs g)
+{
+    constexpr int BM = 128, BN = 128, NT = 256, TN = 4, SUBS = 16;
+    constexpr int ROWS = 32, CP = BN + 8, WIN = 1024;        // WIN: original columns per pass of the column scatter
+    __shared__ __align__(16) E Cs[ROWS * CP];
+    __shared__ __align__(16) uint16_t tab[WIN];
+    __shared__ int sidx[BN];
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int total = g.tiles_i * g.tiles_j;
+    const int t = blockIdx.x >> 2, a = blockIdx.x & 3;
+    int ti, tj;
+    tile_at(g, t, ti, tj);
+    const int i0 = g.i_base + ti * BM, j0 = g.j_base + tj * BN;
+    const int rows_valid = min(BM, g.I - i0), cols_valid = min(BN, g.J - j0);
+    const bool scatter_c = g.epilogue == EPI_COL_SCATTER, scatter_r = g.epilogue == EPI_ROW_SCATTER;
+    if (a * 16 >= rows_valid) return;                         // (then the lower rows 64 + 16 a are empty too)
+
+    // kept rows of the strip: 16 from tile row 16 a, 16 from tile row 64 + 16 a
+    auto tile_row = [&](int r) { return (r >> 4) * 64 + a * 16 + (r & 15); };
+    if (scatter_c && tid < cols_valid) sidx[tid] = clamp_idx(g.keep[j0 + tid], g.out_full);
+    if (scatter_r && tid < ROWS) sidx[tid] = clamp_idx(g.keep[min(i0 + tile_row(tid), g.I - 1)], g.out_full);
+
+    const int wr0 = (wave >> 1) * 64, wc0 = (wave & 1) * 64;
+    if (wr0 + a * 16 < rows_valid && wc0 < cols_valid) {      // uniform for the wavefront
+        const float4* part = (const float4*)g.partial + ((size_t)t * SUBS + a * TN) * NT + tid;
+        const size_t zstride = (size_t)total * (SUBS * NT);
+        // sub-tiles that hold nothing of the output were not stored: the last one that does, again
+        const int last_b = (cols_valid - 1 - wc0) / 16;
+        float4 acc[TN];
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[b] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int z0 = 0; z0 < g.split; z0 += 4) {
+            float4 v[4][TN];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+                    v[u][b] = part[(size_t)min(z0 + u, g.split - 1) * zstride + (size_t)min(b, last_b) * NT];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (z0 + u >= g.split) break;
+#pragma unroll
+                for (int b = 0; b < TN; ++b) {
+                    acc[b].x += v[u][b].x; acc[b].y += v[u][b].y; acc[b].z += v[u][b].z; acc[b].w += v[u][b].w;
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            E* c = Cs + ((wave >> 1) * 16 + 4 * (lane >> 4)) * CP + wc0 + b * 16 + (lane & 15);
+            c[0] = to_bf16(acc[b].x); c[CP] = to_bf16(acc[b].y); c[2 * CP] = to_bf16(acc[b].z); c[3 * CP] = to_bf16(acc[b].w);
+        }
+    }
+    __syncthreads();
+
+    if (scatter_c) {
+        // The tile owns the original columns from its first kept column (0 for the first tile) up to
+        // the next tile's first kept column (the full width for the last one).  A table gives the
+        // result column, if any, of each; 16-byte chunks leave with results and imputed values
+        // together, the chunks shared with the neighbouring tiles element by element.
+        const int start = j0 == 0 ? 0 : sidx[0];
+        const int end = j0 + BN >= g.J ? g.out_full : clamp_idx(g.keep[j0 + BN], g.out_full);
+        for (int base = start & ~7; base < end; base += WIN) {
+            const int nch = (min(WIN, end - base) + 7) >> 3;
+            if (tid < WIN / 8) *(uint4*)(tab + tid * 8) = make_uint4(~0u, ~0u, ~0u, ~0u);
+            __syncthreads();
+            if (tid < cols_valid) {
+                const int p = sidx[tid] - base;
+                if (p >= 0 && p < WIN) tab[p] = (uint16_t)tid;
+            }
+            __syncthreads();
+            for (int u = tid; u < ROWS * nch; u += NT) {
+                const int r = u / nch, c = u - r * nch;
+                if (tile_row(r) >= rows_valid) continue;
+                const int p = base + c * 8;
+                const size_t off = (size_t)(i0 + tile_row(r)) * (size_t)g.ldo + p;
+                const bool whole = p >= start && p + 8 <= end;
+                union { uint4 v; uint16_t e[8]; } k, x;
+                k.v = *(const uint4*)(tab + c * 8);
+                x.v = zero4();
+                if (g.prev) {
+                    if (whole) x.v = *(const uint4*)(g.prev + off);
+                    else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (p + e >= start && p + e < end) x.e[e] = g.prev[off + e];
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const E y = Cs[r * CP + (k.e[e] & (BN - 1))];
+                    x.e[e] = k.e[e] == 0xffffu ? x.e[e] : y;
+                }
+                if (whole) *(uint4*)(g.out + off) = x.v;
+                else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (p + e >= start && p + e < end) g.out[off + e] = x.e[e];
+                }
+            }
+            __syncthreads();
+        }
+        return;
+    }
+
+    for (int q = tid; q < ROWS * (BN / 8); q += NT) {
+        const int r = q / (BN / 8), j = (q % (BN / 8)) * 8;
+        if (tile_row(r) >= rows_valid || j >= cols_valid) continue;      // J is a multiple of 8 on this path
+        const int orow = scatter_r ? sidx[r] : i0 + tile_row(r);
+        *(uint4*)(g.out + (size_t)orow * (size_t)g.ldo + j0 + j) = *(const uint4*)(Cs + r * CP + j);
+    }
+    if (scatter_r) {
+        // Dropped rows: 16 kept rows own the original rows from their first (0 for the first of
+        // all) up to the first of the next 16 (the full extent for the last).  Every lane looks one
+        // row up, then each quarter of the wavefront writes one of the dropped ones, 16 bytes a lane.
+        const int grp = wave >> 1, i = i0 + grp * 64 + a * 16;
+        if (i < g.I) {
+            const int* s16 = sidx + grp * 16;
+            const int cnt = min(16, g.I - i);
+            const int start = i == 0 ? 0 : s16[0];
+            const int end = i + 16 >= g.I ? g.out_full : clamp_idx(g.keep[i + 16], g.out_full);
+            for (int base = start + (wave & 1) * 64; base < end; base += 128) {
+                const int mine = base + lane;
+                bool dropped = false;
+                if (mine < end) {
+                    const int ii = lower_bound_lds(s16, cnt, mine);
+                    dropped = !(ii < cnt && s16[ii] == mine);
+                }
+                unsigned long long todo = __ballot(dropped);
+                while (todo) {
+                    int p = -1;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        if (todo && u == (lane >> 4)) p = base + (__ffsll((long long)todo) - 1);
+                        todo &= todo - 1;                     // (0 stays 0)
+                    }
+                    const int j = (lane & 15) * 8;
+                    if (p >= 0 && j < cols_valid) {
+                        const size_t off = (size_t)p * (size_t)g.ldo + j0 + j;
+                        *(uint4*)(g.out + off) = g.prev ? *(const uint4*)(g.prev + off) : zero4();
+                    }
+                }
+            }
+        }
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
@@ -1626,6 +1732,22 @@ inline bool split_enabled()
 {
     static const bool on = getenv("ZR_NO_SPLIT") == nullptr;
     return on;
+}
+
+// Slices that a launch of `tiles` 128 x 128 tiles cuts its contraction into (1: none).  A slice has
+// at least 8 contraction tiles (512 deep), at most 512 workgroups run side by side, and the chain
+// that a tile gets shorter by has to pay for storing the slices and for the second launch: 9 tiles
+// of 64 or more (8192 x 1024 x 384, 192 tiles, 16 -> 8: 17 + 15 us against 19 in one launch;
+// 1024 x 576 over 2048 tokens, 40 tiles, 32 -> 8: 12 + 6 us against 33).
+inline int slices_for(const FArgs& a, int64_t tiles)
+{
+    const int KT = (a.C + BK - 1) / BK;
+    const size_t per_slice = (size_t)tiles * 128 * 128 * 4;
+    if (!a.partial || a.accumulate || per_slice == 0 || !split_enabled()) return 1;
+    int sp = (int)std::min<int64_t>(std::min<int64_t>(512 / tiles, 8), KT / 8);
+    sp = (int)std::min<size_t>((size_t)std::max(sp, 0), a.partial_bytes / per_slice);
+    if (sp < 2 || KT - (KT + sp - 1) / sp < 9) return 1;
+    return sp;
 }
 
 template <template <int, int> class LA, template <int, int> class LB, int BM, int BN, int WM, int WN>
@@ -1650,42 +1772,34 @@ int launch_inst(const FArgs& a, int i_base, int i_end, int j_base, int j_end, hi
     k.tiles_j = (j_end - j_base + BN - 1) / BN;
     const int64_t tiles = (int64_t)k.tiles_i * k.tiles_j;
     if (tiles > 0x7ffffff0) return ZR_ERR_LIMIT;
-    k.phase = 0; k.split = 1; k.kt_per = 0;
+    k.split = 1; k.kt_per = 0;
     // Split contraction: when this launch has too few tiles for the chip and a long contraction,
-    // s slices per tile (s * tiles workgroups), then one more launch of the same kernel that adds
-    // the slices and runs the epilogue.  Needs scratch for the slices (the caller's workspace).
+    // s slices per tile (s * tiles workgroups), then a launch that adds the slices and runs the
+    // epilogue.  Needs scratch for the slices (the caller's workspace).
     // (Tried on the big ring tiles of the dW products at high pruning ratios as well, 128 tiles
     // of 192 x 256 in two slices each: the slices are 50 MB of fp32 that leave the chip at the
     // end of the first launch and come back in the second, ~35 us per product, which is all
     // that the better fill of the chip gains.  Not instantiated.)
     constexpr bool can_split = A::DMA && B::DMA && !ring && BM == 128 && BN == 128;
     if constexpr (can_split) {
-        const int KT = (a.C + BK - 1) / BK;
-        const int64_t slots = (BM * BN > 128 * 128) ? 256 : 512;          // workgroups the chip holds at once
-        int sp = (int)std::min<int64_t>(slots / tiles, 8);
-        sp = std::min(sp, KT / 8);                                         // at least 8 contraction tiles (512 deep) per slice
-        const size_t per_slice = (size_t)tiles * (size_t)BM * (size_t)BN * 4;
-        if (a.partial && per_slice > 0) sp = (int)std::min<size_t>((size_t)std::max(sp, 0), a.partial_bytes / per_slice);
-        else sp = 1;
-        if (sp >= 2 && !a.accumulate && split_enabled()) {
-            k.split = sp; k.kt_per = (KT + sp - 1) / sp;
+        const int sp = slices_for(a, tiles);
+        if (sp >= 2) {
+            const int KT = (a.C + BK - 1) / BK;
+            k.kt_per = (KT + sp - 1) / sp;
             k.split = (KT + k.kt_per - 1) / k.kt_per;                      // no empty slice
             auto fn1 = fast_kernel<LA, LB, BM, BN, WM, WN, 1>;
-            auto fn2 = fast_kernel<LA, LB, BM, BN, WM, WN, 2>;
-            static AttrFlags attr1, attr2;
-            if (!ensure_max_dynamic_lds((const void*)fn1, smem, &attr1) || !ensure_max_dynamic_lds((const void*)fn2, smem, &attr2))
-                return ZR_ERR_HIP;
-            k.phase = 1;
+            static AttrFlags attr1;
+            if (!ensure_max_dynamic_lds((const void*)fn1, smem, &attr1)) return ZR_ERR_HIP;
             const int64_t g1 = (tiles * k.split + 7) / 8 * 8;
             hipLaunchKernelGGL(fn1, dim3((unsigned)g1), dim3(64 * WM * WN), smem, stream, k);
             if (hipGetLastError() != hipSuccess) return ZR_ERR_HIP;
-            k.phase = 2;
-            hipLaunchKernelGGL(fn2, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(64 * WM * WN), smem, stream, k);
+            hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)(tiles * 4)), dim3(256), 0, stream, k);
             if (debug_names_wanted()) {
                 char nm[128];
                 snprintf(nm, sizeof(nm), "%.90s split %d", g_debug.last_kernel, k.split);
                 snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "%s", nm);
             }
+            a.desc->sums_left = false;          // (the sums of Average imputation come from a pass of their own then)
             return hip_status(hipGetLastError());
         }
     }
@@ -1899,7 +2013,8 @@ int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
     a.tiles_i = a.tiles_j = 0;
     a.i_base = a.j_base = a.i_end = a.j_end = 0;
     a.partial = (float*)d.split_scratch; a.partial_bytes = d.split_scratch ? d.split_scratch_bytes : 0;
-    a.split = 1; a.phase = 0; a.kt_per = 0;
+    a.desc = &d;
+    a.split = 1; a.kt_per = 0;
     const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
     // Direct-to-LDS loaders cannot zero the contraction tail of the last tile
     // themselves: either the tiles are full, or one operand supplies the zeros
