@@ -1739,13 +1739,13 @@ inline bool split_enabled()
 // that a tile gets shorter by has to pay for storing the slices and for the second launch: 9 tiles
 // of 64 or more (8192 x 1024 x 384, 192 tiles, 16 -> 8: 17 + 15 us against 19 in one launch;
 // 1024 x 576 over 2048 tokens, 40 tiles, 32 -> 8: 12 + 6 us against 33).
-inline int slices_for(const FArgs& a, int64_t tiles)
+inline int slices_for(int C, int64_t tiles, const void* partial, size_t partial_bytes, bool accumulate)
 {
-    const int KT = (a.C + BK - 1) / BK;
+    const int KT = (C + BK - 1) / BK;
     const size_t per_slice = (size_t)tiles * 128 * 128 * 4;
-    if (!a.partial || a.accumulate || per_slice == 0 || !split_enabled()) return 1;
+    if (!partial || accumulate || per_slice == 0 || !split_enabled()) return 1;
     int sp = (int)std::min<int64_t>(std::min<int64_t>(512 / tiles, 8), KT / 8);
-    sp = (int)std::min<size_t>((size_t)std::max(sp, 0), a.partial_bytes / per_slice);
+    sp = (int)std::min<size_t>((size_t)std::max(sp, 0), partial_bytes / per_slice);
     if (sp < 2 || KT - (KT + sp - 1) / sp < 9) return 1;
     return sp;
 }
@@ -1782,7 +1782,7 @@ int launch_inst(const FArgs& a, int i_base, int i_end, int j_base, int j_end, hi
     // that the better fill of the chip gains.  Not instantiated.)
     constexpr bool can_split = A::DMA && B::DMA && !ring && BM == 128 && BN == 128;
     if constexpr (can_split) {
-        const int sp = slices_for(a, tiles);
+        const int sp = slices_for(a.C, tiles, a.partial, a.partial_bytes, a.accumulate != 0);
         if (sp >= 2) {
             const int KT = (a.C + BK - 1) / BK;
             k.kt_per = (KT + sp - 1) / sp;
@@ -1993,10 +1993,27 @@ static bool eligible(const GemmDesc& d)
     if (d.accumulate && d.epilogue != EPI_PLAIN) return false;
     // which pairs of operands there are loaders for
     const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
-    if (d.A.c_contig && !d.B.c_contig) return !(ag && bg);
-    if (d.A.c_contig && d.B.c_contig) return bg || !ag;
-    if (!d.A.c_contig && !d.B.c_contig) return !d.A.map_strided && !d.B.map_strided && !(ag && bg);
-    return false;
+    const bool ap = d.A.c_contig, bp = d.B.c_contig;
+    if ((!ap && bp) || (ag && bg)) return false;
+    if (ap && bp && ag) return false;
+    if (!ap && (d.A.map_strided || d.B.map_strided)) return false;
+    if (forced_tiles()) return true;
+
+    // Where the kernel for any alignment is the faster one, although this path could run: its tiles
+    // are smaller, and so are its stages, which is what counts while the chip is not full.  By the
+    // number of 128 x 128 tiles (us on this path / on the other one, 1024 deep unless given):
+    // (Column scatters into rows whose width is no multiple of 8 although their pitch is stay here:
+    // too rare for figures of their own.)
+    if (d.epilogue == EPI_COL_SCATTER && d.out_full % 8 != 0) return true;
+    const int64_t t128 = tiles_of(d.I, d.J, 128, 128);
+    if (ap && ag) return t128 > 512;                // X[:,S] in flight: 128 tiles 28 / 19, 512 44 / 36, 800 (768 deep) 53 / 64
+    if (ap && bp && bg) return t128 > 256;          // W[:,S] along the contraction: 128 tiles 27 / 20, 256 28.5 / 25, 792 91 / 126
+    if (ap && bg) return t128 > 128;                // W[:,S] across it: 96 tiles 29 / 25, 192 30 / 37
+    if (ag || bg) return t128 > 96;                 // dW, a gather in flight, 4096 tokens: 48 tiles 84 / 47, 192 84 / 115
+    // not where the contraction is long enough to be split (48 tiles, 4096 tokens: 21 / 30)
+    if (slices_for(d.C, t128, d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2) return true;
+    if (ap && !bp) return t128 > 256;               // rows of W: 64 tiles 18 / 9, 256 19 / 17, 512 (1536 deep) 43 / 38, 1600 53 / 68
+    return t128 > 128;                              // plain, both along or both across: 48 tiles 18 / 12.6, 96 18 / 16, 192 19.5 / 24
 }
 
 // Returns -1 when the problem is not eligible, else a zr_status.
@@ -2029,13 +2046,12 @@ int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
             if (!dma_ok) return launch_shape<LdPV, LdQV>(a, stream);
             return bm ? launch_shape<DmaP, DmaQM>(a, stream) : launch_shape<DmaP, DmaQ>(a, stream);
         }
-        if (ag && !bg) return bm ? launch_shape<LdPG, DmaQM>(a, stream) : launch_shape<LdPG, DmaQ>(a, stream);
+        if (ag && !bg) return launch_shape<LdPG, DmaQM>(a, stream);
         if (!ag && bg) return launch_shape<DmaP, LdQG>(a, stream);
         return -1;
     }
     if (d.A.c_contig && d.B.c_contig) {             // dX
         if (!ag && !bg) return dma_ok ? launch_shape<DmaP, DmaP>(a, stream) : launch_shape<LdPV, LdPV>(a, stream);
-        if (ag && bg) return launch_shape<LdPG, LdPG>(a, stream);
         if (!ag && bg) return launch_shape<DmaP, LdPG>(a, stream);
         return -1;
     }
