@@ -170,40 +170,56 @@ __global__ __launch_bounds__(SEL_THREADS) void select_multi_kernel(const SelectM
 // ---------------------------------------------------------------------------
 // One long vector on many workgroups (with scratch from the caller).  The same
 // selection as select_body, cut into launches; every launch reads the vector once:
-//   clear     the four global histograms
-//   hist p    (p = 0..3) each workgroup histograms digit p of the keys of its slice that
-//             match the digits chosen so far (which every wavefront first derives again
-//             from the global histograms of the passes before: 256 counters per pass),
-//             in LDS, then adds its 256 counters to the global histogram of the pass
+//   clear     the global histograms of three digits (11, 11 and 10 bits of the key)
+//   hist p    (p = 0..2) each workgroup histograms digit p of the keys of its share that
+//             match the digits chosen so far, in LDS, then adds its counters to the global
+//             histogram of the pass; the digit of the pass before is chosen first, by every
+//             workgroup for itself, from that pass's global histogram
 //   count     the last digit gives T and how many keys equal to T are kept; each
-//             WAVEFRONT counts the keys > T and == T of its 4096 scores
-//   scan      one workgroup: exclusive prefix sums of those counts over the wavefronts
-//   write     the ordered pass, each wavefront on its own 4096 scores with no barrier:
-//             position = the wavefront's prefix + the position inside it
+//             WAVEFRONT counts the keys > T and == T of its slice
+//   write     each workgroup adds up the counts before its own; then the ordered pass, each
+//             wavefront on its own slice with no barrier: position = the counts before it + the
+//             position inside it
 // All counters are integers (order-free); the lists are the same, bit for bit, as
 // those of the single-workgroup kernel.
-// Scratch (uint32 words): [0, 1024) histograms; [1024, 1032) T, kept-equal count;
-// then gt count, eq count, gt prefix, eq prefix: 4 x WIDE_MAX_GROUPS.
+// What bounds it: launches of a few microseconds that wait for memory, so the vector is cut into
+// as many slices as there is room for counts (256 scores and more), and a digit is as wide as its
+// histogram in LDS allows.  395264 scores, against four 8-bit digits, slices of 4096 scores and a
+// launch for the prefix sums: 50 -> 24 us (write 19.4 -> 5.4); 2^24 scores: 115 -> 99 us.
+// Scratch (uint32 words): [0, 5120) histograms; [5120, 5128) {prefix, wanted} after each digit;
+// then gt count, eq count: 2 x WIDE_MAX_GROUPS.
 // ---------------------------------------------------------------------------
 constexpr int WIDE_THREADS = 256;
-constexpr int WIDE_WAVE_SLICE = 4096;                          // scores per wavefront
-constexpr int WIDE_SLICE = WIDE_WAVE_SLICE * (WIDE_THREADS / 64);   // per workgroup (64 KB)
-constexpr int WIDE_MAX_GROUPS = (1 << 24) / WIDE_WAVE_SLICE;   // 4096 wavefronts: the longest vector the entry points take
-constexpr int WIDE_STATE = 1024;
-constexpr int WIDE_COUNTS = 1032;
-constexpr size_t WIDE_WORDS = WIDE_COUNTS + 4 * (size_t)WIDE_MAX_GROUPS;
-constexpr int WIDE_COPIES = 8;                                 // copies of the LDS histogram
+constexpr int WIDE_SLICE = 16384;                              // scores that make a vector worth these launches, an eighth
+constexpr int WIDE_MAX_GROUPS = 4096;                          // wavefronts with counts
+constexpr int WIDE_UNIT = 256;                                 // scores per wavefront: multiples of this
+constexpr int WIDE_STATE = 5120;
+constexpr int WIDE_COUNTS = 5128;
+constexpr size_t WIDE_WORDS = 1032 + 4 * (size_t)WIDE_MAX_GROUPS;      // (more than is used; callers keep such buffers)
+static_assert(WIDE_COUNTS + 2 * WIDE_MAX_GROUPS <= WIDE_WORDS, "the scratch");
+constexpr int WIDE_COPIES = 4;                                 // copies of the LDS histogram
+typedef uint32_t u4_words __attribute__((ext_vector_type(4), aligned(4)));      // 16 bytes at any word
 
-// A wavefront picks the digit of one pass from its 256 counters: the bin that holds the
-// `remaining`-th largest candidate (bins taken from the top), and how many candidates of that
-// bin are still wanted.  Every lane returns the result.
-__device__ __forceinline__ void wide_pick(const uint32_t* __restrict__ h256, uint32_t remaining, int lane,
+__host__ __device__ constexpr int wide_bits(int pass) { return pass < 2 ? 11 : 10; }
+__host__ __device__ constexpr int wide_shift(int pass) { return pass == 0 ? 21 : pass == 1 ? 10 : 0; }
+
+// The first wavefront of a workgroup picks the digit of a pass from its global counters: the bin
+// that holds the `remaining`-th largest candidate (bins taken from the top), and how many
+// candidates of that bin are still wanted.  Every lane returns the result.
+template <int BINS>
+__device__ __forceinline__ void wide_pick(const uint32_t* __restrict__ hist, uint32_t remaining, int lane,
                                           uint32_t& digit, uint32_t& remaining_out)
 {
-    uint32_t h[4];
+    constexpr int PER = BINS / 64;
+    uint32_t h[PER];
+    uint32_t mine = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) h[q] = h256[4 * lane + q];
-    const uint32_t mine = h[0] + h[1] + h[2] + h[3];
+    for (int q = 0; q < PER; q += 4) {
+        const u4_words v = *(const u4_words*)(hist + PER * lane + q);
+        h[q] = v.x; h[q + 1] = v.y; h[q + 2] = v.z; h[q + 3] = v.w;
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) mine += h[q];
     uint32_t incl = mine;                       // inclusive suffix sum over lanes
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -213,8 +229,8 @@ __device__ __forceinline__ void wide_pick(const uint32_t* __restrict__ h256, uin
     uint32_t above = incl - mine;
     uint32_t d = 0xffffffffu, r = 0;
 #pragma unroll
-    for (int q = 3; q >= 0; --q) {
-        if (above < remaining && remaining <= above + h[q]) { d = (uint32_t)(4 * lane + q); r = remaining - above; }
+    for (int q = PER - 1; q >= 0; --q) {
+        if (above < remaining && remaining <= above + h[q]) { d = (uint32_t)(PER * lane + q); r = remaining - above; }
         above += h[q];
     }
     // exactly one lane found it
@@ -224,46 +240,58 @@ __device__ __forceinline__ void wide_pick(const uint32_t* __restrict__ h256, uin
     remaining_out = __shfl(r, src, 64);
 }
 
-// prefix / mask / remaining after the first `passes` digits, from the global histograms
-// (run by every wavefront for itself: no LDS, no barrier)
-__device__ __forceinline__ void wide_replay(const uint32_t* __restrict__ ghist, int passes, uint32_t n_keep, int lane,
-                                            uint32_t& prefix, uint32_t& mask, uint32_t& remaining)
+// Prefix of the wanted key and candidates still wanted before pass PASS (3: T itself and how many
+// keys equal to it are kept), for the whole workgroup; block 0 leaves them for the next launch.
+template <int PASS>
+__device__ __forceinline__ void wide_state(uint32_t* __restrict__ ws, uint32_t n_keep, uint32_t* shared2,
+                                           uint32_t& prefix, uint32_t& remaining)
 {
-    prefix = 0; mask = 0; remaining = n_keep;
-    for (int p = 0; p < passes; ++p) {
-        uint32_t digit, rem;
-        wide_pick(ghist + 256 * p, remaining, lane, digit, rem);
-        const int shift = 24 - 8 * p;
-        prefix |= digit << shift;
-        mask |= 0xffu << shift;
-        remaining = rem;
+    prefix = 0; remaining = n_keep;
+    if constexpr (PASS > 0) {
+        if (threadIdx.x < 64) {
+            const int lane = threadIdx.x;
+            uint32_t before = 0, wanted = n_keep;
+            if constexpr (PASS > 1) { before = ws[WIDE_STATE + 2 * (PASS - 1)]; wanted = ws[WIDE_STATE + 2 * (PASS - 1) + 1]; }
+            uint32_t digit, rem;
+            wide_pick<1 << wide_bits(PASS - 1)>(ws + 2048 * (PASS - 1), wanted, lane, digit, rem);
+            before |= digit << wide_shift(PASS - 1);
+            if (lane == 0) {
+                shared2[0] = before; shared2[1] = rem;
+                if (blockIdx.x == 0) { ws[WIDE_STATE + 2 * PASS] = before; ws[WIDE_STATE + 2 * PASS + 1] = rem; }
+            }
+        }
+        __syncthreads();
+        prefix = shared2[0]; remaining = shared2[1];
     }
 }
 
 __global__ __launch_bounds__(1024) void wide_clear_kernel(uint32_t* __restrict__ ws)
 {
-    if (threadIdx.x < 1024) ws[threadIdx.x] = 0;
+#pragma unroll
+    for (int q = 0; q < 5; ++q) ws[threadIdx.x + 1024 * q] = 0;
 }
 
-// One workgroup of 1024 threads per compute unit, each on a contiguous share of the vector: with
-// one workgroup per 16384 scores the 256 global counters of a pass took a quarter of a million
-// atomic additions (1024 workgroups x 256 bins), and the passes whose digit is spread over all
-// bins ran at half the speed of the others.
+// At most one workgroup of 1024 threads per compute unit, each on a contiguous share of the vector
+// (every workgroup adds its counters to the global ones: more of them, more atomic additions).
 constexpr int WIDE_HIST_THREADS = 1024;
 constexpr int WIDE_HIST_GROUPS = 256;
 
-__global__ __launch_bounds__(WIDE_HIST_THREADS) void wide_hist_kernel(const float* __restrict__ s, int n, int n_keep, int pass,
+template <int PASS>
+__global__ __launch_bounds__(WIDE_HIST_THREADS) void wide_hist_kernel(const float* __restrict__ s, int n, int n_keep,
                                                                       uint32_t* __restrict__ ws, int share)
 {
     // WIDE_COPIES counters per bin, side by side: lanes that hit the same bin (scores cluster in a
     // few exponents, so the first digit has a handful of busy bins) spread over as many addresses
-    __shared__ uint32_t hist[256 * WIDE_COPIES];
+    constexpr int BINS = 1 << wide_bits(PASS);
+    __shared__ __align__(16) uint32_t hist[BINS * WIDE_COPIES];
+    __shared__ uint32_t state[2];
     const int tid = threadIdx.x, lane = tid & 63;
-    uint32_t prefix, mask, remaining;
-    wide_replay(ws, pass, (uint32_t)n_keep, lane, prefix, mask, remaining);
-    for (int q = tid; q < 256 * WIDE_COPIES; q += WIDE_HIST_THREADS) hist[q] = 0;
+    for (int q = tid; q < BINS * WIDE_COPIES; q += WIDE_HIST_THREADS) hist[q] = 0;
+    uint32_t prefix, remaining;
+    wide_state<PASS>(ws, (uint32_t)n_keep, state, prefix, remaining);
     __syncthreads();
-    const int shift = 24 - 8 * pass;
+    constexpr int shift = wide_shift(PASS);
+    constexpr uint32_t mask = PASS == 0 ? 0u : ~0u << wide_shift(PASS > 0 ? PASS - 1 : 0);
     const int copy = lane & (WIDE_COPIES - 1);
     const int64_t lo64 = (int64_t)blockIdx.x * share;
     const int lo = (int)min<int64_t>(lo64, n), hi = (int)min<int64_t>(lo64 + share, n);
@@ -275,34 +303,33 @@ __global__ __launch_bounds__(WIDE_HIST_THREADS) void wide_hist_kernel(const floa
         for (int q = 0; q < 8; ++q) {
             const uint32_t k = order_key(v[q]);
             if (i0 + q * WIDE_HIST_THREADS < hi && (k & mask) == prefix)
-                atomicAdd(&hist[((k >> shift) & 255u) * WIDE_COPIES + copy], 1u);
+                atomicAdd(&hist[((k >> shift) & (BINS - 1)) * WIDE_COPIES + copy], 1u);
         }
     }
     __syncthreads();
-    if (tid < 256) {
-        uint32_t mine = 0;
-#pragma unroll
-        for (int q = 0; q < WIDE_COPIES; ++q) mine += hist[tid * WIDE_COPIES + q];
-        if (mine) atomicAdd(&ws[256 * pass + tid], mine);
+    for (int b = tid; b < BINS; b += WIDE_HIST_THREADS) {
+        const uint4 c = *(const uint4*)(hist + b * WIDE_COPIES);
+        const uint32_t mine = c.x + c.y + c.z + c.w;
+        if (mine) atomicAdd(&ws[2048 * PASS + b], mine);
     }
 }
 
 __global__ __launch_bounds__(WIDE_THREADS) void wide_count_kernel(const float* __restrict__ s, int n, int n_keep,
-                                                                  uint32_t* __restrict__ ws)
+                                                                  uint32_t* __restrict__ ws, int slice)
 {
+    __shared__ uint32_t state[2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t T, mask, need_eq;
-    wide_replay(ws, 4, (uint32_t)n_keep, lane, T, mask, need_eq);
-    if (blockIdx.x == 0 && tid == 0) { ws[WIDE_STATE] = T; ws[WIDE_STATE + 1] = need_eq; }
+    uint32_t T, need_eq;
+    wide_state<3>(ws, (uint32_t)n_keep, state, T, need_eq);
     const int group = blockIdx.x * (WIDE_THREADS / 64) + wave;
-    const int lo = group * WIDE_WAVE_SLICE, hi = min(n, lo + WIDE_WAVE_SLICE);
+    const int lo = (int)min<int64_t>((int64_t)group * slice, n), hi = (int)min<int64_t>((int64_t)lo + slice, n);
     uint32_t gt = 0, eq = 0;
-    for (int i0 = lo + lane; i0 < hi; i0 += 8 * 64) {
-        float v[8];
+    for (int i0 = lo + lane; i0 < hi; i0 += 4 * 64) {
+        float v[4];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = s[min(i0 + q * 64, hi - 1)];
+        for (int q = 0; q < 4; ++q) v[q] = s[min(i0 + q * 64, hi - 1)];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
+        for (int q = 0; q < 4; ++q) {
             const uint32_t k = order_key(v[q]);
             if (i0 + q * 64 < hi) { gt += k > T; eq += k == T; }
         }
@@ -315,52 +342,36 @@ __global__ __launch_bounds__(WIDE_THREADS) void wide_count_kernel(const float* _
     }
 }
 
-// exclusive prefix sums of the per-wavefront counts (groups <= 4096: four consecutive entries per thread)
-__global__ __launch_bounds__(1024) void wide_scan_kernel(uint32_t* __restrict__ ws, int groups)
-{
-    __shared__ uint32_t wsum_gt[16], wsum_eq[16];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t g[4], e[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int j = 4 * tid + q;
-        g[q] = j < groups ? ws[WIDE_COUNTS + j] : 0u;
-        e[q] = j < groups ? ws[WIDE_COUNTS + WIDE_MAX_GROUPS + j] : 0u;
-    }
-    const uint32_t tg = g[0] + g[1] + g[2] + g[3], te = e[0] + e[1] + e[2] + e[3];
-    uint32_t ig = tg, ie = te;                   // inclusive prefix inside the wavefront
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t a = __shfl_up(ig, off, 64), b = __shfl_up(ie, off, 64);
-        if (lane >= off) { ig += a; ie += b; }
-    }
-    if (lane == 63) { wsum_gt[wave] = ig; wsum_eq[wave] = ie; }
-    __syncthreads();
-    uint32_t bg = ig - tg, be = ie - te;         // entries before this thread's four
-    for (int w = 0; w < wave; ++w) { bg += wsum_gt[w]; be += wsum_eq[w]; }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int j = 4 * tid + q;
-        if (j < groups) {
-            ws[WIDE_COUNTS + 2 * WIDE_MAX_GROUPS + j] = bg;
-            ws[WIDE_COUNTS + 3 * WIDE_MAX_GROUPS + j] = be;
-        }
-        bg += g[q];
-        be += e[q];
-    }
-}
-
 __global__ __launch_bounds__(WIDE_THREADS) void wide_write_kernel(const float* __restrict__ s, int n, int n_keep,
-                                                                  const uint32_t* __restrict__ ws,
+                                                                  const uint32_t* __restrict__ ws, int slice,
                                                                   int32_t* __restrict__ keep, int32_t* __restrict__ drop)
 {
+    constexpr int WAVES = WIDE_THREADS / 64;
+    __shared__ uint32_t sum_gt[WAVES], sum_eq[WAVES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int group = blockIdx.x * (WIDE_THREADS / 64) + wave;
-    const int lo = group * WIDE_WAVE_SLICE, hi = min(n, lo + WIDE_WAVE_SLICE);
-    if (lo >= n) return;
-    const uint32_t T = ws[WIDE_STATE], need_eq = ws[WIDE_STATE + 1];
-    uint32_t run_gt = ws[WIDE_COUNTS + 2 * WIDE_MAX_GROUPS + group];
-    uint32_t run_eq = ws[WIDE_COUNTS + 3 * WIDE_MAX_GROUPS + group];
+    // the counts of all wavefronts before this workgroup's
+    const int first = blockIdx.x * WAVES;
+    uint32_t bg = 0, be = 0;
+    for (int j = tid; j < first; j += WIDE_THREADS) {
+        bg += ws[WIDE_COUNTS + j];
+        be += ws[WIDE_COUNTS + WIDE_MAX_GROUPS + j];
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) { bg += __shfl_down(bg, off, 64); be += __shfl_down(be, off, 64); }
+    if (lane == 0) { sum_gt[wave] = bg; sum_eq[wave] = be; }
+    __syncthreads();
+    const int group = first + wave;
+    const int64_t lo64 = (int64_t)group * slice;
+    if (lo64 >= n) return;
+    const int lo = (int)lo64, hi = (int)min<int64_t>(lo64 + slice, n);
+    const uint32_t T = ws[WIDE_STATE + 6], need_eq = ws[WIDE_STATE + 7];
+    uint32_t run_gt = 0, run_eq = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { run_gt += sum_gt[w]; run_eq += sum_eq[w]; }
+    for (int w = 0; w < wave; ++w) {
+        run_gt += ws[WIDE_COUNTS + first + w];
+        run_eq += ws[WIDE_COUNTS + WIDE_MAX_GROUPS + first + w];
+    }
     const uint64_t below = (1ull << lane) - 1ull;
     for (int base = lo; base < hi; base += 4 * 64) {
         float v[4];
@@ -426,7 +437,7 @@ int launch_select(const float* scores, int n, int batch, int n_keep,
 
 size_t select_wide_workspace_bytes() { return WIDE_WORDS * sizeof(uint32_t); }
 
-// shortest vector that goes to the many-workgroup path (below it the seven launches cost more
+// shortest vector that goes to the many-workgroup path (below it the launches cost more
 // than the single workgroup's passes)
 int select_wide_min_n() { return 8 * WIDE_SLICE; }
 
@@ -434,19 +445,20 @@ int launch_select_wide(const float* scores, int n, int n_keep, int32_t* keep_idx
                        void* workspace, hipStream_t stream)
 {
     uint32_t* ws = (uint32_t*)workspace;
-    const int blocks = (n + WIDE_SLICE - 1) / WIDE_SLICE;
-    const int groups = (n + WIDE_WAVE_SLICE - 1) / WIDE_WAVE_SLICE;        // wavefronts with scores
+    // scores per wavefront of the last two launches
+    const int slice = (int)(((int64_t)n + (int64_t)WIDE_MAX_GROUPS * WIDE_UNIT - 1) / ((int64_t)WIDE_MAX_GROUPS * WIDE_UNIT)) * WIDE_UNIT;
+    const int groups = (n + slice - 1) / slice, blocks = (groups + WIDE_THREADS / 64 - 1) / (WIDE_THREADS / 64);
     if (groups > WIDE_MAX_GROUPS) return ZR_ERR_LIMIT;
     hipLaunchKernelGGL(wide_clear_kernel, dim3(1), dim3(1024), 0, stream, ws);
-    const int hist_groups = std::min(WIDE_HIST_GROUPS, blocks);
+    // (shares of 4096 scores and more)
+    const int hist_groups = std::min(WIDE_HIST_GROUPS, (n + 4095) / 4096);
     const int share = (n + hist_groups - 1) / hist_groups;
-    for (int pass = 0; pass < 4; ++pass)
-        hipLaunchKernelGGL(wide_hist_kernel, dim3(hist_groups), dim3(WIDE_HIST_THREADS), 0, stream, scores, n, n_keep, pass,
-                           ws, share);
-    hipLaunchKernelGGL(wide_count_kernel, dim3(blocks), dim3(WIDE_THREADS), 0, stream, scores, n, n_keep, ws);
-    hipLaunchKernelGGL(wide_scan_kernel, dim3(1), dim3(1024), 0, stream, ws, groups);
+    hipLaunchKernelGGL(wide_hist_kernel<0>, dim3(hist_groups), dim3(WIDE_HIST_THREADS), 0, stream, scores, n, n_keep, ws, share);
+    hipLaunchKernelGGL(wide_hist_kernel<1>, dim3(hist_groups), dim3(WIDE_HIST_THREADS), 0, stream, scores, n, n_keep, ws, share);
+    hipLaunchKernelGGL(wide_hist_kernel<2>, dim3(hist_groups), dim3(WIDE_HIST_THREADS), 0, stream, scores, n, n_keep, ws, share);
+    hipLaunchKernelGGL(wide_count_kernel, dim3(blocks), dim3(WIDE_THREADS), 0, stream, scores, n, n_keep, ws, slice);
     hipLaunchKernelGGL(wide_write_kernel, dim3(blocks), dim3(WIDE_THREADS), 0, stream, scores, n, n_keep,
-                       (const uint32_t*)ws, keep_idx, drop_idx);
+                       (const uint32_t*)ws, slice, keep_idx, drop_idx);
     return hip_status(hipGetLastError());
 }
 
