@@ -70,84 +70,143 @@ __device__ __forceinline__ void accum(const T* __restrict__ a, const T* __restri
     }
 }
 
-// true if p is in the ascending list keep[0..n_keep)
-__device__ __forceinline__ bool in_list(const int32_t* __restrict__ keep, int n_keep, int p)
+// Length of the part of the ascending list keep[0..n_keep) below p, for a whole wavefront: 64
+// entries a step (a search by halves is a chain of a dozen loads, 4 us at the end of a launch).
+__device__ __forceinline__ int lower_bound_wave(const int32_t* __restrict__ keep, int n_keep, int p, int lane)
 {
-    int lo = 0, hi = n_keep;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (keep[mid] < p) lo = mid + 1; else hi = mid;
+    int lo = 0, len = n_keep;
+    while (len > 0) {
+        const int step = (len + 63) >> 6;
+        const int i = lane * step;
+        const int below = (int)__popcll(__ballot(i < len && keep[lo + min(i, len - 1)] < p));
+        if (step == 1) return lo + below;
+        if (below == 0) return lo;
+        // entry (below - 1) * step is below p, entry below * step (if there is one) is not
+        const int skip = (below - 1) * step + 1;
+        len = min(step - 1, len - skip);
+        lo += skip;
     }
-    return lo < n_keep && keep[lo] == p;
+    return lo;
 }
 
-__device__ __forceinline__ float finish(float sum, int R, int idx, const float* __restrict__ prev_scores,
-                                        const int32_t* __restrict__ prev_keep, int n_prev_keep)
+// flags[0..width) <- whether column c0 + i is in the list, for i < width <= 256 (the whole
+// workgroup calls it; wavefront 0 searches).  `first` is a word of LDS.  Two barriers.
+__device__ __forceinline__ void mark_kept(const int32_t* __restrict__ keep, int n_keep, int c0, int width,
+                                          uint8_t* flags, int* first)
 {
-    if (prev_keep && !in_list(prev_keep, n_prev_keep, idx)) return prev_scores[idx];
-    return sum / (float)R;
+    const int tid = threadIdx.x;
+    if (tid < 64) {
+        const int lo = lower_bound_wave(keep, n_keep, c0, tid);
+        if (tid == 0) *first = lo;
+    }
+    if (tid < width) flags[tid] = 0;
+    __syncthreads();
+    const int i = *first + tid;
+    if (tid < width && i < n_keep) {
+        const int p = keep[i] - c0;
+        if (p >= 0 && p < width) flags[p] = 1;
+    }
+    __syncthreads();
 }
 
 // Column sums of |W_t - W_prev| over the rows [blockIdx.y * rows_per, +rows_per).
-// A lane owns V adjacent columns, a workgroup 64*V columns; its 16 wavefronts
-// take rows w, w+16, ... and their partial sums are added in wavefront order.
-// FINAL: the grid has one row range and writes the scores; otherwise it writes
-// the range's sums to partial[blockIdx.y][N].
-template <typename T, int V, bool FINAL>
+// A lane owns V adjacent columns, LPR lanes a row, so a workgroup has LPR * V columns and
+// 1024 / LPR rows in flight; the rows' sums are added by a fixed shuffle tree, those of the 16
+// wavefronts in wavefront order.
+// FINAL: the grid has one row range and writes the scores; otherwise it writes the range's sums to
+// partial[blockIdx.y][N].
+// What bounds it: how much the chip has in flight.  With scratch, pieces of 512 bytes and more
+// by as many row ranges as give every compute unit a workgroup; without (or with few rows) a
+// workgroup reads all rows of a piece of 64 bytes, so that there are as many as possible:
+// 4096 x 2752 bf16 without scratch 74 -> 15 us, with it (in a sequence of calls) 12 + 9 -> 12.7 + 3.9.  (Pieces of 64 bytes with scratch too, to save
+// the second launch: 15 us against 17 on matrices in the last-level cache, but 22 to 33 against
+// 12 + 9 from memory.)
+template <typename T, int V, int LPR, bool FINAL>
 __global__ __launch_bounds__(1024) void col_sums_kernel(
     const T* __restrict__ Wt, const T* __restrict__ Wp, int64_t ld, int K, int N, int rows_per,
     const float* __restrict__ prev_scores, const int32_t* __restrict__ prev_keep, int n_prev_keep,
     float* __restrict__ out)
 {
-    __shared__ float part[16][64 * V];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int col = (blockIdx.x * 64 + lane) * V;
+    constexpr int CW = LPR * V, RSTEP = 1024 / LPR, UNROLL = 8;
+    using VT = typename Vec<T, V>::type;
+    __shared__ float part[16][CW];
+    __shared__ uint8_t kept[CW];
+    __shared__ int first;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // neighbouring pieces share lines of memory: every XCD gets a contiguous range of them
+    const int nb = gridDim.x, per = nb / 8;                  // (the host pads the grid to a multiple of 8)
+    const int c0 = ((int)(blockIdx.x % 8) * per + (int)blockIdx.x / 8) * CW;
+    if (c0 >= N) return;
+    if (FINAL && prev_keep) mark_kept(prev_keep, n_prev_keep, c0, CW, kept, &first);
+    const int col = c0 + (tid % LPR) * V;
     const int r0 = blockIdx.y * rows_per;
     const int r1 = min(K, r0 + rows_per);
     float acc[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) acc[i] = 0.f;
     if (col < N) {                      // V > 1 is only launched with N % V == 0
-        const size_t step = (size_t)ld * 16;
-        size_t off = (size_t)(r0 + wave) * (size_t)ld + (size_t)col;
-        int r = r0 + wave;
-        for (; r + 48 < r1; r += 64, off += 4 * step) {
-            accum<T, V>(Wt + off, Wp + off, acc);
-            accum<T, V>(Wt + off + step, Wp + off + step, acc);
-            accum<T, V>(Wt + off + 2 * step, Wp + off + 2 * step, acc);
-            accum<T, V>(Wt + off + 3 * step, Wp + off + 3 * step, acc);
+        for (int r = r0 + tid / LPR; r < r1; r += UNROLL * RSTEP) {
+            // all loads of a batch before its sums; rows past the range repeat the last one and are left out
+            VT a[UNROLL], b[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const size_t off = (size_t)min(r + u * RSTEP, r1 - 1) * (size_t)ld + (size_t)col;
+                a[u] = *reinterpret_cast<const VT*>(Wt + off);
+                b[u] = *reinterpret_cast<const VT*>(Wp + off);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+                if (r + u * RSTEP < r1) accum<T, V>(reinterpret_cast<const T*>(&a[u]), reinterpret_cast<const T*>(&b[u]), acc);
         }
-        for (; r < r1; r += 16, off += step) accum<T, V>(Wt + off, Wp + off, acc);
     }
 #pragma unroll
-    for (int i = 0; i < V; ++i) part[wave][lane * V + i] = acc[i];
+    for (int o = LPR; o < 64; o <<= 1)
+#pragma unroll
+        for (int i = 0; i < V; ++i) acc[i] += __shfl_xor(acc[i], o, 64);
+    if (lane < LPR) {
+#pragma unroll
+        for (int i = 0; i < V; ++i) part[wave][lane * V + i] = acc[i];
+    }
     __syncthreads();
-    for (int t = threadIdx.x; t < 64 * V; t += 1024) {
-        const int c = blockIdx.x * 64 * V + t;
+    for (int t = tid; t < CW; t += 1024) {
+        const int c = c0 + t;
         if (c >= N) continue;
         float sum = 0.f;
 #pragma unroll
         for (int w = 0; w < 16; ++w) sum += part[w][t];
-        if (FINAL) out[c] = finish(sum, K, c, prev_scores, prev_keep, n_prev_keep);
+        if (FINAL) out[c] = prev_keep && !kept[t] ? prev_scores[c] : sum / (float)K;
         else       out[(size_t)blockIdx.y * (size_t)N + c] = sum;
     }
 }
 
-// scores[c] from the per-range sums partial[n_split][N], added in range order
-__global__ __launch_bounds__(256) void col_finish_kernel(
+// scores[c] from the per-range sums partial[n_split][N]: 64 columns a workgroup, each wavefront
+// adds every sixteenth range, then their sums in wavefront order
+__global__ __launch_bounds__(1024) void col_finish_kernel(
     const float* __restrict__ partial, int n_split, int K, int N,
     const float* __restrict__ prev_scores, const int32_t* __restrict__ prev_keep, int n_prev_keep,
     float* __restrict__ scores)
 {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= N) return;
+    __shared__ float part[16][64];
+    __shared__ uint8_t kept[64];
+    __shared__ int first;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c0 = blockIdx.x * 64, c = c0 + lane;
     float sum = 0.f;
-    for (int s = 0; s < n_split; ++s) sum += partial[(size_t)s * (size_t)N + c];
-    scores[c] = finish(sum, K, c, prev_scores, prev_keep, n_prev_keep);
+    for (int s = wave; s < n_split; s += 16) sum += partial[(size_t)s * (size_t)N + min(c, N - 1)];
+    part[wave][lane] = sum;
+    if (prev_keep) mark_kept(prev_keep, n_prev_keep, c0, 64, kept, &first);
+    else __syncthreads();
+    if (wave > 0 || c >= N) return;
+    sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) sum += part[w][lane];
+    scores[c] = prev_keep && !kept[lane] ? prev_scores[c] : sum / (float)K;
 }
 
 // Scores of the ROWS of W[K x N] (pruned axis = K): one wavefront per row, a
-// lane adds its elements in column order, then a fixed shuffle tree.
+// lane adds its elements in column order, then a fixed shuffle tree.  A row that
+// was pruned keeps its score and is not read.
 template <typename T, int V>
 __global__ __launch_bounds__(256) void row_scores_kernel(
     const T* __restrict__ Wt, const T* __restrict__ Wp, int64_t ld, int K, int N,
@@ -157,17 +216,34 @@ __global__ __launch_bounds__(256) void row_scores_kernel(
     const int lane = threadIdx.x & 63;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= K) return;
+    if (prev_keep) {
+        const int at = lower_bound_wave(prev_keep, n_prev_keep, row, lane);
+        if (at >= n_prev_keep || prev_keep[at] != row) {        // uniform
+            if (lane == 0) scores[row] = prev_scores[row];
+            return;
+        }
+    }
     const T* a = Wt + (size_t)row * (size_t)ld;
     const T* b = Wp + (size_t)row * (size_t)ld;
     float acc[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) acc[i] = 0.f;
+    using VT = typename Vec<T, V>::type;
+    // batches of loads, then what is left of a row of no more than three steps, one by one
+    constexpr int UNROLL = V == 1 ? 16 : 8;
     int c = lane * V;                   // V > 1 is only launched with N % V == 0
-    for (; c + 3 * 64 * V < N; c += 4 * 64 * V) {
-        accum<T, V>(a + c, b + c, acc);
-        accum<T, V>(a + c + 64 * V, b + c + 64 * V, acc);
-        accum<T, V>(a + c + 2 * 64 * V, b + c + 2 * 64 * V, acc);
-        accum<T, V>(a + c + 3 * 64 * V, b + c + 3 * 64 * V, acc);
+    for (int base = 0; N - base > 3 * 64 * V; base += UNROLL * 64 * V, c += UNROLL * 64 * V) {
+        VT x[UNROLL], y[UNROLL];
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u) {
+            const int cc = min(c + u * 64 * V, N - V);
+            x[u] = *reinterpret_cast<const VT*>(a + cc);
+            y[u] = *reinterpret_cast<const VT*>(b + cc);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < UNROLL; ++u)
+            if (c + u * 64 * V < N) accum<T, V>(reinterpret_cast<const T*>(&x[u]), reinterpret_cast<const T*>(&y[u]), acc);
     }
     for (; c < N; c += 64 * V) accum<T, V>(a + c, b + c, acc);
     float sum = acc[0];
@@ -175,7 +251,7 @@ __global__ __launch_bounds__(256) void row_scores_kernel(
     for (int i = 1; i < V; ++i) sum += acc[i];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sum += __shfl_down(sum, off, 64);
-    if (lane == 0) scores[row] = finish(sum, N, row, prev_scores, prev_keep, n_prev_keep);
+    if (lane == 0) scores[row] = sum / (float)N;
 }
 
 __global__ __launch_bounds__(1024) void count_above_kernel(const float* __restrict__ scores, int n, float theta,
@@ -195,14 +271,10 @@ __global__ __launch_bounds__(1024) void count_above_kernel(const float* __restri
     }
 }
 
-#ifndef ZR_PRI_BLOCKS
-#define ZR_PRI_BLOCKS 256               // one workgroup of 16 wavefronts per compute unit measured fastest
-#endif
-#ifndef ZR_PRI_MIN_ROWS
-#define ZR_PRI_MIN_ROWS 256
-#endif
-constexpr int kTargetBlocks = ZR_PRI_BLOCKS;
-constexpr int kMinRowsPerSplit = ZR_PRI_MIN_ROWS;
+// Row ranges: of at least 256 rows, until there is one workgroup (of 64 times V columns) per
+// compute unit.  Also what the scratch that callers are told to bring is sized by.
+constexpr int kTargetBlocks = 256;
+constexpr int kMinRowsPerSplit = 256;
 
 template <int V> int col_splits(int K, int N)
 {
@@ -217,21 +289,25 @@ int cols_typed(const T* Wt, const T* Wp, int64_t ld, int K, int N, const float* 
                const int32_t* prev_keep, int n_prev_keep, float* scores, void* workspace, size_t workspace_bytes,
                hipStream_t stream)
 {
-    const int chunks = (N + 64 * V - 1) / (64 * V);
-    int splits = col_splits<V>(K, N);
+    int splits = V == 1 ? col_splits<1>(K, N) : col_splits<4>(K, N);
     const size_t fit = workspace ? workspace_bytes / ((size_t)N * sizeof(float)) : 0;   // row ranges the scratch holds
     if ((size_t)splits > fit) splits = fit < 2 ? 1 : (int)fit;
+    // up to 4 MB a snapshot the second launch costs more than it gains (1024 x 1024 bf16 12.2 us, one launch 9.5)
+    if (K <= 2048 && (int64_t)K * N * (int64_t)sizeof(T) <= (4 << 20)) splits = 1;
+    auto grid = [&](int width) { return ((N + width - 1) / width + 7) / 8 * 8; };
     if (splits == 1) {
-        hipLaunchKernelGGL((col_sums_kernel<T, V, true>), dim3(chunks, 1), dim3(1024), 0, stream,
+        constexpr int LPR = V == 1 ? 32 : 64 / (V * (int)sizeof(T));
+        hipLaunchKernelGGL((col_sums_kernel<T, V, LPR, true>), dim3(grid(LPR * V), 1), dim3(1024), 0, stream,
                            Wt, Wp, ld, K, N, K, prev_scores, prev_keep, n_prev_keep, scores);
         return hip_status(hipGetLastError());
     }
+    constexpr int LPR = V == 8 ? 32 : 64;
     const int rows_per = (((K + splits - 1) / splits) + 15) & ~15;
     splits = (K + rows_per - 1) / rows_per;
     float* partial = (float*)workspace;
-    hipLaunchKernelGGL((col_sums_kernel<T, V, false>), dim3(chunks, splits), dim3(1024), 0, stream,
+    hipLaunchKernelGGL((col_sums_kernel<T, V, LPR, false>), dim3(grid(LPR * V), splits), dim3(1024), 0, stream,
                        Wt, Wp, ld, K, N, rows_per, prev_scores, prev_keep, n_prev_keep, partial);
-    hipLaunchKernelGGL(col_finish_kernel, dim3((N + 255) / 256), dim3(256), 0, stream,
+    hipLaunchKernelGGL(col_finish_kernel, dim3((N + 63) / 64), dim3(1024), 0, stream,
                        partial, splits, K, N, prev_scores, prev_keep, n_prev_keep, scores);
     return hip_status(hipGetLastError());
 }
@@ -278,7 +354,8 @@ int launch_priority_scores(const void* Wt, const void* Wp, int64_t ld, int K, in
     }
     const int v = vec_width((const uint16_t*)Wt, (const uint16_t*)Wp, ld, N, 8);
     if (mode == ZR_DROP_N)
-        return v >= 4 ? cols_typed<uint16_t, 4>(ZR_ARGS(uint16_t), workspace, workspace_bytes, stream)
+        return v == 8 ? cols_typed<uint16_t, 8>(ZR_ARGS(uint16_t), workspace, workspace_bytes, stream)
+             : v == 4 ? cols_typed<uint16_t, 4>(ZR_ARGS(uint16_t), workspace, workspace_bytes, stream)
                       : cols_typed<uint16_t, 1>(ZR_ARGS(uint16_t), workspace, workspace_bytes, stream);
     return v == 8 ? rows_typed<uint16_t, 8>(ZR_ARGS(uint16_t), stream)
          : v == 4 ? rows_typed<uint16_t, 4>(ZR_ARGS(uint16_t), stream)
