@@ -11,11 +11,12 @@
 //   * no load stands under a branch (at a join the compiler waits for every load in flight): rows
 //     and columns are clamped, a chunk at the end of a row is read from the row's last elements and
 //     shifted into place, contraction indices past the end become zeros on the way into LDS;
-//   * a stage is 16 KB of each operand, requested two stages ahead;
+//   * a stage is 16 KB of each operand (32 KB with 512 threads), requested two stages ahead;
 //   * plain operands come in 16-byte loads at 2-byte alignment; kept columns come as the dword that
 //     starts at the element (loads of 16 bits run at a quarter of the rate), two to an LDS word;
 //   * tiles of 128 x 128, 64 x 64 or 32 x 32 by how many of them there are; the 32 x 32 tiles split
-//     each stage's contraction over the four wavefronts.
+//     each stage's contraction over the four wavefronts, the 64 x 64 ones with 512 threads over two
+//     groups of four.
 // Measured against the kernel before this one (128 x 128 tiles, element loads under branches; three
 // quarters of an axis kept): 985 x 1001 x 771 forward 151 -> 18 us, both backward products 253 -> 38;
 // 4095 x 2001 x 1999 forward 544 -> 120 us (205 TFLOP/s), backward 1570 -> 229; accumulating
@@ -33,7 +34,6 @@ namespace zr {
 
 namespace {
 
-constexpr int NT = 256;          // threads per workgroup
 constexpr int NP = 4;            // pieces a stage is brought in: 16 bytes of each operand per thread
 
 typedef uint16_t E;
@@ -44,9 +44,9 @@ typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4_any __attribute__((ext_vector_type(4), aligned(2)));      // 16 bytes at any element
 typedef uint32_t u1_any __attribute__((aligned(2)));                          // 4 bytes at any element
 
-// R x R tiles, BK contraction indices a stage (16 KB of each operand)
-template <int R> struct Geo {
-    static constexpr int BK = 8192 / R;
+// R x R tiles, NT threads, BK contraction indices a stage (64 bytes of each operand per thread)
+template <int R, int NT> struct Geo {
+    static constexpr int BK = 32 * NT / R;
     static constexpr int PP = BK / 2 + 4;                 // words per row of format P: 16 rows of a fragment on 16 bank groups
     static constexpr int PQ = R / 2;                      // words per contraction index of format Q (swizzled)
     static constexpr int WORDS = R * PP;                  // LDS words of one operand's stage (the larger format)
@@ -100,21 +100,21 @@ __device__ __forceinline__ u4 shifted(u4 v, int sh)
 // operand's extent repeat its last row (they only feed results that are never stored);
 // contraction indices past C become zero (commit with TAIL, which only the last stage needs).
 // ---------------------------------------------------------------------------
-template <int R, bool P> struct Lines {
-    static constexpr int BK = Geo<R>::BK;
+template <int R, int NT, bool P> struct Lines {
+    static constexpr int BK = Geo<R, NT>::BK;
     static constexpr int COUNT = P ? R : BK;              // lines of a stage
     static constexpr int LEN = P ? BK : R;                // elements of a line
     // LDS word of 16-byte chunk ch of a line
     static __device__ __forceinline__ int chunk_at(int line, int ch)
     {
-        return P ? line * Geo<R>::PP + ch * 4 : line * Geo<R>::PQ + (ch ^ Geo<R>::swz(line)) * 4;
+        return P ? line * Geo<R, NT>::PP + ch * 4 : line * Geo<R, NT>::PQ + (ch ^ Geo<R, NT>::swz(line)) * 4;
     }
 };
 
 // No list on the contiguous axis, which has at least 8 elements; optional row list.
-template <int R, bool P_> struct Plain {
+template <int R, int NT, bool P_> struct Plain {
     static constexpr bool P = P_;
-    typedef Lines<R, P> L;
+    typedef Lines<R, NT, P> L;
     static constexpr int CPL = L::LEN / 8, LPP = NT / CPL;       // chunks per line, lines per piece
     static_assert(L::COUNT == NP * LPP, "four pieces");
     const E* ptr[NP];       // P: the lines; Q: the lines of the stage being fetched, at this thread's column
@@ -195,9 +195,9 @@ template <int R, bool P_> struct Plain {
 // Kept list on the contiguous axis (of at least 2 elements): a thread owns two neighbours of the
 // list, one LDS word, in every line it visits, so a wavefront's load runs along the (ascending)
 // list in one memory row, or a few.
-template <int R, bool P_> struct Gather {
+template <int R, int NT, bool P_> struct Gather {
     static constexpr bool P = P_;
-    typedef Lines<R, P> L;
+    typedef Lines<R, NT, P> L;
     static constexpr int WPL = L::LEN / 2;                       // words per line
     static constexpr int LPI = NT / WPL;                         // lines per step of the workgroup
     static constexpr int N = L::COUNT / LPI;                     // words per thread
@@ -212,6 +212,7 @@ template <int R, bool P_> struct Gather {
     uint32_t lo[N], hi[N];
 
     // the dword that starts at the element; at the row's last element the one before it
+    // (rounded down to aligned dwords instead, loads take the same time)
     __device__ __forceinline__ void columns(int a, int b, int n_c, bool oka, bool okb)
     {
         a = clamp_idx(a, n_c);
@@ -280,9 +281,9 @@ template <int R, bool P_> struct Gather {
 
 // Element by element through whatever lists there are: for products with a contiguous extent
 // below what the loaders above read at a time.
-template <int R, bool P_> struct Any {
+template <int R, int NT, bool P_> struct Any {
     static constexpr bool P = P_;
-    typedef Lines<R, P> L;
+    typedef Lines<R, NT, P> L;
     static constexpr int WPL = L::LEN / 2, LPI = NT / WPL, N = L::COUNT / LPI;
     int r0_, rlast_;
     uint32_t w_[N];
@@ -315,19 +316,19 @@ template <int R, bool P_> struct Any {
 
 // Operand of a 16 x 16 x 32 MFMA: tile rows r0 .. r0 + 15 (lane & 15), eight contraction indices
 // from 8 (lane >> 4) of the 32 that start at k0.
-template <int R, bool P>
+template <int R, int NT, bool P>
 __device__ __forceinline__ bf16x8 fragment(const uint32_t* lds, int r0, int k0, int lane)
 {
     union { u4 u; v4i16 h[2]; bf16x8 b; } x;
     if constexpr (P) {
-        x.u = *(const u4*)(lds + (r0 + (lane & 15)) * Geo<R>::PP + k0 / 2 + 4 * (lane >> 4));
+        x.u = *(const u4*)(lds + (r0 + (lane & 15)) * Geo<R, NT>::PP + k0 / 2 + 4 * (lane >> 4));
     } else {
         // a 16-lane group reads 4 contraction indices x 16 rows; its lane n gets row n's four
         typedef __attribute__((address_space(3))) v4i16* lp;
         const int t16 = lane & 15, c = k0 + 8 * (lane >> 4) + (t16 >> 2), col = r0 + 4 * (t16 & 3);
-        const uint32_t* p = lds + c * Geo<R>::PQ + (((col >> 3) ^ Geo<R>::swz(c)) << 2) + ((col & 7) >> 1);
+        const uint32_t* p = lds + c * Geo<R, NT>::PQ + (((col >> 3) ^ Geo<R, NT>::swz(c)) << 2) + ((col & 7) >> 1);
         x.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)p);
-        x.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 4 * Geo<R>::PQ));       // (the same swizzle)
+        x.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 4 * Geo<R, NT>::PQ));       // (the same swizzle)
     }
     return x.b;
 }
@@ -345,20 +346,22 @@ __device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
 
 __device__ __forceinline__ uint32_t two(float a, float b) { return f32_to_bf16_bits(a) | (f32_to_bf16_bits(b) << 16); }
 
-template <template <int, bool> class LA_, bool AP, template <int, bool> class LB_, bool BP, int R>
-__global__ __launch_bounds__(NT, 2) void gemm_kernel(const Args g)
+template <template <int, int, bool> class LA_, bool AP, template <int, int, bool> class LB_, bool BP, int R, int NT>
+__global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
 {
-    typedef LA_<R, AP> LA;
-    typedef LB_<R, BP> LB;
-    constexpr int BK = Geo<R>::BK;
-    constexpr int OP_WORDS = Geo<R>::WORDS, STAGE = 2 * OP_WORDS;
+    typedef LA_<R, NT, AP> LA;
+    typedef LB_<R, NT, BP> LB;
+    constexpr int BK = Geo<R, NT>::BK;
+    constexpr int OP_WORDS = Geo<R, NT>::WORDS, STAGE = 2 * OP_WORDS;
     constexpr int WAVES = NT / 64;
-    constexpr bool SPLIT = R == 32;                                   // the wavefronts share the contraction, not the tile
-    constexpr int T = SPLIT ? 2 : R / 32;                             // 16 x 16 results per wavefront and direction
-    constexpr int STEPS = (SPLIT ? BK / WAVES : BK) / 32;             // 32-deep steps per wavefront and stage
+    constexpr int T = R == 32 ? 2 : R / 32;                           // 16 x 16 results per wavefront and direction
+    constexpr int WPT = R == 32 ? 1 : 4;                              // wavefronts that share a tile ...
+    constexpr int KG = WAVES / WPT;                                   // ... and groups of them that share the contraction
+    constexpr bool SPLIT = KG > 1;
+    constexpr int STEPS = BK / KG / 32;                               // 32-deep steps per wavefront and stage
     constexpr int CP = R + 4;                                         // row pitch of the result tile (floats)
     constexpr int TAB = 512;                                          // original columns per pass of the column scatter
-    constexpr int PART = SPLIT ? WAVES * 32 * 36 : 0;                 // the wavefronts' sums
+    constexpr int PART = SPLIT ? KG * R * CP : 0;                     // the groups' sums
     static_assert(R * CP + PART + 2 * R + TAB <= 2 * STAGE, "the epilogue fits the stages");
 
     extern __shared__ __align__(16) uint32_t smem[];
@@ -373,8 +376,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(const Args g)
     const int rows_in = min(4, g.tiles_i - first_i);
     const int i0 = (first_i + within % rows_in) * R, j0 = within / rows_in * R;
 
-    const int wr0 = SPLIT ? 0 : (wave >> 1) * (R / 2), wc0 = SPLIT ? 0 : (wave & 1) * (R / 2);
-    const int k0 = SPLIT ? wave * (BK / WAVES) : 0;
+    const int wr0 = WPT == 1 ? 0 : ((wave >> 1) & 1) * (R / 2), wc0 = WPT == 1 ? 0 : (wave & 1) * (R / 2);
+    const int k0 = wave / WPT * (BK / KG);
 
     f32x4 acc[T][T];
 #pragma unroll
@@ -427,9 +430,9 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(const Args g)
             for (int k = PC * STEPS / NP; k < (PC + 1) * STEPS / NP; ++k) {
                 bf16x8 af[T], bf[T];
 #pragma unroll
-                for (int a = 0; a < T; ++a) af[a] = fragment<R, AP>(as, wr0 + 16 * a, k0 + 32 * k, lane);
+                for (int a = 0; a < T; ++a) af[a] = fragment<R, NT, AP>(as, wr0 + 16 * a, k0 + 32 * k, lane);
 #pragma unroll
-                for (int b = 0; b < T; ++b) bf[b] = fragment<R, BP>(bs, wc0 + 16 * b, k0 + 32 * k, lane);
+                for (int b = 0; b < T; ++b) bf[b] = fragment<R, NT, BP>(bs, wc0 + 16 * b, k0 + 32 * k, lane);
 #pragma unroll
                 for (int a = 0; a < T; ++a)
 #pragma unroll
@@ -446,28 +449,28 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(const Args g)
 
     // ---- result tile in LDS, in fp32 --------------------------------------------
     float* Cs = (float*)smem;
-    float* dst = SPLIT ? Cs + R * CP + wave * 32 * 36 : Cs;
-    constexpr int DP = SPLIT ? 36 : CP;
+    float* dst = SPLIT ? Cs + R * CP + wave / WPT * (R * CP) : Cs;
 #pragma unroll
     for (int a = 0; a < T; ++a)
 #pragma unroll
         for (int b = 0; b < T; ++b)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                dst[(wr0 + 16 * a + 4 * (lane >> 4) + r) * DP + wc0 + 16 * b + (lane & 15)] = acc[a][b][r];
+                dst[(wr0 + 16 * a + 4 * (lane >> 4) + r) * CP + wc0 + 16 * b + (lane & 15)] = acc[a][b][r];
     if constexpr (SPLIT) {
-        // the wavefronts' sums, in wavefront order
+        // the groups' sums, in their order
         __syncthreads();
-        const int row = tid >> 3, col = (tid & 7) * 4;
-        const float* part = Cs + R * CP + row * 36 + col;
-        f32x4 sum = *(const f32x4*)part;
+        for (int q = tid; q < R * R / 4; q += NT) {
+            const int at = q / (R / 4) * CP + q % (R / 4) * 4;
+            f32x4 sum = *(const f32x4*)(Cs + R * CP + at);
 #pragma unroll
-        for (int w = 1; w < WAVES; ++w) {
-            const f32x4 x = *(const f32x4*)(part + w * 32 * 36);
+            for (int w = 1; w < KG; ++w) {
+                const f32x4 x = *(const f32x4*)(Cs + (w + 1) * (R * CP) + at);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum[e] += x[e];
+                for (int e = 0; e < 4; ++e) sum[e] += x[e];
+            }
+            *(f32x4*)(Cs + at) = sum;
         }
-        *(f32x4*)(Cs + row * CP + col) = sum;
     }
     int* sidx = (int*)(smem + R * CP + PART);
     const int rows_valid = min(R, g.I - i0), cols_valid = min(R, g.J - j0);
@@ -595,15 +598,15 @@ __global__ __launch_bounds__(NT, 2) void gemm_kernel(const Args g)
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
-template <template <int, bool> class LA, bool AP, template <int, bool> class LB, bool BP, int R>
+template <template <int, int, bool> class LA, bool AP, template <int, int, bool> class LB, bool BP, int R, int NT>
 int launch_inst(const Args& a, const char* name, hipStream_t stream)
 {
-    constexpr int smem = 2 * 2 * Geo<R>::WORDS * 4;
-    auto fn = gemm_kernel<LA, AP, LB, BP, R>;
+    constexpr int smem = 2 * 2 * Geo<R, NT>::WORDS * 4;
+    auto fn = gemm_kernel<LA, AP, LB, BP, R, NT>;
     static AttrFlags attr_set;      // per instantiation and device
     if (!ensure_max_dynamic_lds((const void*)fn, smem, &attr_set)) return ZR_ERR_HIP;
     if (debug_names_wanted())
-        snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "gemm_kernel<%s, %d>", name, R);
+        snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "gemm_kernel<%s, %d, %d>", name, R, NT);
     Args k = a;
     k.tiles_i = (a.I + R - 1) / R;
     k.tiles_j = (a.J + R - 1) / R;
@@ -613,16 +616,21 @@ int launch_inst(const Args& a, const char* name, hipStream_t stream)
     return hip_status(hipGetLastError());
 }
 
-template <template <int, bool> class LA, bool AP, template <int, bool> class LB, bool BP>
+template <template <int, int, bool> class LA, bool AP, template <int, int, bool> class LB, bool BP>
 int launch_shape(const Args& a, const char* name, hipStream_t stream)
 {
     const int64_t t64 = (int64_t)((a.I + 63) / 64) * ((a.J + 63) / 64), t128 = (int64_t)((a.I + 127) / 128) * ((a.J + 127) / 128);
     // 128 x 128 tiles once there is one for every compute unit (M x K x N = 4001 x 752 x 1003: 256 tiles
     // 28.8 us against 39.0 on 64 x 64; 4001 x 1001 x 752: 192 tiles 49.2 against 40.5); 32 x 32 tiles
     // below 96 of 64 x 64 (dW 376 x 471 over 985 tokens: 48 tiles, 8 us against 15; 985 x 501 x 353:
-    // 96 tiles, 14.1 against 13.6)
-    if (t128 >= 256) return launch_inst<LA, AP, LB, BP, 128>(a, name, stream);
-    return t64 < 96 ? launch_inst<LA, AP, LB, BP, 32>(a, name, stream) : launch_inst<LA, AP, LB, BP, 64>(a, name, stream);
+    // 96 tiles, 14.1 against 13.6);
+    if (t128 >= 256) return launch_inst<LA, AP, LB, BP, 128, 256>(a, name, stream);
+    if (t64 < 96) return launch_inst<LA, AP, LB, BP, 32, 256>(a, name, stream);
+    // and 512 threads on a 64 x 64 tile while each has a compute unit to itself (985 x 1001 x 578
+    // plain 14.1 -> 12.8 us, dW 2024 tokens 27.4 -> 24.7; 288 tiles: 25.0 -> 31.3, so not there; on
+    // 32 x 32 tiles within 5 %, on either side); below four stages of the others it gains nothing
+    if (t64 <= 256 && a.C > 384) return launch_inst<LA, AP, LB, BP, 64, 512>(a, name, stream);
+    return launch_inst<LA, AP, LB, BP, 64, 256>(a, name, stream);
 }
 
 int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
@@ -640,8 +648,8 @@ int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
     const bool ap = d.A.c_contig, bp = d.B.c_contig;
     if (!ap && bp) return ZR_ERR_MODE;
     if (too_short(d.A) || too_short(d.B)) {
-        if (ap) return bp ? launch_inst<Any, true, Any, true, 32>(a, "Pe, Pe", stream) : launch_inst<Any, true, Any, false, 32>(a, "Pe, Qe", stream);
-        return launch_inst<Any, false, Any, false, 32>(a, "Qe, Qe", stream);
+        if (ap) return bp ? launch_inst<Any, true, Any, true, 32, 256>(a, "Pe, Pe", stream) : launch_inst<Any, true, Any, false, 32, 256>(a, "Pe, Qe", stream);
+        return launch_inst<Any, false, Any, false, 32, 256>(a, "Qe, Qe", stream);
     }
     if (ap && !bp) {            // forward, weight stored [K x N]; dX, weight stored [N x K]
         if (ag) return bg ? ZR_ERR_MODE : launch_shape<Gather, true, Plain, false>(a, "Pg, Q", stream);

@@ -1,5 +1,6 @@
 """The bf16 products for any alignment at the edges of their tiles and stages: 32 x 32 tiles (256-deep stages),
-64 x 64 (128-deep, from 96 tiles on) and 128 x 128 (64-deep, from 256 tiles on), contractions of one element
+64 x 64 (128-deep, from 96 tiles on;
+256-deep with 512 threads up to 256 tiles) and 128 x 128 (64-deep, from 256 tiles on), contractions of one element
 up to a little over two stages, rows shorter than the eight elements of a load, odd leading dimensions; both
 layouts, all loaders and epilogues.  Against the float64 oracle with the bounds of parity_util."""
 import numpy as np
@@ -16,7 +17,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("mode", [DROP_N, DROP_K])
 @pytest.mark.parametrize("layout", [W_KN, W_NK])
 @pytest.mark.parametrize("M,K,N", [(31, 33, 32), (33, 255, 64), (65, 257, 3), (64, 3, 130), (2, 515, 5), (9, 1, 2),    # 32 x 32
-                                   (833, 67, 901), (897, 7, 830), (70, 900, 833), (832, 896, 129),                  # 64 x 64
+                                   (833, 67, 901), (897, 7, 830), (70, 900, 833), (832, 896, 129), (641, 771, 1003),                # 64 x 64
                                    (2497, 65, 2433), (2500, 2433, 63), (129, 2561, 2497)])                          # 128 x 128
 def test_bf16_tile_edges(zr, torch_mod, oracle, mode, layout, M, K, N):  # noqa: F811
     case = wl.random_case(31 * M + 7 * K + N, M, K, N, "bf16")
