@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <atomic>
+#include <cstdlib>
+#include <cstring>
 
 #include "zr.h"
 #include "zr_debug.h"
@@ -95,6 +97,23 @@ struct DebugState {
 };
 extern thread_local DebugState g_debug;
 inline bool debug_names_wanted() { return g_debug.record_names || g_debug.armed_once; }
+
+// ZR_FORCE_TILES in the environment (read once): "256", "192x256" or "256x192" sends every bf16 product
+// of aligned tensors to one grid of that tile shape, whatever the schedule would choose, and those that
+// have no kernel of such a shape to 128 x 128 tiles: a test switch (small and ragged shapes then run
+// through the big-tile kernels).  0 = not set.
+inline int forced_tiles()
+{
+    static const int f = [] {
+        const char* e = getenv("ZR_FORCE_TILES");
+        if (!e) return 0;
+        if (!strcmp(e, "256")) return 1;
+        if (!strcmp(e, "192x256")) return 2;
+        if (!strcmp(e, "256x192")) return 3;
+        return 0;
+    }();
+    return f;
+}
 
 // Dynamic-LDS attribute of a kernel: set once per device and instantiation (the call is
 // idempotent, so two threads racing to set it do no harm; the flags are atomic).

@@ -624,7 +624,7 @@ int launch_shape(const Args& a, const char* name, hipStream_t stream)
     // 28.8 us against 39.0 on 64 x 64; 4001 x 1001 x 752: 192 tiles 49.2 against 40.5); 32 x 32 tiles
     // below 96 of 64 x 64 (dW 376 x 471 over 985 tokens: 48 tiles, 8 us against 15; 985 x 501 x 353:
     // 96 tiles, 14.1 against 13.6);
-    if (t128 >= 256) return launch_inst<LA, AP, LB, BP, 128, 256>(a, name, stream);
+    if (t128 >= 256 || forced_tiles()) return launch_inst<LA, AP, LB, BP, 128, 256>(a, name, stream);
     if (t64 < 96) return launch_inst<LA, AP, LB, BP, 32, 256>(a, name, stream);
     // and 512 threads on a 64 x 64 tile while each has a compute unit to itself (985 x 1001 x 578
     // plain 14.1 -> 12.8 us, dW 2024 tokens 27.4 -> 24.7; 288 tiles: 25.0 -> 31.3, so not there; on

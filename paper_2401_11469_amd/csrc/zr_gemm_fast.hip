@@ -1915,22 +1915,6 @@ inline Sched plan_tiles(int I, int J)
     return best;
 }
 
-// ZR_FORCE_TILES in the environment (read once): "256", "192x256" or "256x192" sends every product
-// of this path to one grid of that tile shape, whatever the schedule would choose: a test switch
-// (small and ragged shapes then run through the big-tile kernels).  0 = not set.
-inline int forced_tiles()
-{
-    static const int f = [] {
-        const char* e = getenv("ZR_FORCE_TILES");
-        if (!e) return 0;
-        if (!strcmp(e, "256")) return 1;
-        if (!strcmp(e, "192x256")) return 2;
-        if (!strcmp(e, "256x192")) return 3;
-        return 0;
-    }();
-    return f;
-}
-
 template <template <int, int> class LA, template <int, int> class LB>
 int launch_shape(const FArgs& a, hipStream_t stream)
 {
