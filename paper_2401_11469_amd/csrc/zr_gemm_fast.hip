@@ -1935,6 +1935,15 @@ int launch_shape(const FArgs& a, hipStream_t stream)
             return launch_tile<LA, LB, 192, 256, 2, 4>(a, 0, a.I, 0, a.J, stream);
         }
     }
+    if constexpr (std::is_same<LA<64, 256>, DmaP<64, 256>>::value && std::is_same<LB<128, 256>, DmaP<128, 256>>::value) {
+        // 64 x 128 tiles, three to a compute unit, while 128 x 128 ones would leave units with one
+        // (1024 deep: 192 tiles 19.8 -> 15.7 us, 384 tiles 25 -> 22.7; 2048 deep 384 tiles 36.1 -> 36.7,
+        // 480 tiles 38.5 -> 53).  With a row list on the contraction they are slower (512 tiles 24 -> 33).
+        const int64_t t = tiles_of(a.I, a.J, 128, 128);
+        if (sc.big_i_end == 0 && (t <= 256 || (t <= 384 && a.C <= 1024)) &&
+            slices_for(a.C, t, a.partial, a.partial_bytes, a.accumulate != 0) < 2)
+            return launch_tile<LA, LB, 64, 128, 1, 4>(a, 0, a.I, 0, a.J, stream);
+    }
     if (sc.big_i_end == 0)                     // everything on small tiles
         return launch_tile<LA, LB, 128, 128, 2, 2>(a, 0, a.I, 0, a.J, stream);
     int st = launch_tile<LA, LB, 256, 256, ZR_BIG_WM, ZR_BIG_WN>(a, 0, sc.big_i_end, 0, sc.big_j_end, stream);
@@ -1994,10 +2003,13 @@ static bool eligible(const GemmDesc& d)
     if (ap && bp && bg) return t128 > 256;          // W[:,S] along the contraction: 128 tiles 27 / 20, 256 28.5 / 25, 792 91 / 126
     if (ap && bg) return t128 > 128;                // W[:,S] across it: 96 tiles 29 / 25, 192 30 / 37
     if (ag || bg) return t128 > 96;                 // dW, a gather in flight, 4096 tokens: 48 tiles 84 / 47, 192 84 / 115
-    // not where the contraction is long enough to be split (48 tiles, 4096 tokens: 21 / 30)
-    if (slices_for(d.C, t128, d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2) return true;
+    // direct-to-LDS loaders, and with them split contractions, need a contraction of whole 64-deep
+    // tiles or an operand that supplies the zeros
+    const bool dma = d.C % BK == 0 || (ap && d.A.zero_padded) || (bp && d.B.zero_padded);
+    if (dma && slices_for(d.C, t128, d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2) return true;      // (48 tiles, 4096 tokens: 21 / 30)
     if (ap && !bp) return t128 > 256;               // rows of W: 64 tiles 18 / 9, 256 19 / 17, 512 (1536 deep) 43 / 38, 1600 53 / 68
-    return t128 > 128;                              // plain, both along or both across: 48 tiles 18 / 12.6, 96 18 / 16, 192 19.5 / 24
+    if (ap) return t128 > (dma ? 64 : 128);         // 48 tiles 12.5 / 11, 96 14 / 16.5; 1504 deep (not whole) 72 tiles 27.6 / 19, 168 37 / 37
+    return t128 > (dma ? 128 : 256);                // dW: 48 tiles 18 / 12.6; 3000 tokens 48 tiles 54 / 19, 120 55 / 33, 5000 tokens 192 89 / 80
 }
 
 // Returns -1 when the problem is not eligible, else a zr_status.
