@@ -7,19 +7,24 @@
 // the bf16 rate, so even a 64 x 64 tile asks for only 16 bytes per clock from L2 and its LDS
 // reads are a small fraction of the LDS rate.  What costs time is a chip that is not full and
 // loads that are waited for.  Hence small tiles, deep stages and several workgroups to a unit:
+//   R = 128: 128 x 128 tiles, 32 contraction indices a stage, a 64 x 64 result per wavefront: for
+//           products with many tiles (half the LDS reads and half the operand bytes per FLOP);
 //   R = 64: 64 x 64 tiles, 64 contraction indices a stage, a 32 x 32 result per wavefront;
 //   R = 32: 32 x 32 tiles, 128 contraction indices a stage, of which each of the four
 //           wavefronts multiplies a quarter; their four sums are added in wavefront order in
 //           LDS.  For products with few tiles: four times as many workgroups, half the stages.
-// Both bring 16 KB of each operand per stage (four 16-byte loads or sixteen element loads a
+// All bring 16 KB of each operand per stage (four 16-byte loads or sixteen element loads a
 // thread, in flight for a whole stage of multiplications) and use 72 KB of LDS, so that two
 // workgroups share a compute unit.
 // Measured against the kernel before this one (128 x 128 tiles, 32 deep, element loads under
 // branches): 1576 x 1024 x 1640 plain 94 -> 66 us, with the kept list on the contraction
-// 222 -> 72 us, 256 x 512 x 192 in four launches 132 -> 30 us; 4096^3 runs at 122 TFLOP/s (0.78
-// of the fp32 matrix peak).  Of a launch 10-13 us are start and end (all tiles of a round
-// end together); a chip full of tiles keeps the matrix pipes at 0.9 in between, so what is left
-// is that, and the rounding of the tile count to the compute units.
+// 222 -> 72 us, 256 x 512 x 192 in four launches 132 -> 30 us.  Products with many tiles, 8192 x 4096
+// results (us before / on 64 x 64 tiles / on 128 x 128): contraction 1024, dW 633 / 683 / 580, forward
+// 599 / 619 / 553; contraction 64, kept columns of W gathered 83 / 121 / 79; contraction 8, accumulating
+// 62 / 88 / 56.  4096^3 runs at 122 TFLOP/s on 64 x 64 tiles (0.78 of the fp32 matrix peak).  Of a launch
+// 10-13 us are start and end (all tiles of a round end together); a chip full of tiles keeps the
+// matrix pipes at 0.9 in between, so what is left is that, and the rounding of the tile count to
+// the compute units.
 //
 // LDS formats (32-bit words):
 //   P  [row][contraction]  tensors whose contiguous axis is the contraction axis
@@ -37,16 +42,16 @@ namespace zr {
 namespace {
 
 constexpr int NT = 256;
+constexpr int NP = 4;            // pieces a stage is brought in: 16 bytes of each operand per thread
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef float f4_any __attribute__((ext_vector_type(4), aligned(4)));     // 16 bytes at any element address
 
 template <int R> struct Geo {
-    static constexpr int BK = R == 64 ? 64 : 128;   // contraction depth of a stage
-    static constexpr int NP = R * BK / (4 * NT);          // pieces a stage is brought in: 16 bytes of each operand per thread
+    static constexpr int BK = 16 * NT / R;                // contraction depth of a stage: 32, 64 or 128
     static constexpr int PP = BK + 4;                     // row pitch of format P: 16 rows of a fragment read on 16 bank groups
-    static constexpr int PQ = R == 64 ? 72 : 36;          // row pitch of format Q: rows 4 apart (the two lane halves) on other banks
+    static constexpr int PQ = R == 32 ? 36 : R + 8;       // row pitch of format Q: rows 4 apart (the two lane halves) on other banks
     static constexpr int WORDS = R * PP > BK * PQ ? R * PP : BK * PQ;      // LDS words of one operand's stage
 };
 
@@ -98,7 +103,7 @@ __device__ __forceinline__ f4 shifted(f4 v, int sh)
 template <int R> struct PlainP {
     static constexpr const char* NAME = "P";
     static constexpr bool P = true;
-    static constexpr int BK = Geo<R>::BK, NP = Geo<R>::NP, CPR = BK / 4, RPP = NT / CPR;
+    static constexpr int BK = Geo<R>::BK, CPR = BK / 4, RPP = NT / CPR;
     const float* ptr[NP];
     int off_;
     f4 v[NP];
@@ -139,7 +144,7 @@ template <int R> struct PlainP {
 template <int R> struct GatherP {
     static constexpr const char* NAME = "Pg";
     static constexpr bool P = true;
-    static constexpr int BK = Geo<R>::BK, NP = Geo<R>::NP, RSTEP = NT / BK, N = R / RSTEP;
+    static constexpr int BK = Geo<R>::BK, RSTEP = NT / BK, N = R / RSTEP;
     static constexpr int RPW = BK < 64 ? 64 / BK : 1;                    // memory rows per wavefront load
     const float* base_;
     int64_t ld_;
@@ -187,7 +192,7 @@ template <int R> struct GatherP {
 template <int R> struct PlainQ {
     static constexpr const char* NAME = "Q";
     static constexpr bool P = false;
-    static constexpr int BK = Geo<R>::BK, NP = Geo<R>::NP, CPR = R / 4, RPP = NT / CPR;
+    static constexpr int BK = Geo<R>::BK, CPR = R / 4, RPP = NT / CPR;
     const float* colp;      // base + this thread's (clamped) column
     int sh_;                // how far the clamp moved it
     bool edge_;             // uniform: the tile reaches past the stored rows' end
@@ -236,7 +241,8 @@ template <int R> struct PlainQ {
 template <int R> struct GatherQ {
     static constexpr const char* NAME = "Qg";
     static constexpr bool P = false;
-    static constexpr int BK = Geo<R>::BK, NP = Geo<R>::NP, CSTEP = NT / R, N = BK / CSTEP, RPW = 64 / R;      // RPW: memory rows per wavefront load
+    static constexpr int BK = Geo<R>::BK, CSTEP = NT / R, N = BK / CSTEP;
+    static constexpr int RPW = R < 64 ? 64 / R : 1;                      // memory rows per wavefront load
     const float* base_;
     int64_t ld_;
     int c0_, clast_;        // uniform: first contraction index of this wavefront, last one of all
@@ -246,11 +252,11 @@ template <int R> struct GatherQ {
     {
         col_ = (uint32_t)clamp_idx(op.map_c[min(r0 + tid % R, rlim - 1)], op.n_c);
         base_ = op.base; ld_ = op.ld; clast_ = C - 1; c0_ = 0;
-        second_ = (tid % 64) / R;
+        second_ = RPW == 1 ? 0 : (tid % 64) / R;
     }
     __device__ __forceinline__ void begin(const View&, int c0, int, int tid)
     {
-        c0_ = c0 + RPW * __builtin_amdgcn_readfirstlane(tid / 64);
+        c0_ = c0 + (RPW == 1 ? __builtin_amdgcn_readfirstlane(tid / R) : RPW * __builtin_amdgcn_readfirstlane(tid / 64));
     }
     template <int PC> __device__ __forceinline__ void fetch(const View&, int, int, int)
     {
@@ -336,13 +342,13 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
     typedef LA_<R> LA;
     typedef LB_<R> LB;
     constexpr int BK = Geo<R>::BK;
-    constexpr int NP = Geo<R>::NP;
     constexpr int OP_WORDS = Geo<R>::WORDS, STAGE = 2 * OP_WORDS;
     constexpr int WAVES = NT / 64;
-    constexpr int BLOCKS = R == 64 ? BK / 8 : BK / 8 / WAVES;         // blocks of 8 per wavefront and stage
+    constexpr int T = R == 128 ? 2 : 1;                               // 32 x 32 results per wavefront and direction
+    constexpr int BLOCKS = R == 32 ? BK / 8 / WAVES : BK / 8;         // blocks of 8 per wavefront and stage
     constexpr int CP = R + 4;                                         // row pitch of the result tile
     constexpr int TAB = 512;                                          // original columns per pass of the column scatter
-    constexpr int PART = R == 64 ? 0 : 4 * 32 * 36;                   // the wavefronts' sums
+    constexpr int PART = R == 32 ? 4 * 32 * 36 : 0;                   // the wavefronts' sums
     static_assert(R * CP + PART + 2 * R + TAB <= 2 * STAGE, "the epilogue fits the stages");
 
     extern __shared__ __align__(16) float smem[];
@@ -358,12 +364,16 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
     const int rows_in = min(4, g.tiles_i - first_i);
     const int i0 = (first_i + within % rows_in) * R, j0 = within / rows_in * R;
 
-    const int wr0 = R == 64 ? (wave >> 1) * 32 : 0, wc0 = R == 64 ? (wave & 1) * 32 : 0;
-    const int blk0 = R == 64 ? 0 : wave * BLOCKS;
+    const int wr0 = R == 32 ? 0 : (wave >> 1) * (R / 2), wc0 = R == 32 ? 0 : (wave & 1) * (R / 2);
+    const int blk0 = R == 32 ? wave * BLOCKS : 0;
 
-    f32x16 acc;
+    f32x16 acc[T][T];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int i = 0; i < T; ++i)
+#pragma unroll
+        for (int j = 0; j < T; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
     // While stage k is multiplied, stage k + 1 (requested during stage k - 1) goes from registers
     // to the other LDS buffer and stage k + 2 is requested, a piece at a time between the blocks
@@ -385,13 +395,18 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
     };
     auto all = [](auto f) {
         f(std::integral_constant<int, 0>());
-        if constexpr (NP > 1) f(std::integral_constant<int, 1>());
-        if constexpr (NP > 2) { f(std::integral_constant<int, 2>()); f(std::integral_constant<int, 3>()); }
+        f(std::integral_constant<int, 1>());
+        f(std::integral_constant<int, 2>());
+        f(std::integral_constant<int, 3>());
     };
     begin(0);
     all([&](auto p) { fetch(0, p); });
-    begin(1);                            // (past the end of a short contraction: valid addresses, zeros)
-    all([&](auto p) { commit(smem, 0, p, std::true_type()); fetch(1, p); });
+    if (KT > 1) {                        // (a lone stage with nothing behind it: 2 to 4 % of a launch 8 deep)
+        begin(1);
+        all([&](auto p) { commit(smem, 0, p, std::true_type()); fetch(1, p); });
+    } else {
+        all([&](auto p) { commit(smem, 0, p, std::true_type()); });
+    }
     __syncthreads();
 
     // fetches: there is a stage k + 2; else stage k + 1, if there is one, is the last
@@ -400,7 +415,12 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
         const float* bs = as + OP_WORDS;
         float* nx = smem + ((kt + 1) & 1) * STAGE;
         if constexpr (decltype(fetches)::value) begin(kt + 2);
-        f4 a = fragment<LA::P, R>(as, wr0 + l32, blk0, grp), b = fragment<LB::P, R>(bs, wc0 + l32, blk0, grp);
+        f4 a[T], b[T];
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            a[i] = fragment<LA::P, R>(as, wr0 + 32 * i + l32, blk0, grp);
+            b[i] = fragment<LB::P, R>(bs, wc0 + 32 * i + l32, blk0, grp);
+        }
         all([&](auto piece) {
             constexpr int PC = decltype(piece)::value;
             if constexpr (decltype(commits)::value)
@@ -408,17 +428,26 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
             if constexpr (decltype(fetches)::value) fetch(kt + 2, piece);
 #pragma unroll
             for (int k = PC * BLOCKS / NP; k < (PC + 1) * BLOCKS / NP; ++k) {
-                f4 an = a, bn = b;
-                if (k + 1 < BLOCKS) {
-                    an = fragment<LA::P, R>(as, wr0 + l32, blk0 + k + 1, grp);
-                    bn = fragment<LB::P, R>(bs, wc0 + l32, blk0 + k + 1, grp);
+                f4 an[T], bn[T];
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    an[i] = a[i]; bn[i] = b[i];
+                    if (k + 1 < BLOCKS) {
+                        an[i] = fragment<LA::P, R>(as, wr0 + 32 * i + l32, blk0 + k + 1, grp);
+                        bn[i] = fragment<LB::P, R>(bs, wc0 + 32 * i + l32, blk0 + k + 1, grp);
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);       // the next block's reads stay above this block's MFMAs
 #pragma unroll
-                for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[s], b[s], acc, 0, 0, 0);
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int i = 0; i < T; ++i)
+#pragma unroll
+                        for (int j = 0; j < T; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-                a = an;
-                b = bn;
+#pragma unroll
+                for (int i = 0; i < T; ++i) { a[i] = an[i]; b[i] = bn[i]; }
             }
         });
         __syncthreads();
@@ -430,13 +459,18 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
 
     // ---- result tile in LDS ---------------------------------------------------
     float* Cs = smem;
-    if constexpr (R == 64) {
+    if constexpr (R != 32) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) Cs[(wr0 + (r >> 2) * 8 + grp * 4 + (r & 3)) * CP + wc0 + l32] = acc[r];
+        for (int i = 0; i < T; ++i)
+#pragma unroll
+            for (int j = 0; j < T; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    Cs[(wr0 + 32 * i + (r >> 2) * 8 + grp * 4 + (r & 3)) * CP + wc0 + 32 * j + l32] = acc[i][j][r];
     } else {
         float* part = smem + R * CP;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) part[(wave * 32 + (r >> 2) * 8 + grp * 4 + (r & 3)) * 36 + l32] = acc[r];
+        for (int r = 0; r < 16; ++r) part[(wave * 32 + (r >> 2) * 8 + grp * 4 + (r & 3)) * 36 + l32] = acc[0][0][r];
         __syncthreads();
         const int row = tid >> 3, col = (tid & 7) * 4;
         f4 sum = *(const f4*)(part + row * 36 + col);
@@ -476,7 +510,7 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
                 const int jj = tab[q];
                 float* o = g.out + (size_t)i0 * (size_t)g.ldo + base + q;
                 const float* pv = g.prev ? g.prev + (size_t)i0 * (size_t)g.ldo + base + q : nullptr;
-                constexpr int UB = R / WAVES / 2;
+                constexpr int UB = R == 32 ? 4 : 8;
                 for (int r0 = wave; r0 < rows_valid; r0 += WAVES * UB) {
                     float x[UB];
 #pragma unroll
@@ -495,9 +529,36 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
         return;
     }
 
-    constexpr int CPR = R / 4;
+    constexpr int CPR = R / 4, CHUNKS = R * CPR / NT;
+    if (rows_valid == R && cols_valid == R && g.out_vec) {
+        // a whole tile: the old values of eight chunks are requested together (8192 x 4096, 8 deep: 64 -> 56 us)
+        constexpr int UB = CHUNKS < 8 ? CHUNKS : 8;
+        const int j = tid % CPR * 4;
+        for (int it = 0; it < CHUNKS; it += UB) {
+            float* o[UB];
+            f4 old[UB];
 #pragma unroll
-    for (int it = 0; it < R * CPR / NT; ++it) {
+            for (int u = 0; u < UB; ++u) {
+                const int row = tid / CPR + NT / CPR * (it + u);
+                o[u] = g.out + (size_t)(scatter_r ? sidx[row] : i0 + row) * (size_t)g.ldo + j0 + j;
+            }
+            if (g.accumulate) {
+#pragma unroll
+                for (int u = 0; u < UB; ++u) old[u] = *(const f4*)o[u];
+            } else {
+#pragma unroll
+                for (int u = 0; u < UB; ++u) old[u] = f4{0.f, 0.f, 0.f, 0.f};
+            }
+#pragma unroll
+            for (int u = 0; u < UB; ++u) {
+                f4 x = *(const f4*)(Cs + (tid / CPR + NT / CPR * (it + u)) * CP + j);
+                if (g.accumulate) x += old[u];
+                *(f4*)o[u] = x;
+            }
+        }
+    } else
+#pragma unroll
+    for (int it = 0; it < CHUNKS; ++it) {
         const int q = tid + NT * it;
         const int row = q / CPR, j = (q % CPR) * 4;
         if (row >= rows_valid || j >= cols_valid) continue;
@@ -528,8 +589,8 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
             while (todo) {
                 const int p = base + (__ffsll((long long)todo) - 1);
                 todo &= todo - 1;
-                if (lane < cols_valid) {
-                    const size_t off = (size_t)p * (size_t)g.ldo + j0 + lane;
+                for (int j = lane; j < cols_valid; j += 64) {
+                    const size_t off = (size_t)p * (size_t)g.ldo + j0 + j;
                     g.out[off] = g.prev ? g.prev[off] : 0.f;
                 }
             }
@@ -558,10 +619,17 @@ int launch_inst(const Args& a, hipStream_t stream)
 template <template <int> class LA, template <int> class LB>
 int launch_shape(const Args& a, hipStream_t stream)
 {
+    const int64_t t64 = (int64_t)((a.I + 63) / 64) * ((a.J + 63) / 64), t128 = (int64_t)((a.I + 127) / 128) * ((a.J + 127) / 128);
+    // 128 x 128 tiles where they fill their rounds of 256: per area they are 4 to 24 % faster (contraction 256,
+    // P x Q: 512 tiles 43 us against 48 on 64 x 64, 384 tiles 42 against 37, 256 tiles 25 against 26).  Short
+    // contractions are all epilogue and half empty 64-deep stages: contraction 8, 192 tiles 9 against 10,
+    // 2048 tiles 39 against 72; contraction 64, 192 tiles 11 against 10, 384 tiles 16 against 17.
+    const int64_t rounds64 = (t64 + 255) / 256, rounds128 = (t128 + 255) / 256;
+    const bool big = a.C <= 32 ? t128 >= 192 : a.C <= 96 ? t128 >= 256 : 0.92 * 4 * (double)rounds128 < (double)rounds64;
+    if (big) return launch_inst<LA, LB, 128>(a, stream);
     // 64 x 64 tiles once there is one for most compute units (contraction 1024: 128 tiles 22.0 us
     // against 15.2 on 32 x 32, 192 tiles 22.7 against 21.8, 256 tiles 23.3 against 27.8, 512 tiles
     // 41.1 against 52.1)
-    const int64_t t64 = (int64_t)((a.I + 63) / 64) * ((a.J + 63) / 64);
     return t64 < 192 ? launch_inst<LA, LB, 32>(a, stream) : launch_inst<LA, LB, 64>(a, stream);
 }
 
