@@ -116,6 +116,7 @@ template <int R, int NT, bool P_> struct Plain {
     static constexpr bool P = P_;
     typedef Lines<R, NT, P> L;
     static constexpr int CPL = L::LEN / 8, LPP = NT / CPL;       // chunks per line, lines per piece
+    static constexpr bool ONE_STAGE = false;
     static_assert(L::COUNT == NP * LPP, "four pieces");
     const E* ptr[NP];       // P: the lines; Q: the lines of the stage being fetched, at this thread's column
     const E* colp;
@@ -198,6 +199,7 @@ template <int R, int NT, bool P_> struct Plain {
 template <int R, int NT, bool P_> struct Gather {
     static constexpr bool P = P_;
     typedef Lines<R, NT, P> L;
+    static constexpr bool ONE_STAGE = false;
     static constexpr int WPL = L::LEN / 2;                       // words per line
     static constexpr int LPI = NT / WPL;                         // lines per step of the workgroup
     static constexpr int N = L::COUNT / LPI;                     // words per thread
@@ -280,37 +282,70 @@ template <int R, int NT, bool P_> struct Gather {
 };
 
 // Element by element through whatever lists there are: for products with a contiguous extent
-// below what the loaders above read at a time.
+// below what the loaders above read at a time.  A thread owns two neighbours of every line it
+// visits; lists are read once per tile (tile rows) or per stage (contraction indices).
 template <int R, int NT, bool P_> struct Any {
     static constexpr bool P = P_;
     typedef Lines<R, NT, P> L;
     static constexpr int WPL = L::LEN / 2, LPI = NT / WPL, N = L::COUNT / LPI;
-    int r0_, rlast_;
-    uint32_t w_[N];
-    __device__ __forceinline__ void init(const View&, int r0, int rlim, int, int) { r0_ = r0; rlast_ = rlim - 1; }
-    __device__ __forceinline__ void begin(const View&, int, int, int) {}
-    __device__ __forceinline__ uint32_t element(const View& op, int c0, int C, int line, int e) const
+    static_assert(N == 4 * NP, "four words a piece");
+    static constexpr bool ONE_STAGE = R != 32;            // (the host's rule: larger tiles are for contractions below eight)
+    int line_[N];           // lines of the stage being fetched
+    int a_, b_;             // columns of the stage being fetched
+    uint32_t lo[N], hi[N];
+    __device__ __forceinline__ void lines(const View& op, int first, int last, int tid)
     {
-        const int r = min(r0_ + (P ? line : e), rlast_), c = c0 + (P ? e : line), cc = min(c, C - 1);
-        int s = P ? r : cc, t = P ? cc : r;                     // along the strided and the contiguous axis
-        if (op.map_s) s = clamp_idx(op.map_s[s], op.n_s);
-        if (op.map_c) t = clamp_idx(op.map_c[t], op.n_c);
-        const uint32_t x = op.base[(size_t)s * (size_t)op.ld + t];
-        return c < C ? x : 0u;
+#pragma unroll
+        for (int it = 0; it < N; ++it) line_[it] = min(first + tid / WPL + LPI * it, last);
+        if (op.map_s) {
+#pragma unroll
+            for (int it = 0; it < N; ++it) line_[it] = op.map_s[line_[it]];
+#pragma unroll
+            for (int it = 0; it < N; ++it) line_[it] = clamp_idx(line_[it], op.n_s);
+        }
     }
-    template <int PC> __device__ __forceinline__ void fetch(const View& op, int c0, int C, int tid)
+    __device__ __forceinline__ void columns(const View& op, int first, int last, int tid)
+    {
+        a_ = min(first + 2 * (tid % WPL), last);
+        b_ = min(first + 2 * (tid % WPL) + 1, last);
+        if (op.map_c) {
+            a_ = clamp_idx(op.map_c[a_], op.n_c);
+            b_ = clamp_idx(op.map_c[b_], op.n_c);
+        }
+    }
+    __device__ __forceinline__ void init(const View& op, int r0, int rlim, int, int tid)
+    {
+        if constexpr (P) lines(op, r0, rlim - 1, tid);
+        else columns(op, r0, rlim - 1, tid);
+    }
+    __device__ __forceinline__ void begin(const View& op, int c0, int C, int tid)
+    {
+        if constexpr (P) columns(op, c0, C - 1, tid);
+        else lines(op, c0, C - 1, tid);
+    }
+    template <int PC> __device__ __forceinline__ void fetch(const View& op, int, int, int)
     {
 #pragma unroll
         for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
-            const int line = tid / WPL + LPI * it, e = 2 * (tid % WPL);
-            w_[it] = element(op, c0, C, line, e) | (element(op, c0, C, line, e + 1) << 16);
+            const E* line = op.base + (size_t)line_[it] * (size_t)op.ld;
+            lo[it] = line[a_];
+            hi[it] = line[b_];
         }
     }
-    template <int PC, bool TAIL> __device__ __forceinline__ void commit(uint32_t* lds, int, int, int tid) const
+    template <int PC, bool TAIL> __device__ __forceinline__ void commit(uint32_t* lds, int c0, int C, int tid) const
     {
         const int w = tid % WPL;
 #pragma unroll
-        for (int it = 4 * PC; it < 4 * PC + 4; ++it) lds[L::chunk_at(tid / WPL + LPI * it, w / 4) + w % 4] = w_[it];
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
+            const int line = tid / WPL + LPI * it;
+            uint32_t l = lo[it], h = hi[it];
+            if constexpr (TAIL) {
+                const int c = c0 + (P ? 2 * w : line);
+                l = c < C ? l : 0u;
+                h = c + (P ? 1 : 0) < C ? h : 0u;
+            }
+            lds[L::chunk_at(line, w / 4) + w % 4] = l | (h << 16);
+        }
     }
 };
 
@@ -352,6 +387,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
     typedef LA_<R, NT, AP> LA;
     typedef LB_<R, NT, BP> LB;
     constexpr int BK = Geo<R, NT>::BK;
+    constexpr bool ONE_STAGE = LA::ONE_STAGE || LB::ONE_STAGE;
     constexpr int OP_WORDS = Geo<R, NT>::WORDS, STAGE = 2 * OP_WORDS;
     constexpr int WAVES = NT / 64;
     constexpr int T = R == 32 ? 2 : R / 32;                           // 16 x 16 results per wavefront and direction
@@ -411,8 +447,11 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
     };
     begin(0);
     all([&](auto p) { fetch(0, p); });
-    begin(1);                            // (past the end of a short contraction: valid addresses, zeros)
-    all([&](auto p) { commit(smem, 0, p, std::true_type()); fetch(1, p); });
+    if constexpr (!ONE_STAGE) begin(1);  // (past the end of a short contraction: valid addresses, zeros)
+    all([&](auto p) {
+        commit(smem, 0, p, std::true_type());
+        if constexpr (!ONE_STAGE) fetch(1, p);
+    });
     __syncthreads();
 
     // fetches: there is a stage k + 2; else stage k + 1, if there is one, is the last
@@ -443,8 +482,10 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
         __syncthreads();
     };
     int kt = 0;
-    for (; kt + 2 < KT; ++kt) step(kt, std::true_type(), std::true_type());
-    if (kt + 1 < KT) step(kt++, std::true_type(), std::false_type());
+    if constexpr (!ONE_STAGE) {
+        for (; kt + 2 < KT; ++kt) step(kt, std::true_type(), std::true_type());
+        if (kt + 1 < KT) step(kt++, std::true_type(), std::false_type());
+    }
     step(kt, std::false_type(), std::false_type());
 
     // ---- result tile in LDS, in fp32 --------------------------------------------
@@ -483,7 +524,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
         // The tile owns the original columns from its first kept column (0 for the first tile) up to
         // the next tile's first kept column (the full width for the last tile).  A table says which
         // result column, if any, belongs to each; then whole rows of owned columns leave, kept and
-        // imputed ones together, two columns to a thread and 256 contiguous bytes to a wavefront.
+        // imputed ones together, two columns to a thread.
         int* tab = sidx + 2 * R;
         const int start = j0 == 0 ? 0 : sidx[0];
         const int end = j0 + R >= g.J ? g.out_full : clamp_idx(g.keep[j0 + R], g.out_full);
@@ -496,13 +537,18 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
                 if (p >= 0 && p < width) tab[p] = tid;
             }
             __syncthreads();
-            for (int q = 2 * lane; q < width; q += 128) {
+            for (int cb = 0; cb < width; cb += 128) {
+                // 64, 32 or 16 lanes to a row by what is left of the columns
+                const int left = width - cb, lpr = left > 64 ? 64 : left > 32 ? 32 : 16, rpw = 64 / lpr;
+                const int q = cb + 2 * (lane & (lpr - 1));
+                if (q >= width) continue;
                 const int ja = tab[q], jb = tab[q + 1];
                 const bool pair = q + 1 < width;
                 E* o = g.out + (size_t)i0 * (size_t)g.ldo + base + q;
                 const E* pv = g.prev ? g.prev + (size_t)i0 * (size_t)g.ldo + base + q : nullptr;
+                const int step = WAVES * rpw;
                 constexpr int UB = 8;
-                for (int r0 = wave; r0 < rows_valid; r0 += WAVES * UB) {
+                for (int r0 = wave * rpw + lane / lpr; r0 < rows_valid; r0 += step * UB) {
                     uint32_t x[UB];
 #pragma unroll
                     for (int u = 0; u < UB; ++u) x[u] = 0u;
@@ -512,23 +558,23 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
                         if (pair) {
 #pragma unroll
                             for (int u = 0; u < UB; ++u)
-                                x[u] = *(const u1_any*)(pv + (size_t)min(r0 + WAVES * u, rows_valid - 1) * (size_t)g.ldo);
+                                x[u] = *(const u1_any*)(pv + (size_t)min(r0 + step * u, rows_valid - 1) * (size_t)g.ldo);
                         } else {
 #pragma unroll
                             for (int u = 0; u < UB; ++u)
-                                x[u] = pv[(size_t)min(r0 + WAVES * u, rows_valid - 1) * (size_t)g.ldo];
+                                x[u] = pv[(size_t)min(r0 + step * u, rows_valid - 1) * (size_t)g.ldo];
                         }
                     }
 #pragma unroll
                     for (int u = 0; u < UB; ++u) {
-                        const int row = min(r0 + WAVES * u, rows_valid - 1);
+                        const int row = min(r0 + step * u, rows_valid - 1);
                         if (ja >= 0) x[u] = (x[u] & 0xffff0000u) | f32_to_bf16_bits(Cs[row * CP + ja]);
                         if (jb >= 0) x[u] = (x[u] & 0xffffu) | (f32_to_bf16_bits(Cs[row * CP + jb]) << 16);
                     }
 #pragma unroll
                     for (int u = 0; u < UB; ++u) {
-                        if (r0 + WAVES * u >= rows_valid) break;
-                        E* p = o + (size_t)(r0 + WAVES * u) * (size_t)g.ldo;
+                        if (r0 + step * u >= rows_valid) break;
+                        E* p = o + (size_t)(r0 + step * u) * (size_t)g.ldo;
                         if (pair) *(u1_any*)p = x[u];
                         else *p = (E)x[u];
                     }
@@ -633,6 +679,21 @@ int launch_shape(const Args& a, const char* name, hipStream_t stream)
     return launch_inst<LA, AP, LB, BP, 64, 256>(a, name, stream);
 }
 
+// The element loaders.  A contraction of less than eight is one stage of any tile shape, however
+// little of the stage it fills, so the larger tiles mean fewer of them (accumulating, 3 deep, us on
+// 128 x 128 / 64 x 64 / 32 x 32 tiles: 8192 x 4096 43 / 72 / 267, 1000 x 1000 10.1 / 7.8 / 11.2); otherwise
+// the result has less than eight rows or columns, and the narrowest tiles waste least.
+template <template <int, int, bool> class LA, bool AP, template <int, int, bool> class LB, bool BP>
+int launch_short(const Args& a, const char* name, hipStream_t stream)
+{
+    if (a.C < 8) {
+        const int64_t t64 = (int64_t)((a.I + 63) / 64) * ((a.J + 63) / 64), t128 = (int64_t)((a.I + 127) / 128) * ((a.J + 127) / 128);
+        if (t128 >= 192) return launch_inst<LA, AP, LB, BP, 128, 256>(a, name, stream);
+        if (t64 >= 96) return launch_inst<LA, AP, LB, BP, 64, 256>(a, name, stream);
+    }
+    return launch_inst<LA, AP, LB, BP, 32, 256>(a, name, stream);
+}
+
 int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
 {
     if (d.I < 1 || d.J < 1 || d.C < 1) return ZR_ERR_SHAPE;
@@ -648,8 +709,8 @@ int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
     const bool ap = d.A.c_contig, bp = d.B.c_contig;
     if (!ap && bp) return ZR_ERR_MODE;
     if (too_short(d.A) || too_short(d.B)) {
-        if (ap) return bp ? launch_inst<Any, true, Any, true, 32, 256>(a, "Pe, Pe", stream) : launch_inst<Any, true, Any, false, 32, 256>(a, "Pe, Qe", stream);
-        return launch_inst<Any, false, Any, false, 32, 256>(a, "Qe, Qe", stream);
+        if (ap) return bp ? launch_short<Any, true, Any, true>(a, "Pe, Pe", stream) : launch_short<Any, true, Any, false>(a, "Pe, Qe", stream);
+        return launch_short<Any, false, Any, false>(a, "Qe, Qe", stream);
     }
     if (ap && !bp) {            // forward, weight stored [K x N]; dX, weight stored [N x K]
         if (ag) return bg ? ZR_ERR_MODE : launch_shape<Gather, true, Plain, false>(a, "Pg, Q", stream);

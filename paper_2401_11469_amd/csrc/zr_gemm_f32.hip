@@ -280,34 +280,56 @@ template <int R> struct GatherQ {
 };
 
 // Element by element through whatever lists there are: for products with a contiguous extent
-// below the four elements that the plain loaders read at a time.
+// below the four elements that the plain loaders read at a time.  A thread owns one element of every
+// line it visits; lists are read once per tile (tile rows) or per stage (contraction indices).
 template <int R, bool P_> struct AnyPQ {
     static constexpr const char* NAME = P_ ? "Pe" : "Qe";
     static constexpr bool P = P_;
-    static constexpr int BK = Geo<R>::BK;
-    int r0_, rlast_;
-    float v[16];
-    __device__ __forceinline__ void init(const View&, int r0, int rlim, int, int) { r0_ = r0; rlast_ = rlim - 1; }
-    __device__ __forceinline__ void begin(const View&, int, int, int) {}
-    template <int PC> __device__ __forceinline__ void fetch(const View& op, int c0, int C, int tid)
+    static constexpr int BK = Geo<R>::BK, LEN = P ? BK : R, LPI = NT / LEN, N = 16;      // a line's elements, lines per step
+    static_assert(LPI * N * LEN == R * BK, "the stage");
+    const float* line_[N];  // lines of the stage being fetched
+    int col_;               // column of the stage being fetched
+    float v[N];
+    __device__ __forceinline__ void lines(const View& op, int first, int last, int tid)
+    {
+        int at[N];
+#pragma unroll
+        for (int it = 0; it < N; ++it) at[it] = min(first + tid / LEN + LPI * it, last);
+        if (op.map_s) {
+#pragma unroll
+            for (int it = 0; it < N; ++it) at[it] = op.map_s[at[it]];
+#pragma unroll
+            for (int it = 0; it < N; ++it) at[it] = clamp_idx(at[it], op.n_s);
+        }
+#pragma unroll
+        for (int it = 0; it < N; ++it) line_[it] = op.base + (size_t)at[it] * (size_t)op.ld;
+    }
+    __device__ __forceinline__ void column(const View& op, int first, int last, int tid)
+    {
+        col_ = min(first + tid % LEN, last);
+        if (op.map_c) col_ = clamp_idx(op.map_c[col_], op.n_c);
+    }
+    __device__ __forceinline__ void init(const View& op, int r0, int rlim, int, int tid)
+    {
+        if constexpr (P) lines(op, r0, rlim - 1, tid);
+        else column(op, r0, rlim - 1, tid);
+    }
+    __device__ __forceinline__ void begin(const View& op, int c0, int C, int tid)
+    {
+        if constexpr (P) column(op, c0, C - 1, tid);
+        else lines(op, c0, C - 1, tid);
+    }
+    template <int PC> __device__ __forceinline__ void fetch(const View&, int, int, int)
     {
 #pragma unroll
-        for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
-            const int q = tid + NT * it;
-            const int r = min(r0_ + (P ? q / BK : q % R), rlast_), c = min(c0 + (P ? q % BK : q / R), C - 1);
-            int s = P ? r : c, t = P ? c : r;                   // along the strided and the contiguous axis
-            if (op.map_s) s = clamp_idx(op.map_s[s], op.n_s);
-            if (op.map_c) t = clamp_idx(op.map_c[t], op.n_c);
-            v[it] = op.base[(size_t)s * (size_t)op.ld + t];
-        }
+        for (int it = 4 * PC; it < 4 * PC + 4; ++it) v[it] = line_[it][col_];
     }
     template <int PC, bool TAIL> __device__ __forceinline__ void commit(float* lds, int c0, int C, int tid) const
     {
 #pragma unroll
         for (int it = 4 * PC; it < 4 * PC + 4; ++it) {
-            const int q = tid + NT * it;
-            const int c = P ? q % BK : q / R;
-            lds[P ? q / BK * Geo<R>::PP + c : c * Geo<R>::PQ + q % R] = !TAIL || c0 + c < C ? v[it] : 0.f;
+            const int line = tid / LEN + LPI * it, e = tid % LEN;
+            lds[line * (P ? Geo<R>::PP : Geo<R>::PQ) + e] = !TAIL || c0 + (P ? e : line) < C ? v[it] : 0.f;
         }
     }
 };
@@ -633,6 +655,14 @@ int launch_shape(const Args& a, hipStream_t stream)
     return t64 < 192 ? launch_inst<LA, LB, 32>(a, stream) : launch_inst<LA, LB, 64>(a, stream);
 }
 
+// The element loaders: a contraction of less than four is one stage of any tile shape; otherwise the
+// result has less than four rows or columns, and the narrowest tiles waste least.
+template <template <int> class LA, template <int> class LB>
+int launch_short(const Args& a, hipStream_t stream)
+{
+    return a.C < 4 ? launch_shape<LA, LB>(a, stream) : launch_inst<LA, LB, 32>(a, stream);
+}
+
 }  // namespace
 
 int launch_gemm_f32(const GemmDesc& d, hipStream_t stream)
@@ -649,8 +679,8 @@ int launch_gemm_f32(const GemmDesc& d, hipStream_t stream)
     const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
     auto too_short = [&](const Operand& o) { return !o.map_contig && (o.c_contig ? d.C : o.n_contig) < 4; };
     if (too_short(d.A) || too_short(d.B)) {
-        if (d.A.c_contig) return d.B.c_contig ? launch_inst<AnyP, AnyP, 32>(a, stream) : launch_inst<AnyP, AnyQ, 32>(a, stream);
-        return d.B.c_contig ? ZR_ERR_MODE : launch_inst<AnyQ, AnyQ, 32>(a, stream);
+        if (d.A.c_contig) return d.B.c_contig ? launch_short<AnyP, AnyP>(a, stream) : launch_short<AnyP, AnyQ>(a, stream);
+        return d.B.c_contig ? ZR_ERR_MODE : launch_short<AnyQ, AnyQ>(a, stream);
     }
     if (d.A.c_contig && !d.B.c_contig) {            // forward, weight stored [K x N]
         if (ag) return bg ? ZR_ERR_MODE : launch_shape<GatherP, PlainQ>(a, stream);
