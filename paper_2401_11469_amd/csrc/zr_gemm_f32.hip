@@ -71,7 +71,6 @@ struct Args {
     int epilogue;
     const int32_t* keep;
     int out_full;
-    int out_vec;                // output rows allow 16-byte stores
     int tiles_i, tiles_j;
     const float* prev;          // Same imputation source (layout of out) or nullptr
     int accumulate;             // add the old contents of out (plain epilogue)
@@ -450,6 +449,9 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
             if constexpr (decltype(fetches)::value) fetch(kt + 2, piece);
 #pragma unroll
             for (int k = PC * BLOCKS / NP; k < (PC + 1) * BLOCKS / NP; ++k) {
+                // (blocks past the end of the contraction hold zeros)
+                if constexpr (!decltype(commits)::value && R == 128)
+                    if (kt * BK + 8 * k >= g.C) break;
                 f4 an[T], bn[T];
 #pragma unroll
                 for (int i = 0; i < T; ++i) {
@@ -552,7 +554,7 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
     }
 
     constexpr int CPR = R / 4, CHUNKS = R * CPR / NT;
-    if (rows_valid == R && cols_valid == R && g.out_vec) {
+    if (rows_valid == R && cols_valid == R) {
         // a whole tile: the old values of eight chunks are requested together (8192 x 4096, 8 deep: 64 -> 56 us)
         constexpr int UB = CHUNKS < 8 ? CHUNKS : 8;
         const int j = tid % CPR * 4;
@@ -566,7 +568,7 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
             }
             if (g.accumulate) {
 #pragma unroll
-                for (int u = 0; u < UB; ++u) old[u] = *(const f4*)o[u];
+                for (int u = 0; u < UB; ++u) old[u] = *(const f4_any*)o[u];
             } else {
 #pragma unroll
                 for (int u = 0; u < UB; ++u) old[u] = f4{0.f, 0.f, 0.f, 0.f};
@@ -575,7 +577,7 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
             for (int u = 0; u < UB; ++u) {
                 f4 x = *(const f4*)(Cs + (tid / CPR + NT / CPR * (it + u)) * CP + j);
                 if (g.accumulate) x += old[u];
-                *(f4*)o[u] = x;
+                *(f4_any*)o[u] = x;
             }
         }
     } else
@@ -586,9 +588,9 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
         if (row >= rows_valid || j >= cols_valid) continue;
         float* o = g.out + (size_t)(scatter_r ? sidx[row] : i0 + row) * (size_t)g.ldo + j0 + j;
         f4 x = *(const f4*)(Cs + row * CP + j);
-        if (j + 4 <= cols_valid && g.out_vec) {
-            if (g.accumulate) x += *(const f4*)o;
-            *(f4*)o = x;
+        if (j + 4 <= cols_valid) {
+            if (g.accumulate) x += *(const f4_any*)o;
+            *(f4_any*)o = x;
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
@@ -673,7 +675,6 @@ int launch_gemm_f32(const GemmDesc& d, hipStream_t stream)
     a.B = View{(const float*)d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
     a.I = d.I; a.J = d.J; a.C = d.C;
     a.out = (float*)d.out; a.ldo = d.ldo; a.epilogue = d.epilogue; a.keep = d.keep_idx; a.out_full = d.out_full;
-    a.out_vec = (uintptr_t)d.out % 16 == 0 && d.ldo % 4 == 0;
     a.tiles_i = a.tiles_j = 0;
     a.prev = (const float*)d.prev; a.accumulate = d.accumulate ? 1 : 0;
     const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
