@@ -34,6 +34,25 @@ __device__ __forceinline__ int clamp_idx(int v, int n)
     return v < 0 ? 0 : (v >= n ? n - 1 : v);
 }
 
+// Length of the part of the ascending list keep[0..n_keep) below p, for a whole wavefront: 64
+// entries a step (a search by halves is a chain of a dozen loads, 4 us at the end of a launch).
+__device__ __forceinline__ int lower_bound_wave(const int32_t* __restrict__ keep, int n_keep, int p, int lane)
+{
+    int lo = 0, len = n_keep;
+    while (len > 0) {
+        const int step = (len + 63) >> 6;
+        const int i = lane * step;
+        const int below = (int)__popcll(__ballot(i < len && keep[lo + min(i, len - 1)] < p));
+        if (step == 1) return lo + below;
+        if (below == 0) return lo;
+        // entry (below - 1) * step is below p, entry below * step (if there is one) is not
+        const int skip = (below - 1) * step + 1;
+        len = min(step - 1, len - skip);
+        lo += skip;
+    }
+    return lo;
+}
+
 // ---- problem description handed from the C ABI to the GEMM launcher ---------
 //
 // Every product is brought to the canonical form

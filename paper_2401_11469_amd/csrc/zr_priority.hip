@@ -70,25 +70,6 @@ __device__ __forceinline__ void accum(const T* __restrict__ a, const T* __restri
     }
 }
 
-// Length of the part of the ascending list keep[0..n_keep) below p, for a whole wavefront: 64
-// entries a step (a search by halves is a chain of a dozen loads, 4 us at the end of a launch).
-__device__ __forceinline__ int lower_bound_wave(const int32_t* __restrict__ keep, int n_keep, int p, int lane)
-{
-    int lo = 0, len = n_keep;
-    while (len > 0) {
-        const int step = (len + 63) >> 6;
-        const int i = lane * step;
-        const int below = (int)__popcll(__ballot(i < len && keep[lo + min(i, len - 1)] < p));
-        if (step == 1) return lo + below;
-        if (below == 0) return lo;
-        // entry (below - 1) * step is below p, entry below * step (if there is one) is not
-        const int skip = (below - 1) * step + 1;
-        len = min(step - 1, len - skip);
-        lo += skip;
-    }
-    return lo;
-}
-
 // flags[0..width) <- whether column c0 + i is in the list, for i < width <= 256 (the whole
 // workgroup calls it; wavefront 0 searches).  `first` is a word of LDS.  Two barriers.
 __device__ __forceinline__ void mark_kept(const int32_t* __restrict__ keep, int n_keep, int c0, int width,
@@ -117,26 +98,31 @@ __device__ __forceinline__ void mark_kept(const int32_t* __restrict__ keep, int 
 // partial[blockIdx.y][N].
 // What bounds it: how much the chip has in flight.  With scratch, pieces of 512 bytes and more
 // by as many row ranges as give every compute unit a workgroup; without (or with few rows) a
-// workgroup reads all rows of a piece of 64 bytes, so that there are as many as possible:
-// 4096 x 2752 bf16 without scratch 74 -> 15 us, with it (in a sequence of calls) 12 + 9 -> 12.7 + 3.9.  (Pieces of 64 bytes with scratch too, to save
-// the second launch: 15 us against 17 on matrices in the last-level cache, but 22 to 33 against
-// 12 + 9 from memory.)
+// workgroup reads all rows of a piece, of 64 bytes so that there are as many as possible, or of 512 and
+// more where those are enough: 4096 x 2752 bf16 without scratch 74 -> 15 us, with it (in a sequence
+// of calls) 12 + 9 -> 12.7 + 3.9.  (Pieces of 64 bytes with scratch too, to save the second launch: 15 us
+// against 17 on matrices in the last-level cache, but 22 to 33 against 12 + 9 from memory.)
 template <typename T, int V, int LPR, bool FINAL>
 __global__ __launch_bounds__(1024) void col_sums_kernel(
     const T* __restrict__ Wt, const T* __restrict__ Wp, int64_t ld, int K, int N, int rows_per,
     const float* __restrict__ prev_scores, const int32_t* __restrict__ prev_keep, int n_prev_keep,
     float* __restrict__ out)
 {
-    constexpr int CW = LPR * V, RSTEP = 1024 / LPR, UNROLL = 8;
+    constexpr int CW = LPR * V, RSTEP = 1024 / LPR;
+    constexpr bool NARROW = LPR * V * sizeof(T) <= 128 && LPR <= 32;
+    constexpr int UNROLL = NARROW ? 8 : 4;
     using VT = typename Vec<T, V>::type;
     __shared__ float part[16][CW];
     __shared__ uint8_t kept[CW];
     __shared__ int first;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // neighbouring pieces share lines of memory: every XCD gets a contiguous range of them
-    const int nb = gridDim.x, per = nb / 8;                  // (the host pads the grid to a multiple of 8)
-    const int c0 = ((int)(blockIdx.x % 8) * per + (int)blockIdx.x / 8) * CW;
-    if (c0 >= N) return;
+    int c0 = (int)blockIdx.x * CW;
+    if constexpr (CW * sizeof(T) < 128) {
+        // neighbouring pieces share lines of memory: every XCD gets a contiguous range of them
+        // (the host pads this grid to a multiple of 8)
+        c0 = ((int)(blockIdx.x % 8) * ((int)gridDim.x / 8) + (int)blockIdx.x / 8) * CW;
+        if (c0 >= N) return;
+    }
     if (FINAL && prev_keep) mark_kept(prev_keep, n_prev_keep, c0, CW, kept, &first);
     const int col = c0 + (tid % LPR) * V;
     const int r0 = blockIdx.y * rows_per;
@@ -145,19 +131,26 @@ __global__ __launch_bounds__(1024) void col_sums_kernel(
 #pragma unroll
     for (int i = 0; i < V; ++i) acc[i] = 0.f;
     if (col < N) {                      // V > 1 is only launched with N % V == 0
-        for (int r = r0 + tid / LPR; r < r1; r += UNROLL * RSTEP) {
-            // all loads of a batch before its sums; rows past the range repeat the last one and are left out
+        int r = r0 + tid / LPR;
+        // all loads of a batch before its sums; in narrow pieces rows past the range repeat the last one
+        // and are left out, in wide ones they are added one by one
+        for (; r + (NARROW ? 0 : (UNROLL - 1) * RSTEP) < r1; r += UNROLL * RSTEP) {
             VT a[UNROLL], b[UNROLL];
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
-                const size_t off = (size_t)min(r + u * RSTEP, r1 - 1) * (size_t)ld + (size_t)col;
+                const int row = NARROW ? min(r + u * RSTEP, r1 - 1) : r + u * RSTEP;
+                const size_t off = (size_t)row * (size_t)ld + (size_t)col;
                 a[u] = *reinterpret_cast<const VT*>(Wt + off);
                 b[u] = *reinterpret_cast<const VT*>(Wp + off);
             }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u)
-                if (r + u * RSTEP < r1) accum<T, V>(reinterpret_cast<const T*>(&a[u]), reinterpret_cast<const T*>(&b[u]), acc);
+                if (!NARROW || r + u * RSTEP < r1) accum<T, V>(reinterpret_cast<const T*>(&a[u]), reinterpret_cast<const T*>(&b[u]), acc);
+        }
+        for (; r < r1; r += RSTEP) {
+            const size_t off = (size_t)r * (size_t)ld + (size_t)col;
+            accum<T, V>(Wt + off, Wp + off, acc);
         }
     }
 #pragma unroll
@@ -206,8 +199,10 @@ __global__ __launch_bounds__(1024) void col_finish_kernel(
 
 // Scores of the ROWS of W[K x N] (pruned axis = K): one wavefront per row, a
 // lane adds its elements in column order, then a fixed shuffle tree.  A row that
-// was pruned keeps its score and is not read.
-template <typename T, int V>
+// was pruned keeps its score and is not read.  SHORT: rows of at most three steps (without the
+// batches' registers twice as many wavefronts are resident: 100000 x 16 bf16 18.1 -> 15.1 us).  A batch
+// is requested before the sums of the one in front of it (64 x 32768 fp32 13.6 -> 11.2).
+template <typename T, int V, bool SHORT>
 __global__ __launch_bounds__(256) void row_scores_kernel(
     const T* __restrict__ Wt, const T* __restrict__ Wp, int64_t ld, int K, int N,
     const float* __restrict__ prev_scores, const int32_t* __restrict__ prev_keep, int n_prev_keep,
@@ -229,23 +224,37 @@ __global__ __launch_bounds__(256) void row_scores_kernel(
 #pragma unroll
     for (int i = 0; i < V; ++i) acc[i] = 0.f;
     using VT = typename Vec<T, V>::type;
-    // batches of loads, then what is left of a row of no more than three steps, one by one
-    constexpr int UNROLL = V == 1 ? 16 : 8;
     int c = lane * V;                   // V > 1 is only launched with N % V == 0
-    for (int base = 0; N - base > 3 * 64 * V; base += UNROLL * 64 * V, c += UNROLL * 64 * V) {
-        VT x[UNROLL], y[UNROLL];
+    if constexpr (!SHORT) {
+        // batches of loads, the next one requested before the sums of this one; steps past the row's end
+        // repeat its last elements and are left out
+        constexpr int U = V == 1 ? 8 : 4, STEP = U * 64 * V;
+        VT x[2][U], y[2][U];
+        auto request = [&](int buf, int64_t from) {
 #pragma unroll
-        for (int u = 0; u < UNROLL; ++u) {
-            const int cc = min(c + u * 64 * V, N - V);
-            x[u] = *reinterpret_cast<const VT*>(a + cc);
-            y[u] = *reinterpret_cast<const VT*>(b + cc);
+            for (int u = 0; u < U; ++u) {
+                const int cc = (int)min<int64_t>(from + u * 64 * V, N - V);
+                x[buf][u] = *reinterpret_cast<const VT*>(a + cc);
+                y[buf][u] = *reinterpret_cast<const VT*>(b + cc);
+            }
+        };
+        auto add = [&](int buf, int64_t from) {
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (from + u * 64 * V < N) accum<T, V>(reinterpret_cast<const T*>(&x[buf][u]), reinterpret_cast<const T*>(&y[buf][u]), acc);
+        };
+        request(0, c);
+        for (int64_t at = c, base = 0; base < N; base += 2 * STEP, at += 2 * STEP) {
+            request(1, at + STEP);
+            __builtin_amdgcn_sched_barrier(0);
+            add(0, at);
+            request(0, at + 2 * STEP);
+            __builtin_amdgcn_sched_barrier(0);
+            add(1, at + STEP);
         }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < UNROLL; ++u)
-            if (c + u * 64 * V < N) accum<T, V>(reinterpret_cast<const T*>(&x[u]), reinterpret_cast<const T*>(&y[u]), acc);
+        c = N;
     }
-    for (; c < N; c += 64 * V) accum<T, V>(a + c, b + c, acc);
+    for (; SHORT && c < N; c += 64 * V) accum<T, V>(a + c, b + c, acc);
     float sum = acc[0];
 #pragma unroll
     for (int i = 1; i < V; ++i) sum += acc[i];
@@ -294,18 +303,26 @@ int cols_typed(const T* Wt, const T* Wp, int64_t ld, int K, int N, const float* 
     if ((size_t)splits > fit) splits = fit < 2 ? 1 : (int)fit;
     // up to 4 MB a snapshot the second launch costs more than it gains (1024 x 1024 bf16 12.2 us, one launch 9.5)
     if (K <= 2048 && (int64_t)K * N * (int64_t)sizeof(T) <= (4 << 20)) splits = 1;
-    auto grid = [&](int width) { return ((N + width - 1) / width + 7) / 8 * 8; };
+    constexpr int WIDE = V == 8 ? 32 : 64, NARROW = V == 1 ? 32 : 64 / (V * (int)sizeof(T));       // lanes to a row
+    constexpr int WIDE_COLS = WIDE * V, NARROW_COLS = NARROW * V;
+    const int chunks = (N + WIDE_COLS - 1) / WIDE_COLS;
     if (splits == 1) {
-        constexpr int LPR = V == 1 ? 32 : 64 / (V * (int)sizeof(T));
-        hipLaunchKernelGGL((col_sums_kernel<T, V, LPR, true>), dim3(grid(LPR * V), 1), dim3(1024), 0, stream,
-                           Wt, Wp, ld, K, N, K, prev_scores, prev_keep, n_prev_keep, scores);
+        // The narrow pieces while the wide ones are too few for the chip (us on 64 bytes / on 512 and more,
+        // bf16: 4096 rows, 96 wide pieces 97 / 105, 125 120 / 105, 256 222 / 183; few rows are over at once: 16 rows,
+        // 16384 pieces 912 / 67; fp32 300 rows, 64 pieces 12.7 / 9.4).  In wide pieces batches of four keep two workgroups
+        // on a unit, and the range's last rows one by one.
+        if (chunks >= 112 || (chunks >= 32 && K <= 512))
+            hipLaunchKernelGGL((col_sums_kernel<T, V, WIDE, true>), dim3(chunks, 1), dim3(1024), 0, stream,
+                               Wt, Wp, ld, K, N, K, prev_scores, prev_keep, n_prev_keep, scores);
+        else
+            hipLaunchKernelGGL((col_sums_kernel<T, V, NARROW, true>), dim3(((N + NARROW_COLS - 1) / NARROW_COLS + 7) / 8 * 8, 1),
+                               dim3(1024), 0, stream, Wt, Wp, ld, K, N, K, prev_scores, prev_keep, n_prev_keep, scores);
         return hip_status(hipGetLastError());
     }
-    constexpr int LPR = V == 8 ? 32 : 64;
     const int rows_per = (((K + splits - 1) / splits) + 15) & ~15;
     splits = (K + rows_per - 1) / rows_per;
     float* partial = (float*)workspace;
-    hipLaunchKernelGGL((col_sums_kernel<T, V, LPR, false>), dim3(grid(LPR * V), splits), dim3(1024), 0, stream,
+    hipLaunchKernelGGL((col_sums_kernel<T, V, WIDE, false>), dim3(chunks, splits), dim3(1024), 0, stream,
                        Wt, Wp, ld, K, N, rows_per, prev_scores, prev_keep, n_prev_keep, partial);
     hipLaunchKernelGGL(col_finish_kernel, dim3((N + 63) / 64), dim3(1024), 0, stream,
                        partial, splits, K, N, prev_scores, prev_keep, n_prev_keep, scores);
@@ -316,7 +333,8 @@ template <typename T, int V>
 int rows_typed(const T* Wt, const T* Wp, int64_t ld, int K, int N, const float* prev_scores,
                const int32_t* prev_keep, int n_prev_keep, float* scores, hipStream_t stream)
 {
-    hipLaunchKernelGGL((row_scores_kernel<T, V>), dim3((K + 3) / 4), dim3(256), 0, stream,
+    auto fn = N <= 3 * 64 * V ? row_scores_kernel<T, V, true> : row_scores_kernel<T, V, false>;
+    hipLaunchKernelGGL(fn, dim3((K + 3) / 4), dim3(256), 0, stream,
                        Wt, Wp, ld, K, N, prev_scores, prev_keep, n_prev_keep, scores);
     return hip_status(hipGetLastError());
 }
