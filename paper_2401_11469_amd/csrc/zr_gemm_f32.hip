@@ -521,8 +521,10 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
         int* tab = sidx + 2 * R;
         const int start = j0 == 0 ? 0 : sidx[0];
         const int end = j0 + R >= g.J ? g.out_full : clamp_idx(g.keep[j0 + R], g.out_full);
-        for (int base = start; base < end; base += TAB) {
-            const int width = min(TAB, end - base);
+        // a long range behind the tile's last kept column needs no table
+        const int last = max(start, sidx[cols_valid - 1] + 1), mid = end - last >= 256 ? last : end;
+        for (int base = start; base < mid; base += TAB) {
+            const int width = min(TAB, mid - base);
             for (int q = tid; q < width; q += NT) tab[q] = -1;
             __syncthreads();
             if (tid < cols_valid) {
@@ -549,6 +551,24 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
                 }
             }
             __syncthreads();
+        }
+        // and leaves 16 bytes a lane
+        for (int r0 = wave; r0 < rows_valid && mid < end; r0 += 4 * WAVES) {
+            for (int p = mid + lane * 4; p < end; p += 256) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int row = r0 + WAVES * u;
+                    if (row >= rows_valid) break;
+                    const size_t off = (size_t)(i0 + row) * (size_t)g.ldo + p;
+                    if (p + 4 <= end) {
+                        f4 v = f4{0.f, 0.f, 0.f, 0.f};
+                        if (g.prev) v = *(const f4_any*)(g.prev + off);
+                        *(f4_any*)(g.out + off) = v;
+                    } else {
+                        for (int e = 0; e < end - p; ++e) g.out[off + e] = g.prev ? g.prev[off + e] : 0.f;
+                    }
+                }
+            }
         }
         return;
     }
@@ -611,11 +631,22 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
             }
             unsigned long long todo = __ballot(dropped);
             while (todo) {
-                const int p = base + (__ffsll((long long)todo) - 1);
-                todo &= todo - 1;
-                for (int j = lane; j < cols_valid; j += 64) {
-                    const size_t off = (size_t)p * (size_t)g.ldo + j0 + j;
-                    g.out[off] = g.prev ? g.prev[off] : 0.f;
+                // a row to every CPR lanes, 16 bytes a lane
+                int p = -1;
+#pragma unroll
+                for (int u = 0; u < 64 / CPR; ++u) {
+                    if (todo && u == lane / CPR) p = base + (__ffsll((long long)todo) - 1);
+                    todo &= todo - 1;                         // (0 stays 0)
+                }
+                const int j = lane % CPR * 4;
+                if (p < 0 || j >= cols_valid) continue;
+                const size_t off = (size_t)p * (size_t)g.ldo + j0 + j;
+                if (j + 4 <= cols_valid) {
+                    f4 v = f4{0.f, 0.f, 0.f, 0.f};
+                    if (g.prev) v = *(const f4_any*)(g.prev + off);
+                    *(f4_any*)(g.out + off) = v;
+                } else {
+                    for (int e = 0; e < cols_valid - j; ++e) g.out[off + e] = g.prev ? g.prev[off + e] : 0.f;
                 }
             }
         }
