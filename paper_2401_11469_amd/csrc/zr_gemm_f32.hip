@@ -679,7 +679,7 @@ int launch_shape(const Args& a, hipStream_t stream)
     // P x Q: 512 tiles 43 us against 48 on 64 x 64, 384 tiles 42 against 37, 256 tiles 25 against 26).  Short
     // contractions are all epilogue and half empty 64-deep stages: contraction 8, 192 tiles 9 against 10,
     // 2048 tiles 39 against 72; contraction 64, 192 tiles 11 against 10, 384 tiles 16 against 17.
-    const int64_t rounds64 = (t64 + 255) / 256, rounds128 = (t128 + 255) / 256;
+    const int64_t rounds64 = (t64 + 255) / 256, rounds128 = t128 <= 256 ? 1 : 2 * ((t128 + 511) / 512);
     const bool big = a.C <= 32 ? t128 >= 192 : a.C <= 96 ? t128 >= 256 : 0.92 * 4 * (double)rounds128 < (double)rounds64;
     if (big) return launch_inst<LA, LB, 128>(a, stream);
     // 64 x 64 tiles once there is one for most compute units (contraction 1024: 128 tiles 22.0 us
