@@ -102,28 +102,18 @@ void give_split_scratch(GemmDesc& d, void* workspace, size_t bytes, size_t used)
     d.split_scratch_bytes = bytes - off;
 }
 
-// One product with Average imputation: zero the sums, multiply (the scatter epilogue
-// writes results, +0 and the sums), then mean and fill; or, without room for the
-// sums or from a kernel that leaves none, multiply and run the stand-alone pass that re-reads
-// the kept slices.
+// One product with Average imputation: multiply (the scatter epilogue writes results, +0 and
+// the sums), then mean and fill; or, without room for the sums or from a kernel that leaves none,
+// multiply and run the stand-alone pass that re-reads the kept slices.
 int gemm_with_average(GemmDesc& d, float* sums, void* out, int64_t ld, int rows, int cols, int axis,
                       const int32_t* keep_idx, int n_keep, int dtype, hipStream_t s)
 {
-    int st;
-    if (sums) {
-        const int len = axis == 1 ? rows : cols;
-        const int slots = (n_keep + 127) / 128;
-        st = launch_zero_f32(sums, (size_t)slots * (size_t)len, s);
-        if (st != ZR_OK) return st;
-        d.avg_partial = sums; d.avg_len = len; d.sums_left = true;
-        st = launch_gemm(d, s);
-        d.avg_partial = nullptr;
-        if (st != ZR_OK) return st;
-        if (d.sums_left) return launch_mean_fill(out, ld, rows, cols, axis, keep_idx, n_keep, sums, slots, dtype, s);
-    } else {
-        st = launch_gemm(d, s);
-        if (st != ZR_OK) return st;
-    }
+    bool left = sums != nullptr;
+    d.avg_partial = sums; d.avg_len = axis == 1 ? rows : cols; d.sums_left = &left;
+    const int st = launch_gemm(d, s);
+    d.avg_partial = nullptr; d.sums_left = nullptr;
+    if (st != ZR_OK) return st;
+    if (left) return launch_mean_fill(out, ld, rows, cols, axis, keep_idx, n_keep, sums, (n_keep + 127) / 128, dtype, s);
     return launch_impute(out, ld, rows, cols, axis, keep_idx, n_keep, ZR_IMPUTE_AVERAGE, nullptr, dtype, s);
 }
 

@@ -96,11 +96,11 @@ struct GemmDesc {
     // results it stores, per output row over its columns (column scatter) or per output
     // column over its rows (row scatter), and writes the sums to
     // avg_partial[slot * avg_len + index], slot = the tile's position along the summed
-    // axis.  The buffer holds ceil(extent / 128) slots and must be zero beforehand.
+    // axis.  The buffer holds ceil(extent / 128) slots.
     float* avg_partial = nullptr;
     int avg_len = 0;
-    // set to false by launch_gemm where the product's kernel does not write those sums
-    mutable bool sums_left = true;
+    // where launch_gemm says whether it cleared the buffer and wrote those sums (not every kernel does)
+    bool* sums_left = nullptr;
     // Scratch for a split contraction (16-byte aligned; products with too few tiles to fill the
     // chip cut the contraction into slices and add them up in a second launch); nullptr: never split.
     void* split_scratch = nullptr;
@@ -142,7 +142,9 @@ struct AttrFlags {
 };
 bool ensure_max_dynamic_lds(const void* fn, int bytes, void* flags16);
 int launch_gemm(const GemmDesc& d, hipStream_t stream);
-int launch_gemm_fast(const GemmDesc& d, hipStream_t stream);   // -1: not eligible
+int launch_gemm_fast(const GemmDesc& d, hipStream_t stream);   // -1: not taken
+bool gemm_fast_takes(const GemmDesc& d);
+bool gemm_leaves_sums(const GemmDesc& d);
 int launch_gemm_f32(const GemmDesc& d, hipStream_t stream);
 int launch_select(const float* scores, int n, int batch, int n_keep,
                   int32_t* keep_idx, int32_t* drop_idx, int64_t ld_idx, hipStream_t stream);

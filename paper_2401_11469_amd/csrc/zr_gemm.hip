@@ -778,14 +778,25 @@ static int launch_gemm_untimed(const GemmDesc& d, hipStream_t stream)
 {
     const int fast = launch_gemm_fast(d, stream);   // bf16, 16-byte aligned rows
     if (fast >= 0) return fast;
-    d.sums_left = false;
     if (d.dtype == ZR_BF16) return launch_gemm_any(d, stream);
     if (d.dtype == ZR_F32) return launch_gemm_f32(d, stream);
     return ZR_ERR_DTYPE;
 }
 
-int launch_gemm(const GemmDesc& d, hipStream_t stream)
+int launch_gemm(const GemmDesc& desc, hipStream_t stream)
 {
+    GemmDesc d = desc;
+    if (d.avg_partial) {
+        const bool leaves = gemm_leaves_sums(d);
+        if (d.sums_left) *d.sums_left = leaves;
+        if (leaves) {
+            const int extent = d.epilogue == EPI_COL_SCATTER ? d.J : d.I;
+            const int st = launch_zero_f32(d.avg_partial, (size_t)((extent + 127) / 128) * (size_t)d.avg_len, stream);
+            if (st != ZR_OK) return st;
+        } else {
+            d.avg_partial = nullptr;
+        }
+    }
     if (!g_debug.armed_once) return launch_gemm_untimed(d, stream);
     // measuring aid (zr_debug_time_next_product): events right around this product's own
     // launch(es), without a preceding extraction or a following imputation pass.  One shot.

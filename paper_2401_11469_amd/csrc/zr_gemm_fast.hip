@@ -129,7 +129,6 @@ struct FArgs {
     // second kernel adds the slices in slice order and runs the epilogue.  split <= 1: one launch.
     float* partial;
     size_t partial_bytes;       // host side only: room at `partial`
-    const GemmDesc* desc;       // host side only: where to say that no sums were left
     int split, kt_per;          // kt_per: 64-deep contraction tiles per slice
     // sub-rectangle of D this launch covers, in elements (multiples of 256 except at
     // the far edges of D) and its tile grid
@@ -1573,26 +1572,34 @@ __global__ __launch_bounds__(64 * WM * WN) void fast_kernel(const FArgs g)
 // Second launch of a split contraction on 128 x 128 tiles (four wavefronts as 2 x 2): adds the
 // slices of a tile in slice order (a fixed order: results are repeatable bit by bit) and runs the
 // epilogue.  It is a copy in all but name (the slices come from the last-level cache), so what
-// counts is how many loads are in flight: four workgroups to a tile, each with one 16-row
+// counts is how many loads are in flight: four strips to a tile, each with one 16-row
 // sub-tile row of both wavefront rows, all sub-tiles of up to four slices requested together.
-// (One workgroup to a tile, as before: 48 tiles in 8 slices 14.8-17 us, now 8.5; 8 tiles 14 -> 7.5.)
-__global__ __launch_bounds__(256) void split_reduce_kernel(const FArgs g)
+// (One workgroup of four wavefronts to a tile, as before: 48 tiles in 8 slices 14.8-17 us, now 8.5; 8 tiles
+// 14 -> 7.5.)
+// STRIPS: strips to a workgroup.  1, so that they spread over the chip; 4 for row scatters that leave
+// the sums of Average imputation, which run over all rows of a tile.
+template <int STRIPS>
+__global__ __launch_bounds__(256 * STRIPS) void split_reduce_kernel(const FArgs g)
 {
     constexpr int BM = 128, BN = 128, NT = 256, TN = 4, SUBS = 16;
     constexpr int ROWS = 32, CP = BN + 8, WIN = 1024;        // WIN: original columns per pass of the column scatter
-    __shared__ __align__(16) E Cs[ROWS * CP];
+    __shared__ __align__(16) E Cs_[STRIPS][ROWS * CP];
     __shared__ __align__(16) uint16_t tab[WIN];
-    __shared__ int sidx[BN];
+    __shared__ int sidx_[STRIPS][BN];
+    __shared__ float sums[STRIPS == 1 ? 1 : 8][BN];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int strip = STRIPS == 1 ? 0 : threadIdx.x / NT;
+    E* Cs = Cs_[strip];
+    int* sidx = sidx_[strip];
+    const int tid = threadIdx.x % NT, lane = tid & 63, wave = tid >> 6;
     const int total = g.tiles_i * g.tiles_j;
-    const int t = blockIdx.x >> 2, a = blockIdx.x & 3;
+    const int t = STRIPS == 1 ? blockIdx.x >> 2 : blockIdx.x, a = STRIPS == 1 ? blockIdx.x & 3 : strip;
     int ti, tj;
     tile_at(g, t, ti, tj);
     const int i0 = g.i_base + ti * BM, j0 = g.j_base + tj * BN;
     const int rows_valid = min(BM, g.I - i0), cols_valid = min(BN, g.J - j0);
     const bool scatter_c = g.epilogue == EPI_COL_SCATTER, scatter_r = g.epilogue == EPI_ROW_SCATTER;
-    if (a * 16 >= rows_valid) return;                         // (then the lower rows 64 + 16 a are empty too)
+    if (STRIPS == 1 && a * 16 >= rows_valid) return;          // (then the lower rows 64 + 16 a are empty too)
 
     // kept rows of the strip: 16 from tile row 16 a, 16 from tile row 64 + 16 a
     auto tile_row = [&](int r) { return (r >> 4) * 64 + a * 16 + (r & 15); };
@@ -1631,6 +1638,35 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(const FArgs g)
         }
     }
     __syncthreads();
+
+    if (g.avg_partial && STRIPS == 1) {
+        // column scatter: sums of the stored (rounded) results of each row, eight lanes to a row
+        static_assert(NT == 8 * ROWS, "a row to every eight lanes");
+        const int r = tid >> 3, c0 = (tid & 7) * (BN / 8);
+        float sum = 0.f;
+        for (int c = c0; c < min(c0 + BN / 8, cols_valid); ++c) sum += bf16_bits_to_f32(Cs[r * CP + c]);
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) sum += __shfl_xor(sum, off, 64);
+        if ((tid & 7) == 0 && tile_row(r) < rows_valid)
+            g.avg_partial[(size_t)(g.avg_slot_base + tj) * (size_t)g.avg_len + i0 + tile_row(r)] = sum;
+    }
+    if constexpr (STRIPS == 4) {
+        // row scatter: sums of each column over the tile's rows, eight parts of sixteen rows, then
+        // those in their order
+        const int col = threadIdx.x % BN, part = threadIdx.x / BN, r0 = (part >> 2) * 16;
+        float sum = 0.f;
+        if (col < cols_valid)
+            for (int r = 0; r < 16; ++r)
+                if (part * 16 + r < rows_valid) sum += bf16_bits_to_f32(Cs_[part & 3][(r0 + r) * CP + col]);
+        sums[part][col] = sum;
+        __syncthreads();
+        if (part == 0 && col < cols_valid) {
+            sum = 0.f;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) sum += sums[q][col];
+            g.avg_partial[(size_t)(g.avg_slot_base + ti) * (size_t)g.avg_len + j0 + col] = sum;
+        }
+    }
 
     if (scatter_c) {
         // The tile owns the original columns from its first kept column (0 for the first tile) up to
@@ -1793,13 +1829,15 @@ int launch_inst(const FArgs& a, int i_base, int i_end, int j_base, int j_end, hi
             const int64_t g1 = (tiles * k.split + 7) / 8 * 8;
             hipLaunchKernelGGL(fn1, dim3((unsigned)g1), dim3(64 * WM * WN), smem, stream, k);
             if (hipGetLastError() != hipSuccess) return ZR_ERR_HIP;
-            hipLaunchKernelGGL(split_reduce_kernel, dim3((unsigned)(tiles * 4)), dim3(256), 0, stream, k);
+            if (a.avg_partial && a.epilogue == EPI_ROW_SCATTER)
+                hipLaunchKernelGGL(split_reduce_kernel<4>, dim3((unsigned)tiles), dim3(1024), 0, stream, k);
+            else
+                hipLaunchKernelGGL(split_reduce_kernel<1>, dim3((unsigned)(tiles * 4)), dim3(256), 0, stream, k);
             if (debug_names_wanted()) {
                 char nm[128];
                 snprintf(nm, sizeof(nm), "%.90s split %d", g_debug.last_kernel, k.split);
                 snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "%s", nm);
             }
-            a.desc->sums_left = false;          // (the sums of Average imputation come from a pass of their own then)
             return hip_status(hipGetLastError());
         }
     }
@@ -1966,7 +2004,7 @@ int launch_shape(const FArgs& a, hipStream_t stream)
 }  // namespace
 
 // Whether this path takes the product (else the kernel for any alignment does).
-static bool eligible(const GemmDesc& d)
+bool gemm_fast_takes(const GemmDesc& d)
 {
     if (d.dtype != ZR_BF16) return false;
     auto aligned = [](const void* p, int64_t ld) { return ((uintptr_t)p % 16 == 0) && (ld % 8 == 0); };
@@ -2012,10 +2050,21 @@ static bool eligible(const GemmDesc& d)
     return t128 > (dma ? 128 : 256);                // dW: 48 tiles 18 / 12.6; 3000 tokens 48 tiles 54 / 19, 120 55 / 33, 5000 tokens 192 89 / 80
 }
 
+// Whether the product leaves the sums of Average imputation in avg_partial.  One that is split as a whole
+// has a result that the stand-alone pass reads from the caches, in one launch instead of three; many kept rows are a
+// long chain there (us with the sums / with that pass: dW 768 x 4096 of 576 kept rows 74 / 71, 1024 x 2048 of 1536
+// kept columns 86 / 82, 4096 x 768 of 3072 kept rows 93 / 103).
+bool gemm_leaves_sums(const GemmDesc& d)
+{
+    if (d.epilogue == EPI_PLAIN || !gemm_fast_takes(d)) return false;
+    const bool split = slices_for(d.C, tiles_of(d.I, d.J, 128, 128), d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2;
+    return !split || (d.epilogue == EPI_ROW_SCATTER && d.I > 1536);
+}
+
 // Returns -1 when the problem is not eligible, else a zr_status.
 int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
 {
-    if (!eligible(d)) return -1;
+    if (!gemm_fast_takes(d)) return -1;
     FArgs a;
     a.A = FOp{(const E*)d.A.base, d.A.ld, d.A.map_strided, d.A.map_contig, d.A.n_strided, d.A.n_contig};
     a.B = FOp{(const E*)d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
@@ -2026,7 +2075,6 @@ int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
     a.tiles_i = a.tiles_j = 0;
     a.i_base = a.j_base = a.i_end = a.j_end = 0;
     a.partial = (float*)d.split_scratch; a.partial_bytes = d.split_scratch ? d.split_scratch_bytes : 0;
-    a.desc = &d;
     a.split = 1; a.kt_per = 0;
     const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
     // Direct-to-LDS loaders cannot zero the contraction tail of the last tile
