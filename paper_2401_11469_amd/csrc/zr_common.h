@@ -145,6 +145,13 @@ int launch_gemm(const GemmDesc& d, hipStream_t stream);
 int launch_gemm_fast(const GemmDesc& d, hipStream_t stream);   // -1: not taken
 bool gemm_fast_takes(const GemmDesc& d);
 bool gemm_leaves_sums(const GemmDesc& d);
+// Whether the bf16 kernel for any alignment adds up an I x J product over C in groups of the contraction
+// (its 32 x 32 tiles and its 64 x 64 tiles of 512 threads do): a rule on the product's extents alone.
+inline bool adds_in_groups(int I, int J, int C)
+{
+    const int64_t t64 = (int64_t)((I + 63) / 64) * ((J + 63) / 64);
+    return t64 < 96 || (t64 <= 256 && C >= 256);
+}
 int launch_gemm_f32(const GemmDesc& d, hipStream_t stream);
 int launch_select(const float* scores, int n, int batch, int n_keep,
                   int32_t* keep_idx, int32_t* drop_idx, int64_t ld_idx, hipStream_t stream);

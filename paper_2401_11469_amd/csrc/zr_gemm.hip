@@ -697,16 +697,21 @@ template <template <int, int, bool> class LA, bool AP, template <int, int, bool>
 int launch_shape(const Args& a, const char* name, hipStream_t stream)
 {
     const int64_t t64 = (int64_t)((a.I + 63) / 64) * ((a.J + 63) / 64), t128 = (int64_t)((a.I + 127) / 128) * ((a.J + 127) / 128);
-    // 128 x 128 tiles once there is one for every compute unit (M x K x N = 4001 x 752 x 1003: 256 tiles
-    // 28.8 us against 39.0 on 64 x 64; 4001 x 1001 x 752: 192 tiles 49.2 against 40.5); 32 x 32 tiles
-    // below 96 of 64 x 64 (dW 376 x 471 over 985 tokens: 48 tiles, 8 us against 15; 985 x 501 x 353:
+    // 32 x 32 tiles below 96 of 64 x 64 (dW 376 x 471 over 985 tokens: 48 tiles, 8 us against 15; 985 x 501 x 353:
     // 96 tiles, 14.1 against 13.6);
-    if (t128 >= 256 || forced_tiles()) return launch_inst<LA, AP, LB, BP, 128, 256>(a, name, stream);
+    if (forced_tiles()) return launch_inst<LA, AP, LB, BP, 128, 256>(a, name, stream);
     if (t64 < 96) return launch_inst<LA, AP, LB, BP, 32, 256>(a, name, stream);
-    // and 512 threads on a 64 x 64 tile while each has a compute unit to itself (985 x 1001 x 578
+    // 512 threads on a 64 x 64 tile while each has a compute unit to itself (985 x 1001 x 578
     // plain 14.1 -> 12.8 us, dW 2024 tokens 27.4 -> 24.7; 288 tiles: 25.0 -> 31.3, so not there; on
-    // 32 x 32 tiles within 5 %, on either side); below four stages of the others it gains nothing
-    if (t64 <= 256 && a.C > 384) return launch_inst<LA, AP, LB, BP, 64, 512>(a, name, stream);
+    // 32 x 32 tiles within 5 %, on either side); below two stages of the others it gains nothing
+    // (256 deep, kept columns gathered, 128 tiles 15.1 -> 12.9);
+    if (adds_in_groups(a.I, a.J, a.C)) return launch_inst<LA, AP, LB, BP, 64, 512>(a, name, stream);
+    // 128 x 128 tiles once there is one for every compute unit (M x K x N = 4001 x 752 x 1003: 256 tiles
+    // 28.8 us against 39.0 on 64 x 64; 4001 x 1001 x 752: 192 tiles 49.2 against 40.5), or for half of them
+    // where kept columns of A are gathered (1024 deep, 160 tiles: 27.3 against 35.4, both operands 40.5 against 60.8;
+    // 128 tiles: 27.0 against 24.4)
+    constexpr bool gathers_a = AP && std::is_same<LA<128, 256, AP>, Gather<128, 256, AP>>::value;
+    if (t128 >= 256 || (gathers_a && t128 > 128)) return launch_inst<LA, AP, LB, BP, 128, 256>(a, name, stream);
     return launch_inst<LA, AP, LB, BP, 64, 256>(a, name, stream);
 }
 

@@ -2035,17 +2035,20 @@ bool gemm_fast_takes(const GemmDesc& d)
     // number of 128 x 128 tiles (us on this path / on the other one, 1024 deep unless given):
     // (Column scatters into rows whose width is no multiple of 8 although their pitch is stay here:
     // too rare for figures of their own.)
-    if (d.epilogue == EPI_COL_SCATTER && d.out_full % 8 != 0) return true;
     const int64_t t128 = tiles_of(d.I, d.J, 128, 128);
-    if (ap && ag) return t128 > 512;                // X[:,S] in flight: 128 tiles 28 / 19, 512 44 / 36, 800 (768 deep) 53 / 64
-    if (ap && bp && bg) return t128 > 256;          // W[:,S] along the contraction: 128 tiles 27 / 20, 256 28.5 / 25, 792 91 / 126
-    if (ap && bg) return t128 > 128;                // W[:,S] across it: 96 tiles 29 / 25, 192 30 / 37
-    if (ag || bg) return t128 > 96;                 // dW, a gather in flight, 4096 tokens: 48 tiles 84 / 47, 192 84 / 115
+    if (ap && d.epilogue == EPI_COL_SCATTER && d.out_full % 8 != 0) return true;
     // direct-to-LDS loaders, and with them split contractions, need a contraction of whole 64-deep
     // tiles or an operand that supplies the zeros
     const bool dma = d.C % BK == 0 || (ap && d.A.zero_padded) || (bp && d.B.zero_padded);
-    if (dma && slices_for(d.C, t128, d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2) return true;      // (48 tiles, 4096 tokens: 21 / 30)
-    if (ap && !bp) return t128 > 256;               // rows of W: 64 tiles 18 / 9, 256 19 / 17, 512 (1536 deep) 43 / 38, 1600 53 / 68
+    if (!ag && !bg && dma && slices_for(d.C, t128, d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2) return true;      // (48 tiles, 4096 tokens: 21 / 30)
+    // Products that the other kernel adds up in groups of the contraction are all its own, so that a
+    // result has the same bits whichever of its operands were extracted beforehand (64 x 8192, 4096 deep: 38 / 18).
+    if (adds_in_groups(d.I, d.J, d.C)) return false;
+    if (ap && ag) return t128 > 512;                // X[:,S] in flight: 160 tiles 36 / 27, 512 44 / 36, 800 (768 deep) 53 / 64
+    if (ap && bp && bg) return t128 > 256;          // W[:,S] along the contraction: 128 tiles 27 / 20, 256 28.5 / 25, 792 91 / 126
+    if (ap && bg) return t128 > 96;                 // W[:,S] across it: 96 tiles 28.6 / 30.5 (256 deep 16.4 / 16), 128 29 / 33
+    if (ag || bg) return t128 > 96;                 // dW, a gather in flight, 4096 tokens: 48 tiles 84 / 47, 192 84 / 115
+    if (ap && !bp) return t128 > (d.B.map_strided ? 256 : 128);       // rows of W: 64 tiles 18 / 9, 256 19 / 17, 512 (1536 deep) 43 / 38, 1600 53 / 68; all of W: 128 13.6 / 11.8, 160 14 / 18, 256 14.8 / 19.5
     if (ap) return t128 > (dma ? 64 : 128);         // 48 tiles 12.5 / 11, 96 14 / 16.5; 1504 deep (not whole) 72 tiles 27.6 / 19, 168 37 / 37
     return t128 > (dma ? 128 : 256);                // dW: 48 tiles 18 / 12.6; 3000 tokens 48 tiles 54 / 19, 120 55 / 33, 5000 tokens 192 89 / 80
 }
