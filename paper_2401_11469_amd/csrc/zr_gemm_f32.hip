@@ -422,12 +422,8 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
     };
     begin(0);
     all([&](auto p) { fetch(0, p); });
-    if (KT > 1) {                        // (a lone stage with nothing behind it: 2 to 4 % of a launch 8 deep)
-        begin(1);
-        all([&](auto p) { commit(smem, 0, p, std::true_type()); fetch(1, p); });
-    } else {
-        all([&](auto p) { commit(smem, 0, p, std::true_type()); });
-    }
+    begin(1);                            // (past the end of a short contraction: valid addresses, zeros)
+    all([&](auto p) { commit(smem, 0, p, std::true_type()); fetch(1, p); });
     __syncthreads();
 
     // fetches: there is a stage k + 2; else stage k + 1, if there is one, is the last
