@@ -34,6 +34,17 @@ __device__ __forceinline__ int clamp_idx(int v, int n)
     return v < 0 ? 0 : (v >= n ? n - 1 : v);
 }
 
+// first position in the ascending LDS list s[0..n) with s[pos] >= p
+__device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
+{
+    int lo = 0, hi = n;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (s[mid] < p) lo = mid + 1; else hi = mid;
+    }
+    return lo;
+}
+
 // Length of the part of the ascending list keep[0..n_keep) below p, for a whole wavefront: 64
 // entries a step (a search by halves is a chain of a dozen loads, 4 us at the end of a launch).
 __device__ __forceinline__ int lower_bound_wave(const int32_t* __restrict__ keep, int n_keep, int p, int lane)

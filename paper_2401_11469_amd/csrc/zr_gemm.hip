@@ -2,14 +2,14 @@
 // resized layer's forward, dX and dW (paper Sec. 3.1) in the canonical form
 //     D[i, j] = sum_c A(i, c) * B(j, c)
 // on 64-wide wavefronts with the 16 x 16 x 32 MFMA and fp32 accumulation, for what the kernels
-// with 16-byte aligned rows do not take.  The kept-index list is applied while the operand tiles
+// with 16-byte aligned rows do not take: unaligned tensors, and products with few tiles.  The kept-index list is applied while the operand tiles
 // travel into LDS, and the epilogue writes the result at its original positions together with the
 // imputed values, so no compacted copy of an operand exists and one pass gives the normal shape.
 //
 // What bounds it.  Not the matrix cores: loads of 2-byte granularity that are waited for, and a
 // chip that is not full.  So
-//   * no load stands under a branch (at a join the compiler waits for every load in flight): rows
-//     and columns are clamped, a chunk at the end of a row is read from the row's last elements and
+//   * no load of tile elements stands under a branch (at a join the compiler waits for every load in
+//     flight; lists are read under uniform branches, a stage ahead): rows and columns are clamped, a chunk at the end of a row is read from the row's last elements and
 //     shifted into place, contraction indices past the end become zeros on the way into LDS;
 //   * a stage is 16 KB of each operand (32 KB with 512 threads), requested two stages ahead;
 //   * plain operands come in 16-byte loads at 2-byte alignment; kept columns come as the dword that
@@ -366,17 +366,6 @@ __device__ __forceinline__ bf16x8 fragment(const uint32_t* lds, int r0, int k0, 
         x.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + 4 * Geo<R, NT>::PQ));       // (the same swizzle)
     }
     return x.b;
-}
-
-// first position in the ascending LDS list s[0..n) with s[pos] >= p
-__device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
-{
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (s[mid] < p) lo = mid + 1; else hi = mid;
-    }
-    return lo;
 }
 
 __device__ __forceinline__ uint32_t two(float a, float b) { return f32_to_bf16_bits(a) | (f32_to_bf16_bits(b) << 16); }
@@ -753,6 +742,8 @@ int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
         return bg ? launch_shape<Plain, true, Gather, false>(a, "P, Qg", stream) : launch_shape<Plain, true, Plain, false>(a, "P, Q", stream);
     }
     if (ap && bp) {
+        // (<Plain, true, Gather, true, 128, 256> spills 12 bytes a lane; with the row addresses computed anew in every
+        // stage it does not, but takes 58 us for 50 at 2048 x 2048, 1500 deep, and both operands gathered 73 for 57)
         if (ag) return bg ? launch_shape<Gather, true, Gather, true>(a, "Pg, Pg", stream) : ZR_ERR_MODE;
         return bg ? launch_shape<Plain, true, Gather, true>(a, "P, Pg", stream) : launch_shape<Plain, true, Plain, true>(a, "P, P", stream);
     }

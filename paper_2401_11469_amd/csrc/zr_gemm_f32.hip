@@ -81,8 +81,9 @@ struct Args {
 // and writes it to LDS a stage later (commit, piece by piece).  Rows of the tile beyond the
 // operand's extent repeat its last row (they only feed results that are never stored);
 // contraction indices past C become zero (commit with TAIL, which only the last stage needs).
-// No load stands under a branch: at a join the compiler waits for every load in flight (with
-// branches for the last stage and the edges the loop ran at half of this one's speed).
+// No load of tile elements stands under a branch: at a join the compiler waits for every load in flight
+// (with branches for the last stage and the edges the loop ran at half of this one's speed; lists are
+// read under uniform branches, a stage ahead).
 // ---------------------------------------------------------------------------
 // element e of the result is element e + sh of v, 0 past its end
 __device__ __forceinline__ f4 shifted(f4 v, int sh)
@@ -344,17 +345,6 @@ __device__ __forceinline__ f4 fragment(const float* lds, int row, int block, int
 #pragma unroll
     for (int s = 0; s < 4; ++s) x[s] = lds[(block * 8 + grp * 4 + s) * Geo<R>::PQ + row];
     return x;
-}
-
-// first position in the ascending LDS list s[0..n) with s[pos] >= p
-__device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
-{
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (s[mid] < p) lo = mid + 1; else hi = mid;
-    }
-    return lo;
 }
 
 template <template <int> class LA_, template <int> class LB_, int R>
@@ -715,8 +705,9 @@ int launch_gemm_f32(const GemmDesc& d, hipStream_t stream)
         return bg ? launch_shape<PlainP, GatherQ>(a, stream) : launch_shape<PlainP, PlainQ>(a, stream);
     }
     if (d.A.c_contig && d.B.c_contig) {
-        if (ag) return bg ? launch_shape<GatherP, GatherP>(a, stream) : launch_shape<GatherP, PlainP>(a, stream);
-        return bg ? launch_shape<PlainP, GatherP>(a, stream) : launch_shape<PlainP, PlainP>(a, stream);
+        // (a list on the contraction is on both operands: nothing is extracted in fp32)
+        if (ag != bg) return ZR_ERR_MODE;
+        return ag ? launch_shape<GatherP, GatherP>(a, stream) : launch_shape<PlainP, PlainP>(a, stream);
     }
     if (!d.A.c_contig && !d.B.c_contig) {           // dW
         if (ag) return bg ? ZR_ERR_MODE : launch_shape<GatherQ, PlainQ>(a, stream);

@@ -167,16 +167,6 @@ __device__ __forceinline__ uint4 sel4(bool ok, uint4 v)
     return make_uint4(ok ? v.x : 0u, ok ? v.y : 0u, ok ? v.z : 0u, ok ? v.w : 0u);
 }
 
-__device__ __forceinline__ int lower_bound_lds(const int* s, int n, int p)
-{
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (s[mid] < p) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 // Four memory rows (contraction indices c..c+3) x 8 consecutive columns ->
 // for column m the two words (c,c+1) and (c+2,c+3).
 __device__ __forceinline__ void interleave4x8(const uint4 r[4], uint2 w[8])
