@@ -128,10 +128,11 @@ struct DebugState {
 extern thread_local DebugState g_debug;
 inline bool debug_names_wanted() { return g_debug.record_names || g_debug.armed_once; }
 
-// ZR_FORCE_TILES in the environment (read once): "256", "192x256" or "256x192" sends every bf16 product
-// of aligned tensors to one grid of that tile shape, whatever the schedule would choose, and those that
-// have no kernel of such a shape to 128 x 128 tiles: a test switch (small and ragged shapes then run
-// through the big-tile kernels).  0 = not set.
+// ZR_FORCE_TILES in the environment (read once): "256", "192x256", "256x192", "128" or "64x128" sends every
+// bf16 product of aligned tensors to one grid of that tile shape, whatever the rules on the number of tiles
+// say: a test switch (small and ragged shapes then run through those kernels).  Where a pair of loaders has
+// no kernel of the shape: 256 x 256 tiles instead of 192 x 256 and 256 x 192, 128 x 128 instead of 64 x 128, and
+// 128 x 128 tiles of the kernel for any alignment for pairs that only it has.  0 = not set.
 inline int forced_tiles()
 {
     static const int f = [] {
@@ -140,6 +141,8 @@ inline int forced_tiles()
         if (!strcmp(e, "256")) return 1;
         if (!strcmp(e, "192x256")) return 2;
         if (!strcmp(e, "256x192")) return 3;
+        if (!strcmp(e, "128")) return 4;
+        if (!strcmp(e, "64x128")) return 5;
         return 0;
     }();
     return f;

@@ -1951,6 +1951,9 @@ int launch_shape(const FArgs& a, hipStream_t stream)
             if (f == 2) return launch_tile<LA, LB, 192, 256, 2, 4>(a, 0, a.I, 0, a.J, stream);
             if (f == 3) return launch_tile<LA, LB, 256, 192, 4, 2>(a, 0, a.I, 0, a.J, stream);
         }
+        if constexpr (std::is_same<LA<64, 256>, DmaP<64, 256>>::value && std::is_same<LB<128, 256>, DmaP<128, 256>>::value)
+            if (f == 5) return launch_tile<LA, LB, 64, 128, 1, 4>(a, 0, a.I, 0, a.J, stream);
+        if (f >= 4) return launch_tile<LA, LB, 128, 128, 2, 2>(a, 0, a.I, 0, a.J, stream);
         return launch_tile<LA, LB, 256, 256, ZR_BIG_WM, ZR_BIG_WN>(a, 0, a.I, 0, a.J, stream);
     }
     const Sched sc = plan_tiles(a.I, a.J);

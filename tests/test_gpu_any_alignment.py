@@ -1,6 +1,6 @@
 """The bf16 products for any alignment at the edges of their tiles and stages: 32 x 32 tiles (256-deep stages),
-64 x 64 (128-deep, from 96 tiles on;
-256-deep with 512 threads up to 256 tiles) and 128 x 128 (64-deep, from 256 tiles on), contractions of one element
+64 x 64 (128-deep, from 96 tiles on; 256-deep with 512 threads up to 256 tiles, contractions from 256 on) and
+128 x 128 (64-deep, from 256 tiles on), contractions of one element
 up to a little over two stages, rows shorter than the eight elements of a load, odd leading dimensions; both
 layouts, all loaders and epilogues.  Against the float64 oracle with the bounds of parity_util."""
 import numpy as np

@@ -62,6 +62,14 @@ def test_same_bits_with_and_without_the_buffer(zr, torch_mod, M, K, N, mode, lay
     # kept columns of W across the contraction: from 97 on (256 deep, 100 tiles of 64 rows: 13.5 us against 19.6)
     (512, 304, 4272, DROP_N, W_KN, 3200, "fast_kernel<DmaP, LdQG"),
     (1024, 304, 1536, DROP_N, W_KN, 1152, "gemm_kernel<P, Qg, 64, 256>"),
+    # rows of W, 65 to 256 tiles: 64 x 128 (384 up to 1024 deep), and 128 x 128 above
+    (1352, 192, 1096, DROP_N, W_NK, 1096, "fast_kernel<DmaP, DmaP, 64, 128, 1, 4>"),
+    (3088, 64, 2104, DROP_N, W_NK, 1578, "fast_kernel<DmaP, DmaP, 64, 128, 1, 4>"),
+    (2440, 136, 2600, DROP_N, W_NK, 2600, "fast_kernel<LdPV, LdPV, 128, 128, 2, 2>"),
+    # any alignment: 32 x 32, 64 x 64 (512 threads from 256 deep to 256 tiles), 128 x 128
+    (31, 33, 32, DROP_N, W_KN, 32, "gemm_kernel<P, Q, 32, 256>"), (833, 67, 901, DROP_N, W_KN, 901, "gemm_kernel<P, Q, 64, 256>"),
+    (985, 1001, 771, DROP_N, W_KN, 771, "gemm_kernel<P, Q, 64, 512>"), (2497, 65, 2433, DROP_N, W_KN, 2433, "gemm_kernel<P, Q, 128, 256>"),
+    (985, 1001, 771, DROP_K, W_NK, 751, "gemm_kernel<Pg, Pg, 64, 512>"), (2500, 2433, 65, DROP_K, W_KN, 1825, "gemm_kernel<Pg, Q, 32, 256>"),
     # one column of tiles, 100 of them: 512 threads on 64 x 64
     (64, 512, 12800, DROP_N, W_KN, 12800, "gemm_kernel<P, Q, 64, 512>"),
     (64, 256, 8192, DROP_N, W_NK, 8192, "gemm_kernel<P, P, 64, 512>")])

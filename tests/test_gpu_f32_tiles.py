@@ -1,5 +1,5 @@
-"""The fp32 products at the edges of their tiles and stages: 32 x 32 tiles (128-deep stages), 64 x 64
-tiles (64-deep stages, taken from 192 tiles on), contractions of one element up to a little over a
+"""The fp32 products at the edges of their smaller tiles and stages: 32 x 32 tiles (128-deep stages), 64 x 64
+tiles (64-deep stages, taken from 192 tiles on; 128 x 128 tiles: test_gpu_f32_big_tiles.py), contractions of one element up to a little over a
 stage, and rows shorter than the four elements of a load; both layouts, all loaders.  Against the
 float64 oracle with the bounds of parity_util (fp32: 1e-5 of the largest value)."""
 import numpy as np

@@ -1,6 +1,8 @@
 """Aligned bf16 products around the limits of the rules on the number of 128 x 128 tiles: the 64 x 128
-tiles (65 to 256 tiles, to 384 up to 1024 deep) with ragged last tiles, contractions that are no multiple
-of 64, with and without scratch, all policies.  Against the float64 oracle with the bounds of parity_util."""
+tiles (65 to 256 tiles, to 384 up to 1024 deep; 192 and 64 deep here) with ragged last tiles, and contractions that
+are no multiple of 64 (1128 and 136 deep), which leave the direct-to-LDS loaders and with them those tiles; with and
+without scratch, all policies.  Against the float64 oracle with the bounds of parity_util.  (Which kernel each takes:
+test_gpu_dispatch_rules.py.)"""
 import pytest
 
 from paper_2401_11469_amd import workloads as wl

@@ -83,7 +83,7 @@ def test_select_bit_exact(zr, torch_mod, oracle, n, kind):
                                      ((1 << 20) + 77, 0.0), (300001, 0.999), (1 << 22, 0.4)])
 @pytest.mark.parametrize("kind", ["normal", "ties", "special"])
 def test_select_on_many_workgroups_bit_exact(zr, torch_mod, oracle, n, ratio, kind):
-    """One long vector cut into slices of 16384 scores (with scratch): bit-exact against the oracle and
+    """One long vector cut into slices of 256 scores and more (with scratch): bit-exact against the oracle and
     against the single-workgroup entry point; ties that straddle slices are resolved by index."""
     torch = torch_mod
     g = np.random.Generator(np.random.PCG64(n + int(ratio * 1000)))
@@ -516,9 +516,10 @@ def test_layer_parity_weight_stored_out_by_in(zr, torch_mod, oracle, dtype, mode
 @pytest.mark.parametrize("mode", [DROP_N, DROP_K])
 @pytest.mark.parametrize("M,K,N", [(64, 64, 64), (300, 520, 392), (700, 1100, 900)])
 def test_average_through_the_epilogue_sums(zr, torch_mod, oracle, dtype, mode, M, K, N):
-    """With scratch the Average policy takes its means from sums the product's tiles
-    write; without it from a second pass over the stored output.  Both follow the
-    oracle; shapes span one tile, several tiles, and the two-panel schedule."""
+    """With scratch the Average policy takes its means from sums that the product's tiles
+    write, where its kernel does (aligned bf16 products that are not few tiles: all bf16 shapes here
+    under the forced tile shapes); else, and without scratch, from a second pass over the stored
+    output.  All follow the oracle; shapes span one tile and several tiles."""
     torch = torch_mod
     case = wl.random_case(55 + M, M, K, N, dtype)
     n = N if mode == DROP_N else K
