@@ -19,7 +19,7 @@
  *  - Tensors are row-major; leading dimensions (ld*) are in ELEMENTS and must be
  *    >= the row length.  bf16 tensors whose base is 16-byte aligned and whose
  *    ld is a multiple of 8 (fp32: 4) take the vectorised paths; anything else is
- *    still computed correctly on an element-wise path.
+ *    computed by kernels for any alignment.
  *  - Every call only enqueues work on `stream` (a hipStream_t passed as void*;
  *    NULL = the default stream) and never synchronises, except
  *    zr_validate_keep_idx, which is a debugging aid.
@@ -124,10 +124,10 @@ int zr_resize_select(const float* scores, int32_t n, int32_t batch, double ratio
  * top-L_pri select at lengths far beyond a layer shard's, e.g. one list over
  * a whole model).  With a DEVICE scratch buffer of at least
  * zr_select_workspace_bytes(n) bytes (4-byte aligned; 68 KB) and n >= 131072
- * the vector is cut into slices of 4096 scores, one wavefront each: four
- * histogram launches (one per key byte), a count, a scan of the per-slice
- * counts and the ordered write, every launch reading the vector once; all
- * counters are integers, so the lists are the same, bit for bit, as
+ * the vector is cut into slices of 256 scores and more, one wavefront each: three
+ * histogram launches (11, 11 and 10 bits of the key), a count, and the ordered
+ * write, whose workgroups add up the counts before their own, every launch
+ * reading the vector once; all counters are integers, so the lists are the same, bit for bit, as
  * zr_resize_select's.  Shorter vectors, or a missing / too small buffer, take
  * zr_resize_select's single workgroup.  The buffer's contents are undefined
  * afterwards; calls that share one must be ordered on one stream.
@@ -157,21 +157,25 @@ int zr_resize_select_multi(int32_t count, const float* const* scores, const int3
  * layout.  Without it (NULL, or too small) every gather is done in flight by
  * the GEMM loaders.
  * Layout: the extracted activation (bf16 only); then 64 MiB (bf16 only) for
- * the slices of a split contraction; then, at the tail (both dtypes), the
- * per-tile sums of ZR_IMPUTE_AVERAGE: the products' epilogues leave sums of
- * the stored results there, from which the means of the dropped slices are
- * taken; without it a second pass re-reads the kept slices (means equal up to
- * fp32 summation order).
- * Split contraction: a bf16 product (or remainder panel of one) that would
- * occupy fewer than half of the chip's compute units and whose contraction is
- * at least 1024 long is computed in 2..8 slices of the contraction in a first
- * launch (fp32 partial results in the buffer) and summed, slice after slice,
- * and stored by a second one.  Such a result differs from the one-launch result
- * by fp32 summation order (the element-wise bound of the output type still
- * holds); it is repeatable bit by bit for a given buffer size.  Results of
- * products that are not split are the same to the last bit with and without
- * the buffer.  A buffer smaller than this size is used as far as it reaches
- * (extraction first).  Pure host function; returns 0 on bad sizes. */
+ * the slices of a split contraction; then, at the tail, the per-tile sums of
+ * ZR_IMPUTE_AVERAGE (the room is counted for both dtypes, bf16 uses it): the
+ * epilogues of the kernels for aligned bf16 tensors leave sums of the stored
+ * results there, from which the means of the dropped slices are taken; without
+ * it, and for the products of the other kernels (fp32, unaligned tensors, few
+ * tiles), a second pass re-reads the kept slices (means equal up to fp32
+ * summation order).
+ * Split contraction: an aligned bf16 product (or remainder panel of one) of at
+ * most 256 tiles of 128 x 128, with a contraction long enough that every slice has
+ * 512 of it and a tile's chain gets shorter by at least 576, is computed in 2..8 slices of the
+ * contraction in a first launch (fp32 partial results in the buffer) and summed,
+ * slice after slice, and stored by a second one.  Such a result differs from the
+ * one-launch result by fp32 summation order (the element-wise bound of the output
+ * type still holds); it is repeatable bit by bit for a given buffer size.  Results
+ * of products that are not split are the same to the last bit with and without
+ * the buffer: whether the contraction is added up in one chain or in groups (small
+ * tiles) depends on the product's extents alone.  A buffer smaller than this size
+ * is used as far as it reaches (extraction first).  Pure host function; returns 0
+ * on bad sizes. */
 size_t zr_workspace_bytes(int32_t M, int32_t K, int32_t N, int32_t n_keep, int mode, int dtype);
 
 /* The extraction step on its own (Sec. 3.1, forward paragraph: the kept columns
@@ -196,8 +200,9 @@ int zr_extract_kept_columns(const void* in, int64_t ld, int32_t rows, int32_t n,
  *  contents are undefined afterwards; calls that share one must be ordered on
  *  one stream.
  *  Launches: 1 for ZERO and SAME (both written by the product's own epilogue),
- *  +1 with a workspace in DROP_K; AVERAGE: +1 (stand-alone pass) or +3 small ones
- *  (clear sums, means, fill) with a workspace.
+ *  +1 with a workspace in DROP_K, +1 where the contraction is split; AVERAGE: +1
+ *  (stand-alone pass), or +3 small ones (clear sums, means, fill) where the product
+ *  leaves sums in the workspace.
  *  Errors: NULL, SHAPE, INDEX, DTYPE, MODE (also a bad w_layout), POLICY, LIMIT, HIP. */
 int zr_resized_linear_fwd(const void* X, int64_t ldx, const void* W, int64_t ldw,
                           void* Y, int64_t ldy, int32_t M, int32_t K, int32_t N,
@@ -305,9 +310,10 @@ double zr_layer_ratio(int64_t count_above, int64_t L, double alpha, double gamma
  *   out[M x N] += A[M x C] * B^T         (b_transposed = 1, B is [N x C]: column-parallel backward,
  *                                          A = dY_mig[:, range], B = W_mig[:, range])
  * A, B, out are DEVICE sub-matrix views (pointer to the first element of the
- * range + leading dimension); the old value of out joins the fp32 accumulator
- * before the single rounding to the output type.  One launch.  16-byte aligned
- * views with leading dimensions that are multiples of 8 run on the fast path.
+ * range + leading dimension); the old value of out is added to the fp32 sum
+ * before the single rounding to the output type.  One launch, for views of any
+ * alignment; bf16 products of many tiles run on the direct-to-LDS kernels where
+ * the views are 16-byte aligned with leading dimensions that are multiples of 8.
  * Errors: NULL, DTYPE, SHAPE, HIP. */
 int zr_migration_range(int32_t r_i, int32_t r_k, int32_t e, int64_t L_mig, int64_t* begin, int64_t* end);
 int zr_migrated_accumulate(const void* A, int64_t lda, const void* B, int64_t ldb, int b_transposed,
