@@ -464,7 +464,7 @@ def main() -> int:
     cpu = None
     if not args.no_cpu_baseline:
         from oracle import oracle
-        m_slice = min(M, 3072)          # about 15 s of float64 work on the 16 host threads of a GPU machine
+        m_slice = min(M, 3072)          # about 15 s of float64 work on 16 host threads
         ratio = 0.25
         keeps = run_step(ratio)         # one more step of the timed path; its outputs are checked below
         torch.cuda.synchronize()

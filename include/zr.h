@@ -18,8 +18,8 @@
  *    (zr_debug.h declares optional measuring aids that do keep a little).
  *  - Tensors are row-major; leading dimensions (ld*) are in ELEMENTS and must be
  *    >= the row length.  bf16 tensors whose base is 16-byte aligned and whose
- *    ld is a multiple of 8 (fp32: 4) take the vectorised paths; anything else is
- *    computed by kernels for any alignment.
+ *    ld is a multiple of 8 can take the direct-to-LDS kernels; anything else (fp32,
+ *    other alignments, products of few tiles) is computed by kernels for any alignment.
  *  - Every call only enqueues work on `stream` (a hipStream_t passed as void*;
  *    NULL = the default stream) and never synchronises, except
  *    zr_validate_keep_idx, which is a debugging aid.
@@ -161,9 +161,9 @@ int zr_resize_select_multi(int32_t count, const float* const* scores, const int3
  * ZR_IMPUTE_AVERAGE (the room is counted for both dtypes, bf16 uses it): the
  * epilogues of the kernels for aligned bf16 tensors leave sums of the stored
  * results there, from which the means of the dropped slices are taken; without
- * it, and for the products of the other kernels (fp32, unaligned tensors, few
- * tiles), a second pass re-reads the kept slices (means equal up to fp32
- * summation order).
+ * it, and for other products (fp32, unaligned tensors, few tiles, most that are
+ * split as a whole), a second pass re-reads the kept slices (means equal up to
+ * fp32 summation order).
  * Split contraction: an aligned bf16 product (or remainder panel of one) of at
  * most 256 tiles of 128 x 128, with a contraction long enough that every slice has
  * 512 of it and a tile's chain gets shorter by at least 576, is computed in 2..8 slices of the

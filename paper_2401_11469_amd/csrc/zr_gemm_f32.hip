@@ -21,7 +21,8 @@
 // 222 -> 72 us, 256 x 512 x 192 in four launches 132 -> 30 us.  Products with many tiles, 8192 x 4096
 // results (us before / on 64 x 64 tiles / on 128 x 128): contraction 1024, dW 633 / 683 / 580, forward
 // 599 / 619 / 553; contraction 64, kept columns of W gathered 83 / 121 / 79; contraction 8, accumulating
-// 62 / 88 / 56.  4096^3 runs at 122 TFLOP/s on 64 x 64 tiles (0.78 of the fp32 matrix peak).  Of a launch
+// 62 / 88 / 56.  4096^3 takes 998 us on P x P and 1090 on P x Q (1074 and
+// 1220 on 64 x 64 tiles; 138 and 126 TFLOP/s, 0.88 and 0.80 of the fp32 matrix peak).  Of a launch
 // 10-13 us are start and end (all tiles of a round end together); a chip full of tiles keeps the
 // matrix pipes at 0.9 in between, so what is left is that, and the rounding of the tile count to
 // the compute units.

@@ -1,6 +1,6 @@
 """Turns rocprofv3 --pmc outputs of bench.py into the counter summary under profiles/.
 
-Run on the GPU machine, from /tmp with TMPDIR=/tmp, one counter set per run (rocprofv3 does
+Run from /tmp with TMPDIR=/tmp, one counter set per run (rocprofv3 does
 not split counters over passes), each as
     rocprofv3 --pmc <counters> --output-format csv -d <dir>/<tag> -- python3 bench.py <ARGS>
 with the tags and counter sets of PASSES below, and for the two byte counters also
@@ -76,7 +76,7 @@ def main(d: str, commit: str) -> None:
     kw = COPY_KIB / mean(wc[copy_k]["WRITE_SIZE"])
     kernels = {}
     lines = ["# Hardware counters per kernel: bench.py on the Llama-2-7B TP=4 layer shard (bf16), one MI355X", "",
-             f"Recorded at commit {commit}.  Commands (GPU box, from /tmp with TMPDIR=/tmp; one counter set per run):", ""]
+             f"Recorded at commit {commit}.  Commands (from /tmp with TMPDIR=/tmp; one counter set per run):", ""]
     for tag, ctrs in PASSES.items():
         lines.append(f"    rocprofv3 --pmc {ctrs} --output-format csv -d <dir>/{tag} -- python3 bench.py {BENCH_ARGS}")
     lines += ["    rocprofv3 --pmc FETCH_SIZE --output-format csv -d <dir>/fetch_copy -- python3 bench.py --calibrate-copy",

@@ -1,6 +1,6 @@
 """Turns a `rocprofv3 --kernel-trace --stats` run of bench.py into the short summary under profiles/.
 
-On the GPU machine, from /tmp with TMPDIR=/tmp:
+From /tmp with TMPDIR=/tmp:
     rocprofv3 --kernel-trace --stats --output-format csv -d <dir> -- python3 bench.py <ARGS> > <dir>/bench.json
     python3 -m paper_2401_11469_amd.trace_summary <dir> <dir>/bench.json profiles/<name>.md "<ARGS>"
 """
@@ -27,7 +27,7 @@ def main(d: str, bench_json: str, out_md: str, args: str) -> None:
     bench = json.loads(open(bench_json).read().strip().splitlines()[-1])
     out = [f"# rocprofv3 kernel trace: bench.py {args}", "",
            f"Workload: {bench['config']['workload']}", "",
-           "Command (GPU box, from /tmp with TMPDIR=/tmp):", "",
+           "Command (from /tmp with TMPDIR=/tmp):", "",
            f"    rocprofv3 --kernel-trace --stats --output-format csv -d <dir> -- python3 bench.py {args} > <dir>/bench.json",
            f"    python3 -m paper_2401_11469_amd.trace_summary <dir> <dir>/bench.json {out_md} \"{args}\"", "",
            "The run executes warm-up + timed steps + the per-kernel event pass (a step = one selection launch, then forward and "
