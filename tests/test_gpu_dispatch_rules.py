@@ -59,8 +59,9 @@ def test_same_bits_with_and_without_the_buffer(zr, torch_mod, M, K, N, mode, lay
     (1280, 700, 2048, DROP_K, W_NK, 512, "gemm_kernel<Pg, Pg, 128, 256>"),
     (1280, 700, 2048, DROP_K, W_KN, 512, "gemm_kernel<Pg, Q, 128, 256>"),
     (1024, 700, 2048, DROP_K, W_NK, 512, "gemm_kernel<Pg, Pg, 64, 256>"),
-    # kept columns of W across the contraction: from 97 on (256 deep, 100 tiles of 64 rows: 13.5 us against 19.6)
-    (512, 304, 4272, DROP_N, W_KN, 3200, "fast_kernel<DmaP, LdQG"),
+    # kept columns of W across the contraction: from 129 on (100 tiles, 256 deep: 13 us against 16)
+    (512, 304, 5552, DROP_N, W_KN, 4160, "fast_kernel<DmaP, LdQG"),
+    (512, 304, 4272, DROP_N, W_KN, 3200, "gemm_kernel<P, Qg, 64, 256>"), (6400, 200, 344, DROP_N, W_KN, 256, "gemm_kernel<P, Qg, 64, 256>"),
     (1024, 304, 1536, DROP_N, W_KN, 1152, "gemm_kernel<P, Qg, 64, 256>"),
     # rows of W, 65 to 256 tiles: 64 x 128 (384 up to 1024 deep), and 128 x 128 above
     (1352, 192, 1096, DROP_N, W_NK, 1096, "fast_kernel<DmaP, DmaP, 64, 128, 1, 4>"),
