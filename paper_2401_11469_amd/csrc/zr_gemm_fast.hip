@@ -2042,7 +2042,7 @@ bool gemm_fast_takes(const GemmDesc& d)
     if (ap && bp && bg) return t128 > 256;          // W[:,S] along the contraction: 128 tiles 27 / 20, 256 28.5 / 25, 792 91 / 126
     if (ap && bg) return t128 > 128;                // W[:,S] across it: 100 tiles 28.2 / 25.5 (256 deep 16.1 / 13.3, 4096 81 / 74), 128 28.7 / 25.7, 192 30 / 37
     if (ag || bg) return t128 > 96;                 // dW, a gather in flight, 4096 tokens: 48 tiles 84 / 47, 192 84 / 115
-    if (ap && !bp) return t128 > (d.B.map_strided ? 256 : 128);       // rows of W: 64 tiles 18 / 9, 256 19 / 17, 512 (1536 deep) 43 / 38, 1600 53 / 68; all of W: 128 13.6 / 11.8, 160 14 / 18, 256 14.8 / 19.5
+    if (ap && !bp) return t128 > (d.B.map_strided || (!dma && d.C > 768) ? 256 : 128);   // rows of W: 64 tiles 18 / 9, 256 19 / 17, 512 (1536 deep) 43 / 38, 1600 53 / 68; all of W: 128 13.6 / 11.8, 160 14 / 18, 256 14.8 / 19.5; not whole stages: 520 deep 192 tiles 13.2 / 15.3, 1000 deep 160 tiles 18.8 / 18.1, 4040 deep 183 tiles 67 / 60
     if (ap) return t128 > (dma ? 64 : 128);         // 48 tiles 12.5 / 11, 96 14 / 16.5; 1504 deep (not whole) 72 tiles 27.6 / 19, 168 37 / 37
     return t128 > (dma ? 128 : 256);                // dW: 48 tiles 18 / 12.6; 3000 tokens 48 tiles 54 / 19, 120 55 / 33, 5000 tokens 192 89 / 80
 }
