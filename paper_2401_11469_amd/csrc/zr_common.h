@@ -116,6 +116,9 @@ struct GemmDesc {
     // chip cut the contraction into slices and add them up in a second launch); nullptr: never split.
     void* split_scratch = nullptr;
     size_t split_scratch_bytes = 0;
+    // dW: the same call's dX, where neither writes what the other reads.  launch_gemm computes both, in one
+    // launch or one after the other.
+    const GemmDesc* with = nullptr;
 };
 
 // State of the aids in zr_debug.h, per host thread.  Product calls only test `armed`.
@@ -157,6 +160,8 @@ struct AttrFlags {
 bool ensure_max_dynamic_lds(const void* fn, int bytes, void* flags16);
 int launch_gemm(const GemmDesc& d, hipStream_t stream);
 int launch_gemm_fast(const GemmDesc& d, hipStream_t stream);   // -1: not taken
+int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream);   // both products of a backward call; -1: not taken
+bool gemm_fast_can(const GemmDesc& d);
 bool gemm_fast_takes(const GemmDesc& d);
 bool gemm_leaves_sums(const GemmDesc& d);
 // Whether the bf16 kernel for any alignment adds up an I x J product over C in groups of the contraction
