@@ -4,12 +4,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libzr.so")
-SOURCES = ["zr_api.hip", "zr_select.hip", "zr_impute.hip", "zr_gemm.hip", "zr_gemm_fast.hip", "zr_gemm_f32.hip", "zr_compact.hip", "zr_priority.hip",
+SOURCES = ["zr_api.hip", "zr_select.hip", "zr_impute.hip", "zr_gemm.hip", "zr_gemm_fast.hip", "zr_gemm_pair.hip", "zr_gemm_f32.hip", "zr_compact.hip", "zr_priority.hip",
            "zr_probe.hip"]
 
 FLAGS = [
@@ -56,11 +58,22 @@ def build(verbose: bool = True, out: str = LIB) -> str:
     (a kernel of the fast GEMM path that starts to spill loses 15-20 %, silently)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     extra = os.environ.get("ZR_EXTRA_HIPCC_FLAGS", "").split()      # experiments only
-    cmd = [hipcc, *FLAGS, "-Rpass-analysis=kernel-resource-usage", *extra, "-I", os.path.join(ROOT, "include"),
-           "-I", CSRC, *[os.path.join(CSRC, s) for s in SOURCES], "-o", out]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    flags = [f for f in FLAGS if f != "-shared"] + ["-Rpass-analysis=kernel-resource-usage", *extra, "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+    def run(cmd):
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        return subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+
+    # one compiler per source side by side, then the link
+    with tempfile.TemporaryDirectory() as tmp, ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+        objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
+        done = list(pool.map(lambda so: run([hipcc, *flags, "-c", os.path.join(CSRC, so[0]), "-o", so[1]]), zip(SOURCES, objs)))
+        text = "".join(r.stdout for r in done)
+        if any(r.returncode for r in done):
+            raise RuntimeError("hipcc failed:\n" + text)
+        res = run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", out])
+        res.stdout = text + res.stdout
     if out == LIB and res.returncode == 0:
         rows = _resource_table(res.stdout, hipcc)
         with open(RESOURCES, "w") as f:

@@ -352,6 +352,21 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
         sums = carve_avg(workspace, workspace_bytes, need);
     }
 
+    // Whether the two products may run side by side: neither result lies where the other product reads or
+    // writes (one after the other, dW may for instance replace W, which only dX reads).
+    const size_t esz = dtype == ZR_BF16 ? 2 : 4;
+    auto apart = [&] {
+        auto clear = [&](const void* out, int rows, int cols, int64_t ldo, const void* in, int in_rows, int in_cols, int64_t ldi) {
+            const uintptr_t a = (uintptr_t)out, b = (uintptr_t)in;
+            return !in || a + ((size_t)(rows - 1) * (size_t)ldo + cols) * esz <= b || b + ((size_t)(in_rows - 1) * (size_t)ldi + in_cols) * esz <= a;
+        };
+        const int wr = kn ? K : N, wc = kn ? N : K;
+        auto dx_clear = [&](const void* p, int rows, int cols, int64_t ld) { return clear(dX, M, K, lddx, p, rows, cols, ld); };
+        auto dw_clear = [&](const void* p, int rows, int cols, int64_t ld) { return clear(dW, wr, wc, lddw, p, rows, cols, ld); };
+        return dx_clear(dW, wr, wc, lddw) && dx_clear(X, M, K, ldx) && dx_clear(dY, M, N, lddy) && dx_clear(same ? prev_dW : nullptr, wr, wc, lddw) &&
+               dw_clear(W, wr, wc, ldw) && dw_clear(dY, M, N, lddy) && dw_clear(same ? prev_dX : nullptr, M, K, lddx);
+    };
+
     // one extraction serves both products: X[:,S] (DROP_K, used by dW) or dY[:,S] (DROP_N)
     Extract ex{false, 0};
     if (mode == ZR_DROP_K) {
@@ -366,7 +381,8 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
     }
     if (st != ZR_OK) return st;
 
-    GemmDesc d;
+    GemmDesc d, dx;
+    dx.out = nullptr;           // (dX left for the launch of dW)
     d.dtype = dtype;
     d.keep_idx = S;
     // (in DROP_K the start of the buffer may hold the forward call's X[:,S] even when this call
@@ -392,6 +408,7 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
             d.J = K; d.C = n_keep; d.epilogue = EPI_PLAIN; d.out_full = K;
         }
         if (post && mode == ZR_DROP_K) st = gemm_with_average(d, sums, dX, lddx, M, K, 1, keep_idx, n_keep, dtype, s);
+        else if (dW && !post && apart()) dx = d;
         else st = launch_gemm(d, s);
         if (st != ZR_OK) return st;
     }
@@ -417,7 +434,10 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
         d.out_full = mode == ZR_DROP_K ? K : N;
         if (post) st = gemm_with_average(d, sums, dW, lddw, kn ? K : N, kn ? N : K, rows_pruned ? 0 : 1, keep_idx,
                                          n_keep, dtype, s);
-        else st = launch_gemm(d, s);
+        else {
+            d.with = dx.out ? &dx : nullptr;
+            st = launch_gemm(d, s);
+        }
         if (st != ZR_OK) return st;
     }
     return ZR_OK;
