@@ -367,6 +367,9 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
                dw_clear(W, wr, wc, ldw) && dw_clear(dY, M, N, lddy) && dw_clear(same ? prev_dX : nullptr, M, K, lddx);
     };
 
+    // both at once, the stand-alone passes of Average imputation behind them; with sums from the epilogues one at a time
+    const bool pair = dX && dW && !(post && sums) && apart();
+
     // one extraction serves both products: X[:,S] (DROP_K, used by dW) or dY[:,S] (DROP_N)
     Extract ex{false, 0};
     if (mode == ZR_DROP_K) {
@@ -407,8 +410,8 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
             }
             d.J = K; d.C = n_keep; d.epilogue = EPI_PLAIN; d.out_full = K;
         }
-        if (post && mode == ZR_DROP_K) st = gemm_with_average(d, sums, dX, lddx, M, K, 1, keep_idx, n_keep, dtype, s);
-        else if (dW && !post && apart()) dx = d;
+        if (post && mode == ZR_DROP_K && !pair) st = gemm_with_average(d, sums, dX, lddx, M, K, 1, keep_idx, n_keep, dtype, s);
+        else if (dW && pair) dx = d;
         else st = launch_gemm(d, s);
         if (st != ZR_OK) return st;
     }
@@ -432,11 +435,16 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
         else    { d.A = dys; d.B = xs; d.I = in; d.J = ik; }
         d.epilogue = full ? EPI_PLAIN : (rows_pruned ? EPI_ROW_SCATTER : EPI_COL_SCATTER);
         d.out_full = mode == ZR_DROP_K ? K : N;
-        if (post) st = gemm_with_average(d, sums, dW, lddw, kn ? K : N, kn ? N : K, rows_pruned ? 0 : 1, keep_idx,
-                                         n_keep, dtype, s);
+        if (post && !pair) st = gemm_with_average(d, sums, dW, lddw, kn ? K : N, kn ? N : K, rows_pruned ? 0 : 1, keep_idx,
+                                                  n_keep, dtype, s);
         else {
             d.with = dx.out ? &dx : nullptr;
             st = launch_gemm(d, s);
+            if (st == ZR_OK && post && mode == ZR_DROP_K)
+                st = launch_impute(dX, lddx, M, K, 1, keep_idx, n_keep, ZR_IMPUTE_AVERAGE, nullptr, dtype, s);
+            if (st == ZR_OK && post)
+                st = launch_impute(dW, lddw, kn ? K : N, kn ? N : K, rows_pruned ? 0 : 1, keep_idx, n_keep, ZR_IMPUTE_AVERAGE,
+                                   nullptr, dtype, s);
         }
         if (st != ZR_OK) return st;
     }

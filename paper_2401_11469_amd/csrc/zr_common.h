@@ -4,7 +4,9 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 
@@ -172,6 +174,7 @@ inline bool adds_in_groups(int I, int J, int C)
     return t64 < 96 || (t64 <= 256 && C >= 256);
 }
 int launch_gemm_f32(const GemmDesc& d, hipStream_t stream);
+int launch_gemm_f32_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream);   // -1: not taken
 int launch_select(const float* scores, int n, int batch, int n_keep,
                   int32_t* keep_idx, int32_t* drop_idx, int64_t ld_idx, hipStream_t stream);
 // one long vector on many workgroups, with caller scratch of select_wide_workspace_bytes()
@@ -210,6 +213,23 @@ int launch_count_above(const float* scores, int n, float theta, int32_t* count, 
 int launch_mfma_rate(int blocks, int iters, float* sink, hipStream_t stream);   // zr_probe.hip
 double mfma_rate_flops(int blocks, int iters);
 int launch_validate(const int32_t* keep_idx, int n_keep, int n, int32_t* flag, hipStream_t stream);
+
+// When the last piece ends: n1 pieces of t1, then n2 of t2, each on the first of `slots` that is free.
+inline double two_groups(int n1, double t1, int n2, double t2, int slots)
+{
+    const int q = n1 / slots, r = n1 % slots;
+    const double lo = q * t1, hi = r ? lo + t1 : lo;       // when slots - r, and r, of them are through the first group
+    if (n2 == 0) return hi;
+    const double least = std::max(lo, (n1 * t1 + n2 * t2) / slots);        // (nobody idle)
+    auto room = [&](double T) { return (slots - r) * (int)((T - lo) / t2 + 1e-9) + (r && T > hi ? r * (int)((T - hi) / t2 + 1e-9) : 0); };
+    auto first = [&](double base) {
+        double T = base + t2 * std::max(1.0, std::floor((least - base) / t2));
+        while (room(T) < n2) T += t2;
+        return T;
+    };
+    const double T = r ? std::min(first(lo), first(hi)) : first(lo);
+    return std::max(T, hi);
+}
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? ZR_OK : ZR_ERR_HIP; }
 

@@ -25,6 +25,7 @@
 // LDS formats (bf16):
 //   P  [row][contraction]  tensors whose contiguous axis is the contraction axis: ds_read_b128
 //   Q  [contraction][row]  tensors whose contiguous axis is the other one: transposing reads
+#include <algorithm>
 #include <cstdio>
 #include <type_traits>
 
@@ -79,6 +80,7 @@ struct Args {
     int tiles_i, tiles_j;
     const E* prev;              // Same imputation source (layout of out) or nullptr
     int accumulate;             // add the old contents of out (plain epilogue)
+    int alternate;              // 64 x 64 tiles of 256 threads: every other stage goes to a second sum
 };
 
 // element e of the result is element e + sh of v, 0 past its end (sh >= 0)
@@ -370,8 +372,9 @@ __device__ __forceinline__ bf16x8 fragment(const uint32_t* lds, int r0, int k0, 
 
 __device__ __forceinline__ uint32_t two(float a, float b) { return f32_to_bf16_bits(a) | (f32_to_bf16_bits(b) << 16); }
 
+// One workgroup's tile `lin` of a product.
 template <template <int, int, bool> class LA_, bool AP, template <int, int, bool> class LB_, bool BP, int R, int NT>
-__global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
+__device__ __forceinline__ void gemm_body(const Args& g, uint32_t* smem, const int lin)
 {
     typedef LA_<R, NT, AP> LA;
     typedef LB_<R, NT, BP> LB;
@@ -389,12 +392,8 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
     constexpr int PART = SPLIT ? KG * R * CP : 0;                     // the groups' sums
     static_assert(R * CP + PART + 2 * R + TAB <= 2 * STAGE, "the epilogue fits the stages");
 
-    extern __shared__ __align__(16) uint32_t smem[];
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-    // every XCD gets a contiguous range of tiles, ordered in groups of 4 tile rows
-    const int lin = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     if (lin >= g.tiles_i * g.tiles_j) return;
     const int grp_sz = 4 * g.tiles_j;
     const int first_i = lin / grp_sz * 4, within = lin % grp_sz;
@@ -404,13 +403,19 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
     const int wr0 = WPT == 1 ? 0 : ((wave >> 1) & 1) * (R / 2), wc0 = WPT == 1 ? 0 : (wave & 1) * (R / 2);
     const int k0 = wave / WPT * (BK / KG);
 
-    f32x4 acc[T][T];
+    // (tiles of 512 threads add up the two halves of each stage, 128 deep, on their own; ALT: the same order on 256 threads,
+    // whose stages are those halves)
+    constexpr bool ALT = R == 64 && NT == 256;
+    f32x4 acc[T][T], other[ALT ? T : 1][ALT ? T : 1];
 #pragma unroll
     for (int a = 0; a < T; ++a)
 #pragma unroll
         for (int b = 0; b < T; ++b)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[a][b][r] = 0.f;
+            for (int r = 0; r < 4; ++r) {
+                acc[a][b][r] = 0.f;
+                if constexpr (ALT) other[a][b][r] = 0.f;
+            }
 
     // While stage k is multiplied, stage k + 1 (requested during stage k - 1) goes from registers
     // to the other LDS buffer and stage k + 2 is requested, a piece at a time between the MFMAs.
@@ -468,6 +473,18 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
                         acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
             }
         });
+        if constexpr (ALT) {
+            if (g.alternate) {
+#pragma unroll
+                for (int a = 0; a < T; ++a)
+#pragma unroll
+                    for (int b = 0; b < T; ++b) {
+                        const f32x4 x = acc[a][b];
+                        acc[a][b] = other[a][b];
+                        other[a][b] = x;
+                    }
+            }
+        }
         __syncthreads();
     };
     int kt = 0;
@@ -476,6 +493,17 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
         if (kt + 1 < KT) step(kt++, std::true_type(), std::false_type());
     }
     step(kt, std::false_type(), std::false_type());
+
+    if constexpr (ALT) {
+        if (g.alternate) {
+#pragma unroll
+            for (int a = 0; a < T; ++a)
+#pragma unroll
+                for (int b = 0; b < T; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[a][b][r] += other[a][b][r];
+        }
+    }
 
     // ---- result tile in LDS, in fp32 --------------------------------------------
     float* Cs = (float*)smem;
@@ -661,6 +689,33 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
     }
 }
 
+// every XCD gets a contiguous range of tiles, ordered in groups of 4 tile rows
+template <template <int, int, bool> class LA, bool AP, template <int, int, bool> class LB, bool BP, int R, int NT>
+__global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    gemm_body<LA, AP, LB, BP, R, NT>(g, smem, (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8));
+}
+
+// A pair of loaders, as a type.
+template <template <int, int, bool> class LA, bool AP, template <int, int, bool> class LB, bool BP> struct Loaders {
+    template <int R> static __device__ __forceinline__ void run(const Args& g, uint32_t* smem, int lin)
+    {
+        gemm_body<LA, AP, LB, BP, R, 256>(g, smem, lin);
+    }
+};
+
+// dX and dW of one backward call: the first per_w workgroups of every XCD are dW's, or with x_first the last ones.
+template <class X, int XR, class W, int WR>
+__global__ __launch_bounds__(256, 2) void gemm_pair_kernel(const Args gx, const Args gw, const int per_x, const int per_w, const int x_first)
+{
+    extern __shared__ __align__(16) uint32_t smem[];
+    const int xcd = blockIdx.x % 8, q = blockIdx.x / 8;
+    const int qx = x_first ? q : q - per_w, qw = x_first ? q - per_x : q;
+    if (qw >= 0 && qw < per_w) W::template run<WR>(gw, smem, xcd * per_w + qw);
+    else X::template run<XR>(gx, smem, xcd * per_x + qx);
+}
+
 // ---------------------------------------------------------------------------
 // Host side
 // ---------------------------------------------------------------------------
@@ -719,9 +774,94 @@ int launch_short(const Args& a, const char* name, hipStream_t stream)
     return launch_inst<LA, AP, LB, BP, 32, 256>(a, name, stream);
 }
 
-int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
+// ---------------------------------------------------------------------------
+// dX and dW in one launch
+// ---------------------------------------------------------------------------
+// The order in which a product is added up stays the one it has on its own (see adds_in_groups): 32 x 32
+// tiles below 96 of 64 x 64, 64 x 64 ones with alternating sums where those of 512 threads would be used, and
+// else 64 x 64 or 128 x 128, whichever the model of the schedule finds shorter (every XCD takes its tiles in
+// order, each as soon as one of 64 halves of a unit is free; a tile takes a start and an end, and a time per
+// stage, longer where kept columns are gathered).  Fitted to 56 backward calls (47 to 9500 tokens, 53 to 5100
+// wide), each in seven forms; the form it picks is 1.5 % slower than the best on average.  us before, in two launches,
+// and now: 985 x 1001 x 771 34 -> 25, 489 x 953 x 1073 30 -> 19, 2024 x 1024 x 1024 40 -> 30, 4095 x 2960 x 2304 64 for 130.
+struct Plan { int xr, wr; bool x_first; };
+struct Cost { double start, stage; };
+constexpr Cost kCost32 = {9.7, 0.41}, kCost64 = {7.8, 1.61}, kCost128 = {5.4, 1.59};       // us, us per stage of 128, 128 and 64
+constexpr double kGathered = 0.305, kHalfFree = 0.70, kAlone = 0.55;     // per gathered operand; a unit to itself; a launch more
+
+int64_t tiles_of(const Args& a, int r) { return (int64_t)((a.I + r - 1) / r) * ((a.J + r - 1) / r); }
+
+int tile_of(const Args& a, bool wide) { return tiles_of(a, 64) < 96 ? 32 : wide && !adds_in_groups(a.I, a.J, a.C) ? 128 : 64; }
+
+double tile_us(const Args& a, int r, double f)
 {
-    if (d.I < 1 || d.J < 1 || d.C < 1) return ZR_ERR_SHAPE;
+    const Cost c = r == 32 ? kCost32 : r == 64 ? kCost64 : kCost128;
+    const int bk = r == 128 ? 64 : 128;
+    return c.start + f * c.stage * ((a.C + bk - 1) / bk) * (1 + kGathered * ((a.A.map_c != nullptr) + (a.B.map_c != nullptr)));
+}
+
+double alone_us(const Args& a)
+{
+    double best = 1e30;
+    for (bool wide : {false, true}) {
+        const int r = tile_of(a, wide);
+        const int64_t n = (tiles_of(a, r) + 7) / 8;
+        best = std::min(best, (double)((n + 63) / 64) * tile_us(a, r, n <= 32 ? kHalfFree : 1.0));
+    }
+    return best + kAlone;
+}
+
+// false: two launches
+bool plan_pair(const Args& x, const Args& w, Plan& p)
+{
+    double best = alone_us(x) + alone_us(w);
+    bool found = false;
+    for (bool xwide : {false, true})
+        for (bool wwide : {false, true}) {
+            const int xr = tile_of(x, xwide), wr = tile_of(w, wwide);
+            if (xr + wr == 160) continue;                   // (no kernel of 32 x 32 beside 128 x 128)
+            const int64_t nx = (tiles_of(x, xr) + 7) / 8, nw = (tiles_of(w, wr) + 7) / 8;
+            if (nx + nw > 1 << 20) continue;
+            const double f = nx + nw <= 32 ? kHalfFree : 1.0, tx = tile_us(x, xr, f), tw = tile_us(w, wr, f);
+            const bool x_first = tx > tw;                   // the long tiles first
+            const double us = x_first ? two_groups((int)nx, tx, (int)nw, tw, 64) : two_groups((int)nw, tw, (int)nx, tx, 64);
+            if (us < best) { best = us; p = Plan{xr, wr, x_first}; found = true; }
+        }
+    return found;
+}
+
+template <class X, int XR, class W, int WR>
+int launch_pair_inst(const Args& x, const Args& w, const char* name, bool x_first, hipStream_t stream)
+{
+    constexpr int words = Geo<XR, 256>::WORDS > Geo<WR, 256>::WORDS ? Geo<XR, 256>::WORDS : Geo<WR, 256>::WORDS;
+    constexpr int smem = 2 * 2 * words * 4;
+    auto fn = gemm_pair_kernel<X, XR, W, WR>;
+    static AttrFlags attr_set;      // per instantiation and device
+    if (!ensure_max_dynamic_lds((const void*)fn, smem, &attr_set)) return ZR_ERR_HIP;
+    if (debug_names_wanted())
+        snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "gemm_kernel<%s> beside each other, %d and %d", name, WR, XR);
+    Args kx = x, kw = w;
+    kx.tiles_i = (x.I + XR - 1) / XR; kx.tiles_j = (x.J + XR - 1) / XR;
+    kw.tiles_i = (w.I + WR - 1) / WR; kw.tiles_j = (w.J + WR - 1) / WR;
+    const int64_t px = ((int64_t)kx.tiles_i * kx.tiles_j + 7) / 8, pw = ((int64_t)kw.tiles_i * kw.tiles_j + 7) / 8;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(px + pw) * 8), dim3(256), smem, stream, kx, kw, (int)px, (int)pw, x_first ? 1 : 0);
+    return hip_status(hipGetLastError());
+}
+
+template <class X, class W>
+int launch_pair(const Args& x, const Args& w, const char* name, const Plan& p, hipStream_t stream)
+{
+    if (p.xr == 128 && p.wr == 128) return launch_pair_inst<X, 128, W, 128>(x, w, name, p.x_first, stream);
+    if (p.xr == 128) return launch_pair_inst<X, 128, W, 64>(x, w, name, p.x_first, stream);
+    if (p.wr == 128) return launch_pair_inst<X, 64, W, 128>(x, w, name, p.x_first, stream);
+    if (p.xr == 64 && p.wr == 64) return launch_pair_inst<X, 64, W, 64>(x, w, name, p.x_first, stream);
+    if (p.xr == 64) return launch_pair_inst<X, 64, W, 32>(x, w, name, p.x_first, stream);
+    if (p.wr == 64) return launch_pair_inst<X, 32, W, 64>(x, w, name, p.x_first, stream);
+    return launch_pair_inst<X, 32, W, 32>(x, w, name, p.x_first, stream);
+}
+
+Args args_of(const GemmDesc& d)
+{
     Args a;
     a.A = View{(const E*)d.A.base, d.A.ld, d.A.map_strided, d.A.map_contig, d.A.n_strided, d.A.n_contig};
     a.B = View{(const E*)d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
@@ -729,11 +869,50 @@ int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
     a.out = (E*)d.out; a.ldo = d.ldo; a.epilogue = d.epilogue; a.keep = d.keep_idx; a.out_full = d.out_full;
     a.tiles_i = a.tiles_j = 0;
     a.prev = (const E*)d.prev; a.accumulate = d.accumulate ? 1 : 0;
+    a.alternate = 0;
+    return a;
+}
+
+bool too_short(const GemmDesc& d, const Operand& o) { return o.map_contig ? o.n_contig < 2 : (o.c_contig ? d.C : o.n_contig) < 8; }
+
+int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
+{
+    if (forced_tiles() || dx.I < 1 || dx.J < 1 || dx.C < 1 || dw.I < 1 || dw.J < 1 || dw.C < 1) return -1;
+    for (const GemmDesc* d : {&dx, &dw})
+        if (too_short(*d, d->A) || too_short(*d, d->B)) return -1;
+    if (!dx.A.c_contig || dw.A.c_contig || dw.B.c_contig) return -1;
+    Args x = args_of(dx), w = args_of(dw);
+    Plan p;
+    if (!plan_pair(x, w, p)) return -1;
+    x.alternate = p.xr == 64 && adds_in_groups(x.I, x.J, x.C);
+    w.alternate = p.wr == 64 && adds_in_groups(w.I, w.J, w.C);
+    const bool xa = dx.A.map_contig, xb = dx.B.map_contig, wa = dw.A.map_contig, wb = dw.B.map_contig;
+    typedef Loaders<Plain, false, Plain, false> WPlain;
+    typedef Loaders<Gather, false, Plain, false> WGatherA;
+    typedef Loaders<Plain, false, Gather, false> WGatherB;
+    if (dx.B.c_contig) {                    // weight stored [K x N]
+        if (xa && xb && !wa && wb) return launch_pair<Loaders<Gather, true, Gather, true>, WGatherB>(x, w, "Pg, Pg; Q, Qg", p, stream);
+        if (xa || wb) return -1;
+        if (xb) return wa ? -1 : launch_pair<Loaders<Plain, true, Gather, true>, WPlain>(x, w, "P, Pg; Q, Q", p, stream);
+        if (wa) return launch_pair<Loaders<Plain, true, Plain, true>, WGatherA>(x, w, "P, P; Qg, Q", p, stream);
+        return launch_pair<Loaders<Plain, true, Plain, true>, WPlain>(x, w, "P, P; Q, Q", p, stream);
+    }
+    if (xa && !xb && wa && !wb) return launch_pair<Loaders<Gather, true, Plain, false>, WGatherA>(x, w, "Pg, Q; Qg, Q", p, stream);
+    if (xa || wa) return -1;
+    if (xb && wb) return launch_pair<Loaders<Plain, true, Gather, false>, WGatherB>(x, w, "P, Qg; Q, Qg", p, stream);
+    if (wb) return -1;
+    if (xb) return launch_pair<Loaders<Plain, true, Gather, false>, WPlain>(x, w, "P, Qg; Q, Q", p, stream);
+    return launch_pair<Loaders<Plain, true, Plain, false>, WPlain>(x, w, "P, Q; Q, Q", p, stream);
+}
+
+int launch_gemm_any(const GemmDesc& d, hipStream_t stream)
+{
+    if (d.I < 1 || d.J < 1 || d.C < 1) return ZR_ERR_SHAPE;
+    const Args a = args_of(d);
     const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
-    auto too_short = [&](const Operand& o) { return o.map_contig ? o.n_contig < 2 : (o.c_contig ? d.C : o.n_contig) < 8; };
     const bool ap = d.A.c_contig, bp = d.B.c_contig;
     if (!ap && bp) return ZR_ERR_MODE;
-    if (too_short(d.A) || too_short(d.B)) {
+    if (too_short(d, d.A) || too_short(d, d.B)) {
         if (ap) return bp ? launch_short<Any, true, Any, true>(a, "Pe, Pe", stream) : launch_short<Any, true, Any, false>(a, "Pe, Qe", stream);
         return launch_short<Any, false, Any, false>(a, "Qe, Qe", stream);
     }
@@ -784,7 +963,14 @@ int launch_gemm(const GemmDesc& desc, hipStream_t stream)
     GemmDesc d = desc;
     if (d.with) {
         // (the measuring aid times products one by one)
-        int st = g_debug.armed_once ? -1 : launch_gemm_pair(*d.with, d, stream);
+        int st = -1;
+        if (!g_debug.armed_once) {
+            if (d.dtype == ZR_F32) st = launch_gemm_f32_pair(*d.with, d, stream);
+            else if (d.dtype == ZR_BF16) {
+                st = launch_gemm_pair(*d.with, d, stream);
+                if (st < 0) st = launch_gemm_any_pair(*d.with, d, stream);
+            }
+        }
         if (st >= 0) return st;
         st = launch_gemm(*d.with, stream);
         if (st != ZR_OK) return st;

@@ -33,6 +33,7 @@
 // The order in which the contraction is added up is free as long as both operands agree: of a
 // block of 8 indices, lanes 0-31 take indices 0-3 and lanes 32-63 indices 4-7, so a P operand
 // is read with one ds_read_b128 per four MFMAs.
+#include <algorithm>
 #include <cstdio>
 #include <type_traits>
 
@@ -348,8 +349,9 @@ __device__ __forceinline__ f4 fragment(const float* lds, int row, int block, int
     return x;
 }
 
+// One workgroup's tile `lin` of a product.
 template <template <int> class LA_, template <int> class LB_, int R>
-__global__ __launch_bounds__(NT) void f32_kernel(const Args g)
+__device__ __forceinline__ void f32_body(const Args& g, float* smem, const int lin)
 {
     typedef LA_<R> LA;
     typedef LB_<R> LB;
@@ -363,13 +365,9 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
     constexpr int PART = R == 32 ? 4 * 32 * 36 : 0;                   // the wavefronts' sums
     static_assert(R * CP + PART + 2 * R + TAB <= 2 * STAGE, "the epilogue fits the stages");
 
-    extern __shared__ __align__(16) float smem[];
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, grp = lane >> 5;
 
-    // every XCD gets a contiguous range of tiles, ordered in groups of 4 tile rows
-    const int lin = (blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8;
     if (lin >= g.tiles_i * g.tiles_j) return;
     const int grp_sz = 4 * g.tiles_j;
     const int first_i = lin / grp_sz * 4, within = lin % grp_sz;
@@ -640,6 +638,25 @@ __global__ __launch_bounds__(NT) void f32_kernel(const Args g)
     }
 }
 
+// every XCD gets a contiguous range of tiles, ordered in groups of 4 tile rows
+template <template <int> class LA, template <int> class LB, int R>
+__global__ __launch_bounds__(NT) void f32_kernel(const Args g)
+{
+    extern __shared__ __align__(16) float smem[];
+    f32_body<LA, LB, R>(g, smem, (int)((blockIdx.x % 8) * (gridDim.x / 8) + blockIdx.x / 8));
+}
+
+// dX and dW of one backward call: the first per_w workgroups of every XCD are dW's, or with x_first the last ones.
+template <template <int> class XA, template <int> class XB, int XR, template <int> class WA, template <int> class WB, int WR>
+__global__ __launch_bounds__(NT) void f32_pair_kernel(const Args gx, const Args gw, const int per_x, const int per_w, const int x_first)
+{
+    extern __shared__ __align__(16) float smem[];
+    const int xcd = blockIdx.x % 8, q = blockIdx.x / 8;
+    const int qx = x_first ? q : q - per_w, qw = x_first ? q - per_x : q;
+    if (qw >= 0 && qw < per_w) f32_body<WA, WB, WR>(gw, smem, xcd * per_w + qw);
+    else f32_body<XA, XB, XR>(gx, smem, xcd * per_x + qx);
+}
+
 template <template <int> class LA, template <int> class LB, int R>
 int launch_inst(const Args& a, hipStream_t stream)
 {
@@ -683,11 +700,90 @@ int launch_short(const Args& a, hipStream_t stream)
     return a.C < 4 ? launch_shape<LA, LB>(a, stream) : launch_inst<LA, LB, 32>(a, stream);
 }
 
-}  // namespace
+// ---------------------------------------------------------------------------
+// dX and dW in one launch
+// ---------------------------------------------------------------------------
+// Tiles by a model of the schedule (every XCD takes its tiles in order, each as soon as one of 64 halves of a unit
+// is free; a tile takes a start and an end, and a time per stage, longer where kept columns are gathered).  Fitted to
+// 33 backward calls (32 to 2500 tokens, 64 to 2048 wide), each in nine forms: what it picks is 1.6 % slower than the best
+// of them on average.  us in two launches and now: 1576 x 2048 x 1024 of 1638 kept rows 151 -> 117, 609 x 1414 x 247
+// 31 -> 20, 256 x 512 x 256 14.7 -> 11.6.  A product that takes 32 x 32 tiles on its own keeps them: their four partial
+// sums are the more exact.
+struct Plan { int xr, wr; bool x_first; };
+struct Cost { double start, stage; };
+constexpr Cost kCost32 = {5.4, 1.17}, kCost64 = {9.0, 1.52}, kCost128 = {8.3, 2.2};       // us, us per stage of 128, 64 and 32
+constexpr double kGathered = 0.51, kHalfFree = 0.72, kAlone = 1.2;        // per gathered operand; a unit to itself; a launch more
 
-int launch_gemm_f32(const GemmDesc& d, hipStream_t stream)
+int64_t tiles_of(const Args& a, int r) { return (int64_t)((a.I + r - 1) / r) * ((a.J + r - 1) / r); }
+bool may_take(const Args& a, int r) { return r == 32 || tiles_of(a, 64) >= 192; }
+
+double tile_us(const Args& a, int r, double f)
 {
-    if (d.I < 1 || d.J < 1 || d.C < 1) return ZR_ERR_SHAPE;
+    const Cost c = r == 32 ? kCost32 : r == 64 ? kCost64 : kCost128;
+    const int bk = 16 * NT / r;
+    return c.start + f * c.stage * ((a.C + bk - 1) / bk) * (1 + kGathered * ((a.A.map_c != nullptr) + (a.B.map_c != nullptr)));
+}
+
+double alone_us(const Args& a)
+{
+    double best = 1e30;
+    for (int r : {32, 64, 128}) {
+        if (!may_take(a, r)) continue;
+        const int64_t n = (tiles_of(a, r) + 7) / 8;
+        best = std::min(best, (double)((n + 63) / 64) * tile_us(a, r, n <= 32 ? kHalfFree : 1.0));
+    }
+    return best + kAlone;
+}
+
+// false: two launches
+bool plan_pair(const Args& x, const Args& w, Plan& p)
+{
+    double best = alone_us(x) + alone_us(w);
+    bool found = false;
+    for (int xr : {32, 64, 128})
+        for (int wr : {32, 64, 128}) {
+            if ((xr == 128) != (wr == 128) || !may_take(x, xr) || !may_take(w, wr)) continue;
+            const int64_t nx = (tiles_of(x, xr) + 7) / 8, nw = (tiles_of(w, wr) + 7) / 8;
+            if (nx + nw > 1 << 20) continue;
+            const double f = nx + nw <= 32 ? kHalfFree : 1.0, tx = tile_us(x, xr, f), tw = tile_us(w, wr, f);
+            const bool x_first = tx > tw;                   // the long tiles first
+            const double us = x_first ? two_groups((int)nx, tx, (int)nw, tw, 64) : two_groups((int)nw, tw, (int)nx, tx, 64);
+            if (us < best) { best = us; p = Plan{xr, wr, x_first}; found = true; }
+        }
+    return found;
+}
+
+template <template <int> class XA, template <int> class XB, int XR, template <int> class WA, template <int> class WB, int WR>
+int launch_pair_inst(const Args& x, const Args& w, bool x_first, hipStream_t stream)
+{
+    constexpr int words = Geo<XR>::WORDS > Geo<WR>::WORDS ? Geo<XR>::WORDS : Geo<WR>::WORDS;
+    constexpr int smem = 2 * 2 * words * 4;
+    auto fn = f32_pair_kernel<XA, XB, XR, WA, WB, WR>;
+    static AttrFlags attr_set;      // per instantiation and device
+    if (!ensure_max_dynamic_lds((const void*)fn, smem, &attr_set)) return ZR_ERR_HIP;
+    if (debug_names_wanted())
+        snprintf(g_debug.last_kernel, sizeof(g_debug.last_kernel), "f32_kernel<%s, %s, %d> beside <%s, %s, %d>", WA<WR>::NAME, WB<WR>::NAME, WR,
+                 XA<XR>::NAME, XB<XR>::NAME, XR);
+    Args kx = x, kw = w;
+    kx.tiles_i = (x.I + XR - 1) / XR; kx.tiles_j = (x.J + XR - 1) / XR;
+    kw.tiles_i = (w.I + WR - 1) / WR; kw.tiles_j = (w.J + WR - 1) / WR;
+    const int64_t px = ((int64_t)kx.tiles_i * kx.tiles_j + 7) / 8, pw = ((int64_t)kw.tiles_i * kw.tiles_j + 7) / 8;
+    hipLaunchKernelGGL(fn, dim3((unsigned)(px + pw) * 8), dim3(NT), smem, stream, kx, kw, (int)px, (int)pw, x_first ? 1 : 0);
+    return hip_status(hipGetLastError());
+}
+
+template <template <int> class XA, template <int> class XB, template <int> class WA, template <int> class WB>
+int launch_pair(const Args& x, const Args& w, const Plan& p, hipStream_t stream)
+{
+    if (p.xr == 128) return launch_pair_inst<XA, XB, 128, WA, WB, 128>(x, w, p.x_first, stream);
+    if (p.xr == 64 && p.wr == 64) return launch_pair_inst<XA, XB, 64, WA, WB, 64>(x, w, p.x_first, stream);
+    if (p.xr == 64) return launch_pair_inst<XA, XB, 64, WA, WB, 32>(x, w, p.x_first, stream);
+    if (p.wr == 64) return launch_pair_inst<XA, XB, 32, WA, WB, 64>(x, w, p.x_first, stream);
+    return launch_pair_inst<XA, XB, 32, WA, WB, 32>(x, w, p.x_first, stream);
+}
+
+Args args_of(const GemmDesc& d)
+{
     Args a;
     a.A = View{(const float*)d.A.base, d.A.ld, d.A.map_strided, d.A.map_contig, d.A.n_strided, d.A.n_contig};
     a.B = View{(const float*)d.B.base, d.B.ld, d.B.map_strided, d.B.map_contig, d.B.n_strided, d.B.n_contig};
@@ -695,9 +791,41 @@ int launch_gemm_f32(const GemmDesc& d, hipStream_t stream)
     a.out = (float*)d.out; a.ldo = d.ldo; a.epilogue = d.epilogue; a.keep = d.keep_idx; a.out_full = d.out_full;
     a.tiles_i = a.tiles_j = 0;
     a.prev = (const float*)d.prev; a.accumulate = d.accumulate ? 1 : 0;
+    return a;
+}
+
+bool too_short(const GemmDesc& d, const Operand& o) { return !o.map_contig && (o.c_contig ? d.C : o.n_contig) < 4; }
+
+}  // namespace
+
+int launch_gemm_f32_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
+{
+    if (dx.I < 1 || dx.J < 1 || dx.C < 1 || dw.I < 1 || dw.J < 1 || dw.C < 1) return -1;
+    for (const GemmDesc* d : {&dx, &dw})
+        if (too_short(*d, d->A) || too_short(*d, d->B)) return -1;
+    if (!dx.A.c_contig || dw.A.c_contig || dw.B.c_contig) return -1;
+    const Args x = args_of(dx), w = args_of(dw);
+    Plan p;
+    if (!plan_pair(x, w, p)) return -1;
+    const bool xa = dx.A.map_contig, xb = dx.B.map_contig, wa = dw.A.map_contig, wb = dw.B.map_contig;
+    if (dx.B.c_contig) {                    // weight stored [K x N]
+        if (xa && xb && !wa && wb) return launch_pair<GatherP, GatherP, PlainQ, GatherQ>(x, w, p, stream);
+        if (!xa && !xb && wa && !wb) return launch_pair<PlainP, PlainP, GatherQ, PlainQ>(x, w, p, stream);
+        if (!xa && !xb && !wa && !wb) return launch_pair<PlainP, PlainP, PlainQ, PlainQ>(x, w, p, stream);
+        return -1;
+    }
+    if (xa && !xb && wa && !wb) return launch_pair<GatherP, PlainQ, GatherQ, PlainQ>(x, w, p, stream);
+    if (!xa && xb && !wa && wb) return launch_pair<PlainP, GatherQ, PlainQ, GatherQ>(x, w, p, stream);
+    if (!xa && !xb && !wa && !wb) return launch_pair<PlainP, PlainQ, PlainQ, PlainQ>(x, w, p, stream);
+    return -1;
+}
+
+int launch_gemm_f32(const GemmDesc& d, hipStream_t stream)
+{
+    if (d.I < 1 || d.J < 1 || d.C < 1) return ZR_ERR_SHAPE;
+    const Args a = args_of(d);
     const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
-    auto too_short = [&](const Operand& o) { return !o.map_contig && (o.c_contig ? d.C : o.n_contig) < 4; };
-    if (too_short(d.A) || too_short(d.B)) {
+    if (too_short(d, d.A) || too_short(d, d.B)) {
         if (d.A.c_contig) return d.B.c_contig ? launch_short<AnyP, AnyP>(a, stream) : launch_short<AnyP, AnyQ>(a, stream);
         return d.B.c_contig ? ZR_ERR_MODE : launch_short<AnyQ, AnyQ>(a, stream);
     }

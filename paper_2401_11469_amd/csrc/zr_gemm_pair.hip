@@ -66,23 +66,6 @@ constexpr double kReduce = 8.2, kReduceTile = 0.013;       // and a second launc
 
 struct Plan { int sx, sw, slices; bool x_first; double us; };
 
-// When the last piece ends: n1 pieces of t1, then n2 of t2, each on the first of `slots` that is free.
-inline double two_groups(int n1, double t1, int n2, double t2, int slots)
-{
-    const int q = n1 / slots, r = n1 % slots;
-    const double lo = q * t1, hi = r ? lo + t1 : lo;       // when slots - r, and r, of them are through the first group
-    if (n2 == 0) return hi;
-    const double least = std::max(lo, (n1 * t1 + n2 * t2) / slots);        // (nobody idle)
-    auto room = [&](double T) { return (slots - r) * (int)((T - lo) / t2 + 1e-9) + (r && T > hi ? r * (int)((T - hi) / t2 + 1e-9) : 0); };
-    auto first = [&](double base) {
-        double T = base + t2 * std::max(1.0, std::floor((least - base) / t2));
-        while (room(T) < n2) T += t2;
-        return T;
-    };
-    const double T = r ? std::min(first(lo), first(hi)) : first(lo);
-    return std::max(T, hi);
-}
-
 inline int steps_of(int C) { return (C + BK - 1) / BK; }
 inline int64_t per_xcd(int64_t tiles) { return (tiles + 7) / 8; }
 inline void shape_of(int s, bool x, int& bm, int& bn)

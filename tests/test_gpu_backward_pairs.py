@@ -5,7 +5,7 @@ import pytest
 from parity_util import check_kept_torch
 
 pytestmark = pytest.mark.gpu
-DROP_N, DROP_K, W_KN, W_NK, ZERO, SAME = 0, 1, 0, 1, 0, 2
+DROP_N, DROP_K, W_KN, W_NK, ZERO, AVERAGE, SAME = 0, 1, 0, 1, 0, 1, 2
 
 
 @pytest.fixture(scope="module")
@@ -61,6 +61,38 @@ def test_pair(torch_zr, M, K, N, mode, n_keep, policy):
         rest = ((dWk[:, ~kept], 3.0),)
     for t, v in rest:
         assert torch.all(t == (v if policy == SAME else 0.0))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("policy", [ZERO, AVERAGE, SAME])
+@pytest.mark.parametrize("layout", [W_KN, W_NK])
+@pytest.mark.parametrize("mode", [DROP_N, DROP_K])
+@pytest.mark.parametrize("M,K,N,n_keep", [
+    (2, 9, 12, 5), (31, 33, 65, 32), (200, 77, 1201, 50), (985, 1001, 771, 578),         # few tiles; sums in groups
+    (2497, 1201, 803, 640), (300, 2305, 1999, 1500), (256, 512, 256, 0)])                 # 64 x 64 and 128 x 128; nothing pruned
+def test_pair_of_any_alignment(torch_zr, M, K, N, n_keep, mode, layout, policy, dtype):
+    """Without scratch, so that every list is applied in flight: the same bits as the two products on their own (fp32:
+    to its rounding, where the tiles and with them the order may differ)."""
+    torch, zr = torch_zr
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    X, W, dY = (t.to(dt) for t in tensors(torch, M, K, N, layout == W_NK, M + K + N))
+    n = N if mode == DROP_N else K
+    n_keep = n if n_keep == 0 else min(n_keep, n - 1)
+    keep = torch.randperm(n, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")[:n_keep].sort().values.to(torch.int32)
+    prev = dict(prev_dX=torch.full_like(X, 2.0), prev_dW=torch.full_like(W, 3.0)) if policy == SAME else {}
+    a = zr.resized_linear_bwd(X, W, dY, keep, mode, policy=policy, w_layout=layout, **prev)
+    name = zr.debug_last_kernel()
+    dX = zr.resized_linear_bwd(X, W, dY, keep, mode, policy=policy, w_layout=layout, need_dW=False, **prev)[0]
+    dW = zr.resized_linear_bwd(X, W, dY, keep, mode, policy=policy, w_layout=layout, need_dX=False, **prev)[1]
+    print(name, flush=True)
+    if M in (31, 200, 985):
+        assert "beside" in name, name
+    for what, x, y, C in (("dX", a[0], dX, N), ("dW", a[1], dW, M)):
+        if dtype == "bf16":
+            assert torch.equal(x, y), what
+        else:
+            # two sums of C terms in different orders: C ** 0.5 roundings of 2 ** -24 each, with a factor of 8
+            assert float((x - y).abs().max()) <= 8 * max(C, 16) ** 0.5 * 2.0 ** -24 * float(y.abs().max()), what
 
 
 @pytest.mark.parametrize("what", ["dW over W", "dX over X"])
