@@ -622,9 +622,34 @@ __device__ __forceinline__ void gemm_body(const Args& g, uint32_t* smem, const i
         return;
     }
 
-    constexpr int CPR = R / 8;
+    constexpr int CPR = R / 8, CHUNKS = (R * CPR + NT - 1) / NT;
+    if (g.accumulate && R * CPR % NT == 0 && rows_valid == R && cols_valid == R) {
+        // a whole tile: its old values are requested together
+        E* o[CHUNKS];
+        u4 old[CHUNKS];
 #pragma unroll
-    for (int it = 0; it < (R * CPR + NT - 1) / NT; ++it) {
+        for (int it = 0; it < CHUNKS; ++it) {
+            const int q = tid + NT * it;
+            o[it] = g.out + (size_t)(i0 + q / CPR) * (size_t)g.ldo + j0 + q % CPR * 8;
+            old[it] = *(const u4_any*)o[it];
+        }
+#pragma unroll
+        for (int it = 0; it < CHUNKS; ++it) {
+            const int q = tid + NT * it;
+            const float* c = Cs + q / CPR * CP + q % CPR * 8;
+            const f32x4 x0 = *(const f32x4*)c, x1 = *(const f32x4*)(c + 4);
+            u4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const f32x4 x = e < 2 ? x0 : x1;
+                w[e] = two(x[2 * (e & 1)] + __uint_as_float(old[it][e] << 16), x[2 * (e & 1) + 1] + __uint_as_float(old[it][e] & 0xffff0000u));
+            }
+            *(u4_any*)o[it] = w;
+        }
+        return;
+    }
+#pragma unroll
+    for (int it = 0; it < CHUNKS; ++it) {
         const int q = tid + NT * it;
         const int row = q / CPR, j = (q % CPR) * 8;
         if (row >= rows_valid || j >= cols_valid) continue;
