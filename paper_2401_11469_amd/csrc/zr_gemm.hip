@@ -836,10 +836,10 @@ double alone_us(const Args& a)
     return best + kAlone;
 }
 
-// false: two launches
-bool plan_pair(const Args& x, const Args& w, Plan& p)
+// false: two launches (limit: what those take on other kernels)
+bool plan_pair(const Args& x, const Args& w, double limit, Plan& p)
 {
-    double best = alone_us(x) + alone_us(w);
+    double best = limit;
     bool found = false;
     for (bool xwide : {false, true})
         for (bool wwide : {false, true}) {
@@ -900,7 +900,7 @@ Args args_of(const GemmDesc& d)
 
 bool too_short(const GemmDesc& d, const Operand& o) { return o.map_contig ? o.n_contig < 2 : (o.c_contig ? d.C : o.n_contig) < 8; }
 
-int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
+int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, double limit, hipStream_t stream)
 {
     if (forced_tiles() || dx.I < 1 || dx.J < 1 || dx.C < 1 || dw.I < 1 || dw.J < 1 || dw.C < 1) return -1;
     for (const GemmDesc* d : {&dx, &dw})
@@ -908,7 +908,12 @@ int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t str
     if (!dx.A.c_contig || dw.A.c_contig || dw.B.c_contig) return -1;
     Args x = args_of(dx), w = args_of(dw);
     Plan p;
-    if (!plan_pair(x, w, p)) return -1;
+    // a large dW with a gather in flight has its own kernel (4096 x 2752 x 4096 of 2064 kept rows 247 us in two launches, 262
+    // in one; 2048 x 4096 x 4096, stored [N x K], 206 / 268; up to 256 tiles: 4096 x 2048 x 2048 of 1024 kept columns 251 / 121)
+    const bool w_fast = gemm_fast_takes(dw);
+    if (w_fast && tiles_of(w, 128) > 256) return -1;
+    if (!w_fast) limit = std::min(limit, alone_us(x) + alone_us(w));
+    if (!plan_pair(x, w, limit, p)) return -1;
     x.alternate = p.xr == 64 && adds_in_groups(x.I, x.J, x.C);
     w.alternate = p.wr == 64 && adds_in_groups(w.I, w.J, w.C);
     const bool xa = dx.A.map_contig, xb = dx.B.map_contig, wa = dw.A.map_contig, wb = dw.B.map_contig;
@@ -992,8 +997,9 @@ int launch_gemm(const GemmDesc& desc, hipStream_t stream)
         if (!g_debug.armed_once) {
             if (d.dtype == ZR_F32) st = launch_gemm_f32_pair(*d.with, d, stream);
             else if (d.dtype == ZR_BF16) {
-                st = launch_gemm_pair(*d.with, d, stream);
-                if (st < 0) st = launch_gemm_any_pair(*d.with, d, stream);
+                double alone = 1e30;
+                st = launch_gemm_pair(*d.with, d, stream, alone);
+                if (st < 0) st = launch_gemm_any_pair(*d.with, d, alone, stream);
             }
         }
         if (st >= 0) return st;

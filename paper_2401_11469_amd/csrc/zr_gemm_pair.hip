@@ -191,7 +191,7 @@ int launch_pair_x(const FArgs& x, const FArgs& w, const Plan& p, hipStream_t str
 
 }  // namespace
 
-int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
+int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream, double& alone)
 {
     if (forced_tiles() || !ring_enabled()) return -1;
     if (!gemm_fast_can(dx) || !gemm_fast_can(dw)) return -1;
@@ -201,7 +201,7 @@ int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
     const bool rows = dx.B.c_contig, mapped = !rows && dx.B.map_strided;
     const FArgs x = fargs_of(dx), w = fargs_of(dw);
     const Plan p = plan_pair(x, w, rows, !mapped || dx.C <= ring_list_max<256, 256>());
-    if (p.slices == 0) return -1;
+    if (p.slices == 0) { alone = p.us; return -1; }
     if (p.sx == B64) return launch_pair_small<DmaP, 64, 1, 4>(x, w, p, stream);
     if (p.sx == B128) {
         if (rows) return launch_pair_small<DmaP, 128, 2, 2>(x, w, p, stream);
