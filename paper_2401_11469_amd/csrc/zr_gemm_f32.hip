@@ -703,25 +703,26 @@ int launch_short(const Args& a, hipStream_t stream)
 // ---------------------------------------------------------------------------
 // dX and dW in one launch
 // ---------------------------------------------------------------------------
-// Tiles by a model of the schedule (every XCD takes its tiles in order, each as soon as one of 64 halves of a unit
-// is free; a tile takes a start and an end, and a time per stage, longer where kept columns are gathered).  Fitted to
-// 33 backward calls (32 to 2500 tokens, 64 to 2048 wide), each in nine forms: what it picks is 1.6 % slower than the best
+// Tiles by a model of the schedule: every XCD takes its tiles in order, each on the first of 32 units that is
+// through with its own (two tiles share a unit and its matrix pipes, which takes as long as one after the
+// other); a tile takes a time per stage, longer where kept columns are gathered, and a launch a start and an end. Fitted to
+// 106 backward calls (32 to 4000 tokens, 64 to 2048 wide), each in nine forms: what it picks is 2.1 % slower than the best
 // of them on average.  us in two launches and now: 1576 x 2048 x 1024 of 1638 kept rows 151 -> 117, 609 x 1414 x 247
 // 31 -> 20, 256 x 512 x 256 14.7 -> 11.6.  A product that takes 32 x 32 tiles on its own keeps them: their four partial
 // sums are the more exact.
 struct Plan { int xr, wr; bool x_first; };
 struct Cost { double start, stage; };
-constexpr Cost kCost32 = {5.4, 1.17}, kCost64 = {9.0, 1.52}, kCost128 = {8.3, 2.2};       // us, us per stage of 128, 64 and 32
-constexpr double kGathered = 0.51, kHalfFree = 0.72, kAlone = 1.2;        // per gathered operand; a unit to itself; a launch more
+constexpr Cost kCost32 = {1.5, 0.64}, kCost64 = {1.4, 1.21}, kCost128 = {1.4, 2.19};      // us, us per stage of 128, 64 and 32
+constexpr double kGathered = 0.17, kLaunch = 8.8;                         // per gathered operand; us
 
 int64_t tiles_of(const Args& a, int r) { return (int64_t)((a.I + r - 1) / r) * ((a.J + r - 1) / r); }
 bool may_take(const Args& a, int r) { return r == 32 || tiles_of(a, 64) >= 192; }
 
-double tile_us(const Args& a, int r, double f)
+double tile_us(const Args& a, int r)
 {
     const Cost c = r == 32 ? kCost32 : r == 64 ? kCost64 : kCost128;
     const int bk = 16 * NT / r;
-    return c.start + f * c.stage * ((a.C + bk - 1) / bk) * (1 + kGathered * ((a.A.map_c != nullptr) + (a.B.map_c != nullptr)));
+    return c.start + c.stage * ((a.C + bk - 1) / bk) * (1 + kGathered * ((a.A.map_c != nullptr) + (a.B.map_c != nullptr)));
 }
 
 double alone_us(const Args& a)
@@ -730,24 +731,24 @@ double alone_us(const Args& a)
     for (int r : {32, 64, 128}) {
         if (!may_take(a, r)) continue;
         const int64_t n = (tiles_of(a, r) + 7) / 8;
-        best = std::min(best, (double)((n + 63) / 64) * tile_us(a, r, n <= 32 ? kHalfFree : 1.0));
+        best = std::min(best, (double)((n + 31) / 32) * tile_us(a, r));
     }
-    return best + kAlone;
+    return best + kLaunch;
 }
 
 // false: two launches
 bool plan_pair(const Args& x, const Args& w, Plan& p)
 {
-    double best = alone_us(x) + alone_us(w);
+    double best = 0.95 * (alone_us(x) + alone_us(w));       // (2048 x 2048 x 2048 of 1536 kept rows: 0.97, and 263 us alone, 279 paired)
     bool found = false;
     for (int xr : {32, 64, 128})
         for (int wr : {32, 64, 128}) {
             if ((xr == 128) != (wr == 128) || !may_take(x, xr) || !may_take(w, wr)) continue;
             const int64_t nx = (tiles_of(x, xr) + 7) / 8, nw = (tiles_of(w, wr) + 7) / 8;
             if (nx + nw > 1 << 20) continue;
-            const double f = nx + nw <= 32 ? kHalfFree : 1.0, tx = tile_us(x, xr, f), tw = tile_us(w, wr, f);
+            const double tx = tile_us(x, xr), tw = tile_us(w, wr);
             const bool x_first = tx > tw;                   // the long tiles first
-            const double us = x_first ? two_groups((int)nx, tx, (int)nw, tw, 64) : two_groups((int)nw, tw, (int)nx, tx, 64);
+            const double us = kLaunch + (x_first ? two_groups((int)nx, tx, (int)nw, tw, 32) : two_groups((int)nw, tw, (int)nx, tx, 32));
             if (us < best) { best = us; p = Plan{xr, wr, x_first}; found = true; }
         }
     return found;
