@@ -8,20 +8,16 @@
 // those equal to T, writing kept and pruned indices by prefix position, which
 // makes both lists ascending by construction.
 //
-// One workgroup per score vector: 1024 threads (16 wavefronts of 64) for a single
-// vector, where latency is what counts, 256 threads when many vectors are
-// selected in one launch, so that 8 of them share a compute unit and the chip's
-// memory system stays busy.  Vectors of up to 12288 scores are turned into order
-// keys once and kept in LDS (sized to the vector), so the five passes read HBM a
-// single time; longer ones re-read from memory.
+// One workgroup per score vector.  Vectors of up to 32768 scores are turned into order keys once and kept in
+// registers (select_regs), with as many threads as its length and the number of vectors ask for; longer ones
+// re-read from memory, or go to many workgroups where the caller has scratch.
 #include "zr_common.h"
 
 namespace zr {
 
 namespace {
 
-constexpr int SEL_THREADS = 1024;      // single vector
-constexpr int SEL_THREADS_MANY = 256;  // many vectors per launch
+constexpr int SEL_THREADS = 1024;      // a vector that no registers hold
 
 // Monotone map fp32 -> uint32: larger score <=> larger key.  NaN -> 0 (lowest,
 // below -inf); -0.0 and +0.0 share one key.
@@ -33,16 +29,151 @@ __device__ __forceinline__ uint32_t order_key(float s)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-constexpr int SEL_LDS_KEYS = 12288;    // 48 KB of order keys
+constexpr int SEL_REG_KEYS = 32768;    // order keys in the registers of 1024 threads (twice as many spill)
 
-// One workgroup selects one score vector s[n]: keep[n_keep] and drop[n - n_keep].
-template <bool STAGED, int NT>
+// One workgroup of NT threads selects one score vector of up to NT * K scores, whose order keys it holds in
+// registers.  What bounds it: barriers, and LDS counters that many lanes hit at once (the scores of one
+// layer share their leading bits).  So
+//   * the digits start at the highest bit in which any two keys differ, found with one reduction: they spread
+//     over the 256 bins from the first one on, and the bits that all keys share take no pass;
+//   * every pass has counters of its own, cleared at the start, and every wavefront picks the digit for
+//     itself: one barrier a pass;
+//   * the ordered pass counts all of its chunks before one barrier instead of two barriers a chunk.
+// us a launch, before and now (norms of a layer's columns; 256-thread workgroups, keys in LDS before): 256 scores 5.2 and
+// 4.5, four vectors of up to 1024 6.7 and 5.0, five of up to 3072 11.6 and 6.4, 12000 and 8000 33.7 and 12.6;
+// 4096 vectors of 4096 112 and 46, of 700 26 and 15, 1000 of 9000 82 and 36.
+template <int K, int NT>
+__device__ __forceinline__ void select_regs(const float* __restrict__ s, int n, int n_keep,
+                                            int32_t* __restrict__ keep, int32_t* __restrict__ drop)
+{
+    constexpr int WAVES = NT / 64, CH = 64 / WAVES;     // CH: chunks whose counts one wavefront adds up at a time
+    static_assert(1024 % NT == 0 && NT >= 64, "the counters are cleared 1024 / NT words a thread");
+    __shared__ __align__(16) uint32_t hist[4][256];
+    __shared__ uint32_t wave_lo[WAVES], wave_hi[WAVES];
+    __shared__ uint32_t counts[2][K * WAVES];           // greater, equal: chunk by chunk, wavefront by wavefront
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+
+    uint32_t key[K];
+#pragma unroll
+    for (int q = 0; q < 1024 / NT; ++q) ((uint32_t*)hist)[tid + NT * q] = 0;
+    uint32_t lo = 0xffffffffu, hi = 0;
+#pragma unroll
+    for (int k0 = 0; k0 < K; k0 += 16) {
+        float v[16];
+#pragma unroll
+        for (int k = k0; k < k0 + 16 && k < K; ++k) v[k - k0] = s[min(tid + NT * k, n - 1)];
+#pragma unroll
+        for (int k = k0; k < k0 + 16 && k < K; ++k) {
+            key[k] = order_key(v[k - k0]);               // (past the end: the last key again)
+            lo = min(lo, key[k]);
+            hi = max(hi, key[k]);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+    }
+    if (lane == 0) { wave_lo[wave] = lo; wave_hi[wave] = hi; }
+    __syncthreads();
+    lo = wave_lo[lane & (WAVES - 1)];
+    hi = wave_hi[lane & (WAVES - 1)];
+#pragma unroll
+    for (int off = WAVES / 2; off > 0; off >>= 1) {
+        lo = min(lo, (uint32_t)__shfl_xor((int)lo, off, 64));
+        hi = max(hi, (uint32_t)__shfl_xor((int)hi, off, 64));
+    }
+    // ---- radix select of the n_keep-th largest key over the bits below `top` ----
+    const int top = 32 - __clz((int)(lo ^ hi));          // 0: all keys are equal
+    uint32_t prefix = top >= 32 ? 0u : hi >> top << top, mask = top >= 32 ? 0u : ~0u << top;
+    uint32_t remaining = (uint32_t)n_keep;
+    int shift = top;
+    for (int pass = 0; shift > 0; ++pass) {              // (at most four)
+        shift = max(shift - 8, 0);
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (tid + NT * k < n && (key[k] & mask) == prefix) atomicAdd(&hist[pass][(key[k] >> shift) & 255u & ~(mask >> shift)], 1u);
+        __syncthreads();
+        // lane l owns bins 4l .. 4l + 3; suffix sums give, for each bin, the number of candidates in
+        // strictly higher bins
+        const uint4 h4 = *(const uint4*)&hist[pass][4 * lane];
+        const uint32_t h[4] = {h4.x, h4.y, h4.z, h4.w};
+        const uint32_t mine = h[0] + h[1] + h[2] + h[3];
+        uint32_t incl = mine;                            // inclusive suffix sum over lanes
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t x = __shfl_down(incl, off, 64);
+            if (lane + off < 64) incl += x;
+        }
+        uint32_t above = incl - mine, digit = 0xffffffffu, rem = 0;
+#pragma unroll
+        for (int q = 3; q >= 0; --q) {
+            if (above < remaining && remaining <= above + h[q]) { digit = (uint32_t)(4 * lane + q); rem = remaining - above; }
+            above += h[q];
+        }
+        const uint64_t who = __ballot(digit != 0xffffffffu);       // exactly one lane
+        const int src = who ? (int)(__ffsll((long long)who) - 1) : 0;
+        prefix |= (uint32_t)__shfl((int)digit, src, 64) << shift;
+        remaining = (uint32_t)__shfl((int)rem, src, 64);
+        mask = ~0u << shift;
+    }
+    const uint32_t T = prefix;          // the n_keep-th largest key
+    const uint32_t need_eq = remaining; // how many of the keys == T are kept (>= 1)
+
+    // ---- ordered compaction -----------------------------------------------
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const bool in = tid + NT * k < n;
+        const uint32_t gt = (uint32_t)__popcll(__ballot(in && key[k] > T)), eq = (uint32_t)__popcll(__ballot(in && key[k] == T));
+        if (lane == 0) { counts[0][k * WAVES + wave] = gt; counts[1][k * WAVES + wave] = eq; }
+    }
+    __syncthreads();
+    // what lies before this wavefront's part of each chunk: 64 entries to a step, prefix sums over the lanes
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t run_gt = 0, run_eq = 0;
+#pragma unroll
+    for (int k0 = 0; k0 < K; k0 += CH) {
+        const bool in = k0 * WAVES + lane < K * WAVES;
+        const uint32_t g = in ? counts[0][k0 * WAVES + lane] : 0u, e = in ? counts[1][k0 * WAVES + lane] : 0u;
+        uint32_t sg = g, se = e;                         // inclusive
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t a = __shfl_up(sg, off, 64), b = __shfl_up(se, off, 64);
+            if (lane >= off) { sg += a; se += b; }
+        }
+#pragma unroll
+        for (int k = k0; k < k0 + CH && k < K; ++k) {
+            const int at = (k - k0) * WAVES + wave;
+            const int i = tid + NT * k;
+            const uint64_t bgt = __ballot(i < n && key[k] > T), beq = __ballot(i < n && key[k] == T);
+            const uint32_t pg = run_gt + (uint32_t)__shfl((int)(sg - g), at, 64) + (uint32_t)__popcll(bgt & below);
+            const uint32_t pe = run_eq + (uint32_t)__shfl((int)(se - e), at, 64) + (uint32_t)__popcll(beq & below);
+            if (i < n) {
+                const bool kept = key[k] > T || (key[k] == T && pe < need_eq);
+                // kept indices before i: all greater ones plus the first need_eq equal ones
+                const uint32_t kept_before = pg + (pe < need_eq ? pe : need_eq);
+                // positions are in range by construction; the comparisons only make an
+                // out-of-range store impossible whatever the scores hold
+                if (kept) {
+                    if (kept_before < (uint32_t)n_keep) keep[kept_before] = i;
+                } else if (drop) {
+                    const uint32_t pos = (uint32_t)i - kept_before;
+                    if (pos < (uint32_t)(n - n_keep)) drop[pos] = i;
+                }
+            }
+        }
+        run_gt += (uint32_t)__shfl((int)sg, 63, 64);
+        run_eq += (uint32_t)__shfl((int)se, 63, 64);
+    }
+}
+
+// The same for a vector of any length, read from memory in every pass.
+template <int NT>
 __device__ __forceinline__ void select_body(const float* __restrict__ s, int n, int n_keep,
                                             int32_t* __restrict__ keep, int32_t* __restrict__ drop)
 {
     constexpr int SEL_WAVES = NT / 64;
     static_assert(NT >= 256 && NT % 64 == 0, "the histogram is cleared by the first 256 threads");
-    extern __shared__ uint32_t keys[];            // n order keys when STAGED (dynamic size)
     __shared__ uint32_t hist[256];
     __shared__ uint32_t s_digit, s_remaining;
     __shared__ uint32_t wave_gt[SEL_WAVES], wave_eq[SEL_WAVES];
@@ -51,11 +182,7 @@ __device__ __forceinline__ void select_body(const float* __restrict__ s, int n, 
     const int lane = tid & 63;
     const int wave = tid >> 6;
 
-    if (STAGED) {
-        for (int i = tid; i < n; i += NT) keys[i] = order_key(s[i]);
-        __syncthreads();
-    }
-    auto key_at = [&](int i) -> uint32_t { return STAGED ? keys[i] : order_key(s[i]); };
+    auto key_at = [&](int i) -> uint32_t { return order_key(s[i]); };
 
     // ---- radix select of the n_keep-th largest key -------------------------
     uint32_t prefix = 0, mask = 0, remaining = (uint32_t)n_keep;
@@ -147,24 +274,34 @@ __device__ __forceinline__ void select_body(const float* __restrict__ s, int n, 
     }
 }
 
-template <bool STAGED, int NT>
+template <int NT>
 __global__ __launch_bounds__(NT) void select_kernel(
     const float* __restrict__ scores, int n, int n_keep,
     int32_t* __restrict__ keep_idx, int32_t* __restrict__ drop_idx, int64_t ld_idx)
 {
-    select_body<STAGED, NT>(scores + (size_t)blockIdx.x * (size_t)n, n, n_keep,
+    select_body<NT>(scores + (size_t)blockIdx.x * (size_t)n, n, n_keep,
                         keep_idx + (size_t)blockIdx.x * (size_t)ld_idx,
                         drop_idx ? drop_idx + (size_t)blockIdx.x * (size_t)ld_idx : nullptr);
 }
 
+template <int K, int NT>
+__global__ __launch_bounds__(NT) void select_regs_kernel(
+    const float* __restrict__ scores, int n, int n_keep,
+    int32_t* __restrict__ keep_idx, int32_t* __restrict__ drop_idx, int64_t ld_idx)
+{
+    select_regs<K, NT>(scores + (size_t)blockIdx.x * (size_t)n, n, n_keep, keep_idx + (size_t)blockIdx.x * (size_t)ld_idx,
+                   drop_idx ? drop_idx + (size_t)blockIdx.x * (size_t)ld_idx : nullptr);
+}
+
 // Several vectors of different lengths in one launch (the projections of a layer
 // shard): workgroup b takes descriptor b.  The descriptors travel as a kernel
-// argument, no device memory is involved.
-template <bool STAGED>
-__global__ __launch_bounds__(SEL_THREADS) void select_multi_kernel(const SelectMulti m)
+// argument, no device memory is involved.  K: chunks of NT scores of the longest; 0: longer than registers hold.
+template <int K, int NT>
+__global__ __launch_bounds__(NT) void select_multi_kernel(const SelectMulti m)
 {
     const int b = blockIdx.x;
-    select_body<STAGED, SEL_THREADS>(m.scores[b], m.n[b], m.n_keep[b], m.keep[b], m.drop[b]);
+    if constexpr (K == 0) select_body<NT>(m.scores[b], m.n[b], m.n_keep[b], m.keep[b], m.drop[b]);
+    else select_regs<K, NT>(m.scores[b], m.n[b], m.n_keep[b], m.keep[b], m.drop[b]);
 }
 
 // ---------------------------------------------------------------------------
@@ -422,16 +559,16 @@ __global__ void validate_kernel(const int32_t* __restrict__ keep_idx, int n_keep
 int launch_select(const float* scores, int n, int batch, int n_keep,
                   int32_t* keep_idx, int32_t* drop_idx, int64_t ld_idx, hipStream_t stream)
 {
-    const size_t key_bytes = (size_t)n * sizeof(uint32_t);
-    if (n > SEL_LDS_KEYS)
-        hipLaunchKernelGGL((select_kernel<false, SEL_THREADS>), dim3(batch), dim3(SEL_THREADS), 0, stream,
+    if (n > SEL_REG_KEYS)
+        hipLaunchKernelGGL((select_kernel<SEL_THREADS>), dim3(batch), dim3(SEL_THREADS), 0, stream,
                            scores, n, n_keep, keep_idx, drop_idx, ld_idx);
-    else if (batch >= 512)      // two workgroups per compute unit and more: throughput over latency
-        hipLaunchKernelGGL((select_kernel<true, SEL_THREADS_MANY>), dim3(batch), dim3(SEL_THREADS_MANY), key_bytes,
-                           stream, scores, n, n_keep, keep_idx, drop_idx, ld_idx);
-    else
-        hipLaunchKernelGGL((select_kernel<true, SEL_THREADS>), dim3(batch), dim3(SEL_THREADS), key_bytes, stream,
-                           scores, n, n_keep, keep_idx, drop_idx, ld_idx);
+    else {
+#define ZR_SELECT(K, NT) hipLaunchKernelGGL((select_regs_kernel<K, NT>), dim3(batch), dim3(NT), 0, stream, scores, n, n_keep, keep_idx, drop_idx, ld_idx)
+        // few wavefronts for short vectors: each of them repeats the pick of a digit
+        if (batch >= 512) { if (n <= 1024) ZR_SELECT(16, 64); else if (n <= 4096) ZR_SELECT(16, 256); else if (n <= 12288) ZR_SELECT(24, 512); else ZR_SELECT(32, 1024); }
+        else if (n <= 1024) ZR_SELECT(4, 256); else if (n <= 4096) ZR_SELECT(8, 512); else if (n <= 12288) ZR_SELECT(12, 1024); else ZR_SELECT(32, 1024);
+#undef ZR_SELECT
+    }
     return hip_status(hipGetLastError());
 }
 
@@ -466,12 +603,10 @@ int launch_select_multi(const SelectMulti& m, int count, hipStream_t stream)
 {
     int longest = 0;
     for (int b = 0; b < count; ++b) longest = std::max(longest, m.n[b]);
-    const bool staged = longest <= SEL_LDS_KEYS;
-    if (staged)
-        hipLaunchKernelGGL(select_multi_kernel<true>, dim3(count), dim3(SEL_THREADS),
-                           (size_t)longest * sizeof(uint32_t), stream, m);
-    else
-        hipLaunchKernelGGL(select_multi_kernel<false>, dim3(count), dim3(SEL_THREADS), 0, stream, m);
+#define ZR_SELECT(K, NT) hipLaunchKernelGGL((select_multi_kernel<K, NT>), dim3(count), dim3(NT), 0, stream, m)
+    if (longest <= 1024) ZR_SELECT(4, 256); else if (longest <= 4096) ZR_SELECT(8, 512); else if (longest <= 12288) ZR_SELECT(12, 1024); else if (longest <= SEL_REG_KEYS) ZR_SELECT(32, 1024);
+    else ZR_SELECT(0, 1024);
+#undef ZR_SELECT
     return hip_status(hipGetLastError());
 }
 
