@@ -367,8 +367,9 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
                dw_clear(W, wr, wc, ldw) && dw_clear(dY, M, N, lddy) && dw_clear(same ? prev_dX : nullptr, M, K, lddx);
     };
 
-    // both at once, the stand-alone passes of Average imputation behind them; with sums from the epilogues one at a time
-    const bool pair = dX && dW && !(post && sums) && apart();
+    // both at once, the stand-alone passes of Average imputation behind them; one at a time, the epilogues leave its sums
+    // where there is room for them
+    const bool pair = dX && dW && apart();
 
     // one extraction serves both products: X[:,S] (DROP_K, used by dW) or dY[:,S] (DROP_N)
     Extract ex{false, 0};
@@ -410,8 +411,8 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
             }
             d.J = K; d.C = n_keep; d.epilogue = EPI_PLAIN; d.out_full = K;
         }
-        if (post && mode == ZR_DROP_K && !pair) st = gemm_with_average(d, sums, dX, lddx, M, K, 1, keep_idx, n_keep, dtype, s);
-        else if (dW && pair) dx = d;
+        if (pair) dx = d;
+        else if (post && mode == ZR_DROP_K) st = gemm_with_average(d, sums, dX, lddx, M, K, 1, keep_idx, n_keep, dtype, s);
         else st = launch_gemm(d, s);
         if (st != ZR_OK) return st;
     }
@@ -435,16 +436,23 @@ int zr_resized_linear_bwd(const void* X, int64_t ldx, const void* W, int64_t ldw
         else    { d.A = dys; d.B = xs; d.I = in; d.J = ik; }
         d.epilogue = full ? EPI_PLAIN : (rows_pruned ? EPI_ROW_SCATTER : EPI_COL_SCATTER);
         d.out_full = mode == ZR_DROP_K ? K : N;
-        if (post && !pair) st = gemm_with_average(d, sums, dW, lddw, kn ? K : N, kn ? N : K, rows_pruned ? 0 : 1, keep_idx,
-                                                  n_keep, dtype, s);
-        else {
-            d.with = dx.out ? &dx : nullptr;
+        const int wr = kn ? K : N, wc = kn ? N : K, axis = rows_pruned ? 0 : 1;
+        bool together = false;
+        if (pair) {
+            d.with = &dx;
+            d.only_together = post && sums;
             st = launch_gemm(d, s);
+            together = st >= 0;
+            d.with = nullptr;
+        }
+        if (together) {
             if (st == ZR_OK && post && mode == ZR_DROP_K)
                 st = launch_impute(dX, lddx, M, K, 1, keep_idx, n_keep, ZR_IMPUTE_AVERAGE, nullptr, dtype, s);
-            if (st == ZR_OK && post)
-                st = launch_impute(dW, lddw, kn ? K : N, kn ? N : K, rows_pruned ? 0 : 1, keep_idx, n_keep, ZR_IMPUTE_AVERAGE,
-                                   nullptr, dtype, s);
+            if (st == ZR_OK && post) st = launch_impute(dW, lddw, wr, wc, axis, keep_idx, n_keep, ZR_IMPUTE_AVERAGE, nullptr, dtype, s);
+        } else {
+            if (pair) st = mode == ZR_DROP_K ? gemm_with_average(dx, sums, dX, lddx, M, K, 1, keep_idx, n_keep, dtype, s) : launch_gemm(dx, s);
+            if (st != ZR_OK) return st;
+            st = post ? gemm_with_average(d, sums, dW, lddw, wr, wc, axis, keep_idx, n_keep, dtype, s) : launch_gemm(d, s);
         }
         if (st != ZR_OK) return st;
     }

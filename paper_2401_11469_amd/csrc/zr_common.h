@@ -121,6 +121,8 @@ struct GemmDesc {
     // dW: the same call's dX, where neither writes what the other reads.  launch_gemm computes both, in one
     // launch or one after the other.
     const GemmDesc* with = nullptr;
+    // with `with`: nothing is computed, and launch_gemm returns -1, if one launch is not expected to be the shorter way
+    bool only_together = false;
 };
 
 // State of the aids in zr_debug.h, per host thread.  Product calls only test `armed`.

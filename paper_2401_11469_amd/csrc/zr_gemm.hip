@@ -1002,7 +1002,7 @@ int launch_gemm(const GemmDesc& desc, hipStream_t stream)
                 if (st < 0) st = launch_gemm_any_pair(*d.with, d, alone, stream);
             }
         }
-        if (st >= 0) return st;
+        if (st >= 0 || d.only_together) return st;
         st = launch_gemm(*d.with, stream);
         if (st != ZR_OK) return st;
         d.with = nullptr;
