@@ -1306,12 +1306,16 @@ __device__ __forceinline__ void fast_body(const FArgs& g, uint32_t* smem, const 
                 }
                 __syncthreads();
                 if (g.avg_partial) {
-                    // sum of the row's stored (rounded) results; the imputed zeros add nothing
+                    // sum of the row's stored (rounded) results, four or eight lanes to a row (one lane: 44 us
+                    // for 880 x 1200 of 2400 columns on 64 x 128 tiles, now 25); the imputed zeros add nothing
+                    constexpr int LR = NT / HR >= 8 ? 8 : 4;
                     float* dst = g.avg_partial + (size_t)(g.avg_slot_base + tj) * (size_t)g.avg_len + i0 + hr0;
-                    for (int r = tid; r < hrows; r += NT) {
+                    for (int r = tid / LR; r < hrows; r += NT / LR) {
                         float sum = 0.f;
-                        for (int c = start - a0; c < end - a0; ++c) sum += bf16_bits_to_f32(Co[r * pitch + c]);
-                        dst[r] = sum;
+                        for (int c = start - a0 + tid % LR; c < end - a0; c += LR) sum += bf16_bits_to_f32(Co[r * pitch + c]);
+#pragma unroll
+                        for (int off = 1; off < LR; off <<= 1) sum += __shfl_xor(sum, off, 64);
+                        if (tid % LR == 0) dst[r] = sum;
                     }
                 }
                 for (int u = tid; u < hrows * nchunks; u += NT) {

@@ -221,10 +221,12 @@ bool gemm_fast_takes(const GemmDesc& d)
 // Whether the product leaves the sums of Average imputation in avg_partial.  One that is split as a whole
 // has a result that the stand-alone pass reads from the caches, in one launch instead of three; many kept rows are a
 // long chain there (us with the sums / with that pass: dW 768 x 4096 of 576 kept rows 74 / 71, 1024 x 2048 of 1536
-// kept columns 86 / 82, 4096 x 768 of 3072 kept rows 93 / 103).
+// kept columns 86 / 82, 4096 x 768 of 3072 kept rows 93 / 103).  The sums need three launches (clear, finish, fill: 13 us)
+// where the pass over the columns of a small result is one of 6 to 12 (880 x 2568 26 / 21, 1500 x 2568 27 / 24; 8192 x 3072 240 / 263).
 bool gemm_leaves_sums(const GemmDesc& d)
 {
     if (d.epilogue == EPI_PLAIN || !gemm_fast_takes(d)) return false;
+    if (d.epilogue == EPI_COL_SCATTER && (int64_t)d.I * d.out_full < 8 << 20) return false;
     const bool split = slices_for(d.C, tiles_of(d.I, d.J, 128, 128), d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2;
     return !split || (d.epilogue == EPI_ROW_SCATTER && d.I > 1536);
 }
