@@ -226,7 +226,7 @@ bool gemm_fast_takes(const GemmDesc& d)
 bool gemm_leaves_sums(const GemmDesc& d)
 {
     if (d.epilogue == EPI_PLAIN || !gemm_fast_takes(d)) return false;
-    if (d.epilogue == EPI_COL_SCATTER && (int64_t)d.I * d.out_full < 8 << 20) return false;
+    if (d.epilogue == EPI_COL_SCATTER && (int64_t)d.I * d.out_full < 8 << 20 && !forced_tiles()) return false;
     const bool split = slices_for(d.C, tiles_of(d.I, d.J, 128, 128), d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2;
     return !split || (d.epilogue == EPI_ROW_SCATTER && d.I > 1536);
 }
