@@ -372,8 +372,8 @@ __device__ __forceinline__ bf16x8 fragment(const uint32_t* lds, int r0, int k0, 
 
 __device__ __forceinline__ uint32_t two(float a, float b) { return f32_to_bf16_bits(a) | (f32_to_bf16_bits(b) << 16); }
 
-// One workgroup's tile `lin` of a product.
-template <template <int, int, bool> class LA_, bool AP, template <int, int, bool> class LB_, bool BP, int R, int NT>
+// One workgroup's tile `lin` of a product (PAIRED: of one that may be asked to alternate between two sums).
+template <template <int, int, bool> class LA_, bool AP, template <int, int, bool> class LB_, bool BP, int R, int NT, bool PAIRED = false>
 __device__ __forceinline__ void gemm_body(const Args& g, uint32_t* smem, const int lin)
 {
     typedef LA_<R, NT, AP> LA;
@@ -405,7 +405,7 @@ __device__ __forceinline__ void gemm_body(const Args& g, uint32_t* smem, const i
 
     // (tiles of 512 threads add up the two halves of each stage, 128 deep, on their own; ALT: the same order on 256 threads,
     // whose stages are those halves)
-    constexpr bool ALT = R == 64 && NT == 256;
+    constexpr bool ALT = PAIRED && R == 64 && NT == 256;
     f32x4 acc[T][T], other[ALT ? T : 1][ALT ? T : 1];
 #pragma unroll
     for (int a = 0; a < T; ++a)
@@ -726,7 +726,7 @@ __global__ __launch_bounds__(NT, 512 / NT) void gemm_kernel(const Args g)
 template <template <int, int, bool> class LA, bool AP, template <int, int, bool> class LB, bool BP> struct Loaders {
     template <int R> static __device__ __forceinline__ void run(const Args& g, uint32_t* smem, int lin)
     {
-        gemm_body<LA, AP, LB, BP, R, 256>(g, smem, lin);
+        gemm_body<LA, AP, LB, BP, R, 256, true>(g, smem, lin);
     }
 };
 
