@@ -162,13 +162,15 @@ int zr_resize_select_multi(int32_t count, const float* const* scores, const int3
  * epilogues of the kernels for aligned bf16 tensors leave sums of the stored
  * results there, from which the means of the dropped slices are taken; without
  * it, and for other products (fp32, unaligned tensors, few tiles, most that are
- * split as a whole), a second pass re-reads the kept slices (means equal up to
- * fp32 summation order).
+ * split as a whole, small results, dX and dW computed in one launch), a second
+ * pass re-reads the kept slices (means equal up to fp32 summation order).
  * Split contraction: an aligned bf16 product (or remainder panel of one) of at
  * most 256 tiles of 128 x 128, with a contraction long enough that every slice has
  * 512 of it and a tile's chain gets shorter by at least 576, is computed in 2..8 slices of the
  * contraction in a first launch (fp32 partial results in the buffer) and summed,
- * slice after slice, and stored by a second one.  Such a result differs from the
+ * slice after slice, and stored by a second one.  A backward call for both dX and
+ * dW runs them in one launch where that is expected to be shorter; dW may then be
+ * split in 2..8 slices of any depth.  Such a result differs from the
  * one-launch result by fp32 summation order (the element-wise bound of the output
  * type still holds); it is repeatable bit by bit for a given buffer size.  Results
  * of products that are not split are the same to the last bit with and without
