@@ -413,10 +413,12 @@ struct LdQG {
 // avoided by permuting WHICH chunk a lane fetches (XOR swizzles), never by
 // padding.  No staging registers, no ds_write, and the L1 -> LDS path sustains
 // ~56 B/clk/CU where loads into registers give ~32.
-// Chunks past the contraction's end are read from a chunk of zeros, so a
-// contraction needs no whole stages: a lane's address is its chunk's or that of
-// the zeros.  (Any extent along the strided axis; along the contiguous one rows
-// are a multiple of 8 long, or zero-padded to 64 by the extraction.)
+// A contraction needs no whole stages: what a lane fetches past its end becomes zeros.  (Any
+// extent along the strided axis; along the contiguous one rows are a multiple of 8 long, or
+// zero-padded to 64 by the extraction.)  The 64-deep loops read the last chunk again and write
+// zeros over it once it has landed, in the last stage only; the ring reads the chunk from a chunk of
+// zeros, in its last stages only.  (Selecting the address in every stage cost up to 20 %: 128 x 128
+// tiles, 9088 x 640 x 4864 65 us then 77; dW 64 x 192 of 15488 tokens 22.8 then 25.6.)
 // ---------------------------------------------------------------------------
 __device__ const uint4 zero_chunk = {0u, 0u, 0u, 0u};
 
@@ -497,9 +499,16 @@ struct DmaP {
     __device__ __forceinline__ void issue(const FOp& op, uint32_t* stage, int c0, int C, int tid)
     {
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int c = c0 + chunk_;                               // the readable row length is a multiple of 8
+        const int c = min(c0 + chunk_, op.n_c - 8);              // the readable row length is a multiple of 8
 #pragma unroll
-        for (int q = 0; q < N; ++q) dma16(or_zeros(c < op.n_c, ptr[q] + c), stage + (wave + NW * q) * 256);
+        for (int q = 0; q < N; ++q) dma16(ptr[q] + c, stage + (wave + NW * q) * 256);
+    }
+    // zeros over what this lane fetched past the end of the contraction, in a stage that has landed
+    __device__ __forceinline__ void zero_tail(const FOp& op, uint32_t* stage, int c0, int, int tid) const
+    {
+        if (c0 + chunk_ < op.n_c) return;
+#pragma unroll
+        for (int q = 0; q < N; ++q) *(uint4*)(stage + ((tid >> 6) + NW * q) * 256 + (tid & 63) * 4) = make_uint4(0u, 0u, 0u, 0u);
     }
     __device__ __forceinline__ void settle(const FOp&) {}
     // start the contraction at c0 instead of 0 (a slice of a split contraction): nothing to do,
@@ -631,10 +640,16 @@ struct DmaQT {
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         if (R == RP || active_) {
 #pragma unroll
-            for (int q = 0; q < N; ++q)
-                dma16(or_zeros(c0 + tile_row(q, tid) < C, colp[q] + (size_t)rr[q] * (size_t)op.ld), stage + (wave + NW * q) * 256);
+            for (int q = 0; q < N; ++q) dma16(colp[q] + (size_t)rr[q] * (size_t)op.ld, stage + (wave + NW * q) * 256);
         }
         rows_for(op, c0 + BK, C, tid);
+    }
+    __device__ __forceinline__ void zero_tail(const FOp&, uint32_t* stage, int c0, int C, int tid) const
+    {
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            if ((R == RP || active_) && c0 + tile_row(q, tid) >= C)
+                *(uint4*)(stage + ((tid >> 6) + NW * q) * 256 + (tid & 63) * 4) = make_uint4(0u, 0u, 0u, 0u);
     }
     // start the contraction at c0 instead of 0 (a slice of a split contraction)
     __device__ __forceinline__ void seek(const FOp& op, int c0, int C, int tid)
@@ -748,11 +763,12 @@ struct RingP {
 #pragma unroll
         for (int q = 0; q < NI; ++q) ptr[q] = op.base + (size_t)rows[q] * (size_t)op.ld;
     }
-    __device__ __forceinline__ void issue(const FOp& op, int q, uint32_t lds_bytes, int s, int)
+    // whole: no chunk of stage s lies past the contraction's end
+    template <bool WHOLE> __device__ __forceinline__ void issue(const FOp& op, int q, uint32_t lds_bytes, int s, int)
     {
         if (SHORT && q == NI - 1 && wave_ >= (uint32_t)(NINST % NW)) return;      // uniform
         const int c = s * RK + chunk_;                           // the readable row length is a multiple of 8
-        dma16_ring(or_zeros(c < op.n_c, ptr[q] + c), lds_bytes + (wave_ + NW * q) * 1024u);
+        dma16_ring(WHOLE ? ptr[q] + c : or_zeros(c < op.n_c, ptr[q] + c), lds_bytes + (wave_ + NW * q) * 1024u);
     }
 };
 
@@ -815,13 +831,13 @@ struct RingQT {
         active_ = chunk * 8 < R;
         colp = op.base + min(r0 + chunk * 8, op.n_c - 8);        // the readable row length is a multiple of 8
     }
-    __device__ __forceinline__ void issue(const FOp& op, int q, uint32_t lds_bytes, int s, int C)
+    template <bool WHOLE> __device__ __forceinline__ void issue(const FOp& op, int q, uint32_t lds_bytes, int s, int C)
     {
         const int c = s * RK + row_[q];
         int row = c;
-        if constexpr (MAPPED_) row = list_[min(c, C - 1)];        // clamped when it was copied to LDS
-        if (R == RP || active_)
-            dma16_ring(or_zeros(c < C, colp + (size_t)row * (size_t)op.ld), lds_bytes + (wave_ + NW * q) * 1024u);
+        if constexpr (MAPPED_) row = list_[WHOLE ? c : min(c, C - 1)];        // clamped when it was copied to LDS
+        const E* p = colp + (size_t)row * (size_t)op.ld;
+        if (R == RP || active_) dma16_ring(WHOLE ? p : or_zeros(c < C, p), lds_bytes + (wave_ + NW * q) * 1024u);
     }
 };
 template <int R, int NT> struct RingQ : RingQT<R, NT, false> {};
@@ -869,15 +885,16 @@ __device__ __forceinline__ void ring_main(LA& la, LB& lb, const typename LA::Rea
     static_assert(TM % RA == 0 && TM >= 4 && TN >= 4 && NLW <= TM, "schedule below does not fit this wavefront tile");
     static_assert(TN <= TM - 1 || 2 * (TM - 1) >= TN, "not enough slots for the B fragments");
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)smem);
-    auto load = [&](int s, int j) {
+    auto load = [&](int s, int j, auto whole) {
+        constexpr bool WHOLE = decltype(whole)::value;
         const uint32_t base = lds0 + (uint32_t)(s & 3) * (uint32_t)(STAGE_WORDS * 4);
-        if (j < NA) la.issue(g.A, j, base, s0 + s, g.C);
-        else lb.issue(g.B, j - NA, base + A_WORDS * 4, s0 + s, g.C);
+        if (j < NA) la.template issue<WHOLE>(g.A, j, base, s0 + s, g.C);
+        else lb.template issue<WHOLE>(g.B, j - NA, base + A_WORDS * 4, s0 + s, g.C);
     };
     for (int st = 0; st < 3; ++st) {
         if (st < KT2) {
 #pragma unroll
-            for (int j = 0; j < NLW; ++j) load(st, j);
+            for (int j = 0; j < NLW; ++j) load(st, j, std::false_type());
         }
     }
     // a wavefront waits until at most ITS requests of one stage are outstanding (a loader whose
@@ -899,7 +916,8 @@ __device__ __forceinline__ void ring_main(LA& la, LB& lb, const typename LA::Rea
     afr[1] = ra.read16(smem, 1, 0);
     if (ZR_RING_ADIST == 3 && RA == 4) afr[2] = ra.read16(smem, 2, 0);
 
-    // steady: the step is known to have a stage s + 3 to request (no branches around the loads)
+    // steady: the step is known to have a stage s + 3 to request, and a whole one (no branches around the
+    // loads, no selects: 256 x 256 tiles, 2048 x 4096 x 4096, 2-3 %)
     auto step = [&](int s, auto parity, auto steady) {
         constexpr int P = decltype(parity)::value;
         constexpr bool STEADY = decltype(steady)::value;
@@ -921,7 +939,7 @@ __device__ __forceinline__ void ring_main(LA& la, LB& lb, const typename LA::Rea
                 const int jb = ring_b_read(gi, b, TM, TN);
                 if (jb >= 0) bfr[P ^ 1][jb] = rb.read16(nx + A_WORDS, jb, 0);
                 const int jl = ring_load(gi, b, TM, NLW);
-                if (jl >= 0 && more) load(s + 3, jl);
+                if (jl >= 0 && more) load(s + 3, jl, steady);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -931,7 +949,9 @@ __device__ __forceinline__ void ring_main(LA& la, LB& lb, const typename LA::Rea
     };
     int s = 0;
 #if ZR_RING_PEEL
-    for (; s + 4 < KT2; s += 2) {
+    // (the last two stages may reach past the contraction's end)
+    const int ahead = g.C % BK == 0 ? 4 : 6;
+    for (; s + ahead < KT2; s += 2) {
         step(s, std::integral_constant<int, 0>(), std::true_type());
         step(s + 1, std::integral_constant<int, 1>(), std::true_type());
     }
@@ -956,6 +976,18 @@ constexpr int fast_smem_bytes()
 // entries of the LDS copy of the row list (what is left of 160 KB, or of 80 KB for the tiles
 // that run two to a compute unit)
 template <int BM, int BN> constexpr int ring_list_max() { return BM * BN > 128 * 128 ? 6144 : 3072; }
+
+// The last stage of a contraction of no whole stages, once it has landed.
+template <class LA, class LB>
+__device__ __forceinline__ void zero_tails(const LA& la, const LB& lb, const FArgs& g, uint32_t* stage, int c0, int tid)
+{
+    if constexpr (LA::DMA || LB::DMA) {
+        if (c0 + BK <= g.C) return;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (the writes below stay behind the loads)
+        if constexpr (LA::DMA) la.zero_tail(g.A, stage, c0, g.C, tid);
+        if constexpr (LB::DMA) lb.zero_tail(g.B, stage + LA::WORDS, c0, g.C, tid);
+    }
+}
 
 // One iteration of the contraction pipeline.  `rd` (the stage being multiplied)
 // and `wr` (the stage being filled) never overlap; declaring that lets the
@@ -1048,6 +1080,7 @@ __device__ __forceinline__ void pipeline_step(
         if constexpr (!LB::DMA) lb.commit(g.B, wr + A_WORDS, tid);
         // direct-to-LDS loads are only tracked by the vector-memory counter: vmcnt(0)
         if constexpr (LA::DMA || LB::DMA) __builtin_amdgcn_s_waitcnt(0x0f70);
+        zero_tails(la, lb, g, wr, c_next, tid);
     }
 }
 
@@ -1213,6 +1246,7 @@ __device__ __forceinline__ void fast_body(const FArgs& g, uint32_t* smem, const 
         };
         start_tile(kt0, smem);
         finish_tile(smem);
+        zero_tails(la, lb, g, smem, kt0 * BK, tid);
         __syncthreads();
 
         for (int kt = kt0; kt < kt1; ++kt) {
