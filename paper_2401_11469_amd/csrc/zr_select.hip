@@ -565,7 +565,12 @@ int launch_select(const float* scores, int n, int batch, int n_keep,
     else {
 #define ZR_SELECT(K, NT) hipLaunchKernelGGL((select_regs_kernel<K, NT>), dim3(batch), dim3(NT), 0, stream, scores, n, n_keep, keep_idx, drop_idx, ld_idx)
         // few wavefronts for short vectors: each of them repeats the pick of a digit
-        if (batch >= 512) { if (n <= 1024) ZR_SELECT(16, 64); else if (n <= 4096) ZR_SELECT(16, 256); else if (n <= 12288) ZR_SELECT(24, 512); else ZR_SELECT(32, 1024); }
+        // (and, where the chip is full, little more room than the vector fills: what lies past its end costs as much as
+        // scores.  3104 vectors of 4397 on 512 threads of 24 108 us, on 256 of 24 64; 2366 of 1339 on 256 of 16 27, of 8 21)
+        if (batch >= 512) {
+            if (n <= 1024) ZR_SELECT(16, 64); else if (n <= 2048) ZR_SELECT(8, 256); else if (n <= 4096) ZR_SELECT(16, 256); else if (n <= 6144) ZR_SELECT(24, 256);
+            else if (n <= 8192) ZR_SELECT(16, 512); else if (n <= 12288) ZR_SELECT(24, 512); else ZR_SELECT(32, 1024);
+        }
         else if (n <= 1024) ZR_SELECT(4, 256); else if (n <= 4096) ZR_SELECT(8, 512); else if (n <= 12288) ZR_SELECT(12, 1024); else ZR_SELECT(32, 1024);
 #undef ZR_SELECT
     }
