@@ -57,14 +57,14 @@ __global__ __launch_bounds__(256) void compact_cols_kernel(
 // and what lies past the kept count is read from a zero behind each row instead of under a branch.
 // (8192 rows, us before and now: 2752 of which 2064 are kept 24.7 and 20.6, 4096 of 3072 31.7 and 25.7, 12288 of 7000
 // 107 and 86; 65536 x 8192 all kept 599 and 437, 4.9 TB/s)
-template <int KL, int RB>
+// QN: output dwords of a thread and row, for which it holds the list entries.
+template <int KL, int RB, int QN>
 __global__ __launch_bounds__(256) void compact_rows_lds_kernel(
     const uint16_t* __restrict__ in, int64_t ld, int rows, int n,
     const int32_t* __restrict__ keep, int n_keep,
     uint16_t* __restrict__ out, int64_t ldo, int width)
 {
     extern __shared__ __align__(16) uint16_t stage[];
-    constexpr int QN = 4 * KL;                          // output dwords of a thread and row
     const int tid = threadIdx.x, wave0 = __builtin_amdgcn_readfirstlane(tid & ~63);
     const int r0 = blockIdx.x * RB;
     const int chunks = n >> 3, pitch = n + 8, nq = width >> 1;
@@ -116,11 +116,16 @@ int launch_compact_cols(const void* in, int64_t ld, int rows, int n, const int32
     // LDS-staged rows when every row can be read in 16-byte chunks and a few rows fit
     if ((uintptr_t)in % 16 == 0 && ld % 8 == 0 && n % 8 == 0 && n <= 12288) {
         // few rows to a workgroup, so that thousands of workgroups even out over the units
-#define ZR_COMPACT(KL, RB)                                                                                              \
-        hipLaunchKernelGGL((compact_rows_lds_kernel<KL, RB>), dim3((rows + RB - 1) / RB), dim3(256), (size_t)RB * (n + 8) * 2, stream, \
+#define ZR_COMPACT(KL, RB, QN)                                                                                          \
+        hipLaunchKernelGGL((compact_rows_lds_kernel<KL, RB, QN>), dim3((rows + RB - 1) / RB), dim3(256), (size_t)RB * (n + 8) * 2, stream, \
                            (const uint16_t*)in, ld, rows, n, keep, n_keep, (uint16_t*)out, ldo, width)
+        // (of long rows that keep at most half, half the list: 3062 rows of 6360, 2448 kept, 13.3 us with all of it, 10.5 now)
         const int kl = (n / 8 + 255) / 256;
-        if (kl <= 1) ZR_COMPACT(1, 4); else if (kl == 2) ZR_COMPACT(2, 2); else if (kl == 3) ZR_COMPACT(3, 2); else if (kl == 4) ZR_COMPACT(4, 2); else ZR_COMPACT(6, 2);
+        const bool half = width <= 1024 * kl;
+        if (kl <= 1) ZR_COMPACT(1, 4, 4); else if (kl == 2) ZR_COMPACT(2, 2, 8);
+        else if (kl == 3) { if (half) ZR_COMPACT(3, 2, 6); else ZR_COMPACT(3, 2, 12); }
+        else if (kl == 4) { if (half) ZR_COMPACT(4, 2, 8); else ZR_COMPACT(4, 2, 16); }
+        else if (width <= 6144) ZR_COMPACT(6, 2, 12); else ZR_COMPACT(6, 2, 24);
 #undef ZR_COMPACT
         return hip_status(hipGetLastError());
     }
