@@ -183,6 +183,20 @@ bool gemm_fast_can(const GemmDesc& d)
     return true;
 }
 
+// contractions of whole 64-deep stages, or with an operand that is padded to them
+static bool whole_stages(const GemmDesc& d)
+{
+    return d.C % BK == 0 || (d.A.c_contig && d.A.zero_padded) || (d.B.c_contig && d.B.zero_padded);
+}
+
+// Slices of the contraction that its launch on 128 x 128 tiles will make.  (Two slices of a contraction of no whole stages
+// below 1344 gain nothing: 216 tiles, 1264 deep 26 us in one piece, 30 in two.)
+static bool short_for_slices(const GemmDesc& d) { return !whole_stages(d) && d.C < 1344; }
+static int slices_of(const GemmDesc& d, int64_t t128)
+{
+    return short_for_slices(d) ? 1 : slices_for(d.C, t128, d.split_scratch, d.split_scratch_bytes, d.accumulate);
+}
+
 // Whether this path takes the product (else the kernel for any alignment does).
 bool gemm_fast_takes(const GemmDesc& d)
 {
@@ -199,10 +213,9 @@ bool gemm_fast_takes(const GemmDesc& d)
     // 20.9 / 9.9, 2000 x 1024 x 1500 18.2 / 18.1.)
     const int64_t t128 = tiles_of(d.I, d.J, 128, 128);
     if (ap && d.epilogue == EPI_COL_SCATTER && d.out_full % 8 != 0) return true;
-    // contractions of whole 64-deep stages, or with an operand that is padded to them
-    const bool whole = d.C % BK == 0 || (ap && d.A.zero_padded) || (bp && d.B.zero_padded);
-    if (!ag && !bg && (whole || !adds_in_groups(d.I, d.J, d.C)) &&
-        slices_for(d.C, t128, d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2) return true;      // (48 tiles, 4096 tokens: 21 / 30; 3000 tokens 22 / 18, 128 tiles 28 / 32)
+    const bool whole = whole_stages(d);
+    const bool split = !ag && !bg && slices_of(d, t128) >= 2;
+    if (split && whole) return true;                // (48 tiles, 4096 tokens: 21 / 30)
     // Products that the other kernel adds up in groups of the contraction are all its own, so that a
     // result has the same bits whichever of its operands were extracted beforehand (64 x 8192, 4096 deep: 38 / 18).
     if (adds_in_groups(d.I, d.J, d.C)) return false;
@@ -210,12 +223,27 @@ bool gemm_fast_takes(const GemmDesc& d)
     if (ap && bp && bg) return t128 > 256;          // W[:,S] along the contraction: 128 tiles 27 / 20, 256 28.5 / 25, 792 91 / 126
     if (ap && bg) return t128 > 128;                // W[:,S] across it: 100 tiles 28.2 / 25.5 (256 deep 16.1 / 13.3, 4096 81 / 74), 128 28.7 / 25.7, 192 30 / 37
     if (ag || bg) return t128 > 96;                 // dW, a gather in flight, 4096 tokens: 48 tiles 84 / 47, 192 84 / 115
+    if (!whole) {
+        // The last stage is the same work for less, and rows of such a length straddle cache lines.  2518 products of 60 to
+        // 260 tiles, 8 to 6000 deep, time on this path by that on the other one, by depth; split: all of W in two or more
+        // slices, 128 tiles 1.34 (1600 deep) 1.12 (2048) 0.95 (3200), 160 tiles 1.05 (1600) 0.88 (2048), 192 tiles 0.96 (1600);
+        if (ap && !bp) return split ? t128 > 160 || d.C > (t128 > 128 ? 1600 : 2304)
+        //   in one piece, 160 tiles 776 deep 15.3 us / 17.9, 192 tiles 0.78 (1152) 0.86 (1600);
+                                    : t128 > (d.B.map_strided ? 256 : d.C <= 1152 ? 128 : 160);
+        // rows of W: split, 128 tiles 1.31 (1600) 1.10 (2560) 0.91 (above 3200); in one piece below three stages (LdPV) 1.06 to
+        // 1.17 at any number of tiles to 128, to 1152 deep 0.87 to 0.98, above 1.2 to 1.3;
+        if (ap) return t128 > 128 || (split ? d.C > 2560 : t128 > 64 && d.C >= 3 * BK && d.C <= 1152);
+        // dW: split, 128 tiles 1.11 (1600 tokens) 1.01 (2048) 0.89 (2560), 160 tiles 1.2 (1152) 0.9 (1600), 192 tiles 0.84; in one
+        // piece 0.7 to 1.0, but where dropped rows are copied 144 tiles 1.09 to 1.23, 176 tiles 1.05, 192 tiles 0.98, half
+        // of them dropped 180 tiles 1.25, 198 tiles 1.5
+        return split ? t128 > 128 || d.C > 1664
+                     : t128 > (d.prev && d.epilogue == EPI_ROW_SCATTER ? 256 : 128);
+    }
     // rows of W: 64 tiles 18 / 9, 256 19 / 17, 512 (1536 deep) 43 / 38, 1600 53 / 68; all of W: 128 13.6 / 11.8, 160 14 / 18,
-    // 256 14.8 / 19.5; not whole stages: 520 deep 160 tiles 12.1 / 15.3, 776 deep 512 tiles 21.4 / 26.4, 160 tiles 15.3 / 17.9
-    // (left on the other one, where the tests of these rules expect it)
-    if (ap && !bp) return t128 > (d.B.map_strided ? 256 : !whole && d.C > 768 ? 160 : 128);
-    if (ap) return t128 > 64;                       // 48 tiles 12.5 / 11, 96 14 / 16.5; 1000 deep (not whole) 192 tiles 17 / 19
-    return t128 > 128;                              // dW: 48 tiles 18 / 12.6; 5000 tokens 192 48 / 74, 200 tokens 256 11.7 / 11.5
+    // 256 14.8 / 19.5
+    if (ap && !bp) return t128 > (d.B.map_strided ? 256 : 128);
+    if (ap) return t128 > 64;                       // 48 tiles 12.5 / 11, 96 14 / 16.5
+    return t128 > 128;                              // dW: 48 tiles 18 / 12.6
 }
 
 // Whether the product leaves the sums of Average imputation in avg_partial.  One that is split as a whole
@@ -227,7 +255,7 @@ bool gemm_leaves_sums(const GemmDesc& d)
 {
     if (d.epilogue == EPI_PLAIN || !gemm_fast_takes(d)) return false;
     if (d.epilogue == EPI_COL_SCATTER && (int64_t)d.I * d.out_full < 8 << 20 && !forced_tiles()) return false;
-    const bool split = slices_for(d.C, tiles_of(d.I, d.J, 128, 128), d.split_scratch, d.split_scratch_bytes, d.accumulate) >= 2;
+    const bool split = slices_of(d, tiles_of(d.I, d.J, 128, 128)) >= 2;
     return !split || (d.epilogue == EPI_ROW_SCATTER && d.I > 1536);
 }
 
@@ -235,7 +263,8 @@ bool gemm_leaves_sums(const GemmDesc& d)
 int launch_gemm_fast(const GemmDesc& d, hipStream_t stream)
 {
     if (!gemm_fast_takes(d)) return -1;
-    const FArgs a = fargs_of(d);
+    FArgs a = fargs_of(d);
+    if (short_for_slices(d)) { a.partial = nullptr; a.partial_bytes = 0; }
     const bool ag = d.A.map_contig != nullptr, bg = d.B.map_contig != nullptr;
     if (d.A.c_contig && !d.B.c_contig) {            // forward: X rows, W columns
         const bool bm = d.B.map_strided != nullptr;        // W[S[c], :]: the row list is on the contraction axis
