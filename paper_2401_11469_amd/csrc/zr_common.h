@@ -164,8 +164,8 @@ struct AttrFlags {
 bool ensure_max_dynamic_lds(const void* fn, int bytes, void* flags16);
 int launch_gemm(const GemmDesc& d, hipStream_t stream);
 int launch_gemm_fast(const GemmDesc& d, hipStream_t stream);   // -1: not taken
-// both products of a backward call; -1: not taken, and if they could be, alone_us says how long they are expected to take one by one
-int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream, double& alone_us);
+int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream);   // both products of a backward call; -1: not taken
+double gemm_fast_us(const GemmDesc& d);        // the time expected of a product that gemm_fast_takes
 bool gemm_fast_can(const GemmDesc& d);
 bool gemm_fast_takes(const GemmDesc& d);
 bool gemm_leaves_sums(const GemmDesc& d);

@@ -806,13 +806,17 @@ int launch_short(const Args& a, const char* name, hipStream_t stream)
 // tiles below 96 of 64 x 64, 64 x 64 ones with alternating sums where those of 512 threads would be used, and
 // else 64 x 64 or 128 x 128, whichever the model of the schedule finds shorter (every XCD takes its tiles in
 // order, each as soon as one of 64 halves of a unit is free; a tile takes a start and an end, and a time per
-// stage, longer where kept columns are gathered).  Fitted to 56 backward calls (47 to 9500 tokens, 53 to 5100
-// wide), each in seven forms; the form it picks is 1.5 % slower than the best on average.  us before, in two launches,
-// and now: 985 x 1001 x 771 34 -> 25, 489 x 953 x 1073 30 -> 19, 2024 x 1024 x 1024 40 -> 30, 4095 x 2960 x 2304 64 for 130.
+// stage, longer where kept columns are gathered).  Fitted to 16170 backward calls (32 to 16384 tokens, 64 to 5121
+// wide), each in all forms and in two launches, for the time of what they pick: 0.766 of that of two launches on average (the
+// best form of each would be 0.760), 90 of them more than 8 % slower than two launches.  Each of the 56 forms (seven pairs of tiles for eight
+// of loaders) is picked, for 11 to 981 of the calls, and takes 0.69 to 0.90 of the time in two launches there.  us before, in two launches, and now: 985 x 1001 x 771
+// 34 -> 25, 489 x 953 x 1073 30 -> 19, 2024 x 1024 x 1024 40 -> 30, 4095 x 2960 x 2304 64 for 130.
 struct Plan { int xr, wr; bool x_first; };
 struct Cost { double start, stage; };
-constexpr Cost kCost32 = {9.7, 0.41}, kCost64 = {7.8, 1.61}, kCost128 = {5.4, 1.59};       // us, us per stage of 128, 128 and 64
-constexpr double kGathered = 0.305, kHalfFree = 0.70, kAlone = 0.55;     // per gathered operand; a unit to itself; a launch more
+constexpr Cost kCost32 = {6.0, 0.45}, kCost64 = {7.0, 1.17}, kCost128 = {11.0, 1.09};     // us, us per stage of 128, 128 and 64
+constexpr double kGathered = 0.59, kHalfFree = 0.80, kPair = 2.0, kAlone = 1.0;           // per gathered operand; a unit to itself; a launch
+constexpr double kWide = 0.80, kWideGathered = 0.84;                                      // the same for 512 threads on 64 x 64
+constexpr double kLimit = 1.07;                                                           // two launches take this much more than the model of each says
 
 int64_t tiles_of(const Args& a, int r) { return (int64_t)((a.I + r - 1) / r) * ((a.J + r - 1) / r); }
 
@@ -831,12 +835,15 @@ double alone_us(const Args& a)
     for (bool wide : {false, true}) {
         const int r = tile_of(a, wide);
         const int64_t n = (tiles_of(a, r) + 7) / 8;
-        best = std::min(best, (double)((n + 63) / 64) * tile_us(a, r, n <= 32 ? kHalfFree : 1.0));
+        const int g = (a.A.map_c != nullptr) + (a.B.map_c != nullptr);
+        double f = n <= 32 ? kHalfFree : 1.0;
+        if (r == 64 && adds_in_groups(a.I, a.J, a.C)) f *= kWide * (1 + kWideGathered * g) / (1 + kGathered * g);
+        best = std::min(best, (double)((n + 63) / 64) * tile_us(a, r, f));
     }
     return best + kAlone;
 }
 
-// false: two launches (limit: what those take on other kernels)
+// false: two launches (limit: what those take, on whichever kernels)
 bool plan_pair(const Args& x, const Args& w, double limit, Plan& p)
 {
     double best = limit;
@@ -849,7 +856,7 @@ bool plan_pair(const Args& x, const Args& w, double limit, Plan& p)
             if (nx + nw > 1 << 20) continue;
             const double f = nx + nw <= 32 ? kHalfFree : 1.0, tx = tile_us(x, xr, f), tw = tile_us(w, wr, f);
             const bool x_first = tx > tw;                   // the long tiles first
-            const double us = x_first ? two_groups((int)nx, tx, (int)nw, tw, 64) : two_groups((int)nw, tw, (int)nx, tx, 64);
+            const double us = kPair + (x_first ? two_groups((int)nx, tx, (int)nw, tw, 64) : two_groups((int)nw, tw, (int)nx, tx, 64));
             if (us < best) { best = us; p = Plan{xr, wr, x_first}; found = true; }
         }
     return found;
@@ -900,7 +907,7 @@ Args args_of(const GemmDesc& d)
 
 bool too_short(const GemmDesc& d, const Operand& o) { return o.map_contig ? o.n_contig < 2 : (o.c_contig ? d.C : o.n_contig) < 8; }
 
-int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, double limit, hipStream_t stream)
+int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
 {
     if (forced_tiles() || dx.I < 1 || dx.J < 1 || dx.C < 1 || dw.I < 1 || dw.J < 1 || dw.C < 1) return -1;
     for (const GemmDesc* d : {&dx, &dw})
@@ -912,7 +919,13 @@ int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, double limit, h
     // in one; 2048 x 4096 x 4096, stored [N x K], 206 / 268; up to 256 tiles: 4096 x 2048 x 2048 of 1024 kept columns 251 / 121)
     const bool w_fast = gemm_fast_takes(dw);
     if (w_fast && tiles_of(w, 128) > 256) return -1;
-    if (!w_fast) limit = std::min(limit, alone_us(x) + alone_us(w));
+    const bool x_fast = gemm_fast_takes(dx);
+    double limit = kLimit * ((x_fast ? gemm_fast_us(dx) : alone_us(x)) + (w_fast ? gemm_fast_us(dw) : alone_us(w)));
+    // A clearer gain where the models are the less certain: kept columns of a large [N x K] shard in both products (4832 x 2184 x 2840 of
+    // 1249 193 us, 278 in one launch), and long contractions on 512 threads a tile.
+    if (x_fast && w_fast && x.B.map_c && w.B.map_c && !dx.B.c_contig) limit *= 0.88;
+    auto long_wide = [](const Args& a) { return a.C > 4096 && tiles_of(a, 64) >= 96 && adds_in_groups(a.I, a.J, a.C); };
+    if (long_wide(x) || long_wide(w)) limit *= 0.95;
     if (!plan_pair(x, w, limit, p)) return -1;
     x.alternate = p.xr == 64 && adds_in_groups(x.I, x.J, x.C);
     w.alternate = p.wr == 64 && adds_in_groups(w.I, w.J, w.C);
@@ -995,9 +1008,8 @@ int launch_gemm(const GemmDesc& desc, hipStream_t stream)
         if (!g_debug.armed_once) {
             if (d.dtype == ZR_F32) st = launch_gemm_f32_pair(*d.with, d, stream);
             else if (d.dtype == ZR_BF16) {
-                double alone = 1e30;
-                st = launch_gemm_pair(*d.with, d, stream, alone);
-                if (st < 0) st = launch_gemm_any_pair(*d.with, d, alone, stream);
+                st = launch_gemm_pair(*d.with, d, stream);
+                if (st < 0) st = launch_gemm_any_pair(*d.with, d, stream);
             }
         }
         if (st >= 0 || d.only_together) return st;

@@ -60,8 +60,10 @@ inline void whole_grid(FArgs& k, int bm, int bn)
 enum { B256, B192, B128, B64 };
 struct Cost { double start, step; };               // us, us per 64 of the contraction
 constexpr Cost kCost[4] = {{10.3, 1.48}, {8.6, 1.36}, {5.7, 1.12}, {6.4, 0.84}};
+constexpr double kLaunch = 3.0;                     // what the models of the other kernels count for a launch, and this one does not
 constexpr double kHalfFree = 0.81;                 // time per step of a small tile that has its unit to itself
 constexpr double kSliceBig = 2.0, kSliceSmall = 0.5;       // a slice of a split contraction stores its sums,
+constexpr double kCopiedRow = 0.08;                // us
 constexpr double kReduce = 8.2, kReduceTile = 0.013;       // and a second launch adds them: us, and us per 256 x 256 sums
 
 struct Plan { int sx, sw, slices; bool x_first; double us; };
@@ -80,10 +82,10 @@ inline int64_t shape_tiles(int I, int J, int s, bool x)
     return tiles_of(I, J, bm, bn);
 }
 
-// One product in launches of its own.
-double alone_us(int I, int J, int C)
+// One product in launches of its own, on the direct-to-LDS kernels.
+double fast_alone_us(int I, int J, int C, bool may_split)
 {
-    double best = 4.6 + 0.36 * steps_of(C) * std::max(1.0, (double)tiles_of(I, J, 64, 64) / 256);     // the kernel for any alignment
+    double best = 1e30;
     for (int s = B256; s <= B64; ++s) {
         const int64_t n = per_xcd(shape_tiles(I, J, s, false));
         const int slots = s <= B192 ? 32 : 64;
@@ -91,7 +93,7 @@ double alone_us(int I, int J, int C)
         best = std::min(best, (double)((n + slots - 1) / slots) * (kCost[s].start + f * kCost[s].step * steps_of(C)));
         const int64_t t = tiles_of(I, J, 128, 128);
         const int sp = (int)std::min<int64_t>(std::min<int64_t>(512 / t, 8), steps_of(C) / 8);
-        if (s == B128 && sp >= 2) {
+        if (s == B128 && sp >= 2 && may_split) {
             const double g = per_xcd(t * sp) <= 32 ? kHalfFree : 1.0;
             best = std::min(best, kCost[s].start + g * kCost[s].step * ((steps_of(C) + sp - 1) / sp) + kSliceSmall + kReduce + kReduceTile * (double)(t * sp) / 4);
         }
@@ -99,7 +101,15 @@ double alone_us(int I, int J, int C)
     return best;
 }
 
-Plan plan_pair(const FArgs& x, const FArgs& w, bool x_rows, bool big_ok)
+// ... or on the kernel for any alignment, whichever is the shorter.
+double alone_us(int I, int J, int C)
+{
+    return std::min(4.6 + 0.36 * steps_of(C) * std::max(1.0, (double)tiles_of(I, J, 64, 64) / 256), fast_alone_us(I, J, C, true));
+}
+
+// (A clear gain only with a row list on the contraction of small tiles and dW in one piece: 41 calls of those took 0.85 of the time of two
+// launches on average, but 6 of them more than 1.08, 3584 x 472 x 4432 of 3408 kept columns 94 us for 75.)
+Plan plan_pair(const FArgs& x, const FArgs& w, bool x_rows, bool mapped, bool big_ok)
 {
     Plan best{0, 0, 0, false, alone_us(x.I, x.J, x.C) + alone_us(w.I, w.J, w.C)};
     // Products that the kernel for any alignment adds up in groups of the contraction keep that order, unless they are split.
@@ -121,10 +131,13 @@ Plan plan_pair(const FArgs& x, const FArgs& w, bool x_rows, bool big_ok)
                 if (nx + nw > 1 << 20) break;
                 const double f = small && nx + nw <= 32 ? kHalfFree : 1.0;
                 const double tx = kCost[sx].start + f * kCost[sx].step * steps_of(x.C);
-                const double tp = kCost[sw].start + f * kCost[sw].step * ((steps_of(w.C) + sl - 1) / sl) + (sl > 1 ? (small ? kSliceSmall : kSliceBig) : 0.0);
+                double tp = kCost[sw].start + f * kCost[sw].step * ((steps_of(w.C) + sl - 1) / sl) + (sl > 1 ? (small ? kSliceSmall : kSliceBig) : 0.0);
+                // rows that Same copies between a tile's kept ones (192 x 2288 x 608 of 248 kept rows 18 us in two launches, 33 in one)
+                if (sl == 1 && w.prev && w.epilogue == EPI_ROW_SCATTER) tp += kCopiedRow * bm * (w.out_full - w.I) / w.I;
                 const bool x_first = tx > tp;               // the long pieces first
                 double us = x_first ? two_groups((int)nx, tx, (int)nw, tp, slots) : two_groups((int)nw, tp, (int)nx, tx, slots);
                 if (sl > 1) us += kReduce + kReduceTile * (double)(tw * sl) * tile_bytes / (65536.0 * 4);
+                if (mapped && small && sl == 1) us *= 1.09;
                 if (us < best.us) best = Plan{sx, sw, sl, x_first, us};
             }
         }
@@ -191,7 +204,24 @@ int launch_pair_x(const FArgs& x, const FArgs& w, const Plan& p, hipStream_t str
 
 }  // namespace
 
-int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream, double& alone)
+// A product with a gather in flight takes a time per 64-deep step that grows with what is read and left
+// out (whole rows are, of which the kept columns go on).  Fitted to 1278 products of 64 to 16384 tokens, 64 to 5120
+// wide, within 15 % (us: dW of 192 tiles, 2000 of 2048 kept columns, 16384 tokens 316, of 1024 of 2048 818), and 10 % less than that,
+// so that it errs on the side of two launches.
+double gemm_fast_us(const GemmDesc& d)
+{
+    const Operand* gathered = d.A.map_contig ? &d.A : d.B.map_contig ? &d.B : nullptr;
+    if (!gathered) return fast_alone_us(d.I, d.J, d.C, d.split_scratch != nullptr) + kLaunch;
+    const double steps = steps_of(d.C), span = (double)gathered->n_contig / (gathered->c_contig ? d.C : gathered == &d.A ? d.I : d.J);
+    const int64_t t = tiles_of(d.I, d.J, 128, 128);
+    const double pairs = (double)((t + 511) / 512), big = (double)((tiles_of(d.I, d.J, 256, 256) + 255) / 256);
+    if (!d.A.c_contig) return 11.3 + 0.68 * steps * span * std::sqrt(span) * pairs;
+    if (gathered == &d.A) return 9.1 + 3.28 * steps * big;
+    if (!gathered->c_contig) return std::min(12.9 + steps * span * (t <= 256 ? 0.77 : 1.16 * pairs), 20.7 + 1.77 * steps * span * big);
+    return std::min(9.2 + 2.18 * steps * std::sqrt(span) * pairs, 13.3 + 3.45 * steps * big);
+}
+
+int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
 {
     if (forced_tiles() || !ring_enabled()) return -1;
     if (!gemm_fast_can(dx) || !gemm_fast_can(dw)) return -1;
@@ -200,8 +230,8 @@ int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream,
     if (!dx.A.c_contig || dx.A.map_strided || dw.A.c_contig || dw.B.c_contig || dx.avg_partial || dw.avg_partial) return -1;
     const bool rows = dx.B.c_contig, mapped = !rows && dx.B.map_strided;
     const FArgs x = fargs_of(dx), w = fargs_of(dw);
-    const Plan p = plan_pair(x, w, rows, !mapped || dx.C <= ring_list_max<256, 256>());
-    if (p.slices == 0) { alone = p.us; return -1; }
+    const Plan p = plan_pair(x, w, rows, mapped, !mapped || dx.C <= ring_list_max<256, 256>());
+    if (p.slices == 0) return -1;
     if (p.sx == B64) return launch_pair_small<DmaP, 64, 1, 4>(x, w, p, stream);
     if (p.sx == B128) {
         if (rows) return launch_pair_small<DmaP, 128, 2, 2>(x, w, p, stream);
