@@ -675,8 +675,8 @@ int launch_inst(const Args& a, hipStream_t stream)
     return hip_status(hipGetLastError());
 }
 
-template <template <int> class LA, template <int> class LB>
-int launch_shape(const Args& a, hipStream_t stream)
+// Extent of the tiles of a product on its own.
+int tile_of(const Args& a)
 {
     const int64_t t64 = (int64_t)((a.I + 63) / 64) * ((a.J + 63) / 64), t128 = (int64_t)((a.I + 127) / 128) * ((a.J + 127) / 128);
     // 128 x 128 tiles where they fill their rounds of 256: per area they are 4 to 24 % faster (contraction 256,
@@ -685,11 +685,21 @@ int launch_shape(const Args& a, hipStream_t stream)
     // 2048 tiles 39 against 72; contraction 64, 192 tiles 11 against 10, 384 tiles 16 against 17.
     const int64_t rounds64 = (t64 + 255) / 256, rounds128 = t128 <= 256 ? 1 : 2 * ((t128 + 511) / 512);
     const bool big = a.C <= 32 ? t128 >= 192 : a.C <= 96 ? t128 >= 256 : 0.92 * 4 * (double)rounds128 < (double)rounds64;
-    if (big) return launch_inst<LA, LB, 128>(a, stream);
+    if (big) return 128;
     // 64 x 64 tiles once there is one for most compute units (contraction 1024: 128 tiles 22.0 us
     // against 15.2 on 32 x 32, 192 tiles 22.7 against 21.8, 256 tiles 23.3 against 27.8, 512 tiles
     // 41.1 against 52.1)
-    return t64 < 192 ? launch_inst<LA, LB, 32>(a, stream) : launch_inst<LA, LB, 64>(a, stream);
+    return t64 < 192 ? 32 : 64;
+}
+
+template <template <int> class LA, template <int> class LB>
+int launch_shape(const Args& a, hipStream_t stream)
+{
+    switch (tile_of(a)) {
+        case 128: return launch_inst<LA, LB, 128>(a, stream);
+        case 64: return launch_inst<LA, LB, 64>(a, stream);
+        default: return launch_inst<LA, LB, 32>(a, stream);
+    }
 }
 
 // The element loaders: a contraction of less than four is one stage of any tile shape; otherwise the
@@ -705,15 +715,17 @@ int launch_short(const Args& a, hipStream_t stream)
 // ---------------------------------------------------------------------------
 // Tiles by a model of the schedule: every XCD takes its tiles in order, each on the first of 32 units that is
 // through with its own (two tiles share a unit and its matrix pipes, which takes as long as one after the
-// other); a tile takes a time per stage, longer where kept columns are gathered, and a launch a start and an end. Fitted to
-// 106 backward calls (32 to 4000 tokens, 64 to 2048 wide), each in nine forms: what it picks is 2.1 % slower than the best
-// of them on average.  us in two launches and now: 1576 x 2048 x 1024 of 1638 kept rows 151 -> 117, 609 x 1414 x 247
-// 31 -> 20, 256 x 512 x 256 14.7 -> 11.6.  A product that takes 32 x 32 tiles on its own keeps them: their four partial
-// sums are the more exact.
+// other); a tile takes a start and an end, and a time per stage, longer where kept columns are gathered, and a launch a start
+// and an end.  Fitted to 7328 backward calls (32 to 16384 tokens, 64 to 5120 wide), each in all forms and in two launches, for the time of what
+// they pick: 0.800 of that of two launches on average (the best form of each would be 0.795), 16 of them more than 8 % slower.  us in two
+// launches and now: 1576 x 2048 x 1024 of 1638 kept rows 151 -> 117, 609 x 1414 x 247 31 -> 20, 256 x 512 x 256
+// 14.7 -> 11.6.  A product that takes 32 x 32 tiles on its own keeps them: their four partial sums are the more
+// exact.  Pairs have no 128 x 128 tiles: where both products could take them, one launch of those took 1.18 of the time of two
+// (13120 x 704 x 2599 963 us in two launches, 1360 in one; 1088 x 3324 x 484 of 465 kept columns 107, 143).
 struct Plan { int xr, wr; bool x_first; };
 struct Cost { double start, stage; };
-constexpr Cost kCost32 = {1.5, 0.64}, kCost64 = {1.4, 1.21}, kCost128 = {1.4, 2.19};      // us, us per stage of 128, 64 and 32
-constexpr double kGathered = 0.17, kLaunch = 8.8;                         // per gathered operand; us
+constexpr Cost kCost32 = {1.55, 0.7}, kCost64 = {1.38, 1.11}, kCost128 = {1.4, 2.06};     // us, us per stage of 128, 64 and 32
+constexpr double kGathered = 0.18, kAlone = 9.2, kPair = 8.6;                             // per gathered operand; us a launch of one, of both
 
 int64_t tiles_of(const Args& a, int r) { return (int64_t)((a.I + r - 1) / r) * ((a.J + r - 1) / r); }
 bool may_take(const Args& a, int r) { return r == 32 || tiles_of(a, 64) >= 192; }
@@ -727,28 +739,24 @@ double tile_us(const Args& a, int r)
 
 double alone_us(const Args& a)
 {
-    double best = 1e30;
-    for (int r : {32, 64, 128}) {
-        if (!may_take(a, r)) continue;
-        const int64_t n = (tiles_of(a, r) + 7) / 8;
-        best = std::min(best, (double)((n + 31) / 32) * tile_us(a, r));
-    }
-    return best + kLaunch;
+    const int r = tile_of(a);
+    const int64_t n = (tiles_of(a, r) + 7) / 8;
+    return (double)((n + 31) / 32) * tile_us(a, r) + kAlone;
 }
 
 // false: two launches
 bool plan_pair(const Args& x, const Args& w, Plan& p)
 {
-    double best = 0.95 * (alone_us(x) + alone_us(w));       // (2048 x 2048 x 2048 of 1536 kept rows: 0.97, and 263 us alone, 279 paired)
+    double best = alone_us(x) + alone_us(w);
     bool found = false;
-    for (int xr : {32, 64, 128})
-        for (int wr : {32, 64, 128}) {
-            if ((xr == 128) != (wr == 128) || !may_take(x, xr) || !may_take(w, wr)) continue;
+    for (int xr : {32, 64})
+        for (int wr : {32, 64}) {
+            if (!may_take(x, xr) || !may_take(w, wr)) continue;
             const int64_t nx = (tiles_of(x, xr) + 7) / 8, nw = (tiles_of(w, wr) + 7) / 8;
             if (nx + nw > 1 << 20) continue;
             const double tx = tile_us(x, xr), tw = tile_us(w, wr);
             const bool x_first = tx > tw;                   // the long tiles first
-            const double us = kLaunch + (x_first ? two_groups((int)nx, tx, (int)nw, tw, 32) : two_groups((int)nw, tw, (int)nx, tx, 32));
+            const double us = kPair + (x_first ? two_groups((int)nx, tx, (int)nw, tw, 32) : two_groups((int)nw, tw, (int)nx, tx, 32));
             if (us < best) { best = us; p = Plan{xr, wr, x_first}; found = true; }
         }
     return found;
@@ -776,7 +784,6 @@ int launch_pair_inst(const Args& x, const Args& w, bool x_first, hipStream_t str
 template <template <int> class XA, template <int> class XB, template <int> class WA, template <int> class WB>
 int launch_pair(const Args& x, const Args& w, const Plan& p, hipStream_t stream)
 {
-    if (p.xr == 128) return launch_pair_inst<XA, XB, 128, WA, WB, 128>(x, w, p.x_first, stream);
     if (p.xr == 64 && p.wr == 64) return launch_pair_inst<XA, XB, 64, WA, WB, 64>(x, w, p.x_first, stream);
     if (p.xr == 64) return launch_pair_inst<XA, XB, 64, WA, WB, 32>(x, w, p.x_first, stream);
     if (p.wr == 64) return launch_pair_inst<XA, XB, 32, WA, WB, 64>(x, w, p.x_first, stream);
