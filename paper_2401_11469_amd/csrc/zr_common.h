@@ -155,6 +155,14 @@ inline int forced_tiles()
     return f;
 }
 
+// ZR_NO_RING in the environment (read once) keeps every product on the 64-deep two-stage loop, and dX and
+// dW in launches of their own: an A/B switch for measurements.
+inline bool ring_enabled()
+{
+    static const bool on = getenv("ZR_NO_RING") == nullptr;
+    return on;
+}
+
 // Dynamic-LDS attribute of a kernel: set once per device and instantiation (the call is
 // idempotent, so two threads racing to set it do no harm; the flags are atomic).
 struct AttrFlags {

@@ -910,7 +910,7 @@ bool too_short(const GemmDesc& d, const Operand& o) { return o.map_contig ? o.n_
 
 int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
 {
-    if (forced_tiles() || dx.I < 1 || dx.J < 1 || dx.C < 1 || dw.I < 1 || dw.J < 1 || dw.C < 1) return -1;
+    if (forced_tiles() || !ring_enabled() || dx.I < 1 || dx.J < 1 || dx.C < 1 || dw.I < 1 || dw.J < 1 || dw.C < 1) return -1;
     for (const GemmDesc* d : {&dx, &dw})
         if (too_short(*d, d->A) || too_short(*d, d->B)) return -1;
     if (!dx.A.c_contig || dw.A.c_contig || dw.B.c_contig) return -1;

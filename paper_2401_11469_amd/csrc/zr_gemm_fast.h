@@ -1757,14 +1757,6 @@ inline int slices_for(int C, int64_t tiles, const void* partial, size_t partial_
     return sp;
 }
 
-// ZR_NO_RING in the environment (read once) keeps every product on the 64-deep two-stage loop:
-// an A/B switch for measurements.
-inline bool ring_enabled()
-{
-    static const bool on = getenv("ZR_NO_RING") == nullptr;
-    return on;
-}
-
 // Tile schedule.  The chip has 256 CUs; a 256 x 256 tile occupies one CU (one
 // "round" = 256 such tiles), two 128 x 128 tiles share a CU.  A grid whose tile
 // count is just above a multiple of 256 would leave most CUs idle in its last

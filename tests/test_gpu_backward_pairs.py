@@ -1,5 +1,9 @@
 """dX and dW of one backward call in one launch: against fp32 products of the masked operands, with the previous tensors
 as imputed values, repeatable bit by bit, and one after the other where dW takes the place of W."""
+import os
+import subprocess
+import sys
+
 import pytest
 
 from parity_util import check_kept_torch
@@ -218,6 +222,26 @@ def test_forms_that_take_longer(torch_zr, M, K, N, mode, layout, n_keep, scratch
     same = dict(policy=SAME, prev_dX=torch.zeros_like(X), prev_dW=torch.zeros_like(W)) if dtype == "same" else dict(policy=ZERO)
     zr.resized_linear_bwd(X, W, dY, keep, mode, workspace=ws, w_layout=layout, **same)
     assert refused not in zr.debug_last_kernel(), zr.debug_last_kernel()
+
+
+def test_ring_switch_keeps_the_products_apart(torch_zr):
+    """ZR_NO_RING is read once per process: in a child process, a call that is paired without it."""
+    M, K, N, n_keep = 1984, 3600, 2720, 3008               # (see test_every_form)
+    code = f"""
+import torch
+from paper_2401_11469_amd import zr
+zr.debug_record_kernel_names(True)
+r = lambda a, b: torch.zeros(a, b, dtype=torch.bfloat16, device="cuda")
+ws = torch.empty(zr.workspace_bytes({M}, {K}, {N}, {n_keep}, 1, torch.bfloat16), dtype=torch.uint8, device="cuda")
+zr.resized_linear_bwd(r({M}, {K}), r({K}, {N}), r({M}, {N}), torch.arange({n_keep}, dtype=torch.int32, device="cuda"), 1, workspace=ws)
+torch.cuda.synchronize()
+print(zr.debug_last_kernel())
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    res = subprocess.run([sys.executable, "-c", code], cwd=root, env=dict(os.environ, ZR_NO_RING="1"), stdout=subprocess.PIPE, text=True, timeout=100)
+    assert res.returncode == 0
+    name = res.stdout.splitlines()[-1]
+    assert "kernel<" in name and "Ring" not in name and "beside" not in name, name
 
 
 @pytest.mark.parametrize("what", ["dW over W", "dX over X", "dX over dY", "dW over dY", "dW over dX", "prev_dW in dX", "dW over prev_dX"])
