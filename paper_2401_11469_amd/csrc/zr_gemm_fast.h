@@ -1099,10 +1099,13 @@ __device__ __forceinline__ void tile_at(const FArgs& g, int t, int& ti, int& tj)
 // One workgroup's tile `lin` (of an XCD-aware numbering, see the kernels) of a product.
 // PHASE: 0 = the whole product; 1 = the first launch of a split contraction (a separate kernel, so
 // that the ordinary one keeps its register allocation).
-template <template <int, int> class LA_, template <int, int> class LB_, int BM, int BN, int WM, int WN, int PHASE>
+// PART: the dX or the dW of a pair, whose scatter is of columns, or of rows, and which leave no sums.
+enum { PART_NONE, PART_DX, PART_DW };
+template <template <int, int> class LA_, template <int, int> class LB_, int BM, int BN, int WM, int WN, int PHASE, int PART = PART_NONE>
 __device__ __forceinline__ void fast_body(const FArgs& g, uint32_t* smem, const int lin)
 {
     constexpr int NT = 64 * WM * WN;
+    constexpr bool COLS = PART != PART_DW, ROWS = PART != PART_DX, SUMS = PART == PART_NONE;
     typedef LA_<BM, NT> LA;
     typedef LB_<BN, NT> LB;
     // (not where both operands come through the transposing reads on a tile larger than
@@ -1169,7 +1172,7 @@ __device__ __forceinline__ void fast_body(const FArgs& g, uint32_t* smem, const 
     // (Unconditional loads: a conditional one would leave a join whose register copies
     // wait for the load right here.  Without a scatter epilogue the address is any
     // readable one, the output's first word, and the value is ignored.)
-    const bool scatter_c = g.epilogue == EPI_COL_SCATTER, scatter_r = g.epilogue == EPI_ROW_SCATTER;
+    const bool scatter_c = COLS && g.epilogue == EPI_COL_SCATTER, scatter_r = ROWS && g.epilogue == EPI_ROW_SCATTER;
     const int k_first = scatter_c ? j0 : i0, k_count = scatter_c ? g.J : g.I, k_tile = scatter_c ? BN : BM;
     const int32_t* k_list = (scatter_c || scatter_r) ? g.keep : (const int32_t*)g.out;
     const int k_last = (scatter_c || scatter_r) ? k_count - 1 : 0;
@@ -1286,7 +1289,7 @@ __device__ __forceinline__ void fast_body(const FArgs& g, uint32_t* smem, const 
                 for (int r = 0; r < AR; ++r) Cs[acc_row(a, r) * CP + acc_col(b)] = to_bf16(acc[a][b][r]);
     };
 
-    if (g.epilogue == EPI_COL_SCATTER) {
+    if (COLS && g.epilogue == EPI_COL_SCATTER) {
         // The tile owns the original columns from its first kept column (0 for the
         // first tile) up to the next tile's first kept column (the full width for
         // the last one).
@@ -1339,7 +1342,7 @@ __device__ __forceinline__ void fast_body(const FArgs& g, uint32_t* smem, const 
                     }
                 }
                 __syncthreads();
-                if (g.avg_partial) {
+                if (SUMS && g.avg_partial) {
                     // sum of the row's stored (rounded) results, four or eight lanes to a row (one lane: 44 us
                     // for 880 x 1200 of 2400 columns on 64 x 128 tiles, now 25); the imputed zeros add nothing
                     constexpr int LR = NT / HR >= 8 ? 8 : 4;
@@ -1381,7 +1384,7 @@ __device__ __forceinline__ void fast_body(const FArgs& g, uint32_t* smem, const 
         // over one of RG row groups, consecutive threads on consecutive pairs.
         stage_compacted();
         __syncthreads();
-        if (g.avg_partial) {
+        if (SUMS && g.avg_partial) {
             // sum of this tile's stored (rounded) results per output row, in column order
             float* dst = g.avg_partial + (size_t)(g.avg_slot_base + tj) * (size_t)g.avg_len + i0;
             for (int row = tid; row < rows_valid; row += NT) {
@@ -1478,10 +1481,10 @@ __device__ __forceinline__ void fast_body(const FArgs& g, uint32_t* smem, const 
     }
 
     stage_compacted();
-    const bool scatter_rows = g.epilogue == EPI_ROW_SCATTER;
+    const bool scatter_rows = ROWS && g.epilogue == EPI_ROW_SCATTER;
     if (scatter_rows && tid < rows_valid) idxA[tid] = clamp_idx(keep_mine, g.out_full);
     __syncthreads();
-    if (scatter_rows && g.avg_partial) {
+    if (SUMS && scatter_rows && g.avg_partial) {
         // sum of this tile's stored (rounded) results per output column, in row order
         float* dst = g.avg_partial + (size_t)(g.avg_slot_base + ti) * (size_t)g.avg_len + j0;
         for (int col = tid; col < cols_valid; col += NT) {
@@ -1551,6 +1554,7 @@ template <int STRIPS, int TM = 4, int WN = 2>
 __global__ __launch_bounds__(128 * WN * STRIPS) void split_reduce_kernel(const FArgs g)
 {
     static_assert(STRIPS == 1 || (STRIPS == TM && TM == 4 && WN == 2), "the sums of Average imputation: 128 x 128 tiles");
+    constexpr bool PAIRED = WN == 4;          // 192 x 256 and 256 x 256 tiles: dW of a pair only, which scatters no columns and leaves no sums
     constexpr int BM = 32 * TM, BN = 64 * WN, NT = 128 * WN, TN = 4, SUBS = TM * TN;
     constexpr int ROWS = 32, CP = BN + 8, WIN = 1024;        // WIN: original columns per pass of the column scatter
     __shared__ __align__(16) E Cs_[STRIPS][ROWS * CP];
@@ -1568,7 +1572,7 @@ __global__ __launch_bounds__(128 * WN * STRIPS) void split_reduce_kernel(const F
     tile_at(g, t, ti, tj);
     const int i0 = g.i_base + ti * BM, j0 = g.j_base + tj * BN;
     const int rows_valid = min(BM, g.I - i0), cols_valid = min(BN, g.J - j0);
-    const bool scatter_c = g.epilogue == EPI_COL_SCATTER, scatter_r = g.epilogue == EPI_ROW_SCATTER;
+    const bool scatter_c = !PAIRED && g.epilogue == EPI_COL_SCATTER, scatter_r = g.epilogue == EPI_ROW_SCATTER;
     if (STRIPS == 1 && a * 16 >= rows_valid) return;          // (then the lower rows BM / 2 + 16 a are empty too)
 
     // kept rows of the strip: 16 from tile row 16 a, 16 from tile row BM / 2 + 16 a
@@ -1609,7 +1613,7 @@ __global__ __launch_bounds__(128 * WN * STRIPS) void split_reduce_kernel(const F
     }
     __syncthreads();
 
-    if (g.avg_partial && STRIPS == 1) {
+    if (!PAIRED && g.avg_partial && STRIPS == 1) {
         // column scatter: sums of the stored (rounded) results of each row, LR (8 or 16) lanes to a row
         constexpr int LR = NT / ROWS;
         const int r = tid / LR, c0 = tid % LR * (BN / LR);

@@ -38,7 +38,8 @@ int launch_inst(const FArgs& a, int i_base, int i_end, int j_base, int j_end, hi
     // (Tried on the big ring tiles of the dW products at high pruning ratios as well, 128 tiles
     // of 192 x 256 in two slices each: the slices are 50 MB of fp32 that leave the chip at the
     // end of the first launch and come back in the second, ~35 us per product, which is all
-    // that the better fill of the chip gains.  Not instantiated.)
+    // that the better fill of the chip gains.  A product on its own has no such form; a dW in one
+    // launch with its dX has, see zr_gemm_pair.hip: there the slices run beside the tiles of dX.)
     constexpr bool can_split = A::DMA && B::DMA && !ring && BM == 128 && BN == 128;
     if constexpr (can_split) {
         const int sp = slices_for(a.C, tiles, a.partial, a.partial_bytes, a.accumulate != 0);

@@ -16,7 +16,7 @@ namespace zr {
 namespace {
 
 // A tile shape with its loaders, as a type.
-template <template <int, int> class LA_, template <int, int> class LB_, int BM_, int BN_, int WM, int WN, int PHASE_>
+template <int PART, template <int, int> class LA_, template <int, int> class LB_, int BM_, int BN_, int WM, int WN, int PHASE_>
 struct Shape {
     static constexpr int BM = BM_, BN = BN_, NT = 64 * WM * WN, PHASE = PHASE_;
     typedef LA_<BM, NT> LA;
@@ -25,7 +25,7 @@ struct Shape {
                                [] { if constexpr (LA::RING) return LB::MAPPED ? ring_list_max<BM, BN>() * 4 : 0; else return 0; }();
     static __device__ __forceinline__ void run(const FArgs& g, uint32_t* smem, int lin)
     {
-        fast_body<LA_, LB_, BM_, BN_, WM, WN, PHASE_>(g, smem, lin);
+        fast_body<LA_, LB_, BM_, BN_, WM, WN, PHASE_, PART>(g, smem, lin);
     }
 };
 
@@ -178,21 +178,21 @@ int launch_pair_inst(const FArgs& x, const FArgs& w, const Plan& p, hipStream_t 
 template <template <int, int> class LB, int XM, int XN, int XWM, int XWN>
 int launch_pair_w(const FArgs& x, const FArgs& w, const Plan& p, hipStream_t stream)
 {
-    typedef Shape<RingP, LB, XM, XN, XWM, XWN, 0> SX;
+    typedef Shape<PART_DX, RingP, LB, XM, XN, XWM, XWN, 0> SX;
     if (p.slices > 1) {
-        if (p.sw == B256) return launch_pair_inst<SX, Shape<RingQ, RingQ, 256, 256, 2, 4, 1>>(x, w, p, stream);
-        return launch_pair_inst<SX, Shape<RingQ, RingQ, 192, 256, 2, 4, 1>>(x, w, p, stream);
+        if (p.sw == B256) return launch_pair_inst<SX, Shape<PART_DW, RingQ, RingQ, 256, 256, 2, 4, 1>>(x, w, p, stream);
+        return launch_pair_inst<SX, Shape<PART_DW, RingQ, RingQ, 192, 256, 2, 4, 1>>(x, w, p, stream);
     }
-    if (p.sw == B256) return launch_pair_inst<SX, Shape<RingQ, RingQ, 256, 256, 2, 4, 0>>(x, w, p, stream);
-    return launch_pair_inst<SX, Shape<RingQ, RingQ, 192, 256, 2, 4, 0>>(x, w, p, stream);
+    if (p.sw == B256) return launch_pair_inst<SX, Shape<PART_DW, RingQ, RingQ, 256, 256, 2, 4, 0>>(x, w, p, stream);
+    return launch_pair_inst<SX, Shape<PART_DW, RingQ, RingQ, 192, 256, 2, 4, 0>>(x, w, p, stream);
 }
 
 template <template <int, int> class LB, int XM, int XWM, int XWN>
 int launch_pair_small(const FArgs& x, const FArgs& w, const Plan& p, hipStream_t stream)
 {
-    typedef Shape<DmaP, LB, XM, 128, XWM, XWN, 0> SX;
-    if (p.slices > 1) return launch_pair_inst<SX, Shape<DmaQ, DmaQ, 128, 128, 2, 2, 1>>(x, w, p, stream);
-    return launch_pair_inst<SX, Shape<DmaQ, DmaQ, 128, 128, 2, 2, 0>>(x, w, p, stream);
+    typedef Shape<PART_DX, DmaP, LB, XM, 128, XWM, XWN, 0> SX;
+    if (p.slices > 1) return launch_pair_inst<SX, Shape<PART_DW, DmaQ, DmaQ, 128, 128, 2, 2, 1>>(x, w, p, stream);
+    return launch_pair_inst<SX, Shape<PART_DW, DmaQ, DmaQ, 128, 128, 2, 2, 0>>(x, w, p, stream);
 }
 
 template <template <int, int> class LB>
@@ -228,6 +228,8 @@ int launch_gemm_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t stream)
     // operands as they lie, or by rows; no sums of Average imputation
     if (dx.A.map_contig || dx.B.map_contig || dw.A.map_contig || dw.B.map_contig) return -1;
     if (!dx.A.c_contig || dx.A.map_strided || dw.A.c_contig || dw.B.c_contig || dx.avg_partial || dw.avg_partial) return -1;
+    // (a dW that scatters columns comes with kept columns of W in dX, which are refused above)
+    if (dx.epilogue == EPI_ROW_SCATTER || dw.epilogue == EPI_COL_SCATTER) return -1;
     const bool rows = dx.B.c_contig, mapped = !rows && dx.B.map_strided;
     const FArgs x = fargs_of(dx), w = fargs_of(dw);
     const Plan p = plan_pair(x, w, rows, mapped, !mapped || dx.C <= ring_list_max<256, 256>());
