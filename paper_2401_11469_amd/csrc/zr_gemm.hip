@@ -924,7 +924,7 @@ int launch_gemm_any_pair(const GemmDesc& dx, const GemmDesc& dw, hipStream_t str
     double limit = kLimit * ((x_fast ? gemm_fast_us(dx) : alone_us(x)) + (w_fast ? gemm_fast_us(dw) : alone_us(w)));
     // A clearer gain where the models are the less certain: kept columns of a large [N x K] shard in both products (4832 x 2184 x 2840 of
     // 1249 193 us, 278 in one launch), and long contractions on 512 threads a tile.
-    if (x_fast && w_fast && x.B.map_c && w.B.map_c && !dx.B.c_contig) limit *= 0.78;
+    if (x_fast && w_fast && x.B.map_c && w.B.map_c && !dx.B.c_contig) limit *= 0.70;
     auto long_wide = [](const Args& a) { return a.C > 4096 && tiles_of(a, 64) >= 96 && adds_in_groups(a.I, a.J, a.C); };
     if (long_wide(x) || long_wide(w)) limit *= 0.95;
     if (!plan_pair(x, w, limit, p)) return -1;
