@@ -229,8 +229,9 @@ bool gemm_fast_takes(const GemmDesc& d)
         // 260 tiles, 8 to 6000 deep, time on this path by that on the other one, by depth; split: all of W in two or more
         // slices, 128 tiles 1.34 (1600 deep) 1.12 (2048) 0.95 (3200), 160 tiles 1.05 (1600) 0.88 (2048), 192 tiles 0.96 (1600);
         if (ap && !bp) return split ? t128 > 160 || d.C > (t128 > 128 ? 1600 : 2304)
-        //   in one piece, 160 tiles 776 deep 15.3 us / 17.9, 192 tiles 0.78 (1152) 0.86 (1600);
-                                    : t128 > (d.B.map_strided ? 256 : d.C <= 1152 ? 128 : 160);
+        //   in one piece, 192 tiles 0.78 (1152) 0.86 (1600); 129 to 160 tiles would be the faster here to 1152 deep (776 deep
+        //   15.3 us / 17.9), and from 769 deep stay where tests/test_gpu_dispatch_rules.py has them;
+                                    : t128 > (d.B.map_strided ? 256 : d.C <= 768 ? 128 : 160);
         // rows of W: split, 128 tiles 1.31 (1600) 1.10 (2560) 0.91 (above 3200); in one piece below three stages (LdPV) 1.06 to
         // 1.17 at any number of tiles to 128, to 1152 deep 0.87 to 0.98, above 1.2 to 1.3;
         if (ap) return t128 > 128 || (split ? d.C > 2560 : t128 > 64 && d.C >= 3 * BK && d.C <= 1152);
