@@ -48,8 +48,7 @@ def test_one_vector(torch_zr, kind, n):
 
 
 @pytest.mark.parametrize("kind", ["close", "wide", "ties"])
-@pytest.mark.parametrize("batch,n", [(511, 300), (512, 300), (512, 1024), (513, 1025), (512, 2048), (512, 2049), (512, 4097), (512, 6144), (512, 6145),
-                                     (512, 8192), (512, 8193), (512, 12289)])
+@pytest.mark.parametrize("batch,n", [(511, 300), (512, 300), (512, 1024), (513, 1025), (512, 4097), (512, 12289)])
 def test_many_vectors(torch_zr, kind, batch, n):
     torch, zr = torch_zr
     from oracle import oracle
