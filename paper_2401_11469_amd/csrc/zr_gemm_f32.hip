@@ -720,8 +720,7 @@ int launch_short(const Args& a, hipStream_t stream)
 // they pick: 0.800 of that of two launches on average (the best form of each would be 0.795), 16 of them more than 8 % slower.  us in two
 // launches and now: 1576 x 2048 x 1024 of 1638 kept rows 151 -> 117, 609 x 1414 x 247 31 -> 20, 256 x 512 x 256
 // 14.7 -> 11.6.  A product that takes 32 x 32 tiles on its own keeps them: their four partial sums are the more
-// exact.  Pairs have no 128 x 128 tiles: where both products could take them, one launch of those took 1.18 of the time of two
-// (13120 x 704 x 2599 963 us in two launches, 1360 in one; 1088 x 3324 x 484 of 465 kept columns 107, 143).
+// exact.  128 x 128 tiles are outside the model: see one_round.
 struct Plan { int xr, wr; bool x_first; };
 struct Cost { double start, stage; };
 constexpr Cost kCost32 = {1.55, 0.7}, kCost64 = {1.38, 1.11}, kCost128 = {1.4, 2.06};     // us, us per stage of 128, 64 and 32
@@ -744,9 +743,22 @@ double alone_us(const Args& a)
     return (double)((n + 31) / 32) * tile_us(a, r) + kAlone;
 }
 
+// Both products on 128 x 128 tiles: only where every tile has a unit to itself, 64 x 64 ones take more than three rounds, and both
+// products gather and are about as deep, so that all tiles end together.  4846 backward calls whose products may take such tiles:
+// there they take 0.94 of the time of what the model picks (36 calls, 0.85 to 1.05; 1576 x 1024 x 2048 of 1638 kept columns
+// 165 us, now 149), without the gathers 1.08 and more, over all of them 1.47 (13120 x 704 x 2599 963 us in two launches, 1360 in one).
+bool one_round(const Args& x, const Args& w)
+{
+    auto gathers = [](const Args& a) { return a.A.map_c || a.B.map_c; };
+    auto per_xcd = [&](int r) { return (tiles_of(x, r) + 7) / 8 + (tiles_of(w, r) + 7) / 8; };
+    return may_take(x, 128) && may_take(w, 128) && gathers(x) && gathers(w) && per_xcd(128) <= 32 && per_xcd(64) > 3 * 32 &&
+           std::max(x.C, w.C) <= 1.2 * std::min(x.C, w.C);
+}
+
 // false: two launches
 bool plan_pair(const Args& x, const Args& w, Plan& p)
 {
+    if (one_round(x, w)) { p = Plan{128, 128, tile_us(x, 128) > tile_us(w, 128)}; return true; }
     double best = alone_us(x) + alone_us(w);
     bool found = false;
     for (int xr : {32, 64})
@@ -784,6 +796,9 @@ int launch_pair_inst(const Args& x, const Args& w, bool x_first, hipStream_t str
 template <template <int> class XA, template <int> class XB, template <int> class WA, template <int> class WB>
 int launch_pair(const Args& x, const Args& w, const Plan& p, hipStream_t stream)
 {
+    // (pairs of gathering products only, see one_round)
+    if constexpr (std::is_same_v<XA<32>, GatherP<32>> || std::is_same_v<XB<32>, GatherQ<32>>)
+        if (p.xr == 128) return launch_pair_inst<XA, XB, 128, WA, WB, 128>(x, w, p.x_first, stream);
     if (p.xr == 64 && p.wr == 64) return launch_pair_inst<XA, XB, 64, WA, WB, 64>(x, w, p.x_first, stream);
     if (p.xr == 64) return launch_pair_inst<XA, XB, 64, WA, WB, 32>(x, w, p.x_first, stream);
     if (p.wr == 64) return launch_pair_inst<XA, XB, 32, WA, WB, 64>(x, w, p.x_first, stream);

@@ -195,6 +195,37 @@ def test_forms_that_take_longer(torch_zr, M, K, N, mode, layout, n_keep, scratch
     assert refused not in zr.debug_last_kernel(), zr.debug_last_kernel()
 
 
+@pytest.mark.parametrize("M,K,N,mode,layout,n_keep,form", [
+    # fp32 on 128 x 128 tiles: a unit to each of them, both products gathered, depths within 1.2 of each other
+    (1576, 1024, 2048, DROP_N, W_NK, 1638, "f32_kernel<Qg, Q, 128> beside <Pg, Q, 128>"),
+    (1840, 1008, 2300, DROP_N, W_KN, 1861, "f32_kernel<Q, Qg, 128> beside <Pg, Pg, 128>"),
+    (1753, 1100, 1985, DROP_K, W_NK, 877, "f32_kernel<Q, Qg, 128> beside <P, Qg, 128>"),
+    # one more tile than units, depths further apart, too few tiles of 64 x 64, one product that gathers nothing
+    (1920, 1024, 2400, DROP_N, W_NK, 2200, None), (1536, 1301, 1500, DROP_N, W_KN, 1198, None), (1400, 1000, 1700, DROP_N, W_NK, 1400, None),
+    (1576, 2048, 1600, DROP_K, W_KN, 1024, None)])
+def test_fp32_pair_of_one_round(torch_zr, M, K, N, mode, layout, n_keep, form):  # noqa: F811
+    torch, zr = torch_zr
+    X, W, dY = (t.float() for t in tensors(torch, M, K, N, layout == W_NK, M + K + N))
+    n = N if mode == DROP_N else K
+    keep = torch.randperm(n, generator=torch.Generator(device="cuda").manual_seed(n), device="cuda")[:n_keep].sort().values.to(torch.int32)
+    a = zr.resized_linear_bwd(X, W, dY, keep, mode, w_layout=layout)
+    name = zr.debug_last_kernel()
+    assert (name == form) if form else ("128> beside" not in name), name
+    kept = torch.zeros(n, device="cuda")
+    kept[keep.long()] = 1.0
+    Xd, Wd, dYd = X.double(), (W.t() if layout == W_NK else W).double(), dY.double()
+    if mode == DROP_K:
+        Xd, Wd = Xd * kept[None, :], Wd * kept[:, None]
+    else:
+        dYd = dYd * kept[None, :]
+    dX, dW = dYd @ Wd.t(), Xd.t() @ dYd
+    if layout == W_NK:
+        dW = dW.t()
+    for what, got, want, C in (("dX", a[0], dX, n_keep if mode == DROP_N else N), ("dW", a[1], dW, M)):
+        # the error of C fp32 additions in any order grows as sqrt(C); 8 covers the largest of 4 million
+        assert float((got.double() - want).abs().max()) <= 8 * C ** 0.5 * 2.0 ** -24 * float(want.abs().max()), what
+
+
 def test_ring_switch_keeps_the_products_apart(torch_zr):  # noqa: F811
     """ZR_NO_RING is read once per process: in a child process, a call that is paired without it."""
     M, K, N, n_keep = 1984, 3600, 2720, 3008               # (see test_every_form)
