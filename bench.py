@@ -265,7 +265,8 @@ def main() -> int:
                                   "not measured in this run)") if dom_pmc else None,
                 "avg_launch_ms": dom[1][2] / dom[1][0], "launches": dom[1][0],
                 "note": "achieved = kept FLOPs of the launches of this instantiation / their summed durations "
-                        "(HIP events on the launch stream)"}
+                        "(HIP events on the launch stream), product by product; the timed steps run dX and dW of a "
+                        "call in one launch where that is the shorter"}
     ex_ms = sum(a.elapsed_time(b) for a, b, _ in extracts)
     ex_bytes = sum(b for _, _, b in extracts)
     extract = {"kernel": "compact_rows_lds_kernel", "launches": len(extracts),

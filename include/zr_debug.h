@@ -22,7 +22,10 @@ void zr_debug_record_kernel_names(int on);
 
 /* Name (as a profiler prints it, without namespaces) of the GEMM kernel
  * instantiation that the last forward / backward / accumulate product of this
- * thread launched while recording was on; "" if none. */
+ * thread launched while recording was on; "" if none.  A launch of dX and dW
+ * together (pair_kernel, gemm_pair_kernel, f32_pair_kernel to a profiler) is named
+ * by its two products, dW's "beside" dX's.  zr_debug_time_next_product times
+ * products one by one: a call that it is armed for pairs none. */
 const char* zr_debug_last_kernel(void);
 
 /* The NEXT forward / backward / accumulate product of this thread records the
